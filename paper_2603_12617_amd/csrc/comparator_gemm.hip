@@ -16,6 +16,11 @@
 // an inner product is free, and it is the same for every output whatever the call boundaries
 // are, so results do not depend on how the horizon is cut.
 //
+// A few runs and rounds of a wide model leave most of the chip without a tile (4 runs, 2000 rounds,
+// d = 32768: 32 workgroups, 1460 us); with scratch for partial sums the depth is then cut into a.chunks ranges of
+// coordinates, a workgroup each, and comparator_sum_kernel adds them in order.  (Only callers whose results need
+// not be the same bits under every cut of the horizon give that scratch: the number of ranges depends on n.)
+//
 // A tile of rounds that straddles a segment boundary is computed once per segment it touches;
 // each pass writes only the rounds of its own segment.
 #include "oco_internal.h"
@@ -50,6 +55,10 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
     int s_hi = s_lo;
     while (s_hi + 1 < a.S && a.seg_start[s_hi + 1] <= t_last) ++s_hi;
 
+    // this workgroup's range of coordinates (whole LDS chunks)
+    const int nkc = (d + kKC - 1) / kKC;
+    const int kc_lo = (int)((int64_t)blockIdx.z * nkc / gridDim.z) * kKC, kc_hi = min(d, (int)((int64_t)(blockIdx.z + 1) * nkc / gridDim.z) * kKC);
+
     const int half = lane >> 5;                        // which of the two depth indices of an MFMA
     const int l32 = lane & 31;
     const float *ua = us + ((wave >> 1) * 32 + l32) * kRow + 4 * half;
@@ -60,7 +69,7 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 
-        for (int kc = 0; kc < d; kc += kKC) {
+        for (int kc = kc_lo; kc < kc_hi; kc += kKC) {
             // stage 64 rows x kKC coordinates of U (segment s) and of X
             if (VEC) {
 #pragma unroll
@@ -109,10 +118,22 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int run = rb + (wave >> 1) * 32 + 8 * (v / 4) + 4 * half + (v % 4);
-                if (run < a.R) a.Z[(int64_t)run * a.zl.zs_r + (int64_t)a.K * a.zl.zs_i + (int64_t)t * a.zl.zs_t] = acc[v];
+                if (run >= a.R) continue;
+                if (gridDim.z > 1) a.part[((int64_t)blockIdx.z * a.R + run) * a.n + t] = acc[v];
+                else a.Z[(int64_t)run * a.zl.zs_r + (int64_t)a.K * a.zl.zs_i + (int64_t)t * a.zl.zs_t] = acc[v];
             }
         }
     }
+}
+
+__global__ void __launch_bounds__(256) comparator_sum_kernel(ComparatorGemmArgs a)
+{
+    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x), run = blockIdx.y;
+    if (t >= a.n) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < a.chunks; ++c) s += (double)a.part[((int64_t)c * a.R + run) * a.n + t];
+    a.Z[(int64_t)run * a.zl.zs_r + (int64_t)a.K * a.zl.zs_i + (int64_t)t * a.zl.zs_t] = (float)s;
 }
 
 }  // namespace
@@ -120,11 +141,14 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
 hipError_t launch_comparator_gemm(const ComparatorGemmArgs &a, hipStream_t s)
 {
     if (a.n <= 0 || a.R <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((a.n + kTileRounds - 1) / kTileRounds), (unsigned)((a.R + kTileRuns - 1) / kTileRuns));
+    const bool split = a.part && a.chunks > 1 && a.R <= 65535;
+    const dim3 grid((unsigned)((a.n + kTileRounds - 1) / kTileRounds), (unsigned)((a.R + kTileRuns - 1) / kTileRuns),
+                    split ? (unsigned)a.chunks : 1u);
     if (a.vec_ok)
         hipLaunchKernelGGL(comparator_gemm_kernel<true>, grid, dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL(comparator_gemm_kernel<false>, grid, dim3(256), 0, s, a);
+    if (split) hipLaunchKernelGGL(comparator_sum_kernel, dim3((unsigned)((a.n + 255) / 256), (unsigned)a.R), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,509 @@
+// Dense rounds of a few base learners of a wide model on a shared round stream: the windows of
+// dense_window.hip with the coordinates of a tile of 16 learners split over many workgroups.
+//
+// dense_window_kernel gives a tile (or two) of learners to one workgroup for a whole launch.  With few
+// learners that leaves the chip empty: 16 learners of d = 32768 are one workgroup on 256 compute units and a
+// window of 64 rounds takes 940 us, nearly all of it one compute unit's matrix instructions and loads.  Here
+// a window is ONE launch in which workgroup (tile, chunk) owns a range of the tile's coordinates:
+//   (1) it sums the chunks' shares of W X_k^T that the launch before left (fixed order, float64),
+//   (2) runs the 64 dependent rounds of its tile (chain_window) on one wavefront -- every chunk of a tile
+//       repeats them from the same inputs, which costs nothing on compute units that would idle and saves a
+//       second launch per window --, while the other seven wavefronts fetch the operands of (3),
+//   (3) applies the window's step to its coordinates, W <- F W - Bm X_k, and takes its share of
+//       W X_{k+1}^T and of ||W||^2 of the new iterates for the launch after.
+// The launch boundary is the only synchronisation between workgroups: what a launch reads of other
+// workgroups' work (shares, hint scalars) it reads from one of two buffers and writes the other.  The inner
+// products are those of the iterates themselves (no cross-Gram correction as in dense_window_kernel) and
+// ||w||^2 is measured every window.
+// What bounds it: the dependent rounds (9 us per window), the turn-around of a launch and the sum over the
+// chunks' shares in front of them.  A window is one launch of 20 us at d = 2048 (256 learners) and of 29 us at
+// d = 32768 (16 learners, 64 chunks of 512 coordinates); 4000 optimistic rounds of the former take 1.5 ms against
+// 3.0 ms on the register kernel, 2000 rounds of the latter 1.3 ms against 29.4 ms on dense_window_kernel.
+//
+// The round rows are read as they are, without the re-tiled copies of dense_window.hip: with few tiles
+// a copy would cost more than it saves.  The Gram matrices of the windows are taken by
+// split_gram_kernel, depth-split as well, from the same rows.
+#include "dense_window_common.h"
+#include "../../include/oco.h"
+
+#include <algorithm>
+#include <cstdio>
+
+namespace oco {
+namespace {
+
+constexpr int kSW = 8;                        // wavefronts per workgroup: one runs the dependent rounds, seven sweep
+constexpr int kSweepers = kSW - 1;
+constexpr int kPre = 4;                       // blocks of 16 coordinates a sweeping wavefront fetches beside the dependent rounds
+constexpr int kShareFloats = kB * kM + kM;    // a chunk's share of W X^T, then of ||W||^2
+
+struct LdsS {
+    using G = double;
+    using S = double;
+    static constexpr bool has_corr = false;
+    static constexpr int gd_bytes = kB * 4 * kGStride * 8;
+    static constexpr int tile_f = kB * kM * 4, tile_s = kB * kM * 8;
+    static constexpr int yb_bytes = tile_f, zb_bytes = tile_f, bm_bytes = tile_f, fv_bytes = kM * 4, hg_bytes = kB * 4;
+    static constexpr int gd = 0;
+    static constexpr int yb = gd + gd_bytes;
+    static constexpr int zb = yb + yb_bytes;
+    static constexpr int bm = zb + zb_bytes;
+    static constexpr int fv = bm + bm_bytes;
+    static constexpr int q0 = fv + fv_bytes;
+    static constexpr int fl = q0 + tile_s;
+    static constexpr int st = fl + tile_s;
+    static constexpr int hg = st + tile_f;
+    static constexpr int n2 = hg + hg_bytes;                       // float [kSweepers][4][16]: shares of ||w||^2
+    static constexpr int corr = 0;                                 // (unused)
+    static constexpr int total = n2 + kSweepers * 4 * kM * 4;
+    // once the dependent rounds are done the Gram table's space holds the wavefronts' shares of W X^T
+    static constexpr int part = gd;
+};
+static_assert(LdsS::part + kSweepers * LdsS::tile_f <= LdsS::yb, "shares in the Gram table's space");
+
+struct SplitArgs {
+    WinPlanD plan;
+    int wu;                  // window whose rounds and step this launch works; -1: none (the call's first launch)
+    int chunks;              // workgroups per tile
+    const float *gram;       // of window wu
+    const float *pin;        // shares of W X_wu^T and ||W||^2, [tile][chunk][kShareFloats]
+    float *pout;             // ... of W X_{wu+1}^T
+    const float *ha_in, *hp_in;   // [R K]: the hint scalars before window wu
+    float *ha_out, *hp_out;
+};
+
+// A block of the sweep as a wavefront holds it: 16 coordinates of 16 learners (lane: 4 coordinates of one
+// learner), the rows of window wu in the order of (3) and those of window wu + 1 in the order of (1).
+struct SplitBlock { f4 v; float xu[16]; f4 xq[4]; };
+
+template <int LOSS, bool OPT>
+__global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs a, const SplitArgs sp)
+{
+    using Lds = LdsS;
+    constexpr int NT = kSW * kWave;
+    extern __shared__ __align__(16) char lds[];
+    const int d = a.d, K = a.K, nq = a.R * K;
+    const int nblk = (d + 15) / 16;
+    const int chunk = (int)blockIdx.x % sp.chunks, tile = (int)blockIdx.x / sp.chunks;
+    const int b_lo = (int)((int64_t)chunk * nblk / sp.chunks), b_hi = (int)((int64_t)(chunk + 1) * nblk / sp.chunks);
+    const int q_base = tile * kM;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const bool upd = sp.wu >= 0;                                    // uniform over the grid
+    const bool do_q = sp.wu + 1 < sp.plan.count();
+    const int wu_s = upd ? sp.plan.start(sp.wu) : 0, wu_l = upd ? sp.plan.len(sp.wu) : 0;
+    const int wq_s = do_q ? sp.plan.start(sp.wu + 1) : 0, wq_l = do_q ? sp.plan.len(sp.wu + 1) : 0;
+
+    // ---- inputs of the dependent rounds to LDS -----------------------------------------------------
+    if (upd) {
+        constexpr int kGPer = kB * kB / NT;                         // 8 consecutive entries of a row of G
+        f4 gv[kGPer / 4];
+#pragma unroll
+        for (int i = 0; i < kGPer / 4; ++i) gv[i] = *reinterpret_cast<const f4 *>(sp.gram + tid * kGPer + 4 * i);
+        float yv[kB * kM / NT];
+#pragma unroll
+        for (int i = 0; i < kB * kM / NT; ++i) {
+            const int e = tid + i * NT, l = e >> 6, t = e & 63, q = q_base + l;
+            yv[i] = (a.y && q < nq && t < wu_l) ? a.y[(int64_t)(q / K) * a.y_run_stride + wu_s + t] : 0.f;
+        }
+        // the chunks' shares, summed in chunk order
+        const float *p0 = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + tid * 2;
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll 16
+        for (int c = 0; c < sp.chunks; ++c) {
+            const float2 v = *reinterpret_cast<const float2 *>(p0 + (int64_t)c * kShareFloats);
+            s0 += (double)v.x;
+            s1 += (double)v.y;
+        }
+        double *q0d = reinterpret_cast<double *>(lds + Lds::q0);
+        q0d[tid * 2] = s0;
+        q0d[tid * 2 + 1] = s1;
+        double *gd = reinterpret_cast<double *>(lds + Lds::gd);
+        const int t = (tid * kGPer) >> 6, t2b = (tid * kGPer) & 63;
+#pragma unroll
+        for (int i = 0; i < kGPer; ++i) {                           // masked to t2 > t, the diagonal in the rows' padding
+            const int t2 = t2b + i;
+            const float v = gv[i >> 2][i & 3];
+            gd[(t * 4 + (i & 3)) * kGStride + (t2 >> 2)] = t2 > t ? (double)v : 0.0;
+            if (t2 == t) gd[t * 4 * kGStride + 16] = (double)v;
+        }
+        float *yb = reinterpret_cast<float *>(lds + Lds::yb);
+#pragma unroll
+        for (int i = 0; i < kB * kM / NT; ++i) {
+            const int e = tid + i * NT;
+            yb[(e & 63) * kM + (e >> 6)] = yv[i];
+        }
+        if (OPT && tid < kB) reinterpret_cast<float *>(lds + Lds::hg)[tid] = tid < wu_l ? a.g01[wu_s + tid] : 0.f;
+        __syncthreads();
+    }
+
+    // ---- the sweep's side: blocks b_lo + wave - 1, + kSweepers, ... --------------------------------
+    const int q_sw = q_base + lr;
+    const bool q_ok = q_sw < nq;
+    float *vrow = a.V + (int64_t)(q_ok ? q_sw : 0) * d + 4 * lk;
+    auto fetch = [&](int blk, SplitBlock &o) __attribute__((always_inline)) {
+        const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
+        const bool in4 = blk < b_hi && blk * 16 + 4 * lk < d, in1 = blk < b_hi && blk * 16 + lr < d;
+        o.v = (in4 && q_ok) ? *reinterpret_cast<const f4 *>(vrow + blk * 16) : zero;
+        if (upd) {
+            const float *x = a.x + (int64_t)wu_s * d + blk * 16 + lr;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int t = 4 * i + lk;
+                o.xu[i] = (in1 && t < wu_l) ? x[(int64_t)t * d] : 0.f;
+            }
+        }
+        if (do_q) {
+            const float *x = a.x + (int64_t)wq_s * d + blk * 16 + 4 * lk;
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb) {
+                const int t = 16 * rb + lr;
+                o.xq[rb] = (in4 && t < wq_l) ? *reinterpret_cast<const f4 *>(x + (int64_t)t * d) : zero;
+            }
+        }
+    };
+    SplitBlock pre[kPre];
+    if (wave == 0) {
+        if (upd) {
+            const int q = q_base + (lane >> 2);
+            // ||w||^2 of the stored iterates: a quad's lanes take every fourth chunk
+            const float *pn = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + kB * kM + (lane >> 2);
+            double n2 = 0.0;
+            for (int c = lane & 3; c < sp.chunks; c += 4) n2 += (double)pn[(int64_t)c * kShareFloats];
+            n2 = (quad_bcast<0>(n2) + quad_bcast<1>(n2)) + (quad_bcast<2>(n2) + quad_bcast<3>(n2));
+            float eta = 0.f;
+            Hint hint{0.f, 0.f, 0.f};
+            if (q < nq) {
+                eta = a.eta[q % K];
+                if (OPT) {
+                    hint.ha = sp.ha_in[q];
+                    hint.hp = sp.hp_in[q];
+                    hint.x2p = wu_s == 0 ? a.x2last[0] : a.x2[wu_s - 1];
+                }
+            }
+            bool projected;
+            (void)chain_window<LOSS, Lds, OPT>(lds, 0, 0, lane, wu_l, eta, (double)a.D, 1.0, 1.0, n2, projected, &hint);
+            if (OPT && chunk == 0 && q < nq && (lane & 3) == 0) {
+                sp.ha_out[q] = hint.ha;
+                sp.hp_out[q] = hint.hp;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kPre; ++i) fetch(b_lo + wave - 1 + kSweepers * i, pre[i]);
+    }
+    __syncthreads();
+
+    if (upd && chunk == 0) {                                        // the window's predictions
+        const float *zb = reinterpret_cast<const float *>(lds + Lds::zb);
+        for (int e = tid; e < kM * kB; e += NT) {
+            const int l = e >> 6, t = e & 63, q = q_base + l;
+            if (q < nq && t < wu_l)
+                a.Z[(int64_t)(q / K) * a.zl.zs_r + (int64_t)(q % K) * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = zb[t * kM + l];
+        }
+    }
+    if (wave != 0) {
+        float bmr[16];
+        float F = 1.f;
+        if (upd) {
+            const float *bml = reinterpret_cast<const float *>(lds + Lds::bm);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) bmr[i] = bml[(4 * i + lk) * kM + lr];
+            F = reinterpret_cast<const float *>(lds + Lds::fv)[lr];
+        } else if (q_ok) {
+            F = a.sigma[q_sw];                                      // the state's lazy scale goes into the iterates
+        }
+        f4 acc[4];
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) acc[rb] = f4{0.f, 0.f, 0.f, 0.f};
+        float nn = 0.f;
+        auto step = [&](int blk, SplitBlock &o) __attribute__((always_inline)) {
+            if (blk >= b_hi) return;                                // uniform over the wavefront
+            f4 vb = o.v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vb[r] *= F;
+            if (upd) {
+                f4 vo = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 16; i += 2) {
+                    vb = __builtin_amdgcn_mfma_f32_16x16x4f32(o.xu[i], bmr[i], vb, 0, 0, 0);
+                    vo = __builtin_amdgcn_mfma_f32_16x16x4f32(o.xu[i + 1], bmr[i + 1], vo, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) vb[r] += vo[r];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) nn = fmaf(vb[r], vb[r], nn);
+            if (q_ok && blk * 16 + 4 * lk < d) *reinterpret_cast<f4 *>(vrow + blk * 16) = vb;
+            if (do_q) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb)
+                        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.xq[rb][r], vb[r], acc[rb], 0, 0, 0);
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < kPre; ++i) step(b_lo + wave - 1 + kSweepers * i, pre[i]);
+        for (int blk = b_lo + wave - 1 + kSweepers * kPre; blk < b_hi; blk += kSweepers) {
+            fetch(blk, pre[0]);
+            step(blk, pre[0]);
+        }
+        float *part = reinterpret_cast<float *>(lds + Lds::part) + (wave - 1) * kB * kM;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[(rb * 16 + 4 * lk + r) * kM + lr] = acc[rb][r];
+        reinterpret_cast<float *>(lds + Lds::n2)[((wave - 1) * 4 + lk) * kM + lr] = nn;
+    }
+    __syncthreads();
+    float *po = sp.pout + (int64_t)blockIdx.x * kShareFloats;
+    if (do_q) {
+        const float *part = reinterpret_cast<const float *>(lds + Lds::part);
+#pragma unroll
+        for (int u = 0; u < kB * kM / NT; ++u) {
+            const int e = tid + u * NT;
+            double sum = 0.0;
+#pragma unroll
+            for (int v = 0; v < kSweepers; ++v) sum += (double)part[v * kB * kM + e];
+            po[e] = (float)sum;
+        }
+    }
+    if (tid < kM) {
+        const float *n2s = reinterpret_cast<const float *>(lds + Lds::n2) + tid;
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSweepers * 4; ++i) sum += (double)n2s[i * kM];
+        po[kB * kM + tid] = (float)sum;
+    }
+}
+
+// State out after the last window: the iterates carry scale 1, their squared norms from the chunks' shares.
+__global__ void __launch_bounds__(64) split_finish_kernel(const DenseArgs a, int chunks, const float *share, const float *ha, const float *hp)
+{
+    const int q = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (q >= a.R * a.K) return;
+    const float *pn = share + (int64_t)(q / kM) * chunks * kShareFloats + kB * kM + q % kM;
+    double n2 = 0.0;
+#pragma unroll 16
+    for (int c = 0; c < chunks; ++c) n2 += (double)pn[(int64_t)c * kShareFloats];
+    a.sigma[q] = 1.f;
+    a.n2[q] = n2;
+    if (a.optimistic) { a.ha[q] = ha[q]; a.hp[q] = hp[q]; }
+}
+
+// G = X_w X_w^T of window w0 + blockIdx.x over the depth blocks of chunk blockIdx.y, out[(window gridDim.y +
+// chunk) 4096].  The dependent rounds of a window read G[t][t2] for t2 >= t only: of the sixteen 16 x 16 blocks
+// the ten on and above the diagonal are taken, dealt to the four wavefronts, the others are left unwritten.
+// Every wavefront reads the 64 rows (from L1 for three of the four), two depth blocks ahead of its matrix instructions.
+__device__ __forceinline__ void gram_blocks(int wave, int (&ra)[3], int (&cb)[3])
+{
+    ra[0] = wave == 0 ? 0 : wave == 1 ? 1 : wave == 2 ? 2 : 3; cb[0] = ra[0];         // the diagonal
+    ra[1] = wave == 1 ? 1 : wave == 3 ? 2 : 0; cb[1] = wave == 0 ? 1 : wave == 1 ? 2 : 3;   // (0,1) (1,2) (0,3) (2,3)
+    ra[2] = wave == 1 ? 1 : 0; cb[2] = wave == 1 ? 3 : 2;                             // wavefronts 0, 1 only: (0,2) (1,3)
+}
+__global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, WinPlanD plan, int w0, float *out)
+{
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int w = w0 + (int)blockIdx.x, nblk = (d + 15) / 16;
+    const int ws = plan.start(w), wl = plan.len(w);
+    const int b_lo = (int)((int64_t)blockIdx.y * nblk / gridDim.y), b_hi = (int)((int64_t)(blockIdx.y + 1) * nblk / gridDim.y);
+    f4 acc[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) acc[b] = f4{0.f, 0.f, 0.f, 0.f};
+    const float *xr = x + (int64_t)ws * d + 4 * lk;
+    auto fetch = [&](int blk, f4 (&o)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int t = 16 * b + lr;
+            const bool ok = t < wl && blk < b_hi && blk * 16 + 4 * lk < d;
+            o[b] = ok ? *reinterpret_cast<const f4 *>(xr + (int64_t)t * d + blk * 16) : f4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    auto times = [&](auto wc, const f4 (&o)[4]) __attribute__((always_inline)) {
+        constexpr int W = decltype(wc)::value;
+        constexpr int ra1 = W == 1 ? 1 : W == 3 ? 2 : 0, cb1 = W == 0 ? 1 : W == 1 ? 2 : 3;
+        constexpr int ra2 = W == 1 ? 1 : 0, cb2 = W == 1 ? 3 : 2;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[W][r], o[W][r], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[ra1][r], o[cb1][r], acc[1], 0, 0, 0);
+            if (W < 2) acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[ra2][r], o[cb2][r], acc[2], 0, 0, 0);
+        }
+    };
+    auto depth = [&](auto wc) __attribute__((always_inline)) {
+        f4 o[4][4];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) fetch(b_lo + i, o[i]);
+        for (int blk = b_lo; blk < b_hi; blk += 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                           // (past b_hi: zeros)
+                fetch(blk + i + 3, o[(i + 3) & 3]);
+                times(wc, o[i]);
+            }
+        }
+    };
+    if (wave == 0) depth(std::integral_constant<int, 0>{});
+    else if (wave == 1) depth(std::integral_constant<int, 1>{});
+    else if (wave == 2) depth(std::integral_constant<int, 2>{});
+    else depth(std::integral_constant<int, 3>{});
+    int ra[3], cb[3];
+    gram_blocks(wave, ra, cb);
+    float *g = out + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * kB * kB;
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+        if (b < 2 || wave < 2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) g[(ra[b] * 16 + 4 * lk + r) * kB + cb[b] * 16 + lr] = acc[b][r];
+        }
+}
+
+// ... and the chunks' sum, in chunk order
+__global__ void __launch_bounds__(256) split_gram_sum_kernel(const float *part, int chunks, float *gram)
+{
+    const int e = (int)(blockIdx.x & 15) * 256 + threadIdx.x;
+    const int64_t w = blockIdx.x >> 4;
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) s += (double)part[(w * chunks + c) * kB * kB + e];
+    gram[w * kB * kB + e] = (float)s;
+}
+
+// How a call is laid out in the windowed kernels' scratch: two buffers of shares and of hint scalars, the Gram
+// matrices of `group` windows at a time and their partial sums.
+struct SplitPlan {
+    int tiles, chunks, gram_chunks, group;
+    size_t share_floats, hint_floats;
+    size_t cmp_off;          // where the comparator's partial sums start
+    int cmp_chunks;
+};
+bool make_split_plan(const DenseArgs &a, SplitPlan *p)
+{
+    const int nblk = (a.d + 15) / 16;
+    const int64_t nq = (int64_t)a.R * a.K;
+    p->tiles = (int)((nq + kM - 1) / kM);
+    if (p->tiles > 64) return false;
+    // (everything that decides how a sum is grouped follows from the configuration, not from the call: calls
+    // cut at multiples of 64 rounds then give the same bits)
+    const int nwin = (int)std::min<int64_t>(a.n_max / kB + 2, 1 << 20);
+    const size_t room = dense_window_scratch_floats(a.n_max, a.d);
+    p->hint_floats = (size_t)(nq + 63) / 64 * 64;
+    p->chunks = std::max(1, std::min({64, 256 / p->tiles, (nblk + kSweepers - 1) / kSweepers}));
+    if (p->chunks >= 8) p->chunks &= ~7;
+    for (;; --p->chunks) {
+        p->share_floats = (size_t)p->tiles * p->chunks * kShareFloats;
+        const size_t fixed = 2 * p->share_floats + 4 * p->hint_floats;
+        const size_t one = (size_t)2 * kB * kB;                   // a Gram matrix and one partial of it
+        if (fixed + one <= room) {
+            const size_t wins = (room - fixed) / (kB * kB);       // Gram-sized pieces left
+            const size_t all = (size_t)std::min(nwin, 256), per = wins / all;
+            p->gram_chunks = per < 2 ? 1 : std::max(1, std::min({32, nblk / 16, (int)std::min<size_t>(32, per - 1)}));
+            p->group = (int)std::min<size_t>(all, wins / (1 + p->gram_chunks));
+            if (p->group >= 1) {
+                // what is left takes the partial sums of the comparators' predictions, where their tiles
+                // (64 runs x 64 rounds) are too few for the chip
+                p->cmp_off = fixed + (size_t)p->group * (1 + p->gram_chunks) * kB * kB;
+                const int64_t tiles = ((a.n_max + 63) / 64) * (((int64_t)a.R + 63) / 64);
+                const int64_t fit = (int64_t)((room - p->cmp_off) / ((size_t)a.R * a.n_max));
+                p->cmp_chunks = (int)std::max<int64_t>(1, std::min<int64_t>({512 / tiles, (int64_t)a.d / 512, fit, 64}));
+                return true;
+            }
+        }
+        if (p->chunks <= 1) return false;
+    }
+}
+
+}  // namespace
+
+bool dense_split_wanted(const DenseArgs &a)
+{
+    if (!a.x_shared || !a.vec_ok || !a.gram || a.tune->get(OCO_OPT_DENSE_PATH) == 1) return false;
+    const int64_t ropt = a.tune->get(OCO_OPT_WINDOW_RESIDENT);
+    if (ropt != -1 && ropt != 5) return false;
+    SplitPlan p;
+    if (!make_split_plan(a, &p)) return false;
+    // Measured per call of 2048 rounds, register kernel (d <= 4096) or dense_window_kernel against this one, ms:
+    // d = 512 0.69 / 0.67 (4 learners) and 0.85 / 0.77 (1024); d = 1024 1.12 / 0.71 and 1.38 / 0.82; d = 4096
+    // 2.10 / 0.77 and 2.99 / 1.29; of 640 rounds, d = 8192 2.51 / 0.36 (2 learners) and 2.61 / 0.72 (1024),
+    // d = 65536 28.6 / 4.5 (1024).  A call costs about 60 us here whatever its length, hence the least n; one
+    // that need not come here (d <= 4096) stays with the register kernel, whose results no cut of the horizon changes.
+    return ropt == 5 || a.d > 64 * kWave || (a.d > 512 && a.n >= 512 && a.tune->get(OCO_OPT_DENSE_PATH) < 0);
+}
+
+hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook)
+{
+    if (a.n <= 0) return hipSuccess;
+    SplitPlan p;
+    if (!make_split_plan(a, &p)) return hipErrorInvalidValue;
+    const WinPlanD plan{a.t0, a.n};
+    const int nwin = plan.count();
+    float *share[2] = {a.gram, a.gram + p.share_floats};
+    float *hint0 = share[1] + p.share_floats;
+    float *gram = hint0 + 4 * p.hint_floats, *gpart = gram + (size_t)p.group * kB * kB;
+    const bool beside = hook && hook->fn && hook->beside && a.n >= 512;
+    ComparatorGemmArgs g{};
+    g.x = a.x; g.u = a.u; g.seg_start = a.seg_start; g.S = a.S; g.Z = a.Z; g.zl = a.zl;
+    g.d = a.d; g.K = a.K; g.R = a.R; g.t0 = a.t0; g.n = a.n; g.vec_ok = a.vec_ok;
+    g.chunks = p.cmp_chunks; g.part = a.gram + p.cmp_off;
+    hipStream_t cs = s;
+    hipError_t e = beside ? hook->beside(hook->ctx, &cs) : hipSuccess;   // only the meta kernel reads its output
+    if (e == hipSuccess) e = launch_comparator_gemm(g, cs);
+    if (e == hipSuccess && a.optimistic) e = launch_hint_scalars(a, s);
+    if (e != hipSuccess) return e;
+    void (*kern)(const DenseArgs, const SplitArgs) = nullptr;
+    switch (loss * 2 + (a.optimistic ? 1 : 0)) {
+        case 0: kern = dense_split_kernel<0, false>; break;
+        case 1: kern = dense_split_kernel<0, true>; break;
+        case 2: kern = dense_split_kernel<1, false>; break;
+        case 3: kern = dense_split_kernel<1, true>; break;
+        case 4: kern = dense_split_kernel<2, false>; break;
+        case 5: kern = dense_split_kernel<2, true>; break;
+        default: return hipErrorInvalidValue;
+    }
+    if (a.tune->get(OCO_OPT_VERBOSE) == 1)
+        fprintf(stderr, "dense plan: windowed contraction kernel, %d windows, %d tiles in %d chunks of coordinates, Gram matrices of %d windows at a time in %d chunks\n",
+                nwin, p.tiles, p.chunks, p.group, p.gram_chunks);
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LdsS::total);
+    if (e != hipSuccess) return e;
+    int done = 0;                                                   // rounds handed to the hook
+    for (int w = -1; w < nwin; ++w) {
+        const int in_group = w < 0 ? 0 : w % p.group;
+        if (w >= 0 && in_group == 0) {
+            const int nw = std::min(p.group, nwin - w);
+            float *to = p.gram_chunks > 1 ? gpart : gram;
+            hipLaunchKernelGGL(split_gram_kernel, dim3((unsigned)nw, (unsigned)p.gram_chunks), dim3(256), 0, s, a.x, a.d, plan, w, to);
+            if (p.gram_chunks > 1)
+                hipLaunchKernelGGL(split_gram_sum_kernel, dim3((unsigned)nw * 16), dim3(256), 0, s, gpart, p.gram_chunks, gram);
+        }
+        SplitArgs sp{};
+        sp.plan = plan; sp.wu = w; sp.chunks = p.chunks;
+        sp.gram = gram + (size_t)in_group * kB * kB;
+        sp.pin = share[w & 1]; sp.pout = share[(w + 1) & 1];
+        float *hin = hint0 + (size_t)(w & 1) * 2 * p.hint_floats, *hout = hint0 + (size_t)((w + 1) & 1) * 2 * p.hint_floats;
+        sp.ha_in = w == 0 ? a.ha : hin; sp.hp_in = w == 0 ? a.hp : hin + p.hint_floats;
+        sp.ha_out = hout; sp.hp_out = hout + p.hint_floats;
+        e = clock_begin(a.clock, s, "dense_split_kernel");
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles * p.chunks)), dim3(kSW * kWave), LdsS::total, s, a, sp);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = clock_end(a.clock, s);
+        if (e == hipSuccess && beside && w >= 0) {
+            const int end = plan.start(w) + plan.len(w);
+            if (w + 1 == nwin || end - done >= 1024) {
+                e = hook->fn(hook->ctx, done, end - done);
+                done = end;
+            }
+        }
+        if (e != hipSuccess) return e;
+    }
+    const int nq = a.R * a.K;
+    const float *hl = hint0 + (size_t)(nwin & 1) * 2 * p.hint_floats;
+    hipLaunchKernelGGL(split_finish_kernel, dim3((unsigned)((nq + 63) / 64)), dim3(64), 0, s, a, p.chunks, share[nwin & 1], hl, hl + p.hint_floats);
+    e = hipGetLastError();
+    if (e != hipSuccess || !a.optimistic) return e;
+    return launch_keep_last_row(a, s);
+}
+
+}  // namespace oco

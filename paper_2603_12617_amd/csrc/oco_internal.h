@@ -118,6 +118,9 @@ hipError_t launch_dense_rounds(const DenseArgs &a, int loss, hipStream_t s, cons
 // the windowed path (dense_window.hip): whether a configuration takes it, and its launcher
 bool dense_window_wanted(const DenseArgs &a);
 hipError_t launch_dense_window(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
+// the windowed path with a tile's coordinates split over workgroups (dense_split.hip)
+bool dense_split_wanted(const DenseArgs &a);
+hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
 hipError_t launch_hint_scalars(const DenseArgs &a, hipStream_t s);
 hipError_t launch_keep_last_row(const DenseArgs &a, hipStream_t s);
 size_t dense_gram_bytes(int64_t n_max, int64_t d);
@@ -134,6 +137,8 @@ struct ComparatorGemmArgs {
     int64_t t0;
     int n;
     int vec_ok;              // rows of x and u are 16-byte aligned and d % 4 == 0
+    int chunks = 1;          // ranges of coordinates summed apart, with
+    float *part = nullptr;   // chunks R n floats of scratch (null: one range)
 };
 hipError_t launch_comparator_gemm(const ComparatorGemmArgs &a, hipStream_t s);
 bool dense_supported(int64_t d, int x_shared);

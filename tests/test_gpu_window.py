@@ -185,3 +185,33 @@ def test_option_errors():
         B.oco_run_rounds(sim.h, 0, 10, x_ptr=sim.x.data_ptr() + 4, y=sim.y)   # rows not 16-byte aligned
     assert e.value.status == B.OCO_EUNSUPPORTED
     sim.close()
+
+
+# a tile's coordinates split over workgroups (the default beyond d = 4096 for at most 64 tiles): more learners than
+# a tile, fewer coordinates than a workgroup has wavefronts for, a last block that is not full, ragged windows,
+# a call in several groups of Gram matrices, the optimistic update
+@pytest.mark.parametrize("name,over", [
+    ("c1", dict(T=257, d=64, R=3)),
+    ("c3", dict(T=65, R=2, d=4, K=2, seg_len=10)),
+    ("c3", dict(T=1000, R=3, d=132, K=17, seg_len=100)),
+    ("c4", dict(T=301, R=3, d=4096, K=16)),
+    ("c4", dict(T=200, R=40, d=1024, K=16)),
+    ("c3", dict(T=640, R=1, d=8204, K=3, seg_len=64)),
+    ("c4", dict(T=130, R=5, d=16384, K=16)),
+    ("c1", dict(T=20000, d=8, R=1)),
+])
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_coordinates_split_over_workgroups_match_the_oracle(name, over, optimistic):
+    wl = WL.make(name, optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    print("case split", name, over, "optimistic", optimistic, flush=True)
+    opt = dict(window_resident=5)
+    got = _gpu(wl, data, options=opt)
+    _check(wl, data, got, label="split %s %s optimistic=%d" % (name, over, optimistic))
+    again = _gpu(wl, data, options=opt)
+    part = _gpu(wl, data, chunk=100, n_max=100, options=opt)
+    for k in ("regret", "L", "W", "p", "wbar"):
+        assert np.array_equal(got[k], again[k]), k
+        scale = max(1.0, float(np.abs(got[k]).max()))
+        # other cuts regroup float32 sums: the bound of the other windowed kernels, twice for the regret's second sum
+        np.testing.assert_allclose(part[k], got[k], rtol=0, atol=4e-6 * scale, err_msg=k)
