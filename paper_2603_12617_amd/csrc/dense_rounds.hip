@@ -138,18 +138,34 @@ template <int VW> __device__ __forceinline__ float combine(const float (&acc)[VW
     return acc[0];
 }
 
+// Tile k of the ring for rows that are not 16-byte aligned (any d, any 4-byte address): copied straight to LDS
+// like the aligned ones, a word per lane and 64 words of a row per instruction.  Four times the copy
+// instructions of the aligned tiles, but asynchronous like those: read into registers and written to LDS,
+// every tile waited for its own loads (d = 777, 240 learners: 1.6 us per round, now 0.8).  (A scalar row address
+// with a lane offset, for these and the aligned copies: 5 % slower, the scalar index arithmetic is as long.)
+template <int DP>
+__device__ __forceinline__ void stage_words(const float *xg, int d, int n, int k, int RT, float *dst, int wave, int wpb, int lane)
+{
+    static_assert(DP % kWave == 0, "an instruction stays inside a row");
+    for (int ii = wave; ii < RT * (DP / kWave); ii += wpb) {
+        const int rr = ii / (DP / kWave), j = (ii % (DP / kWave)) * kWave + lane;
+        const int tt = k * RT + rr;
+        if (tt < n && j < d)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(xg + (int64_t)tt * d + j),
+                                             (__attribute__((address_space(3))) void *)(dst + ii * kWave), 4, 0, 0);
+    }
+}
+
 template <int NPL, int LOSS, bool OPT>
 __global__ void __launch_bounds__(DenseCfg<NPL>::MAXW * kWave)
 dense_rounds_kernel(const DenseArgs a)
 {
-    using C = DenseCfg<NPL>;
     constexpr int VW = NPL >= 4 ? 4 : NPL;      // floats per LDS read
     constexpr int NV = NPL / VW;                // LDS reads per lane and round
     constexpr int DP = NPL * kWave;             // padded dimension
-    constexpr int RT = C::RT;
-    constexpr int TILE = RT * DP;               // floats per tile
-    constexpr int RING_ROUNDS = kRing * RT;
-    constexpr int NI = TILE / 4 / kWave;        // 1 KB copy instructions per tile
+    const int RT = a.rt;                        // rounds per tile: even, divides 64 (tile_rounds)
+    const int TILE = RT * DP;                   // floats per tile
+    const int NI = TILE / 4 / kWave;            // 1 KB copy instructions per tile
     constexpr int CH = NV >= 2 ? 2 : 1;         // LDS reads per chunk
 #ifndef OCO_NACC64
 #define OCO_NACC64 4
@@ -158,8 +174,8 @@ dense_rounds_kernel(const DenseArgs a)
     // chains would get 32 FMAs long
     constexpr int NACC = NPL >= 64 ? OCO_NACC64 : (VW >= 2 ? 2 : 1);
     constexpr int NCH = NV / CH;
-    static_assert(TILE % (4 * kWave) == 0, "tile must be a whole number of 1 KB copies");
-    static_assert(RT % 2 == 0, "the round loop is unrolled by two");
+    static_assert(DenseCfg<NPL>::RT * DP % (4 * kWave) == 0, "tile must be a whole number of 1 KB copies");
+    static_assert(DenseCfg<NPL>::RT % 2 == 0, "the round loop is unrolled by two");
     using V = typename VecT<VW>::type;
 
     extern __shared__ float4 smem4[];
@@ -204,12 +220,8 @@ dense_rounds_kernel(const DenseArgs a)
                         (const __attribute__((address_space(1))) void *)(xg + (int64_t)tt * d + j4 * 4),
                         (__attribute__((address_space(3))) void *)(dst + ii * 4 * kWave), 16, 0, 0);
             }
-        } else {                                               // any d, any alignment
-            for (int e = tid; e < TILE; e += nthreads) {
-                const int rr = e / DP, j = e % DP;
-                const int tt = k * RT + rr;
-                if (tt < n && j < d) dst[e] = xg[(int64_t)tt * d + j];
-            }
+        } else {
+            stage_words<DP>(xg, d, n, k, RT, dst, wave, wpb, lane);
         }
     };
 
@@ -221,7 +233,7 @@ dense_rounds_kernel(const DenseArgs a)
     if (ntiles > 1) issue_tile(1);
     tile_sync();
 
-    auto xrow = [&](int t) { return reinterpret_cast<const V *>(ring + (t % RING_ROUNDS) * DP); };
+    const V *row0 = reinterpret_cast<const V *>(ring);
     const float *yrow = a.y ? a.y + (int64_t)r * a.y_run_stride : nullptr;
 
     // Each role runs its own copy of the tile loop (same number of barriers in each), so
@@ -265,11 +277,12 @@ dense_rounds_kernel(const DenseArgs a)
         while (seg + 1 < a.S && a.seg_start[seg + 1] <= a.t0) ++seg;
         int64_t next_seg = seg + 1 < a.S ? a.seg_start[seg + 1] : INT64_MAX;   // absolute round
         load_u(seg);
-        float z = dot_u(xrow(0)), zreg = 0.f;
+        float z = dot_u(row0), zreg = 0.f;
         float *zrow = a.Z + (int64_t)r * a.zl.zs_r + (int64_t)K * a.zl.zs_i;
         for (int k = 0; k < ntiles; ++k) {
             if (k + 2 < ntiles) issue_tile(k + 2);
             const int rmax = min(RT, n - k * RT);
+            const float *rows = ring + (k % kRing) * TILE, *rows_next = ring + ((k + 1) % kRing) * TILE;
 #pragma unroll 1
             for (int rr = 0; rr < rmax; ++rr) {
                 const int t = k * RT + rr;
@@ -279,7 +292,7 @@ dense_rounds_kernel(const DenseArgs a)
                     next_seg = seg + 1 < a.S ? a.seg_start[seg + 1] : INT64_MAX;
                     load_u(seg);
                 }
-                z = dot_u(xrow(t + 1));
+                z = dot_u(reinterpret_cast<const V *>(rr + 1 < RT ? rows + (rr + 1) * DP : rows_next));
                 if ((t & 63) == 63 || t == n - 1) {
                     const int tb = t & ~63;
                     if (tb + lane <= t) zrow[(int64_t)(tb + lane) * a.zl.zs_t] = zreg;
@@ -316,7 +329,7 @@ dense_rounds_kernel(const DenseArgs a)
         for (int e = 0; e < VW; ++e) acc[e] = 0.f;
 #pragma unroll
         for (int m = 0; m < NV; ++m) {
-            unpack<VW>(xrow(0)[m * kWave + lane], xa[m]);
+            unpack<VW>(row0[m * kWave + lane], xa[m]);
 #pragma unroll
             for (int e = 0; e < VW; ++e) {
                 const int j = (m * kWave + lane) * VW + e;
@@ -491,7 +504,7 @@ dense_rounds_kernel(const DenseArgs a)
         }
     };
 
-    static_assert(64 % RT == 0, "tiles do not straddle the 64-round groups of labels and predictions");
+    static_assert(64 % DenseCfg<NPL>::RT == 0, "tiles do not straddle the 64-round groups of labels and predictions");
     for (int k = 0; k < ntiles; ++k) {
         if (k + 2 < ntiles) issue_tile(k + 2);
         const int t0 = k * RT;
@@ -616,11 +629,7 @@ dense_rounds_half_kernel(const DenseArgs a)
                         (__attribute__((address_space(3))) void *)(dst + ii * 4 * kWave), 16, 0, 0);
             }
         } else {
-            for (int e = tid; e < TILE; e += nthreads) {
-                const int rr = e / DP, j = e % DP;
-                const int tt = k * RT + rr;
-                if (tt < n && j < d) dst[e] = xg[(int64_t)tt * d + j];
-            }
+            stage_words<DP>(xg, d, n, k, RT, dst, wave, wpb, lane);
         }
     };
 
@@ -851,10 +860,24 @@ struct DensePlan {
     void (*kern)(const DenseArgs) = nullptr;
     size_t smem = 0;
     int wpb = 0;              // wavefronts per workgroup
+    int rt = 0;               // rounds per tile of the ring
     int64_t nwg = 0;          // workgroups
     int64_t batches = 0;      // passes the grid needs when the chip cannot hold it at once
     double cost = 0.0;        // modelled duration, in units of one lightly loaded pass
 };
+
+// Rounds per tile.  A tile is waited for at the end of the tile before it, so a tile has to last as long as a load
+// from HBM takes (1 - 2 us) or every tile waits for the rest; the tiles of DenseCfg last that long only beside other
+// wavefronts (two rounds of d = 1024: 1 us).  Where the grid leaves LDS idle -- `resident` workgroups per compute
+// unit are all it needs -- tiles grow into it, to at most 32 rounds: no result depends on their length.
+// Measured, streams of their own, 2000 rounds: 48 runs of 5 learners, d = 777 0.80 -> 0.68 us per round; 64 runs of 15,
+// d = 1000 0.73 -> 0.53, d = 2048 1.01 -> 0.84; one run of 4, d = 1000 0.53 -> 0.41.
+int tile_rounds(int rt, size_t round_bytes, int64_t resident)
+{
+    const size_t room = (size_t)(160 * 1024) / (size_t)std::max<int64_t>(1, resident);
+    while (rt < 32 && kRing * 2 * (size_t)rt * round_bytes <= room) rt *= 2;
+    return rt;
+}
 
 template <int NPL>
 hipError_t plan_npl(const DenseArgs &a, int loss, DensePlan *plan)
@@ -871,9 +894,9 @@ hipError_t plan_npl(const DenseArgs &a, int loss, DensePlan *plan)
         case 5: kern = dense_rounds_kernel<NPL, 2, true>; break;
         default: return hipErrorInvalidValue;
     }
-    if (smem > 64 * 1024) {
+    {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
     }
     int dev = 0, ncu = 256;
@@ -925,10 +948,12 @@ hipError_t plan_npl(const DenseArgs &a, int loss, DensePlan *plan)
                                                      smem) != hipSuccess || c <= 0)
         c = 1;
     plan->kern = kern;
-    plan->smem = smem;
     plan->wpb = best;
     plan->nwg = a.x_shared ? ((int64_t)a.R * per_run + best - 1) / best
                            : (int64_t)a.R * ((per_run + best - 1) / best);
+    const size_t round_bytes = sizeof(float) * NPL * kWave;
+    plan->rt = tile_rounds(C::RT, round_bytes, std::min<int64_t>(c, (plan->nwg + ncu - 1) / ncu));
+    plan->smem = kRing * plan->rt * round_bytes;
     plan->batches = ((plan->nwg + ncu - 1) / ncu + c - 1) / c;
     return hipSuccess;
 }
@@ -1121,14 +1146,14 @@ hipError_t launch_dense_rounds(const DenseArgs &a0, int loss, hipStream_t s, con
     DensePlan plan;
     if (a.plan->valid) {
         plan.kern = reinterpret_cast<void (*)(const DenseArgs)>(const_cast<void *>(a.plan->kern));
-        plan.smem = a.plan->smem; plan.wpb = a.plan->wpb; plan.nwg = a.plan->nwg;
+        plan.smem = a.plan->smem; plan.wpb = a.plan->wpb; plan.rt = a.plan->rt; plan.nwg = a.plan->nwg;
         plan.batches = a.plan->batches;
         a.per_run = a.plan->per_run;
     } else {
         hipError_t e = make_dense_plan(a, loss, &plan);
         if (e != hipSuccess) return e;
         a.plan->kern = reinterpret_cast<const void *>(plan.kern);
-        a.plan->smem = plan.smem; a.plan->wpb = plan.wpb; a.plan->nwg = plan.nwg;
+        a.plan->smem = plan.smem; a.plan->wpb = plan.wpb; a.plan->rt = plan.rt; a.plan->nwg = plan.nwg;
         a.plan->batches = plan.batches; a.plan->per_run = a.per_run;
         a.plan->valid = true;
     }
@@ -1155,6 +1180,7 @@ hipError_t launch_dense_rounds(const DenseArgs &a0, int loss, hipStream_t s, con
     for (int64_t off = 0; off < a.n; off += step) {
         const int64_t len = std::min<int64_t>(step, a.n - off);
         DenseArgs b = a;
+        b.rt = plan.rt;
         b.x = a.x + off * a.d; b.t0 = a.t0 + off; b.n = (int)len;
         if (b.y) b.y = a.y + off;
         b.x2 = a.x2 + off;

@@ -32,7 +32,7 @@ struct DensePlanCache {
     bool valid = false;
     const void *kern = nullptr;
     size_t smem = 0;
-    int wpb = 0;
+    int wpb = 0, rt = 0;
     int64_t nwg = 0, batches = 0;
     int per_run = 0;
 };
@@ -101,6 +101,7 @@ struct DenseArgs {
     int vec_ok;              // rows of x are 16-byte aligned and d % 4 == 0
     int per_run;             // wavefront tasks per run: K + 1 with the comparator's, K when its
                              // predictions come from the contraction kernel (set by the launcher)
+    int rt;                  // rounds per tile of the register kernel's ring (set by the launcher)
     // optimistic two-step update (Eq. (3)); V then holds the intermediate model w^
     int optimistic;
     float *ha;               // [R][K]  eta_i c_{t-1}^i: the hint is ha * x_{t-1}

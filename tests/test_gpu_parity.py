@@ -495,6 +495,32 @@ def test_results_do_not_depend_on_how_a_call_is_enqueued(name, over):
     sim.close()
 
 
+# every coordinates-per-lane variant, a tile shorter / longer than the call, learners that share a tile with others
+# and (many runs) tiles that have not grown
+@pytest.mark.parametrize("d,R,K,n", [(64, 3, 2, 130), (100, 2, 15, 333), (200, 70, 15, 70), (512, 3, 4, 65), (1000, 5, 5, 301),
+                                     (2048, 2, 3, 131), (4092, 1, 2, 67)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_rounds_do_not_depend_on_the_alignment_of_the_stream(d, R, K, n, shared):
+    """Rows that do not start on 16 bytes are copied to LDS word by word; the arithmetic is the same, and so
+    are all bits (the comparators' predictions taken in the round kernel in both)."""
+    wl = WL.make("c2", T=n, d=d, R=R, K=K, x_shared=shared)
+    data = WL.generate(wl)
+    out = []
+    for shift in (0, 1, 3):
+        sim = B.Simulation(wl, data, options=dict(dense_path=1, comparator_gemm=0, dense_half=0))
+        flat = sim.torch.zeros(sim.x.numel() + 4, dtype=sim.torch.float32, device=sim.dev)
+        flat[shift:shift + sim.x.numel()] = sim.x.reshape(-1)
+        B.oco_run_rounds(sim.h, 0, n, x_ptr=flat.data_ptr() + 4 * shift, x_run_stride=0 if shared else n * d, y=sim.y)
+        got = dict(regret=sim.regret(), L=sim.cum_losses())
+        got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+        sim.close()
+        out.append(got)
+    _check(wl, data, out[0], label="aligned d=%d" % d)
+    for got in out[1:]:
+        for k in got:
+            assert np.array_equal(got[k], out[0][k]), k
+
+
 def test_degenerate_inputs():
     # T = 1
     wl = WL.make("c2", T=1, R=2, d=8, K=3)
