@@ -156,6 +156,93 @@ __device__ __forceinline__ void stage_words(const float *xg, int d, int n, int k
     }
 }
 
+// ||x||^2 of a round row and, if prev is given, its inner product with the row before: one wavefront, fixed order
+// (one chain per sum; the loads of sixteen steps are issued together).
+__device__ __forceinline__ void row_scalars(const float *src, const float *prev, int d, int lane, float &x2, float &g01)
+{
+    constexpr int U = 16;
+    float acc = 0.f, ac2 = 0.f;
+    int j = lane;
+    for (; j + 64 * (U - 1) < d; j += 64 * U) {
+        float v[U], w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { v[u] = src[j + 64 * u]; w[u] = prev ? prev[j + 64 * u] : 0.f; }
+#pragma unroll
+        for (int u = 0; u < U; ++u) { acc = fmaf(v[u], v[u], acc); ac2 = fmaf(w[u], v[u], ac2); }
+    }
+    for (int j0 = j; j0 < d; j0 += 64 * U) {               // the rest of the row (adds of +0 past it change no bit of a sum
+        float v[U], w[U];                                  // of squares, and of the other at most the sign of a zero)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = j0 + 64 * u < d;
+            v[u] = in ? src[j0 + 64 * u] : 0.f;
+            w[u] = in && prev ? prev[j0 + 64 * u] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) { acc = fmaf(v[u], v[u], acc); ac2 = fmaf(w[u], v[u], ac2); }
+    }
+    x2 = wave_sum(acc);
+    if (prev) g01 = wave_sum(ac2);
+}
+
+// ---- short calls -----------------------------------------------------------------------------
+// A serving loop updates a learner after every few verification steps: calls of a handful of rounds, in which
+// the launches around the rounds (norms, meta kernel on the second stream with its two waits, last row) are most
+// of the time (one run of 3 learners, d = 1000, 8 rounds: 53 us per call of which the rounds are 8).  For at most
+// kWholeRounds rounds, where a run's wavefronts fit one workgroup and the grid leaves the chip mostly idle, the
+// workgroup of a run does that work itself; same arithmetic in the same order as the kernels it replaces (meta.hip),
+// so the bits do not depend on how a horizon is cut.
+constexpr int kWholeRounds = 64;
+
+// LDS words behind the ring: ||x_t||^2, then <x_{t-1}, x_t>
+constexpr int kWholeFloats = 2 * kWholeRounds;
+
+// The meta kernel's work on run r for the n rounds of a short call: called by all wavefronts (wavefront i holds the
+// predictions of learner i, i = K the comparator, a round per lane; those behind only help) once the ring's space is free.
+template <int LOSS>
+__device__ __forceinline__ void whole_meta(const DenseArgs &a, float *ring, int r, int i, int lane, float zreg)
+{
+    const int K = a.K, n = a.n;
+    float *zs = ring;                                               // [K + 1][64]
+    double *lm = reinterpret_cast<double *>(ring + (K + 1) * 64);   // [n][K]: losses, then cumulative losses before the round
+    double *diff = lm + 64 * K;
+    const float *yrow = a.y ? a.y + (int64_t)r * a.y_run_stride : nullptr;
+    const double yt = (yrow && lane < n) ? (double)yrow[lane] : 0.0;
+    if (i <= K) zs[i * 64 + lane] = zreg;
+    if (i < K && lane < n) lm[lane * K + i] = phi<LOSS>((double)zreg, yt);
+    __syncthreads();
+    const bool hint = a.last != nullptr;
+    if (i == 0 && lane < K) {                                       // running sums in round order
+        double Lacc = a.L[(int64_t)r * K + lane], lprev = hint ? a.last[(int64_t)r * K + lane] : 0.0;
+        for (int t = 0; t < n; ++t) {
+            const double l = lm[t * K + lane];
+            lm[t * K + lane] = hint ? Lacc + lprev : Lacc;
+            Lacc += l;
+            lprev = l;
+        }
+        a.L[(int64_t)r * K + lane] = Lacc;
+        if (hint) a.last[(int64_t)r * K + lane] = lprev;
+    }
+    __syncthreads();
+    if (i == 0 && lane < n) {
+        double Lmin = lm[lane * K];
+        for (int k = 1; k < K; ++k) Lmin = fmin(Lmin, lm[lane * K + k]);
+        double S = 0.0, zsum = 0.0;
+        for (int k = 0; k < K; ++k) {
+            const double e = exp(-a.eps * (lm[lane * K + k] - Lmin));
+            S += e;
+            zsum += e * (double)zs[k * 64 + lane];
+        }
+        diff[lane] = phi<LOSS>(zsum / S, yt) - phi<LOSS>((double)zs[K * 64 + lane], yt);
+    }
+    __syncthreads();
+    if (i == 0 && lane == 0) {
+        double reg = a.regret[r];
+        for (int t = 0; t < n; ++t) reg += diff[t];
+        a.regret[r] = reg;
+    }
+}
+
 template <int NPL, int LOSS, bool OPT>
 __global__ void __launch_bounds__(DenseCfg<NPL>::MAXW * kWave)
 dense_rounds_kernel(const DenseArgs a)
@@ -193,7 +280,11 @@ dense_rounds_kernel(const DenseArgs a)
     // ---- which task this wavefront owns: learner i < K, or the comparator (i == K) ----
     int r, i;
     bool active;
-    if (a.x_shared) {
+    if (a.whole) {                              // a workgroup per run; wavefronts behind the run's tasks stage rows
+        r = a.x_shared ? blockIdx.x : blockIdx.y;
+        i = wave;
+        active = i < a.per_run;
+    } else if (a.x_shared) {
         const int64_t q = (int64_t)blockIdx.x * wpb + wave;
         active = q < (int64_t)a.R * a.per_run;
         r = active ? (int)(q / a.per_run) : 0;
@@ -226,11 +317,20 @@ dense_rounds_kernel(const DenseArgs a)
     };
 
     // padding coordinates (j >= d) of the ring are never written again: zero them once
-    for (int e = tid; e < kRing * TILE / 4; e += nthreads) smem4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-    tile_sync();
     const int ntiles = (n + RT - 1) / RT;
+    for (int e = tid; e < min(kRing, ntiles + 1) * TILE / 4; e += nthreads) smem4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    tile_sync();
     issue_tile(0);
     if (ntiles > 1) issue_tile(1);
+    float *whole_x2 = ring + kRing * TILE;
+    if (a.whole) {
+        for (int t = wave; t < n; t += wpb) {
+            const float *src = xg + (int64_t)t * d;
+            float x2, g01 = 0.f;
+            row_scalars(src, OPT ? (t > 0 ? src - d : a.xlast + (a.x_shared ? 0 : (int64_t)r * d)) : nullptr, d, lane, x2, g01);
+            if (lane == 0) { whole_x2[t] = x2; whole_x2[kWholeRounds + t] = g01; }
+        }
+    }
     tile_sync();
 
     const V *row0 = reinterpret_cast<const V *>(ring);
@@ -243,6 +343,7 @@ dense_rounds_kernel(const DenseArgs a)
             if (k + 2 < ntiles) issue_tile(k + 2);
             tile_sync();
         }
+        if (a.whole) whole_meta<LOSS>(a, ring, r, i, lane, 0.f);
         return;
     }
 
@@ -293,13 +394,14 @@ dense_rounds_kernel(const DenseArgs a)
                     load_u(seg);
                 }
                 z = dot_u(reinterpret_cast<const V *>(rr + 1 < RT ? rows + (rr + 1) * DP : rows_next));
-                if ((t & 63) == 63 || t == n - 1) {
+                if (!a.whole && ((t & 63) == 63 || t == n - 1)) {
                     const int tb = t & ~63;
                     if (tb + lane <= t) zrow[(int64_t)(tb + lane) * a.zl.zs_t] = zreg;
                 }
             }
             tile_sync();
         }
+        if (a.whole) whole_meta<LOSS>(a, ring, r, i, lane, zreg);
         return;
     }
 
@@ -434,12 +536,17 @@ dense_rounds_kernel(const DenseArgs a)
     // 64), so the tile loop does them and a round does not test for them.
     auto load_round_scalars = [&](int t) {
         if (yrow) yreg = (t + lane < n) ? yrow[t + lane] : 0.f;
+        if (a.whole) {
+            x2reg = (lane < n) ? whole_x2[lane] : 0.f;
+            if (OPT) g01reg = (lane < n) ? whole_x2[kWholeRounds + lane] : 0.f;
+            return;
+        }
         x2reg = (t + lane < n) ? x2row[t + lane] : 0.f;
         if (OPT) g01reg = (t + lane < n) ? g01row[t + lane] : 0.f;
     };
     auto flush_predictions = [&](int t) {
         const int tb = t & ~63;
-        if (tb + lane <= t) zrow[(int64_t)(tb + lane) * a.zl.zs_t] = zreg;
+        if (tb + lane <= t && !a.whole) zrow[(int64_t)(tb + lane) * a.zl.zs_t] = zreg;
     };
     // one round: consumes xc = x_t, fills xn = x_{t+1} from xnext; remeasure: ||v||^2 is summed afresh after the step
     auto round = [&](int t, const V *xnext, bool remeasure, float (&xc)[NV][VW], float (&xn)[NV][VW]) {
@@ -542,6 +649,16 @@ dense_rounds_kernel(const DenseArgs a)
             }
         if (lane == 0) { a.sigma[(int64_t)r * K + i] = sigma; a.n2[(int64_t)r * K + i] = (double)n2; }
         if (OPT && lane == 0) { a.ha[(int64_t)r * K + i] = ha; a.hp[(int64_t)r * K + i] = hp; }
+    }
+    if (a.whole) {
+        whole_meta<LOSS>(a, ring, r, i, lane, zreg);
+        // the last row, for the next call's hint (the only workgroup that read the old one; the launcher does not
+        // send a shared stream of several runs here)
+        if (OPT && i == 0) {
+            const int64_t rr = a.x_shared ? 0 : r;
+            for (int j = lane; j < d; j += kWave) a.xlast[rr * d + j] = xg[(int64_t)(n - 1) * d + j];
+            if (lane == 0) a.x2last[rr] = whole_x2[n - 1];
+        }
     }
 }
 
@@ -823,16 +940,11 @@ __global__ void __launch_bounds__(256) xnorm2_kernel(const float *x, int64_t run
     if (row >= (int64_t)nruns * n) return;
     const int rr = (int)(row / n), t = (int)(row % n);
     const float *src = x + (int64_t)rr * run_stride + (int64_t)t * d;
-    float acc = 0.f;
-    for (int j = lane; j < d; j += 64) acc = fmaf(src[j], src[j], acc);
-    const float tot = wave_sum(acc);
-    if (lane == 0) out[(int64_t)rr * out_stride + t] = tot;
-    if (g01) {
-        const float *prev = t > 0 ? src - d : xlast + (int64_t)rr * d;
-        float ac2 = 0.f;
-        for (int j = lane; j < d; j += 64) ac2 = fmaf(prev[j], src[j], ac2);
-        const float t2 = wave_sum(ac2);
-        if (lane == 0) g01[(int64_t)rr * out_stride + t] = t2;
+    float x2, g = 0.f;
+    row_scalars(src, g01 ? (t > 0 ? src - d : xlast + (int64_t)rr * d) : nullptr, d, lane, x2, g);
+    if (lane == 0) {
+        out[(int64_t)rr * out_stride + t] = x2;
+        if (g01) g01[(int64_t)rr * out_stride + t] = g;
     }
 }
 
@@ -860,7 +972,8 @@ struct DensePlan {
     void (*kern)(const DenseArgs) = nullptr;
     size_t smem = 0;
     int wpb = 0;              // wavefronts per workgroup
-    int rt = 0;               // rounds per tile of the ring
+    int rt = 0, rt0 = 0;      // rounds per tile of the ring, and the fewest
+    int max_wpb = 0;          // wavefronts a workgroup of this kernel may have (0: not the kernel for short calls)
     int64_t nwg = 0;          // workgroups
     int64_t batches = 0;      // passes the grid needs when the chip cannot hold it at once
     double cost = 0.0;        // modelled duration, in units of one lightly loaded pass
@@ -952,6 +1065,8 @@ hipError_t plan_npl(const DenseArgs &a, int loss, DensePlan *plan)
     plan->nwg = a.x_shared ? ((int64_t)a.R * per_run + best - 1) / best
                            : (int64_t)a.R * ((per_run + best - 1) / best);
     const size_t round_bytes = sizeof(float) * NPL * kWave;
+    plan->rt0 = C::RT;
+    plan->max_wpb = C::MAXW;
     plan->rt = tile_rounds(C::RT, round_bytes, std::min<int64_t>(c, (plan->nwg + ncu - 1) / ncu));
     plan->smem = kRing * plan->rt * round_bytes;
     plan->batches = ((plan->nwg + ncu - 1) / ncu + c - 1) / c;
@@ -1135,7 +1250,24 @@ static hipError_t make_dense_plan(DenseArgs &a, int loss, DensePlan *out)
     return hipSuccess;
 }
 
-hipError_t launch_dense_rounds(const DenseArgs &a0, int loss, hipStream_t s, const PieceHook *hook)
+// A short call as one kernel (see kWholeRounds).
+static hipError_t launch_whole(const DensePlan &plan, DenseArgs a, hipStream_t s)
+{
+    a.whole = 1;
+    a.rt = plan.rt0;                                 // no longer than the call (what the ring need not hold is not cleared)
+    while (a.rt < a.n && 2 * a.rt <= plan.rt) a.rt *= 2;
+    const int npl_bytes = (int)(plan.smem / (kRing * plan.rt));      // bytes of a padded row
+    const size_t ring = (size_t)kRing * a.rt * npl_bytes;            // >= 24 KB: whole_meta's 12.3 KB (K = 15) fit
+    hipError_t e = clock_begin(a.clock, s, "dense_round_kernel");
+    if (e != hipSuccess) return e;
+    const dim3 grid = a.x_shared ? dim3((unsigned)a.R, 1, 1) : dim3(1, (unsigned)a.R, 1);
+    hipLaunchKernelGGL(plan.kern, grid, dim3(plan.max_wpb * kWave), ring + sizeof(float) * kWholeFloats, s, a);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = clock_end(a.clock, s);
+    return e;
+}
+
+hipError_t launch_dense_rounds(const DenseArgs &a0, int loss, hipStream_t s, const PieceHook *hook, bool *meta_done)
 {
     if (a0.n <= 0) return hipSuccess;
     if (dense_split_wanted(a0)) return launch_dense_split(a0, loss, s, hook);
@@ -1146,18 +1278,31 @@ hipError_t launch_dense_rounds(const DenseArgs &a0, int loss, hipStream_t s, con
     DensePlan plan;
     if (a.plan->valid) {
         plan.kern = reinterpret_cast<void (*)(const DenseArgs)>(const_cast<void *>(a.plan->kern));
-        plan.smem = a.plan->smem; plan.wpb = a.plan->wpb; plan.rt = a.plan->rt; plan.nwg = a.plan->nwg;
+        plan.smem = a.plan->smem; plan.wpb = a.plan->wpb; plan.nwg = a.plan->nwg;
+        plan.rt = a.plan->rt; plan.rt0 = a.plan->rt0; plan.max_wpb = a.plan->max_wpb;
         plan.batches = a.plan->batches;
         a.per_run = a.plan->per_run;
     } else {
         hipError_t e = make_dense_plan(a, loss, &plan);
         if (e != hipSuccess) return e;
         a.plan->kern = reinterpret_cast<const void *>(plan.kern);
-        a.plan->smem = plan.smem; a.plan->wpb = plan.wpb; a.plan->rt = plan.rt; a.plan->nwg = plan.nwg;
+        a.plan->smem = plan.smem; a.plan->wpb = plan.wpb; a.plan->nwg = plan.nwg;
+        a.plan->rt = plan.rt; a.plan->rt0 = plan.rt0; a.plan->max_wpb = plan.max_wpb;
         a.plan->batches = plan.batches; a.plan->per_run = a.per_run;
         a.plan->valid = true;
     }
     hipError_t e = hipSuccess;
+
+    // A short call of few learners, as one kernel: 64 calls of 8 optimistic rounds with the combined model read back
+    // after each (3 learners, d = 1000) 3.39 -> 1.18 ms; 32 calls, 16 runs of 8 learners: of 8 rounds, d = 10
+    // 1.25 -> 0.44 ms, d = 4096 2.24 -> 1.45; of 64 rounds (the longest that a wavefront's lanes hold) 1.63 -> 0.92
+    // and 4.32 -> 3.72.
+    if (a.n <= kWholeRounds && a.per_run == a.K + 1 && a.per_run <= plan.max_wpb && (int64_t)a.R * a.per_run <= kBesideMaxWaves &&
+        a.tune->get(OCO_OPT_DENSE_WPB) < 0 && !(a.optimistic && a.x_shared && a.R > 1)) {
+        e = launch_whole(plan, a, s);
+        *meta_done = e == hipSuccess;
+        return e;
+    }
 
     // Rounds give the same bits under any split of a call, so a call may go as several launches:
     //  - A grid that takes several passes over the chip has workgroups at unrelated positions of a

@@ -434,6 +434,7 @@ int oco_run_rounds(oco_state *st, const oco_rounds *rd, int64_t t0, int64_t n)
     const PieceHook hook{&MetaPipe::piece, &pipe, &MetaPipe::beside, &MetaPipe::mark, &MetaPipe::wait_mark};
     const bool overlap = st->side != nullptr && st->tune.get(OCO_OPT_META_BESIDE) != 0;
 
+    bool meta_done = false;
     if (sparse) {
         SparseArgs a{};
         a.col = rd->col; a.val = rd->val; a.y = rd->y; a.y_run_stride = yrs;
@@ -471,14 +472,15 @@ int oco_run_rounds(oco_state *st, const oco_rounds *rd, int64_t t0, int64_t n)
         a.tune = &st->tune; a.plan = &st->dense_plan; a.clock = st->timing ? &st->clock : nullptr;
         a.gram = l.off_gram ? st->at<float>(l.off_gram) : nullptr;
         a.n_max = l.n_max;
-        e = launch_dense_rounds(a, c.loss, st->stream, overlap ? &hook : nullptr);
+        a.L = m.L; a.last = m.last; a.regret = m.regret; a.eps = m.eps;
+        e = launch_dense_rounds(a, c.loss, st->stream, overlap ? &hook : nullptr, &meta_done);
     }
     if (e != hipSuccess) return fail();
     // timing: [ev0, ev1] spans the round kernels, [ev1, ev2] whatever meta work is left after them
     if (st->timing && hipEventRecord(st->ev[1], st->stream) != hipSuccess) return fail();
     if (pipe.used) {
         if (pipe.join() != hipSuccess) return fail();
-    } else if (launch_meta(m, c.loss, st->stream) != hipSuccess) {
+    } else if (!meta_done && launch_meta(m, c.loss, st->stream) != hipSuccess) {
         return fail();
     }
     if (st->timing) {

@@ -32,7 +32,7 @@ struct DensePlanCache {
     bool valid = false;
     const void *kern = nullptr;
     size_t smem = 0;
-    int wpb = 0, rt = 0;
+    int wpb = 0, rt = 0, rt0 = 0, max_wpb = 0;
     int64_t nwg = 0, batches = 0;
     int per_run = 0;
 };
@@ -102,6 +102,11 @@ struct DenseArgs {
     int per_run;             // wavefront tasks per run: K + 1 with the comparator's, K when its
                              // predictions come from the contraction kernel (set by the launcher)
     int rt;                  // rounds per tile of the register kernel's ring (set by the launcher)
+    // A short call whose runs have a workgroup each is one kernel: its workgroups also take the norms of the
+    // rounds (x2, g01), keep the last row and do the meta kernel's work on their run (set by the launcher).
+    int whole;
+    double *L, *last, *regret;   // of the meta learner, as in MetaArgs
+    double eps;
     // optimistic two-step update (Eq. (3)); V then holds the intermediate model w^
     int optimistic;
     float *ha;               // [R][K]  eta_i c_{t-1}^i: the hint is ha * x_{t-1}
@@ -115,7 +120,8 @@ struct DenseArgs {
     float *gram;             // shared streams: dense_gram_bytes(n_max, d) of scratch for the windowed path
     int64_t n_max;           // the state's largest call (lays that scratch out)
 };
-hipError_t launch_dense_rounds(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
+// *meta_done: the call's meta work is enqueued as well (a.L, a.last, a.regret)
+hipError_t launch_dense_rounds(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook, bool *meta_done);
 // the windowed path (dense_window.hip): whether a configuration takes it, and its launcher
 bool dense_window_wanted(const DenseArgs &a);
 hipError_t launch_dense_window(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
@@ -191,6 +197,19 @@ struct MetaArgs {
     int K, R, n;
 };
 hipError_t launch_meta(const MetaArgs &a, int loss, hipStream_t s);
+
+// The losses (meta kernel and short dense calls).
+template <int LOSS> __device__ __forceinline__ double phi(double z, double y)
+{
+    if (LOSS == 0) return z;
+    if (LOSS == 1) { const double e = z - y; return e * e; }
+    // log(1 + exp(-m)) without overflow: log1p(exp(-|m|)) + max(-m, 0).  One exp and one log1p
+    // for every lane (a branch on the sign of m would run both sides in most wavefronts).
+    const double m = y * z;
+    const double am = fabs(m);
+    const double lp = log1p(exp(-am));
+    return m > 0.0 ? lp : lp + am;
+}
 
 // ---- state export -----------------------------------------------------------
 struct ExportArgs {

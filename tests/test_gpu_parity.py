@@ -521,6 +521,24 @@ def test_rounds_do_not_depend_on_the_alignment_of_the_stream(d, R, K, n, shared)
             assert np.array_equal(got[k], out[0][k]), k
 
 
+@pytest.mark.parametrize("name,over", [
+    ("c1", dict(d=1, R=2)), ("c1", dict(d=64, R=1, x_shared=False)), ("c2", dict(d=131, R=3, K=15)), ("c2", dict(d=1000, R=2, K=3)),
+    ("c3", dict(d=1001, R=1, K=8, seg_len=40)), ("c4", dict(d=4093, R=2, K=11)), ("c4", dict(d=2048, R=1, K=1)),
+])
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_short_calls_as_one_kernel_change_no_bit(name, over, optimistic):
+    """A call of at most 64 rounds is one kernel (norms, rounds, meta work, last row); with a workgroup size
+    asked for it goes through the separate ones.  Same arithmetic in the same order."""
+    wl = WL.make(name, T=198, optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    whole = _gpu(wl, data, chunk=66, options=dict(dense_path=1, comparator_gemm=0, dense_wpb=4))
+    _check(wl, data, whole, label="separate kernels")
+    for c in (64, 63, 33, 1):
+        got = _gpu(wl, data, chunk=c, options=dict(dense_path=1, comparator_gemm=0))
+        for k in ("regret", "L", "W", "p", "wbar"):
+            assert np.array_equal(whole[k], got[k]), (k, c)
+
+
 def test_degenerate_inputs():
     # T = 1
     wl = WL.make("c2", T=1, R=2, d=8, K=3)
