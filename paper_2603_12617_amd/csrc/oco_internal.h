@@ -32,7 +32,7 @@ struct DensePlanCache {
     bool valid = false;
     const void *kern = nullptr;
     size_t smem = 0;
-    int wpb = 0, rt = 0, rt0 = 0, max_wpb = 0;
+    int wpb = 0, rt = 0, rt0 = 0;
     int64_t nwg = 0, batches = 0;
     int per_run = 0;
 };
@@ -102,9 +102,8 @@ struct DenseArgs {
     int per_run;             // wavefront tasks per run: K + 1 with the comparator's, K when its
                              // predictions come from the contraction kernel (set by the launcher)
     int rt;                  // rounds per tile of the register kernel's ring (set by the launcher)
-    // A short call whose runs have a workgroup each is one kernel: its workgroups also take the norms of the
-    // rounds (x2, g01), keep the last row and do the meta kernel's work on their run (set by the launcher).
-    int whole;
+    // A short call whose runs have a workgroup each is one kernel (dense_short.hip): its workgroups also take the norms
+    // of the rounds (x2, g01), keep the last row and do the meta kernel's work on their run.
     double *L, *last, *regret;   // of the meta learner, as in MetaArgs
     double eps;
     // optimistic two-step update (Eq. (3)); V then holds the intermediate model w^
@@ -122,6 +121,8 @@ struct DenseArgs {
 };
 // *meta_done: the call's meta work is enqueued as well (a.L, a.last, a.regret)
 hipError_t launch_dense_rounds(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook, bool *meta_done);
+bool dense_short_supported(const DenseArgs &a);
+hipError_t launch_dense_short(const DenseArgs &a, int loss, hipStream_t s);
 // the windowed path (dense_window.hip): whether a configuration takes it, and its launcher
 bool dense_window_wanted(const DenseArgs &a);
 hipError_t launch_dense_window(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
