@@ -43,9 +43,10 @@
  *    whose inner products are grouped differently at the start of a call than
  *    inside it: the same calls give the same bits, different splits agree to
  *    float32 rounding.  (By default: shared streams of d > 4096, of at least 2048
- *    learners with d >= 512, and calls of at least 512 rounds of at most 1024
- *    learners with d > 512, whose splits at multiples of 64 are bit-identical
- *    where every call is that long.)  Sparse configurations work in segments of 4096 rounds of
+ *    learners with d >= 512, and calls of at least 512 rounds with at least 3072
+ *    learners or, with d > 512, at most 2048: with the coordinates split over
+ *    workgroups, where splits at multiples of 64 are bit-identical if every call
+ *    is that long.)  Sparse configurations work in segments of 4096 rounds of
  *    the horizon: splits at multiples of 4096 are bit-identical, other splits
  *    regroup float32 sums and agree to rounding.
  *  - Arithmetic: iterates, inner products and the projection in float32;
@@ -188,7 +189,7 @@ typedef enum {
                                     3: HBM, four tiles, operands brought to LDS by loading wavefronts;
                                     4: registers, two tiles per workgroup (d <= 1024, else as 0);
                                     5: HBM, a tile's coordinates split over workgroups, one launch per
-                                    window (at most 1024 learners, else as unset)
+                                    window (at most 2048 learners, else as unset)
                                     (with the optimistic update 1 and 2 are taken as 0) */
     OCO_OPT_SPARSE_FETCH = 10,   /* 0: no workgroups that fetch the rows of coming sparse windows into L2 ahead of
                                     the working ones (the library adds them where the grid leaves most of the chip idle) */

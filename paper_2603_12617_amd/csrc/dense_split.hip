@@ -35,6 +35,7 @@ namespace {
 constexpr int kSW = 8;                        // wavefronts per workgroup: one runs the dependent rounds, seven sweep
 constexpr int kSweepers = kSW - 1;
 constexpr int kPre = 4;                       // blocks of 16 coordinates a sweeping wavefront fetches beside the dependent rounds
+constexpr int kSplitMaxTiles = 128;           // two chunks each on 256 compute units (beyond: dense_window_kernel, two tiles per workgroup)
 constexpr int kShareFloats = kB * kM + kM;    // a chunk's share of W X^T, then of ||W||^2
 
 struct LdsS {
@@ -384,7 +385,7 @@ bool make_split_plan(const DenseArgs &a, SplitPlan *p)
     const int nblk = (a.d + 15) / 16;
     const int64_t nq = (int64_t)a.R * a.K;
     p->tiles = (int)((nq + kM - 1) / kM);
-    if (p->tiles > 64) return false;
+    if (p->tiles > kSplitMaxTiles) return false;
     // (everything that decides how a sum is grouped follows from the configuration, not from the call: calls
     // cut at multiples of 64 rounds then give the same bits)
     const int nwin = (int)std::min<int64_t>(a.n_max / kB + 2, 1 << 20);
@@ -427,7 +428,8 @@ bool dense_split_wanted(const DenseArgs &a)
     // Measured per call of 2048 rounds, register kernel (d <= 4096) or dense_window_kernel against this one, ms:
     // d = 512 0.69 / 0.67 (4 learners) and 0.85 / 0.77 (1024); d = 1024 1.12 / 0.71 and 1.38 / 0.82; d = 4096
     // 2.10 / 0.77 and 2.99 / 1.29; of 640 rounds, d = 8192 2.51 / 0.36 (2 learners) and 2.61 / 0.72 (1024),
-    // d = 65536 28.6 / 4.5 (1024).  A call costs about 60 us here whatever its length, hence the least n; one
+    // d = 65536 28.6 / 4.5 (1024).  128 tiles (2048 learners, 2048 rounds): d = 520 0.89 (dense_window_kernel) / 0.84,
+    // d = 1000 1.12 / 0.97, d = 4096 2.52 / 1.90; 160 tiles, one chunk each: d = 2048 1.63 / 1.81, d = 520 0.89 / 0.93.  A call costs about 60 us here whatever its length, hence the least n; one
     // that need not come here (d <= 4096) stays with the register kernel, whose results no cut of the horizon changes.
     return ropt == 5 || a.d > 64 * kWave || (a.d > 512 && a.n >= 512 && a.tune->get(OCO_OPT_DENSE_PATH) < 0);
 }
