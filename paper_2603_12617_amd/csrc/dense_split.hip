@@ -36,11 +36,13 @@ constexpr int kSW = 8;                        // wavefronts per workgroup: one r
 constexpr int kSweepers = kSW - 1;
 constexpr int kPre = 4;                       // blocks of 16 coordinates a sweeping wavefront fetches beside the dependent rounds
 constexpr int kSplitMaxTiles = 128;           // two chunks each on 256 compute units (beyond: dense_window_kernel, two tiles per workgroup)
+constexpr int kHookRounds = 256;              // rounds whose meta work goes beside the following windows (one tile of the meta kernel; the last are on their own)
 constexpr int kShareFloats = kB * kM + kM;    // a chunk's share of W X^T, then of ||W||^2
 
 struct LdsS {
     using G = double;
     using S = double;
+    static constexpr int g_reads = 2;
     static constexpr bool has_corr = false;
     static constexpr int gd_bytes = kB * 4 * kGStride * 8;
     static constexpr int tile_f = kB * kM * 4, tile_s = kB * kM * 8;
@@ -127,7 +129,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
             const int t2 = t2b + i;
             const float v = gv[i >> 2][i & 3];
             gd[(t * 4 + (i & 3)) * kGStride + (t2 >> 2)] = t2 > t ? (double)v : 0.0;
-            if (t2 == t) gd[t * 4 * kGStride + 16] = (double)v;
+            if (t2 == t) *reinterpret_cast<float *>(gd + t * 4 * kGStride + 16) = v;
         }
         float *yb = reinterpret_cast<float *>(lds + Lds::yb);
 #pragma unroll
@@ -493,7 +495,7 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
         if (e == hipSuccess) e = clock_end(a.clock, s);
         if (e == hipSuccess && beside && w >= 0) {
             const int end = plan.start(w) + plan.len(w);
-            if (w + 1 == nwin || end - done >= 1024) {
+            if (w + 1 == nwin || end - done >= kHookRounds) {
                 e = hook->fn(hook->ctx, done, end - done);
                 done = end;
             }

@@ -178,6 +178,7 @@ template <int NW, int MT> struct LdsT {
     static constexpr bool wide = NW == kNW8 && MT == 1;
     using G = double;                                              // Gram table
     using S = std::conditional_t<wide, double, float>;             // inner products handed to the rounds, f_t
+    static constexpr int g_reads = 1;                               // how the rounds read the Gram table (chain_window)
     static constexpr bool has_corr = true;                         // the rounds start from pmul q0 + corr
     static constexpr int gd_bytes = kB * 4 * kGStride * (int)sizeof(G);   // G [64][4][kGStride]: G[t][t2], zero for t2 <= t;
                                                                    //   [t][0][16] holds G[t][t]
@@ -351,7 +352,7 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
             const int t2 = t2b + i;
             const float v = gv[i >> 2][i & 3];
             gd[(t * 4 + (i & 3)) * kGStride + (t2 >> 2)] = t2 > t ? (GT)v : (GT)0;   // (t2b is a multiple of 4: t2 & 3 == i & 3)
-            if (t2 == t) gd[t * 4 * kGStride + 16] = (GT)v;
+            if (t2 == t) *reinterpret_cast<float *>(gd + t * 4 * kGStride + 16) = v;
         }
     };
     // LDS inputs of the dependent rounds of window wi: the labels.  `nthr` threads numbered tid share the work.
@@ -777,6 +778,7 @@ constexpr int kQL = 4, kQSets = 4;           // loading wavefronts; steps of loa
 struct LdsQ {
     using G = double;
     using S = float;
+    static constexpr int g_reads = 0;
     static constexpr bool has_corr = false;
     static constexpr int gd_bytes = kB * 4 * kGStride * 8;
     static constexpr int tile_f = kB * kM * 4, tile_s = tile_f;
@@ -963,7 +965,7 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
             const int t2 = t2b + i;
             const float v = gpre[i >> 2][i & 3];
             gd[(t * 4 + (i & 3)) * kGStride + (t2 >> 2)] = t2 > t ? (double)v : 0.0;
-            if (t2 == t) gd[t * 4 * kGStride + 16] = (double)v;
+            if (t2 == t) *reinterpret_cast<float *>(gd + t * 4 * kGStride + 16) = v;
         }
         float *yb = reinterpret_cast<float *>(lds + Lds::yb);
 #pragma unroll

@@ -11,7 +11,7 @@ namespace {
 
 constexpr int kB = 64;            // rounds per window
 constexpr int kM = 16;            // learners per tile
-constexpr int kGStride = 18;      // doubles per (round, quad lane) row of the masked Gram table (16 + padding)
+constexpr int kGStride = 18;      // doubles per (round, quad lane) row of the masked Gram table (16 + padding, where quad lane 0's row keeps ||x||^2 as a float)
 constexpr int64_t kPieceBytes = 64ll << 20;   // stream per launch (each tiled copy is as large)
 constexpr int kTileFloats = kB * 16;          // one window x one block of 16 coordinates
 // A little scratch that lets the streamed sweep load and store without branches (a load or store
@@ -20,6 +20,8 @@ constexpr int kTileFloats = kB * 16;          // one window x one block of 16 co
 constexpr int kMiscZeros = 16, kMiscFloats = kMiscZeros + 1024 * 4;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+static_assert(kGStride % 2 == 0, "rows of the Gram table start on 16 bytes");
 
 struct WinPlanD {
     int64_t t0;      // absolute round of the call's first round
@@ -79,7 +81,8 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
     using ST = typename Lds::S;
     const int lc = lane >> 2, s = lane & 3;
     const GT *gd = reinterpret_cast<const GT *>(lds + Lds::gd) + s * kGStride;
-    const GT *x2d = reinterpret_cast<const GT *>(lds + Lds::gd) + 16;
+    const float *x2d = reinterpret_cast<const float *>(reinterpret_cast<const GT *>(lds + Lds::gd) + 16);
+    constexpr int kX2 = 4 * kGStride * (int)(sizeof(GT) / sizeof(float));   // floats from one round's ||x||^2 to the next
     const ST *q0d = reinterpret_cast<const ST *>(lds + Lds::q0 + m * Lds::tile_s) + s * kM + lc;
     const float *cr = reinterpret_cast<const float *>(lds + Lds::corr + m * Lds::tile_f) + s * kM + lc;
     ST *fl = reinterpret_cast<ST *>(lds + Lds::fl + m * Lds::tile_s) + lc;
@@ -104,13 +107,22 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
     // predictions themselves stay float64 (their recurrence is 64 rounds long); round t - 1's
     // update of them shares a scheduling region with the dependent part of round t and fills its
     // latencies.
+    double gahead[16];                // the coming round's row of G
+    if constexpr (Lds::g_reads == 2) {
+#pragma unroll
+        for (int j = 0; j < 16; j += 2) {
+            const d2 g2 = *reinterpret_cast<const d2 *>(gd + j);
+            gahead[j] = g2[0];
+            gahead[j + 1] = g2[1];
+        }
+    }
     double gprev[16];                 // round t - 1's row of G (elements j >= (t - 1) / 4)
     double aprev = 0.0, fprev = 1.0;
     float n2f = (float)n2;
     float znext = (float)p[0];        // this lane's candidate for the next prediction (round 0: lane 0's is the one)
     // label and ||x||^2 of a round are read from LDS one round ahead: they are the first things the
     // dependent part needs, and nothing else would cover the latency of the read
-    float ynext = yb[0], x2next = (float)x2d[0];
+    float ynext = yb[0], x2next = x2d[0];
     const float *hg = reinterpret_cast<const float *>(lds + Lds::hg + buf * Lds::hg_bytes);
     float gnext = OPT ? hg[0] : 0.f;
     float ha = 0.f, hp = 0.f, x2p = 0.f;
@@ -119,14 +131,39 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
         constexpr int t = decltype(tc)::value;
         constexpr int j0 = t >> 2;                                   // pending elements of this lane: j >= j0
         constexpr int jn = (t + 1) >> 2;                             // holds the prediction of round t + 1
-        // this round's row of G first: it does not depend on the scalars below
-        double gr[16 - j0];
+        // this round's row of G.  Two entries at a time from an even one on are 16-byte reads whose offset is a
+        // constant (8-byte pairs reach 2 KB only: an address computed for each was one instruction in twelve of a
+        // round); read a round ahead, nothing waits for them.  Which form a kernel takes is what its registers allow:
+        // dense_window_kernel spills 130 more with the rows a round ahead, dense_window_shared_kernel is 0.6 % slower
+        // with the 16-byte reads (piecewise streams of d = 1000 gain 1.5 % by them).
+        constexpr int je = Lds::g_reads > 0 ? j0 & ~1 : j0;
+        double gr[16 - je];
+        if constexpr (Lds::g_reads == 2) {
 #pragma unroll
-        for (int j = j0; j < 16; ++j) gr[j - j0] = gd[t * 4 * kGStride + j];
+            for (int j = je; j < 16; ++j) gr[j - je] = gahead[j];
+            if constexpr (t + 1 < kB) {
+#pragma unroll
+                for (int j = jn & ~1; j < 16; j += 2) {
+                    const d2 g2 = *reinterpret_cast<const d2 *>(gd + (t + 1) * 4 * kGStride + j);
+                    gahead[j] = g2[0];
+                    gahead[j + 1] = g2[1];
+                }
+            }
+        } else if constexpr (Lds::g_reads == 1) {
+#pragma unroll
+            for (int j = je; j < 16; j += 2) {
+                const d2 g2 = *reinterpret_cast<const d2 *>(gd + t * 4 * kGStride + j);
+                gr[j - je] = g2[0];
+                gr[j - je + 1] = g2[1];
+            }
+        } else {
+#pragma unroll
+            for (int j = j0; j < 16; ++j) gr[j - j0] = gd[t * 4 * kGStride + j];
+        }
         const float yt = ynext, x2t = x2next, g01t = gnext;
         if constexpr (t + 1 < kB) {
             ynext = yb[(t + 1) * kM];
-            x2next = (float)x2d[(t + 1) * 4 * kGStride];
+            x2next = x2d[(t + 1) * kX2];
             if (OPT) gnext = hg[t + 1];
         }
         if constexpr (t > 0) {
@@ -162,9 +199,9 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
             x2p = live ? x2t : x2p;
         }
         // (p[jn] has the updates of the rounds before this one: the loop above ran)
-        if constexpr (jn < 16) znext = f32v * fmaf(-a32, (float)gr[jn - j0], (float)p[jn]);
+        if constexpr (jn < 16) znext = f32v * fmaf(-a32, (float)gr[jn - je], (float)p[jn]);
 #pragma unroll
-        for (int j = j0; j < 16; ++j) gprev[j] = gr[j - j0];
+        for (int j = j0; j < 16; ++j) gprev[j] = gr[j - je];
         aprev = (double)a32;
         fprev = (double)f32v;
         __builtin_amdgcn_sched_barrier(0);                           // at most two rounds overlap: registers
