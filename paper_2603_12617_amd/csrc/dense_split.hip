@@ -98,8 +98,24 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     const int wu_s = upd ? sp.plan.start(sp.wu) : 0, wu_l = upd ? sp.plan.len(sp.wu) : 0;
     const int wq_s = do_q ? sp.plan.start(sp.wu + 1) : 0, wq_l = do_q ? sp.plan.len(sp.wu + 1) : 0;
 
-    // ---- inputs of the dependent rounds to LDS -----------------------------------------------------
+    // ---- inputs of the dependent rounds: scalars of the wavefront that runs them, the rest to LDS ----
+    // (all loads are on their way before the first is waited for: with the scalars and the sum of ||w||^2 loaded
+    // behind the barrier the rounds of 64 chunks started 3 us later)
+    double n2 = 0.0;                                                // wavefront 0, lane = 4 learner + quad lane
+    float eta = 0.f;
+    Hint hint{0.f, 0.f, 0.f};
     if (upd) {
+        if (wave == 0) {
+            const int q = q_base + (lane >> 2);
+            if (q < nq) {
+                eta = a.eta[q % K];
+                if (OPT) {
+                    hint.ha = sp.ha_in[q];
+                    hint.hp = sp.hp_in[q];
+                    hint.x2p = wu_s == 0 ? a.x2last[0] : a.x2[wu_s - 1];
+                }
+            }
+        }
         constexpr int kGPer = kB * kB / NT;                         // 8 consecutive entries of a row of G
         f4 gv[kGPer / 4];
 #pragma unroll
@@ -113,12 +129,19 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         // the chunks' shares, summed in chunk order
         const float *p0 = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + tid * 2;
         double s0 = 0.0, s1 = 0.0;
+        auto sum_shares = [&](auto norms) __attribute__((always_inline)) {
+            constexpr bool N = decltype(norms)::value;              // ||w||^2 of the stored iterates as well
+            const float *pn = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + kB * kM + (lane >> 2);
 #pragma unroll 16
-        for (int c = 0; c < sp.chunks; ++c) {
-            const float2 v = *reinterpret_cast<const float2 *>(p0 + (int64_t)c * kShareFloats);
-            s0 += (double)v.x;
-            s1 += (double)v.y;
-        }
+            for (int c = 0; c < sp.chunks; ++c) {
+                const float2 v = *reinterpret_cast<const float2 *>(p0 + (int64_t)c * kShareFloats);
+                s0 += (double)v.x;
+                s1 += (double)v.y;
+                if (N) n2 += (double)pn[(int64_t)c * kShareFloats];
+            }
+        };
+        if (wave == 0) sum_shares(std::true_type{});
+        else sum_shares(std::false_type{});
         double *q0d = reinterpret_cast<double *>(lds + Lds::q0);
         q0d[tid * 2] = s0;
         q0d[tid * 2 + 1] = s1;
@@ -170,21 +193,6 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     if (wave == 0) {
         if (upd) {
             const int q = q_base + (lane >> 2);
-            // ||w||^2 of the stored iterates: a quad's lanes take every fourth chunk
-            const float *pn = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + kB * kM + (lane >> 2);
-            double n2 = 0.0;
-            for (int c = lane & 3; c < sp.chunks; c += 4) n2 += (double)pn[(int64_t)c * kShareFloats];
-            n2 = (quad_bcast<0>(n2) + quad_bcast<1>(n2)) + (quad_bcast<2>(n2) + quad_bcast<3>(n2));
-            float eta = 0.f;
-            Hint hint{0.f, 0.f, 0.f};
-            if (q < nq) {
-                eta = a.eta[q % K];
-                if (OPT) {
-                    hint.ha = sp.ha_in[q];
-                    hint.hp = sp.hp_in[q];
-                    hint.x2p = wu_s == 0 ? a.x2last[0] : a.x2[wu_s - 1];
-                }
-            }
             bool projected;
             (void)chain_window<LOSS, Lds, OPT>(lds, 0, 0, lane, wu_l, eta, (double)a.D, 1.0, 1.0, n2, projected, &hint);
             if (OPT && chunk == 0 && q < nq && (lane & 3) == 0) {
