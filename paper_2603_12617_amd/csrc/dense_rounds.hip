@@ -419,7 +419,7 @@ hipError_t plan_npl(const DenseArgs &a, int loss, DensePlan *plan)
                            : (int64_t)a.R * ((per_run + best - 1) / best);
     const size_t round_bytes = sizeof(float) * NPL * kWave;
     plan->rt0 = C::RT;
-    plan->rt = tile_rounds(C::RT, round_bytes, std::min<int64_t>(c, (plan->nwg + ncu - 1) / ncu));
+    plan->rt = kGrowTiles<NPL> ? tile_rounds(C::RT, round_bytes, std::min<int64_t>(c, (plan->nwg + ncu - 1) / ncu)) : C::RT;
     plan->smem = kRing * plan->rt * round_bytes;
     plan->batches = ((plan->nwg + ncu - 1) / ncu + c - 1) / c;
     return hipSuccess;

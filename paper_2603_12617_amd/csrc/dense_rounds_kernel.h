@@ -62,6 +62,9 @@ template <> struct DenseCfg<64> { static constexpr int MAXW = OCO_MAXW64,  RT = 
 // coordinates per lane is the difference between two and three wavefronts per SIMD.
 template <int NPL> constexpr bool kOneRowSet = NPL >= 64;   // at 32 it measured 4 % slower
 constexpr int kRing = 3;   // LDS tiles
+// Tiles may be longer than DenseCfg's.  Up to 128 coordinates theirs already outlast a load (4 us and more), and as a
+// variable the length cost 64 coordinates 6 % per round (3000 rounds 0.60 -> 0.64 ms).
+template <int NPL> constexpr bool kGrowTiles = NPL >= 4;
 
 template <int VW> struct VecT;
 template <> struct VecT<1> { using type = float; };
@@ -241,7 +244,8 @@ dense_rounds_kernel(const DenseArgs a)
     constexpr int VW = NPL >= 4 ? 4 : NPL;      // floats per LDS read
     constexpr int NV = NPL / VW;                // LDS reads per lane and round
     constexpr int DP = NPL * kWave;             // padded dimension
-    const int RT = a.rt;                        // rounds per tile: even, divides 64 (tile_rounds)
+    // rounds per tile: even, divides 64; a constant where tiles never grow (tile_rounds)
+    const int RT = kGrowTiles<NPL> ? a.rt : DenseCfg<NPL>::RT;
     const int TILE = RT * DP;                   // floats per tile
     const int NI = TILE / 4 / kWave;            // 1 KB copy instructions per tile
     constexpr int CH = NV >= 2 ? 2 : 1;         // LDS reads per chunk
