@@ -62,8 +62,8 @@ template <> struct DenseCfg<64> { static constexpr int MAXW = OCO_MAXW64,  RT = 
 // coordinates per lane is the difference between two and three wavefronts per SIMD.
 template <int NPL> constexpr bool kOneRowSet = NPL >= 64;   // at 32 it measured 4 % slower
 constexpr int kRing = 3;   // LDS tiles
-// Tiles may be longer than DenseCfg's.  Up to 128 coordinates theirs already outlast a load (4 us and more), and as a
-// variable the length cost 64 coordinates 6 % per round (3000 rounds 0.60 -> 0.64 ms).
+// Tiles may be longer than DenseCfg's.  Up to 128 coordinates theirs already outlast a load (4 us and more); longer
+// ones cost 200 runs of 20 learners, d = 100, 5 % (1.41 -> 1.45 ms per 3000 rounds).
 template <int NPL> constexpr bool kGrowTiles = NPL >= 4;
 
 template <int VW> struct VecT;
