@@ -151,30 +151,40 @@ __device__ __forceinline__ void stage_words(const float *xg, int d, int n, int k
 }
 
 // ||x||^2 of a round row and, if prev is given, its inner product with the row before: one wavefront, fixed order
-// (one chain per sum; the loads of sixteen steps are issued together).
+// (one chain per sum).  The loads of U steps of 64 coordinates are issued together, U no larger than the row has
+// steps left: a row of d = 64 taken as sixteen steps, fifteen of them empty, made the norms of 192000 rows 14.4 us
+// instead of 8.4.  (Steps past the row add +0, which changes no bit of a sum of squares, and of the other at most the
+// sign of a zero.)
+template <int U, bool PREV, bool GUARD>
+__device__ __forceinline__ void row_steps(const float *src, const float *prev, int j, int d, float &acc, float &ac2)
+{
+    float v[U], w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool in = !GUARD || j + 64 * u < d;
+        v[u] = in ? src[j + 64 * u] : 0.f;
+        if (PREV) w[u] = in ? prev[j + 64 * u] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        acc = fmaf(v[u], v[u], acc);
+        if (PREV) ac2 = fmaf(w[u], v[u], ac2);
+    }
+}
+template <bool PREV>
+__device__ __forceinline__ void row_sums(const float *src, const float *prev, int d, int lane, float &acc, float &ac2)
+{
+    int j = lane, left = d;                                // left: the same in every lane
+    for (; left >= 64 * 16; left -= 64 * 16, j += 64 * 16) row_steps<16, PREV, false>(src, prev, j, d, acc, ac2);
+    if (left > 64 * 4) row_steps<16, PREV, true>(src, prev, j, d, acc, ac2);
+    else if (left > 64) row_steps<4, PREV, true>(src, prev, j, d, acc, ac2);
+    else if (left > 0) row_steps<1, PREV, true>(src, prev, j, d, acc, ac2);
+}
 __device__ __forceinline__ void row_scalars(const float *src, const float *prev, int d, int lane, float &x2, float &g01)
 {
-    constexpr int U = 16;
     float acc = 0.f, ac2 = 0.f;
-    int j = lane;
-    for (; j + 64 * (U - 1) < d; j += 64 * U) {
-        float v[U], w[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) { v[u] = src[j + 64 * u]; w[u] = prev ? prev[j + 64 * u] : 0.f; }
-#pragma unroll
-        for (int u = 0; u < U; ++u) { acc = fmaf(v[u], v[u], acc); ac2 = fmaf(w[u], v[u], ac2); }
-    }
-    for (int j0 = j; j0 < d; j0 += 64 * U) {               // the rest of the row (adds of +0 past it change no bit of a sum
-        float v[U], w[U];                                  // of squares, and of the other at most the sign of a zero)
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = j0 + 64 * u < d;
-            v[u] = in ? src[j0 + 64 * u] : 0.f;
-            w[u] = in && prev ? prev[j0 + 64 * u] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) { acc = fmaf(v[u], v[u], acc); ac2 = fmaf(w[u], v[u], ac2); }
-    }
+    if (prev) row_sums<true>(src, prev, d, lane, acc, ac2);
+    else row_sums<false>(src, prev, d, lane, acc, ac2);
     x2 = wave_sum(acc);
     if (prev) g01 = wave_sum(ac2);
 }

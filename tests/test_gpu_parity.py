@@ -495,6 +495,16 @@ def test_results_do_not_depend_on_how_a_call_is_enqueued(name, over):
     sim.close()
 
 
+# the norms of the round rows take 1, 4 or 16 steps of 64 coordinates at a time: a step, a group and a row that are full,
+# one coordinate short and one over
+@pytest.mark.parametrize("d", [63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 1279, 1280, 1281])
+@pytest.mark.parametrize("n", [70, 20])
+def test_norms_of_round_rows_at_the_edges_of_their_steps(d, n):
+    wl = WL.make("c2", T=n, d=d, R=2, K=2, optimistic=1, eta=(0.3, 30.0))
+    data = WL.generate(wl)
+    _check(wl, data, _gpu(wl, data), label="norms d=%d n=%d" % (d, n))
+
+
 # every coordinates-per-lane variant, a tile shorter / longer than the call, learners that share a tile with others
 # and (many runs) tiles that have not grown
 @pytest.mark.parametrize("d,R,K,n", [(64, 3, 2, 130), (100, 2, 15, 333), (200, 70, 15, 70), (512, 3, 4, 65), (1000, 5, 5, 301),
