@@ -549,6 +549,21 @@ def test_short_calls_as_one_kernel_change_no_bit(name, over, optimistic):
             assert np.array_equal(whole[k], got[k]), (k, c)
 
 
+@pytest.mark.parametrize("name,d,optimistic,cuts", [("c2", 1100, 1, (33, 32)), ("c3", 2052, 0, (9, 8)), ("c2", 1024, 2, (33,))])
+def test_short_calls_of_more_runs_than_compute_units(name, d, optimistic, cuts):
+    """Beyond 256 runs of wide rows only the shortest calls are one kernel, on either side of the line: no bit depends
+    on which."""
+    wl = WL.make(name, T=67, d=d, R=258, K=2, optimistic=optimistic, seg_len=0)
+    data = WL.generate(wl)
+    opt = dict(dense_path=1, comparator_gemm=0)
+    whole = _gpu(wl, data, options=dict(opt, dense_wpb=4))
+    _check(wl, data, whole, runs=[0, 255, 256, 257], label="separate kernels")
+    for c in cuts:
+        got = _gpu(wl, data, chunk=c, options=opt)
+        for k in ("regret", "L", "W", "p", "wbar"):
+            assert np.array_equal(whole[k], got[k]), (k, c)
+
+
 def test_degenerate_inputs():
     # T = 1
     wl = WL.make("c2", T=1, R=2, d=8, K=3)
