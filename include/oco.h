@@ -189,7 +189,8 @@ typedef enum {
                                     3: HBM, four tiles, operands brought to LDS by loading wavefronts;
                                     4: registers, two tiles per workgroup (d <= 1024, else as 0);
                                     5: HBM, a tile's coordinates split over workgroups, one launch per
-                                    window (at most 2048 learners, else as unset)
+                                    window (at most 2048 learners and where its sums fit the scratch of
+                                    calls of n_max rounds, else as unset)
                                     (with the optimistic update 1 and 2 are taken as 0) */
     OCO_OPT_SPARSE_FETCH = 10,   /* 0: no workgroups that fetch the rows of coming sparse windows into L2 ahead of
                                     the working ones (the library adds them where the grid leaves most of the chip idle) */

@@ -1272,7 +1272,8 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
     // wavefronts have several blocks each (c3: 41.8 against 46.4 ms), or, with at least four tiles per compute unit's
     // workgroup on every one of 256 compute units and wide rows, the loading wavefronts (c4: 67.4 against
     // 70.4 ms; c3, bound by the dependent rounds, which that kernel does not overlap: 101 against 47.5 ms).
-    const int64_t ropt = a.tune->get(OCO_OPT_WINDOW_RESIDENT);
+    // (5, the kernel with split coordinates, which did not take the call: as unset)
+    const int64_t ropt = a.tune->get(OCO_OPT_WINDOW_RESIDENT) == 5 ? -1 : a.tune->get(OCO_OPT_WINDOW_RESIDENT);
     const bool fits = a.d <= 16 * kNW8 * 32;
     const bool many = (int64_t)a.R * a.K >= 1024 * kM && nblk >= 128;
     const bool fits2 = a.d <= 16 * kNW8 * 8;

@@ -187,6 +187,26 @@ def test_option_errors():
     sim.close()
 
 
+def _plan_lines(err):
+    return [l for l in err.splitlines() if l.startswith("dense plan: windowed")]
+
+
+@pytest.mark.parametrize("over", [
+    dict(T=130, R=129, d=512, K=16),         # 2064 learners, one more tile than the chunks are for: two tiles in registers
+    dict(T=65, R=1024, d=2048, K=16),        # the kernel with loading wavefronts
+])
+def test_split_coordinates_asked_for_beyond_their_range_are_as_unset(over, capfd):
+    wl = WL.make("c4", **over)
+    data = WL.generate(wl)
+    capfd.readouterr()
+    unset = _gpu(wl, data, options=dict(verbose=1))
+    plan = _plan_lines(capfd.readouterr().err)
+    got = _gpu(wl, data, options=dict(verbose=1, window_resident=5))
+    assert _plan_lines(capfd.readouterr().err) == plan and len(plan) == 1
+    for k in ("regret", "L", "W", "p", "wbar"):
+        assert np.array_equal(got[k], unset[k]), k
+
+
 # a tile's coordinates split over workgroups (the default beyond d = 4096 for at most 64 tiles): more learners than
 # a tile, fewer coordinates than a workgroup has wavefronts for, a last block that is not full, ragged windows,
 # a call in several groups of Gram matrices, the optimistic update
