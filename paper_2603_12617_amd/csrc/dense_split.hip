@@ -441,7 +441,10 @@ bool dense_split_wanted(const DenseArgs &a)
     // d = 65536 28.6 / 4.5 (1024).  128 tiles (2048 learners, 2048 rounds): d = 520 0.89 (dense_window_kernel) / 0.84,
     // d = 1000 1.12 / 0.97, d = 4096 2.52 / 1.90; 160 tiles, one chunk each: d = 2048 1.63 / 1.81, d = 520 0.89 / 0.93.  A call costs about 60 us here whatever its length, hence the least n; one
     // that need not come here (d <= 4096) stays with the register kernel, whose results no cut of the horizon changes.
-    return ropt == 5 || a.d > 64 * kWave || (a.d > 512 && a.n >= 512 && a.tune->get(OCO_OPT_DENSE_PATH) < 0);
+    // The horizon's last call, which is as short as the cuts leave it, stays with the kernel of the calls before it: equal
+    // calls and a rest give the bits of one call (cuts at multiples of 64).
+    const bool rest = a.plan->after_split && a.t0 + a.n == a.T;
+    return ropt == 5 || a.d > 64 * kWave || (a.d > 512 && (a.n >= 512 || rest) && a.tune->get(OCO_OPT_DENSE_PATH) < 0);
 }
 
 hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook)

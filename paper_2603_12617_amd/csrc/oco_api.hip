@@ -249,6 +249,7 @@ int oco_reset(oco_state *st)
         return OCO_EHIP;
     st->t_done = 0;
     st->failed = false;
+    st->dense_plan.after_split = false;
     return OCO_OK;
 }
 
@@ -471,7 +472,7 @@ int oco_run_rounds(oco_state *st, const oco_rounds *rd, int64_t t0, int64_t n)
         }
         a.tune = &st->tune; a.plan = &st->dense_plan; a.clock = st->timing ? &st->clock : nullptr;
         a.gram = l.off_gram ? st->at<float>(l.off_gram) : nullptr;
-        a.n_max = l.n_max;
+        a.n_max = l.n_max; a.T = c.T;
         a.L = m.L; a.last = m.last; a.regret = m.regret; a.eps = m.eps;
         e = launch_dense_rounds(a, c.loss, st->stream, overlap ? &hook : nullptr, &meta_done);
     }

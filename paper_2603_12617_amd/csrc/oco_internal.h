@@ -35,6 +35,7 @@ struct DensePlanCache {
     int wpb = 0, rt = 0, rt0 = 0;
     int64_t nwg = 0, batches = 0;
     int per_run = 0;
+    bool after_split = false;    // the call before was worked by dense_split.hip (not part of the plan: survives a change of options)
 };
 
 // Called after the round kernel of every piece of a call has been enqueued: rounds
@@ -118,6 +119,7 @@ struct DenseArgs {
     DensePlanCache *plan;    // never null
     float *gram;             // shared streams: dense_gram_bytes(n_max, d) of scratch for the windowed path
     int64_t n_max;           // the state's largest call (lays that scratch out)
+    int64_t T;               // the horizon
 };
 // *meta_done: the call's meta work is enqueued as well (a.L, a.last, a.regret)
 hipError_t launch_dense_rounds(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook, bool *meta_done);

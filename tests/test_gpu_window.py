@@ -235,3 +235,24 @@ def test_coordinates_split_over_workgroups_match_the_oracle(name, over, optimist
         scale = max(1.0, float(np.abs(got[k]).max()))
         # other cuts regroup float32 sums: the bound of the other windowed kernels, twice for the regret's second sum
         np.testing.assert_allclose(part[k], got[k], rtol=0, atol=4e-6 * scale, err_msg=k)
+
+
+# by default: calls of at least 512 rounds, the horizon's last as short as it comes; d = 2048 has the comparators'
+# predictions summed in several ranges of coordinates
+@pytest.mark.parametrize("over,chunks", [
+    (dict(T=1500, R=3, d=1000, K=17, seg_len=400), (512, 576, 1024)),
+    (dict(T=1090, R=2, d=2048, K=3, seg_len=0), (512, 1088)),
+])
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_split_coordinates_give_the_same_bits_under_long_cuts(over, chunks, optimistic, capfd):
+    wl = WL.make("c3", optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    capfd.readouterr()
+    whole = _gpu(wl, data, options=dict(verbose=1))
+    assert "chunks of coordinates" in capfd.readouterr().err
+    _check(wl, data, whole, label="split by default d=%d optimistic=%d" % (wl.d, optimistic))
+    for c in chunks:
+        got = _gpu(wl, data, chunk=c, options=dict(verbose=1))
+        assert capfd.readouterr().err.count("chunks of coordinates") == -(-wl.T // c), c
+        for k in ("regret", "L", "W", "p", "wbar"):
+            assert np.array_equal(got[k], whole[k]), (k, c)
