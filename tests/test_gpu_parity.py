@@ -465,6 +465,7 @@ def test_results_do_not_depend_on_how_the_horizon_is_cut(name, over, chunks):
     ("c2", dict(T=2100, R=3, d=100, K=15)),
     ("c3", dict(T=2200, R=2, d=320, K=3, seg_len=500, optimistic=True)),
     ("c5", dict(T=4500, R=3, d=4096, K=8, wstar_nnz=64)),
+    ("c3", dict(T=1600, R=2, d=1000, K=5, seg_len=700)),
 ])
 def test_results_do_not_depend_on_how_a_call_is_enqueued(name, over):
     """One call may go to the GPU as several launches, with the meta kernel of a piece on a
@@ -490,7 +491,9 @@ def test_results_do_not_depend_on_how_a_call_is_enqueued(name, over):
     assert both.min() > 0.0
     # the dominant kernel alone, launch by launch: inside the bracket of all round kernels
     kt = B.oco_last_kernel_timing(sim.h)
-    assert kt["kernel"] in ("dense_round_kernel", "dense_window_kernel", "dense_window_shared_kernel", "sparse_window_kernel")
+    assert kt["kernel"] in ("dense_round_kernel", "dense_window_kernel", "dense_window_shared_kernel", "sparse_window_kernel",
+                            "dense_split_kernel")
+    assert (kt["kernel"] == "dense_split_kernel") == (name == "c3" and wl.d > 512)
     assert 1 <= kt["timed"] <= kt["launches"] and 0.0 < kt["ms_sum"] <= both[0] * 1.05
     sim.close()
 

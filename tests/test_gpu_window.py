@@ -207,7 +207,7 @@ def test_split_coordinates_asked_for_beyond_their_range_are_as_unset(over, capfd
         assert np.array_equal(got[k], unset[k]), k
 
 
-# a tile's coordinates split over workgroups (the default beyond d = 4096 for at most 64 tiles): more learners than
+# a tile's coordinates split over workgroups (the default beyond d = 4096 for at most 128 tiles): more learners than
 # a tile, fewer coordinates than a workgroup has wavefronts for, a last block that is not full, ragged windows,
 # a call in several groups of Gram matrices, the optimistic update
 @pytest.mark.parametrize("name,over", [
@@ -219,6 +219,7 @@ def test_split_coordinates_asked_for_beyond_their_range_are_as_unset(over, capfd
     ("c3", dict(T=640, R=1, d=8204, K=3, seg_len=64)),
     ("c4", dict(T=130, R=5, d=16384, K=16)),
     ("c1", dict(T=20000, d=8, R=1)),
+    ("c4", dict(T=130, R=128, d=516, K=16)),                       # 128 tiles, the most
 ])
 @pytest.mark.parametrize("optimistic", [0, 1, 2])
 def test_coordinates_split_over_workgroups_match_the_oracle(name, over, optimistic):
@@ -256,3 +257,79 @@ def test_split_coordinates_give_the_same_bits_under_long_cuts(over, chunks, opti
         assert capfd.readouterr().err.count("chunks of coordinates") == -(-wl.T // c), c
         for k in ("regret", "L", "W", "p", "wbar"):
             assert np.array_equal(got[k], whole[k]), (k, c)
+
+
+# asked for, and the default beyond d = 4096: every call's length, cut at multiples of 64
+@pytest.mark.parametrize("over,options", [
+    (dict(T=450, R=3, d=1000, K=17, seg_len=100), dict(window_resident=5)),
+    (dict(T=450, R=2, d=2048, K=3, seg_len=0), dict(window_resident=5)),
+    (dict(T=450, R=40, d=132, K=16, seg_len=0), dict(window_resident=5)),
+    (dict(T=450, R=2, d=8192, K=5, seg_len=70), dict()),
+])
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_split_coordinates_give_the_same_bits_under_cuts_at_windows(over, options, optimistic):
+    wl = WL.make("c3", optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    whole = _gpu(wl, data, options=options)
+    for c in (64, 128, 192):
+        got = _gpu(wl, data, chunk=c, options=options)             # (the same n_max: it lays the sums out)
+        for k in ("regret", "L", "W", "p", "wbar"):
+            assert np.array_equal(got[k], whole[k]), (k, c)
+
+
+# by default a shared stream of d = 1000 changes kernel with the length of its calls: split coordinates, separate kernels,
+# the one kernel of short calls.  Cuts inside a window, steps that project, the hint scalars across the change.
+@pytest.mark.parametrize("K,eta", [(5, None), (6, (0.01, 0.1, 1.0, 10.0, 100.0, 1000.0))])
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_a_state_changes_between_split_coordinates_and_the_register_kernel(K, eta, optimistic, capfd):
+    calls = (600, 40, 130, 512, 1, 64, 700, 8, 515, 30)
+    over = dict(T=sum(calls), R=3, d=1000, K=K, seg_len=333, optimistic=optimistic)
+    if eta is not None:
+        over["eta"] = eta
+    wl = WL.make("c3", **over)
+    data = WL.generate(wl)
+    sim = B.Simulation(wl, data, options=dict(verbose=1))
+    capfd.readouterr()
+    t0 = 0
+    for n in calls:
+        sim.run(t0, n)
+        t0 += n
+    # (the last call, of 30 rounds, follows the call before it)
+    assert capfd.readouterr().err.count("chunks of coordinates") == sum(n >= 512 for n in calls) + 1
+    got = dict(regret=sim.regret(), L=sim.cum_losses())
+    got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+    sim.close()
+    _check(wl, data, got, label="split and register optimistic=%d" % optimistic)
+
+
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_split_coordinates_with_steps_far_larger_than_the_ball_and_a_tiny_radius(optimistic):
+    """As for the other windowed kernels: the projection factors of a window multiply to far below float32's range."""
+    opt = dict(window_resident=5)
+    wl = WL.make("c3", T=200, R=2, d=20, K=3, eta=(1e4, 1e6, 3.0), D=1e-3, seg_len=0, optimistic=optimistic)
+    data = WL.generate(wl)
+    _check(wl, data, _gpu(wl, data, options=opt), label="split huge eta")
+    for d in (64, 516, 8192):
+        wl = WL.make("c4", T=200, R=2, d=d, K=4, eta=(1e-3, 1.0, 1e3, 1e8), optimistic=optimistic)
+        data = WL.generate(wl)
+        _check(wl, data, _gpu(wl, data, options=opt), label="split logistic huge eta d=%d" % d)
+
+
+@pytest.mark.parametrize("over,n_min", [(dict(R=192, d=100), 512), (dict(R=128, d=512), 0), (dict(R=192, d=4), 512)])
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_windows_are_the_default_for_many_learners_of_narrow_models(over, n_min, optimistic, capfd):
+    wl = WL.make("c4", T=520, K=16, optimistic=optimistic, **over)        # 3072 learners; 2048 of d = 512
+    data = WL.generate(wl)
+    for chunk, windowed in ((0, True), (260, n_min == 0)):
+        capfd.readouterr()
+        got = _gpu(wl, data, chunk=chunk, options=dict(verbose=1))
+        assert ("windowed contraction kernel" in capfd.readouterr().err) == windowed
+        _check(wl, data, got, runs=[0, 65, wl.R - 1], label="narrow %s chunk=%d" % (over, chunk))
+    over = dict(over, R=over["R"] - 1)                                    # a run fewer: the register kernel
+    if n_min == 0:
+        over["d"] = 508
+    wl = WL.make("c4", T=520, K=16, optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    capfd.readouterr()
+    _check(wl, data, _gpu(wl, data, options=dict(verbose=1)), runs=[0, wl.R - 1], label="one run fewer")
+    assert "windowed contraction kernel" not in capfd.readouterr().err
