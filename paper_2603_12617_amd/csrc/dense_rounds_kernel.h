@@ -62,11 +62,13 @@ template <> struct DenseCfg<64> { static constexpr int MAXW = OCO_MAXW64,  RT = 
 // coordinates per lane is the difference between two and three wavefronts per SIMD.
 template <int NPL> constexpr bool kOneRowSet = NPL >= 64;   // at 32 it measured 4 % slower
 constexpr int kRing = 3;   // LDS tiles
-// Where the round loop of rows of at most 64 coordinates starts, in instructions of 4 bytes past a multiple of 64: a round
+// Where the round loop of rows of at most 128 coordinates starts, in instructions of 4 bytes past a multiple of 64: a round
 // there is so short that how its branch targets lie in the 32-byte blocks instructions are fetched in is up to 7 % of
-// it, and left alone that changes with any code before the loop (3000 plain rounds of two learners, us, best / worst of
-// the sixteen offsets: squared 593 / 638, logistic 662 / 704, linear 574 / 618; the ends are offsets 13, 7 and 15).
-template <int NPL, int LOSS> constexpr int kLoopOffset = NPL == 1 ? (LOSS == 1 ? 13 : 15) : -1;   // -1: wherever it falls
+// it, and left alone that changes with any code before the loop.  3000 plain rounds, us, best / worst of the sixteen
+// offsets: two learners, d = 64, squared 593 / 638, logistic 662 / 704, linear 574 / 618 (13, 7, 15 / 3); eight runs of three on
+// streams of their own, d = 96, 648 / 701, 721 / 768, 640 / 697 (6, 7, 6 / 1, 10, 12).
+template <int NPL, int LOSS>
+constexpr int kLoopOffset = NPL == 1 ? (LOSS == 1 ? 13 : 15) : NPL == 2 ? (LOSS == 2 ? 7 : 6) : -1;   // -1: wherever it falls
 // Tiles may be longer than DenseCfg's.  Up to 128 coordinates theirs already outlast a load (4 us and more); longer
 // ones cost 200 runs of 20 learners, d = 100, 5 % (1.41 -> 1.45 ms per 3000 rounds).
 template <int NPL> constexpr bool kGrowTiles = NPL >= 4;
