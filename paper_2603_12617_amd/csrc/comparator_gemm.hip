@@ -18,8 +18,9 @@
 //
 // A few runs and rounds of a wide model leave most of the chip without a tile (4 runs, 2000 rounds,
 // d = 32768: 32 workgroups, 1460 us); with scratch for partial sums the depth is then cut into a.chunks ranges of
-// coordinates, a workgroup each, and comparator_sum_kernel adds them in order.  (Only callers whose results need
-// not be the same bits under every cut of the horizon give that scratch: the number of ranges depends on n.)
+// coordinates, a workgroup each, and comparator_sum_kernel adds them in order.  How many is the caller's choice, which it
+// has to make from the configuration (the largest call n_max, not this call's n): then cutting the horizon
+// changes no bit here either.
 //
 // A tile of rounds that straddles a segment boundary is computed once per segment it touches;
 // each pass writes only the rounds of its own segment.
