@@ -307,13 +307,10 @@ __global__ void __launch_bounds__(64) split_finish_kernel(const DenseArgs a, int
 // G = X_w X_w^T of window w0 + blockIdx.x over the depth blocks of chunk blockIdx.y, out[(window gridDim.y +
 // chunk) 4096].  The dependent rounds of a window read G[t][t2] for t2 >= t only: of the sixteen 16 x 16 blocks
 // the ten on and above the diagonal are taken, dealt to the four wavefronts, the others are left unwritten.
-// Every wavefront reads the 64 rows (from L1 for three of the four), two depth blocks ahead of its matrix instructions.
-__device__ __forceinline__ void gram_blocks(int wave, int (&ra)[3], int (&cb)[3])
-{
-    ra[0] = wave == 0 ? 0 : wave == 1 ? 1 : wave == 2 ? 2 : 3; cb[0] = ra[0];         // the diagonal
-    ra[1] = wave == 1 ? 1 : wave == 3 ? 2 : 0; cb[1] = wave == 0 ? 1 : wave == 1 ? 2 : 3;   // (0,1) (1,2) (0,3) (2,3)
-    ra[2] = wave == 1 ? 1 : 0; cb[2] = wave == 1 ? 3 : 2;                             // wavefronts 0, 1 only: (0,2) (1,3)
-}
+// Every wavefront reads the 64 rows (from L1 for three of the four), three depth blocks ahead of its matrix instructions.
+constexpr int kGramBlocks[4] = {3, 3, 2, 2};                        // of a wavefront, and where they lie
+constexpr int kGramRow[4][3] = {{0, 0, 0}, {1, 1, 1}, {2, 0, 0}, {3, 2, 0}};
+constexpr int kGramCol[4][3] = {{0, 1, 2}, {1, 2, 3}, {2, 3, 0}, {3, 3, 0}};
 __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, WinPlanD plan, int w0, float *out)
 {
     const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
@@ -321,9 +318,6 @@ __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, 
     const int w = w0 + (int)blockIdx.x, nblk = (d + 15) / 16;
     const int ws = plan.start(w), wl = plan.len(w);
     const int b_lo = (int)((int64_t)blockIdx.y * nblk / gridDim.y), b_hi = (int)((int64_t)(blockIdx.y + 1) * nblk / gridDim.y);
-    f4 acc[3];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) acc[b] = f4{0.f, 0.f, 0.f, 0.f};
     const float *xr = x + (int64_t)ws * d + 4 * lk;
     auto fetch = [&](int blk, f4 (&o)[4]) __attribute__((always_inline)) {
 #pragma unroll
@@ -333,42 +327,37 @@ __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, 
             o[b] = ok ? *reinterpret_cast<const f4 *>(xr + (int64_t)t * d + blk * 16) : f4{0.f, 0.f, 0.f, 0.f};
         }
     };
-    auto times = [&](auto wc, const f4 (&o)[4]) __attribute__((always_inline)) {
-        constexpr int W = decltype(wc)::value;
-        constexpr int ra1 = W == 1 ? 1 : W == 3 ? 2 : 0, cb1 = W == 0 ? 1 : W == 1 ? 2 : 3;
-        constexpr int ra2 = W == 1 ? 1 : 0, cb2 = W == 1 ? 3 : 2;
+    auto blocks = [&](auto wc) __attribute__((always_inline)) {
+        constexpr int W = decltype(wc)::value, N = kGramBlocks[W];
+        f4 acc[N], o[4][4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[W][r], o[W][r], acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[ra1][r], o[cb1][r], acc[1], 0, 0, 0);
-            if (W < 2) acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[ra2][r], o[cb2][r], acc[2], 0, 0, 0);
-        }
-    };
-    auto depth = [&](auto wc) __attribute__((always_inline)) {
-        f4 o[4][4];
+        for (int b = 0; b < N; ++b) acc[b] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < 3; ++i) fetch(b_lo + i, o[i]);
         for (int blk = b_lo; blk < b_hi; blk += 4) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {                           // (past b_hi: zeros)
+            static_for<4>([&](auto ic) __attribute__((always_inline)) {   // (past b_hi: zeros)
+                constexpr int i = decltype(ic)::value;
                 fetch(blk + i + 3, o[(i + 3) & 3]);
-                times(wc, o[i]);
-            }
+                static_for<4>([&](auto rc) __attribute__((always_inline)) {
+                    constexpr int r = decltype(rc)::value;
+                    static_for<N>([&](auto bc) __attribute__((always_inline)) {
+                        constexpr int b = decltype(bc)::value, ra = kGramRow[W][b], cb = kGramCol[W][b];
+                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[i][ra][r], o[i][cb][r], acc[b], 0, 0, 0);
+                    });
+                });
+            });
         }
+        float *g = out + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * kB * kB;
+        static_for<N>([&](auto bc) __attribute__((always_inline)) {
+            constexpr int b = decltype(bc)::value, ra = kGramRow[W][b], cb = kGramCol[W][b];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) g[(ra * 16 + 4 * lk + r) * kB + cb * 16 + lr] = acc[b][r];
+        });
     };
-    if (wave == 0) depth(std::integral_constant<int, 0>{});
-    else if (wave == 1) depth(std::integral_constant<int, 1>{});
-    else if (wave == 2) depth(std::integral_constant<int, 2>{});
-    else depth(std::integral_constant<int, 3>{});
-    int ra[3], cb[3];
-    gram_blocks(wave, ra, cb);
-    float *g = out + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * kB * kB;
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-        if (b < 2 || wave < 2) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) g[(ra[b] * 16 + 4 * lk + r) * kB + cb[b] * 16 + lr] = acc[b][r];
-        }
+    if (wave == 0) blocks(std::integral_constant<int, 0>{});
+    else if (wave == 1) blocks(std::integral_constant<int, 1>{});
+    else if (wave == 2) blocks(std::integral_constant<int, 2>{});
+    else blocks(std::integral_constant<int, 3>{});
 }
 
 // ... and the chunks' sum, in chunk order
