@@ -124,14 +124,6 @@ __device__ __forceinline__ void tile_sync()
     __syncthreads();
 }
 
-template <int LOSS> __device__ __forceinline__ float slope(float z, float y)
-{
-    if (LOSS == 0) return 1.0f;
-    if (LOSS == 1) return 2.0f * (z - y);
-    // logistic: -y / (1 + exp(y z)); exp overflow gives -y * (1/inf) = -0
-    return -y * fast_rcp(1.0f + __expf(y * z));
-}
-
 template <int VW> __device__ __forceinline__ float combine(const float (&acc)[VW])
 {
     if (VW == 4) return (acc[0] + acc[1]) + (acc[2] + acc[3]);

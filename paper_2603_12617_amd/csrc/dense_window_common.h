@@ -32,13 +32,6 @@ struct WinPlanD {
     __host__ __device__ int len(int w) const { const int s = start(w); const int l = w == 0 ? first_len() : kB; return l < n - s ? l : n - s; }
 };
 
-template <int LOSS> __device__ __forceinline__ float slope(float z, float y)
-{
-    if (LOSS == 0) return 1.0f;
-    if (LOSS == 1) return 2.0f * (z - y);
-    return -y * __builtin_amdgcn_rcpf(1.0f + __expf(y * z));
-}
-
 // every lane of a quad gets the value of the quad's lane SEL
 template <int SEL> __device__ __forceinline__ double quad_bcast(double v)
 {

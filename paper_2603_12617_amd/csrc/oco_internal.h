@@ -214,6 +214,15 @@ template <int LOSS> __device__ __forceinline__ double phi(double z, double y)
     return m > 0.0 ? lp : lp + am;
 }
 
+// Their slopes, in float32 (round kernels).
+template <int LOSS> __device__ __forceinline__ float slope(float z, float y)
+{
+    if (LOSS == 0) return 1.0f;
+    if (LOSS == 1) return 2.0f * (z - y);
+    // logistic: -y / (1 + exp(y z)); exp overflow gives -y * (1/inf) = -0
+    return -y * __builtin_amdgcn_rcpf(1.0f + __expf(y * z));
+}
+
 // ---- state export -----------------------------------------------------------
 struct ExportArgs {
     const float *V;

@@ -78,13 +78,6 @@
 namespace oco {
 namespace {
 
-template <int LOSS> __device__ __forceinline__ float slope(float z, float y)
-{
-    if (LOSS == 0) return 1.0f;
-    if (LOSS == 1) return 2.0f * (z - y);
-    return -y * __builtin_amdgcn_rcpf(1.0f + __expf(y * z));
-}
-
 // V is updated by float atomics, which execute in L2, or by plain stores, which write through to it: every
 // read of V in the window kernel goes to L2 as well, past the compute unit's own cache.  (Plain cached loads with
 // that cache dropped once per window measured slower: 23.7 against 20.6 ms on the largest sparse workload.)
