@@ -15,10 +15,11 @@
 // workgroups' work (shares, hint scalars) it reads from one of two buffers and writes the other.  The inner
 // products are those of the iterates themselves (no cross-Gram correction as in dense_window_kernel) and
 // ||w||^2 is measured every window.
-// What bounds it: the dependent rounds (9 - 10 us per window), the turn-around of a launch (3.6 us) and the sum
-// over the chunks' shares in front of them (2.6 us for 16 chunks, 5 for 64).  4000 optimistic rounds of 256
-// learners, d = 2048, take 1.44 ms against 3.0 ms on the register kernel; 2000 rounds of 16 learners,
-// d = 32768 (64 chunks of 512 coordinates), 1.1 ms against 29.4 ms on dense_window_kernel.
+// What bounds it (wall clock per window; 256 learners of d = 2048, optimistic, logistic / 16 learners of d = 32768, plain,
+// squared): the dependent rounds 10.9 / 8.1 us, the sum over the chunks' shares and the other inputs in front of them
+// 2.6 (16 chunks) / 5.3 (64), the sweep 2.2 / 6.1, shares out 0.5, start and end of a launch 2.5.  4000 rounds of the first take
+// 1.44 ms against 3.0 ms on the register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 1.1 ms against
+// 29.4 ms on dense_window_kernel.
 //
 // The round rows are read as they are, without the re-tiled copies of dense_window.hip: with few tiles
 // a copy would cost more than it saves.  The Gram matrices of the windows are taken by
