@@ -35,7 +35,10 @@ constexpr int kRow = kKC + 4;      // padded row length in floats (keeps 16-byte
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-template <bool VEC>
+// FINE: the matrix instructions' sums of 8 coordinates are added up to one per LDS chunk, those in float64.  One chain over
+// the whole depth has 500 roundings at d = 1000, and its error in u x was most of the error in the regret of split windows
+// (2 - 10 times that of the register kernel, whose lanes and tree have 22; now no larger on any case tried).
+template <bool VEC, bool FINE>
 __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs a)
 {
     __shared__ __attribute__((aligned(16))) float us[kTileRuns * kRow];
@@ -67,10 +70,14 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
 
     for (int s = s_lo; s <= s_hi; ++s) {
         floatx16 acc;
+        double tot[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        for (int v = 0; v < 16; ++v) { acc[v] = 0.f; tot[v] = 0.0; }
 
         for (int kc = kc_lo; kc < kc_hi; kc += kKC) {
+            floatx16 sum;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] = 0.f;
             // stage 64 rows x kKC coordinates of U (segment s) and of X
             if (VEC) {
 #pragma unroll
@@ -103,10 +110,22 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
             for (int kk = 0; kk < kKC; kk += 8) {
                 const float4 av = *reinterpret_cast<const float4 *>(ua + kk);
                 const float4 bv = *reinterpret_cast<const float4 *>(xa + kk);
+                if (FINE) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                }
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv.w, acc, 0, 0, 0);
+                if (FINE) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) sum[v] += acc[v];
+                }
+            }
+            if (FINE) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) tot[v] += (double)sum[v];
             }
             __syncthreads();
         }
@@ -120,8 +139,9 @@ __global__ void __launch_bounds__(256) comparator_gemm_kernel(ComparatorGemmArgs
             for (int v = 0; v < 16; ++v) {
                 const int run = rb + (wave >> 1) * 32 + 8 * (v / 4) + 4 * half + (v % 4);
                 if (run >= a.R) continue;
-                if (gridDim.z > 1) a.part[((int64_t)blockIdx.z * a.R + run) * a.n + t] = acc[v];
-                else a.Z[(int64_t)run * a.zl.zs_r + (int64_t)a.K * a.zl.zs_i + (int64_t)t * a.zl.zs_t] = acc[v];
+                const float z = FINE ? (float)tot[v] : acc[v];
+                if (gridDim.z > 1) a.part[((int64_t)blockIdx.z * a.R + run) * a.n + t] = z;
+                else a.Z[(int64_t)run * a.zl.zs_r + (int64_t)a.K * a.zl.zs_i + (int64_t)t * a.zl.zs_t] = z;
             }
         }
     }
@@ -145,10 +165,13 @@ hipError_t launch_comparator_gemm(const ComparatorGemmArgs &a, hipStream_t s)
     const bool split = a.part && a.chunks > 1 && a.R <= 65535;
     const dim3 grid((unsigned)((a.n + kTileRounds - 1) / kTileRounds), (unsigned)((a.R + kTileRuns - 1) / kTileRuns),
                     split ? (unsigned)a.chunks : 1u);
-    if (a.vec_ok)
-        hipLaunchKernelGGL(comparator_gemm_kernel<true>, grid, dim3(256), 0, s, a);
+    if (a.fine && !a.vec_ok) return hipErrorInvalidValue;
+    if (a.fine)
+        hipLaunchKernelGGL((comparator_gemm_kernel<true, true>), grid, dim3(256), 0, s, a);
+    else if (a.vec_ok)
+        hipLaunchKernelGGL((comparator_gemm_kernel<true, false>), grid, dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(comparator_gemm_kernel<false>, grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((comparator_gemm_kernel<false, false>), grid, dim3(256), 0, s, a);
     if (split) hipLaunchKernelGGL(comparator_sum_kernel, dim3((unsigned)((a.n + 255) / 256), (unsigned)a.R), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -309,6 +309,9 @@ __global__ void __launch_bounds__(64) split_finish_kernel(const DenseArgs a, int
 // chunk) 4096].  The dependent rounds of a window read G[t][t2] for t2 >= t only: of the sixteen 16 x 16 blocks
 // the ten on and above the diagonal are taken, dealt to the four wavefronts, the others are left unwritten.
 // Every wavefront reads the 64 rows (from L1 for three of the four), three depth blocks ahead of its matrix instructions.
+// The sums of a depth block (16 products) are added up in float64: as one float32 chain over a chunk's depth (270 products
+// at d = 516) their error was that of ||x||^2 in every projection, and the iterates of large steps had up to three times the
+// register kernel's.
 constexpr int kGramBlocks[4] = {3, 3, 2, 2};                        // of a wavefront, and where they lie
 constexpr int kGramRow[4][3] = {{0, 0, 0}, {1, 1, 1}, {2, 0, 0}, {3, 2, 0}};
 constexpr int kGramCol[4][3] = {{0, 1, 2}, {1, 2, 3}, {2, 3, 0}, {3, 3, 0}};
@@ -331,14 +334,19 @@ __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, 
     auto blocks = [&](auto wc) __attribute__((always_inline)) {
         constexpr int W = decltype(wc)::value, N = kGramBlocks[W];
         f4 acc[N], o[4][4];
+        double tot[N][4];
 #pragma unroll
-        for (int b = 0; b < N; ++b) acc[b] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < N; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tot[b][r] = 0.0;
 #pragma unroll
         for (int i = 0; i < 3; ++i) fetch(b_lo + i, o[i]);
         for (int blk = b_lo; blk < b_hi; blk += 4) {
             static_for<4>([&](auto ic) __attribute__((always_inline)) {   // (past b_hi: zeros)
                 constexpr int i = decltype(ic)::value;
                 fetch(blk + i + 3, o[(i + 3) & 3]);
+#pragma unroll
+                for (int b = 0; b < N; ++b) acc[b] = f4{0.f, 0.f, 0.f, 0.f};
                 static_for<4>([&](auto rc) __attribute__((always_inline)) {
                     constexpr int r = decltype(rc)::value;
                     static_for<N>([&](auto bc) __attribute__((always_inline)) {
@@ -346,13 +354,17 @@ __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, 
                         acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[i][ra][r], o[i][cb][r], acc[b], 0, 0, 0);
                     });
                 });
+#pragma unroll
+                for (int b = 0; b < N; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) tot[b][r] += (double)acc[b][r];
             });
         }
         float *g = out + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * kB * kB;
         static_for<N>([&](auto bc) __attribute__((always_inline)) {
             constexpr int b = decltype(bc)::value, ra = kGramRow[W][b], cb = kGramCol[W][b];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) g[(ra * 16 + 4 * lk + r) * kB + cb * 16 + lr] = acc[b][r];
+            for (int r = 0; r < 4; ++r) g[(ra * 16 + 4 * lk + r) * kB + cb * 16 + lr] = (float)tot[b][r];
         });
     };
     if (wave == 0) blocks(std::integral_constant<int, 0>{});
@@ -451,7 +463,7 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
     ComparatorGemmArgs g{};
     g.x = a.x; g.u = a.u; g.seg_start = a.seg_start; g.S = a.S; g.Z = a.Z; g.zl = a.zl;
     g.d = a.d; g.K = a.K; g.R = a.R; g.t0 = a.t0; g.n = a.n; g.vec_ok = a.vec_ok;
-    g.chunks = p.cmp_chunks; g.part = a.gram + p.cmp_off;
+    g.chunks = p.cmp_chunks; g.part = a.gram + p.cmp_off; g.fine = true;
     hipStream_t cs = s;
     hipError_t e = beside ? hook->beside(hook->ctx, &cs) : hipSuccess;   // only the meta kernel reads its output
     if (e == hipSuccess) e = launch_comparator_gemm(g, cs);

@@ -333,3 +333,36 @@ def test_windows_are_the_default_for_many_learners_of_narrow_models(over, n_min,
     capfd.readouterr()
     _check(wl, data, _gpu(wl, data, options=dict(verbose=1)), runs=[0, wl.R - 1], label="one run fewer")
     assert "windowed contraction kernel" not in capfd.readouterr().err
+
+
+# One entry of the Gram matrix and the comparator's predictions can be seen through the ABI: with the linear loss and a
+# ball that is never left, z_1 = -eta <x_0, x_1>, and with a step of 1e-30 the regret of two rounds is -<u, x_0 + x_1>.  Products of
+# one sign, so that a long float32 chain shows: one chain over a range of the depth is off by 3.0 to 5.8 units of 2^-24 in the
+# mean square here.  Bound: 2^-24 in the mean square over 100 pairs of rows; the result's own float32 roundings
+# (two, each 0.4 2^-24) and the short sums in front of them are 0.7 of it.
+@pytest.mark.parametrize("d", [516, 1000])
+@pytest.mark.parametrize("what", ["gram", "comparator"])
+def test_sums_of_split_coordinates_are_as_good_as_their_rounding(d, what):
+    eta = 0.01 if what == "gram" else 1e-30
+    wl = WL.make("c1", T=2, d=d, R=1, K=1, eta=(eta,), D=1e6)
+    data = WL.generate(wl)
+    sim = B.Simulation(wl, data, options=dict(window_resident=5))
+    rng = np.random.default_rng(5)
+    x = rng.uniform(0.5, 1.0, (100, 2, d)).astype(np.float32)
+    u = rng.uniform(0.5, 1.0, (1, 1, d)).astype(np.float32)
+    xd, ud = sim.torch.from_numpy(x).to(sim.dev), sim.torch.from_numpy(u).to(sim.dev)
+    B.oco_set_comparator(sim.h, ud, [0, wl.T])
+    err = []
+    for i in range(len(x)):
+        B.oco_reset(sim.h)
+        B.oco_run_rounds(sim.h, 0, 2, x_ptr=xd.data_ptr() + 4 * 2 * d * i)
+        x0, x1 = x[i].astype(np.float64)
+        if what == "gram":
+            got, want = sim.cum_losses().ravel()[0], -float(np.float32(eta)) * (x0 @ x1)
+        else:
+            got, want = sim.regret()[0], -(u[0, 0].astype(np.float64) @ (x0 + x1))
+        err.append(got / want - 1.0)
+    sim.close()
+    rms = float(np.sqrt(np.mean(np.square(err))))
+    print("%s d=%d: rms %.2f of 2^-24" % (what, d, rms * 2 ** 24))
+    assert rms <= 2.0 ** -24
