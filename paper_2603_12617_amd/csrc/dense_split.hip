@@ -44,6 +44,7 @@ struct LdsS {
     using G = double;
     using S = double;
     static constexpr int g_reads = 2;
+    static constexpr bool carry_norm = true;
     static constexpr bool has_corr = false;
     static constexpr int gd_bytes = kB * 4 * kGStride * 8;
     static constexpr int tile_f = kB * kM * 4, tile_s = kB * kM * 8;

@@ -179,6 +179,7 @@ template <int NW, int MT> struct LdsT {
     using G = double;                                              // Gram table
     using S = std::conditional_t<wide, double, float>;             // inner products handed to the rounds, f_t
     static constexpr int g_reads = 1;                               // how the rounds read the Gram table (chain_window)
+    static constexpr bool carry_norm = false;
     static constexpr bool has_corr = true;                         // the rounds start from pmul q0 + corr
     static constexpr int gd_bytes = kB * 4 * kGStride * (int)sizeof(G);   // G [64][4][kGStride]: G[t][t2], zero for t2 <= t;
                                                                    //   [t][0][16] holds G[t][t]
@@ -779,6 +780,7 @@ struct LdsQ {
     using G = double;
     using S = float;
     static constexpr int g_reads = 0;
+    static constexpr bool carry_norm = false;
     static constexpr bool has_corr = false;
     static constexpr int gd_bytes = kB * 4 * kGStride * 8;
     static constexpr int tile_f = kB * kM * 4, tile_s = tile_f;

@@ -96,7 +96,9 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
     // dependent part runs in float32: the next prediction is taken from the float64 pending value
     // by one float32 step, f (p - a G), as exact as a float32 inner product of that size; the
     // squared norm is carried in float32 within the window like the register kernel carries it
-    // between its exact measurements (the caller re-anchors it every window).  The pending
+    // between its exact measurements (the caller re-anchors it every window), or, with Lds::carry_norm, in float64 and
+    // as the factor applied leaves it: taken as D^2 after a projection it loses the errors of the factors, which then
+    // add up over the window (norm off by 1.5e-7 after 56 rounds, 9e-8 on the register kernel; so 2.8e-8).  The pending
     // predictions themselves stay float64 (their recurrence is 64 rounds long); round t - 1's
     // update of them shares a scheduling region with the dependent part of round t and fills its
     // latencies.
@@ -112,6 +114,7 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
     double gprev[16];                 // round t - 1's row of G (elements j >= (t - 1) / 4)
     double aprev = 0.0, fprev = 1.0;
     float n2f = (float)n2;
+    double n2c = n2;                  // ||w_t||^2 where Lds::carry_norm
     float znext = (float)p[0];        // this lane's candidate for the next prediction (round 0: lane 0's is the one)
     // label and ||x||^2 of a round are read from LDS one round ahead: they are the first things the
     // dependent part needs, and nothing else would cover the latency of the read
@@ -177,10 +180,15 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
         float a32 = LOSS == 1 ? eta2 * (zp - yt) : eta * slope<LOSS>(zp, yt);
         a32 = t < wl ? a32 : 0.f;
         // ||w_t - a_t x_t||^2 and the projection factor
-        const float m2 = fmaxf(fmaf(a32, fmaf(a32, x2t, -2.f * z32), n2f), 0.f);
+        const float dn = fmaf(a32, x2t, -2.f * z32);                 // (||w_t - a_t x_t||^2 - ||w_t||^2) / a_t
+        double m2d = 0.0;
+        float m2;
+        if constexpr (Lds::carry_norm) { m2d = fmax(fma((double)a32, (double)dn, n2c), 0.0); m2 = (float)m2d; }
+        else m2 = fmaxf(fmaf(a32, dn, n2f), 0.f);
         const bool pj = m2 > D2f;
         const float f32v = pj ? Df * __builtin_amdgcn_rsqf(m2) : 1.f;
-        n2f = pj ? D2f : m2;
+        if constexpr (Lds::carry_norm) { n2c = m2d * (double)f32v * (double)f32v; n2f = (float)n2c; }
+        else n2f = pj ? D2f : m2;
         anyp = anyp || pj;
         zb[t * kM] = zp;                                             // (the quad's four lanes write the same value)
         stl[t * kM] = a32;
@@ -199,7 +207,7 @@ __device__ __forceinline__ double chain_window(char *lds, int buf, int m, int la
         fprev = (double)f32v;
         __builtin_amdgcn_sched_barrier(0);                           // at most two rounds overlap: registers
     });
-    n2 = (double)n2f;
+    n2 = Lds::carry_norm ? n2c : (double)n2f;
     if (OPT) { hint->ha = ha; hint->hp = hp; hint->x2p = x2p; }
 
     // Bm[r] = a_r f_r f_{r+1} ... f_63 and F = fscale f_0 ... f_63: quad lane s takes the rounds

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2603_12617_amd import binding as B
 from paper_2603_12617_amd import workloads as WL
-from test_gpu_parity import _check, _gpu
+from test_gpu_parity import _check, _gpu, _oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -365,4 +365,21 @@ def test_sums_of_split_coordinates_are_as_good_as_their_rounding(d, what):
     sim.close()
     rms = float(np.sqrt(np.mean(np.square(err))))
     print("%s d=%d: rms %.2f of 2^-24" % (what, d, rms * 2 ** 24))
+    assert rms <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("d", [516, 1000])
+def test_projections_of_split_coordinates_do_not_add_up_their_errors(d):
+    """Learners that project in nearly every round: the error of the iterate along itself is that of the last window's
+    fold (a float32 factor) and of a factor's rounding, not of the window's up to 64 factors together.  Bound: 2^-24 in the
+    mean square over 48 learners and more (half of it measured; taken as D after every projection 2.5 times it)."""
+    wl = WL.make("c4", T=3000, d=d, R=16, K=4)
+    data = WL.generate(wl)
+    got = _gpu(wl, data, options=dict(window_resident=5))
+    ref = _oracle().run_workload(wl, data)["W"]
+    n2 = (ref ** 2).sum(2)
+    along = ((got["W"] - ref) * ref).sum(2)[n2 > 0.98 * wl.D ** 2] / wl.D ** 2
+    assert along.size >= 48
+    rms = float(np.sqrt(np.mean(along ** 2)))
+    print("d=%d: %d learners at the boundary, rms %.2f of 2^-24" % (d, along.size, rms * 2 ** 24))
     assert rms <= 2.0 ** -24
