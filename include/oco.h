@@ -43,11 +43,11 @@
  *    whose inner products are grouped differently at the start of a call than
  *    inside it: the same calls give the same bits, different splits agree to
  *    float32 rounding.  (By default: shared streams of d > 4096, of at least 2048
- *    learners with d >= 512, and calls of at least 512 rounds with at least 3072
- *    learners or, with d > 512, at most 2048: with the coordinates split over
- *    workgroups, where splits at multiples of 64 are bit-identical if every call
- *    but the last of the horizon is that long.  With OCO_OPT_DENSE_PATH 1 a stream
- *    of d <= 4096 stays on the register kernel, and any split gives the same bits.)
+ *    learners with d >= 512, and calls of at least 512 rounds with d > 512 and
+ *    at most 2048 learners: those with the coordinates split over workgroups,
+ *    where splits at multiples of 64 are bit-identical if every call but the last
+ *    of the horizon is that long.  With OCO_OPT_DENSE_PATH 1 a stream of d <= 4096
+ *    stays on the register kernel, and any split gives the same bits.)
  *    Sparse configurations work in segments of 4096 rounds of
  *    the horizon: splits at multiples of 4096 are bit-identical, other splits
  *    regroup float32 sums and agree to rounding.

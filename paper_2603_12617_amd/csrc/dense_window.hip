@@ -1233,14 +1233,11 @@ bool dense_window_wanted(const DenseArgs &a)
     if (path == 2) return true;
     // measured on MI355X: c4 (16384 learners, d = 4096) 72 ms against the register kernel's 136 ms; c3 (4352
     // learners, d = 1000) 50 ms against 62 ms.  Fewer learners stay with the register kernel (a round costs about
-    // 0.35 us here whatever d is, as long as the workgroups fit the chip at once); narrower problems come here
-    // with learners enough that their wavefronts share the register kernel's issue slots.  2048 rounds, register
-    // kernel / windows, ms: 2048 learners 0.71 / 0.68 (d = 16) to 0.87 / 0.92 (d = 512); 4096 learners 0.92 / 0.68
-    // to 1.21 / 0.94; 8192 learners 1.48 / 0.74 to 1.65 / 1.02; 24576 learners 3.80 / 1.84 to 4.38 / 2.68; of 512
-    // rounds, 8192 learners, d = 256 0.37 / 0.28.  (Shorter calls of narrow problems keep the kernel whose results no
-    // cut of the horizon changes.)
-    const int64_t learners = (int64_t)a.R * a.K;
-    return a.d > 64 * kWave || (learners >= 2048 && a.d >= 512) || (learners >= 3072 && a.n >= 512);
+    // 0.35 us here whatever d is, as long as the workgroups fit the chip at once), and so do narrower models: from 3072
+    // learners on this kernel would be up to twice as fast there (8192 learners, 2048 rounds 1.48 / 0.74 ms at d = 16, 1.65 / 1.02 at
+    // d = 512), but its float32 hand-overs make the results less accurate against float64 (4096 learners, 1024 squared-loss
+    // rounds of d = 256: iterates 4.5e-7 / 1.3e-6, combined 1.7e-7 / 7.4e-7) and dependent on how the horizon is cut.
+    return a.d > 64 * kWave || ((int64_t)a.R * a.K >= 2048 && a.d >= 512);
 }
 
 hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, const PieceHook *hook)
