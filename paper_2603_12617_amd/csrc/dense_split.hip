@@ -16,9 +16,9 @@
 // products are those of the iterates themselves (no cross-Gram correction as in dense_window_kernel) and
 // ||w||^2 is measured every window.
 // What bounds it (wall clock per window; 256 learners of d = 2048, optimistic, logistic / 16 learners of d = 32768, plain,
-// squared): the dependent rounds 10.9 / 8.1 us, the sum over the chunks' shares and the other inputs in front of them
-// 2.6 (16 chunks) / 5.3 (64), the sweep 2.2 / 6.1, shares out 0.5, start and end of a launch 2.5.  4000 rounds of the first take
-// 1.44 ms against 3.0 ms on the register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 1.1 ms against
+// squared): the dependent rounds 11.1 / 8.2 us, the sum over the chunks' shares and the other inputs in front of them
+// 2.5 (16 chunks) / 5.4 (64), the sweep 2.2 / 6.1, shares out 0.5, start and end of a launch 2.5 - 3.  4000 rounds of the first take
+// 1.48 ms against 3.0 ms on the register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 1.1 ms against
 // 29.4 ms on dense_window_kernel.
 //
 // The round rows are read as they are, without the re-tiled copies of dense_window.hip: with few tiles
@@ -438,11 +438,12 @@ bool dense_split_wanted(const DenseArgs &a)
     if (ropt != -1 && ropt != 5) return false;
     SplitPlan p;
     if (!make_split_plan(a, &p)) return false;
-    // Measured per call of 2048 rounds, register kernel (d <= 4096) or dense_window_kernel against this one, ms:
-    // d = 512 0.69 / 0.67 (4 learners) and 0.85 / 0.77 (1024); d = 1024 1.12 / 0.71 and 1.38 / 0.82; d = 4096
-    // 2.10 / 0.77 and 2.99 / 1.29; of 640 rounds, d = 8192 2.51 / 0.36 (2 learners) and 2.61 / 0.72 (1024),
-    // d = 65536 28.6 / 4.5 (1024).  128 tiles (2048 learners, 2048 rounds): d = 520 0.89 (dense_window_kernel) / 0.84,
-    // d = 1000 1.12 / 0.97, d = 4096 2.52 / 1.90; 160 tiles, one chunk each: d = 2048 1.63 / 1.81, d = 520 0.89 / 0.93.  A call costs about 60 us here whatever its length, hence the least n; one
+    // Measured per pass of 2048 squared-loss rounds, register kernel / this one, ms: d = 516 0.81 / 0.63 (4 learners) and 0.94 / 0.72
+    // (2048); d = 1000 0.83 / 0.67 and 0.98 / 0.85; d = 4096 1.95 / 0.71 and, 1024 learners, 2.73 / 1.23; of 512 rounds, d = 516 0.26 /
+    // 0.25 and 0.31 / 0.27, d = 1000 0.26 / 0.24 and 0.34 / 0.32 (512 learners 0.265 / 0.275, the one point that lost).  Against
+    // dense_window_kernel: 640 rounds, d = 8192 2.50 / 0.31 (2 learners) and 2.60 / 0.69 (1024), d = 65536 28.7 / 4.5 (1024); 128
+    // tiles (2048 learners, 2048 rounds), d = 520 0.82 / 0.74, d = 1000 1.11 / 0.85, d = 4096 3.5 / 1.8; 160 tiles, one chunk each, lost
+    // (d = 2048 1.63 / 1.81, d = 520 0.89 / 0.93).  A call costs about 60 us here whatever its length, hence the least n; one
     // that need not come here (d <= 4096) stays with the register kernel, whose results no cut of the horizon changes.
     // The horizon's last call, which is as short as the cuts leave it, stays with the kernel of the calls before it: equal
     // calls and a rest give the bits of one call (cuts at multiples of 64).
