@@ -131,6 +131,15 @@ constexpr double kSparseFoldSoft = OCO_FOLD_SOFT;  // fold between segments
 #define OCO_SEGMENT 4096
 #endif
 constexpr int kSegment = OCO_SEGMENT;        // rounds per launch segment (absolute alignment)
+// The fold inside the kernel: learners below this scale are folded (the one that stopped the chain and whoever will
+// soon follow), the others of the workgroup keep their scale.
+constexpr float kSparseFoldJoinF = 0x1p-72f;
+// The 32 words that pad a row of V (oco_create): words 0 .. 15 of row j mark column j as visited, a bit per workgroup
+// (all clear outside a fold), words 16 .. 18 of row q hold the rounds learner q was last folded at (below).
+constexpr int kPadWords = 32, kPadFolds = 16, kMarkWorkgroups = 32 * kPadFolds;
+// A fold visits the columns of the rounds in question while their entries are fewer than this many times d, else all d.
+// (one visit by entry: a mark, the row, the mark again; by row: the row)
+constexpr int kFoldEntriesPerRow = 2;
 constexpr int kWin = 64;                     // rounds per window (absolute alignment)
 constexpr int kSpWaves = 16;                 // wavefronts per workgroup
 constexpr int kBesideMaxWorkgroups = 128;    // window grids up to this size leave half the chip idle
@@ -193,7 +202,8 @@ static_assert(kHeadOffs == 4 * kWin && kHeadG01 == 4 * kWin + 32 && kHeadCross =
 
 __global__ void __launch_bounds__(1024) sparse_gram_kernel(const int32_t *col, const float *val, int nnz,
                                                           WinPlan plan, WinRec *recs, int optimistic,
-                                                          const int32_t *last_col, const float *last_val, int shares, int wofs)
+                                                          const int32_t *last_col, const float *last_val, int shares, int wofs,
+                                                          float *V, int d, int RKp, int nq)
 {
     __shared__ unsigned int xm[kWin][2];
     __shared__ int xrowoff[kWin + 1];
@@ -208,6 +218,10 @@ __global__ void __launch_bounds__(1024) sparse_gram_kernel(const int32_t *col, c
     const int total = wl * nnz;
     const unsigned mdiv = ((1u << 18) + nnz - 1) / nnz;       // e / nnz == (e * mdiv) >> 18 for e < 4096
     WinRec &rec = recs[w];
+    if (w == 0)      // before the horizon's first round V is zero; what earlier calls touched is not known here
+        for (int q = threadIdx.x; q < nq && q < d; q += blockDim.x)
+            for (int i = 0; i < 3; ++i)
+                reinterpret_cast<int *>(V)[(int64_t)q * RKp + RKp - kPadWords + kPadFolds + i] = plan.t0 == 0 ? 0 : -1;
     for (int e = threadIdx.x; e < total; e += blockDim.x) {
         const int c = col[(int64_t)ws * nnz + e];
         cs[e] = c;
@@ -542,9 +556,9 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
     auto stage_of = [&](int w) { return stage_at(stage0 + (PIPE ? (w - wbeg) % 3 : (w - wbeg) & 1) * stage_n, a.nnz); };
     // in-kernel fold: round after which the chain stopped (-1: none), the learners' scales, and
     // one partial squared norm per wavefront and learner
-    __shared__ int fold_t, fold_gp, met;
+    __shared__ int fold_t, fold_gp, fold_lo, met;
     __shared__ float fold_sf[LPW];
-    __shared__ double fold_part[kSpWaves][LPW];
+    __shared__ long long fold_part[kSpWaves][LPW];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -633,6 +647,7 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
     const float *yrow = a.y ? a.y + (int64_t)r * a.y_run_stride : nullptr;
     const unsigned zoff4 = 4u * (unsigned)(r * a.zl.zs_r + i * a.zl.zs_i);    // byte offset inside a round's slice of Z
     const int64_t zstep = 4 * a.zl.zs_t;
+    const bool fold_sel = nq <= a.d && nblk <= kMarkWorkgroups;   // the padding holds the marks and every learner's folds
     const WinRec *recs = reinterpret_cast<const WinRec *>(static_cast<const char *>(a.scratch) + kProgBytes);
     // the lanes that run the dependent rounds (padding learners of the last workgroup take no part:
     // their step sizes stay zero and their scale stays one)
@@ -1141,28 +1156,96 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
         const int gp0 = fold_gp;
         have_q0 = false;           // what was gathered for the next window is void after a fold
         // ---- fold inside the window (sigma below 2^-100 before the segment ended): apply the
-        // steps taken so far, scale the workgroup's columns of V by sigma with all wavefronts,
-        // measure ||v||^2 exactly, and take the remaining rounds' <v, x_t> afresh ----------------
+        // steps taken so far, scale the columns of the learners at or near the threshold by their
+        // sigma with all wavefronts, measure their ||v||^2, and take the remaining rounds' <v, x_t>
+        // afresh.  Which rows of V: a column holds values of at most D sigma after the first fold that
+        // follows its last touch, so of at most D 2^-144 after the third, and what falls below the
+        // smallest normal number is set to zero.  So a learner's columns are those of the rounds since
+        // its third-last fold (a stretch of the stream), each visited once by way of a mark; rounds
+        // of earlier calls are not at hand, and a long stretch has more entries than V rows: then all
+        // rows.  Either way the same values come out.  (Steps larger than the ball shrink sigma by a
+        // constant factor per round, a fold every 10 .. 100 rounds; visiting all rows each time, 3435 rounds
+        // of 348 learners, d = 745735, took 456 ms.) -----------------------------------------------------
         apply(v, bw, ft, std::true_type());
+        if (wave == 0) {
+            int lo = 0x7fffffff;
+            if (chain && fold_sf[l] < kSparseFoldJoinF && fold_sel) {
+                int *h = reinterpret_cast<int *>(a.V) + (int64_t)q * a.RKp + a.RKp - kPadWords + kPadFolds;
+                const int h0 = __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int h1 = __hip_atomic_load(h + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lo = __hip_atomic_load(h + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(h, v.ws + ft + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(h + 1, h0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(h + 2, h1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int sh = 32; sh; sh >>= 1) { const int o = __shfl_xor(lo, sh); lo = o < lo ? o : lo; }
+            if (lane == 0) fold_lo = fold_sel ? lo : -1;
+        }
         wg_sync();
         {
             for (int rd = (int)threadIdx.x / LPW; rd <= ft; rd += kSpWaves * EPI) bw[rd][l] = 0.f;   // applied
             const float fs = fold_sf[l];
+            const bool mine = fs < kSparseFoldJoinF;
             const int64_t nslots = kSpWaves * EPI;
-                double m2 = 0.0;
-            for (int64_t j0 = wave * EPI + e; j0 < a.d; j0 += 4 * nslots) {
-                float vv[4];
+            // ||v||^2 of a folded learner (at most about D^2) in units of 2^-52 D^2: whole numbers, whose sum does
+            // not depend on which entry of a column was first
+            double Dv = a.D;
+            int blkv = blk, dv = a.d;
+            asm volatile("" : "+v"(Dv), "+s"(blkv), "+s"(dv));   // nothing of the fold is taken out of the window loop: registers
+            const double unit = 0x1p52 / (Dv * Dv);
+            long long m2 = 0;
+            auto folded = [&](float vv) {
+                float wv = vv * fs;
+                wv = fabsf(wv) < 0x1p-126f ? 0.f : wv;
+                m2 += (long long)((double)wv * (double)wv * unit);
+                return wv;
+            };
+            const int lo = fold_lo;
+            const int64_t e0 = (int64_t)lo * nnz, e1 = (int64_t)(v.ws + ft + 1) * nnz;
+            if (lo >= 0 && kFoldEntriesPerRow * (e1 - e0) < dv) {
+                unsigned *mark = reinterpret_cast<unsigned *>(a.V) + a.RKp - kPadWords + blkv / 32;
+                const unsigned bit = 1u << (blkv % 32);
+                constexpr int NF = 4;                        // entries in flight per slot
+                for (int64_t k0 = e0 + wave * EPI + e; k0 < e1; k0 += NF * nslots) {
+                    int cc[NF];
+                    unsigned seen[NF];
+                    float vv[NF];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t j = j0 + u * nslots;
-                    vv[u] = j < a.d ? ldv(Vq + j * a.RKp) : 0.f;
+                    for (int u = 0; u < NF; ++u) {
+                        const int64_t k = k0 + u * nslots;
+                        cc[u] = a.col[k < e1 ? k : k0];
+                    }
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) {
+                        seen[u] = bit;
+                        if (l == 0 && k0 + u * nslots < e1)
+                            seen[u] = __hip_atomic_fetch_or(mark + (int64_t)cc[u] * a.RKp, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) vv[u] = ldv(Vq + (int64_t)cc[u] * a.RKp);
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) {
+                        const bool first = (__shfl(seen[u], e * LPW) & bit) == 0;
+                        if (first && mine) Vq[(int64_t)cc[u] * a.RKp] = folded(vv[u]);
+                    }
                 }
+                wg_sync();
+                for (int64_t k = e0 + threadIdx.x; k < e1; k += kSpWaves * kWave)
+                    __hip_atomic_fetch_and(mark + (int64_t)a.col[k] * a.RKp, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                for (int64_t j0 = wave * EPI + e; j0 < dv; j0 += 4 * nslots) {
+                    float vv[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t j = j0 + u * nslots;
-                    const float wv = vv[u] * fs;
-                    if (j < a.d) Vq[j * a.RKp] = wv;
-                    m2 += (double)wv * (double)wv;
+                    for (int u = 0; u < 4; ++u) {
+                        const int64_t j = j0 + u * nslots;
+                        vv[u] = j < dv ? ldv(Vq + j * a.RKp) : 0.f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int64_t j = j0 + u * nslots;
+                        if (j < dv && mine) Vq[j * a.RKp] = folded(vv[u]);
+                    }
                 }
             }
 #pragma unroll
@@ -1170,10 +1253,10 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
             if (lane < LPW) fold_part[wave][l] = m2;
         }
         wg_sync();
-        if (chain) {
-            double m2 = 0.0;
+        if (chain && fold_sf[l] < kSparseFoldJoinF) {
+            long long m2 = 0;
             for (int wv = 0; wv < kSpWaves; ++wv) m2 += fold_part[wv][l];
-            hd = 0.5 * m2;
+            hd = 0.5 * (double)m2 * (a.D * a.D * 0x1p-52);
             sigma = 1.0; sf = 1.f; isf = 1.f;
         }
         if (threadIdx.x == 0) fold_t = -1;
@@ -1396,7 +1479,7 @@ hipError_t launch_sparse_rounds(const SparseArgs &a0, int loss, hipStream_t s, c
     const bool split = hook && hook->beside && hook->mark && hook->wait_mark && nwin1 < nwin;
     const int nfirst = split ? nwin1 : nwin;
     hipLaunchKernelGGL(sparse_gram_kernel, dim3(nfirst), dim3(1024), 0, s, a.col, a.val, a.nnz, plan, recs, a.optimistic,
-                       a.last_col, a.last_val, kSpWaves - 1, 0);
+                       a.last_col, a.last_val, kSpWaves - 1, 0, a.V, a.d, a.RKp, a.R * a.K);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
 
@@ -1410,7 +1493,7 @@ hipError_t launch_sparse_rounds(const SparseArgs &a0, int loss, hipStream_t s, c
         }
         if (split) {
             hipLaunchKernelGGL(sparse_gram_kernel, dim3(nwin - nfirst), dim3(1024), 0, cs, a.col, a.val, a.nnz, plan, recs,
-                               a.optimistic, a.last_col, a.last_val, kSpWaves - 1, nfirst);
+                               a.optimistic, a.last_col, a.last_val, kSpWaves - 1, nfirst, a.V, a.d, a.RKp, a.R * a.K);
             e = hipGetLastError();
             if (e == hipSuccess) e = hook->mark(hook->ctx);
             if (e != hipSuccess) return e;

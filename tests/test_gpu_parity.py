@@ -414,6 +414,25 @@ def test_sparse_rounds_with_steps_far_larger_than_the_ball(lpw):
     _check_sparse_optimistic(wl, data, _gpu(wl, data, options=opt), "c5 optimistic big steps lpw=%d" % lpw)
 
 
+@pytest.mark.parametrize("lpw", [4, 16, 64])
+@pytest.mark.parametrize("d,nnz", [(20011, 4), (3001, 32), (40000, 8)])
+def test_folds_that_visit_the_columns_of_recent_rounds(lpw, d, nnz):
+    """Steps from well inside the ball to thousands of times its radius: learners of one workgroup fold at
+    rates of their own, from every few hundred rounds to every few rounds.  With few entries per round and a
+    long d a fold visits the columns of the rounds since the third-last fold; in a call that begins after the
+    horizon's start the first folds visit all rows, and so does every one where d is short.  Calls that end at a
+    multiple of 4096 give the bits of one call all the same."""
+    T = 4500
+    wl = WL.make("c5", T=T, R=3, d=d, K=5, nnz=nnz, wstar_nnz=32, eta=(0.02, 0.9, 3.0, 40.0, 5000.0))
+    data = WL.generate(wl)
+    print("case c5 folds lpw", lpw, "d", d, "nnz", nnz, flush=True)
+    whole = _gpu(wl, data, options=dict(sparse_lpw=lpw))
+    _check(wl, data, whole, norm_every=0, label="c5 folds lpw=%d d=%d" % (lpw, d))
+    part = _gpu(wl, data, chunk=4096, n_max=4096, options=dict(sparse_lpw=lpw))
+    for k in ("regret", "L", "W", "p", "wbar"):
+        assert np.array_equal(whole[k], part[k]), k
+
+
 @pytest.mark.parametrize("lpw", [4, 8, 64])
 def test_sparse_rounds_with_a_column_in_every_round(lpw):
     """A feature present in every round (a bias column) makes every pair of rounds of a window
