@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(64) dense_tile_kernel(const float *x, int d, W
             *reinterpret_cast<f4 *>(xq + tile + (rb * 64 + l) * 4) = v;
         }
     }
-    {
+    if (xu) {
         const int c = blk * 16 + lr;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -117,6 +117,86 @@ __global__ void __launch_bounds__(64) dense_tile_kernel(const float *x, int d, W
                 v[r] = (c < d && t < wl) ? xw[(int64_t)t * d + lr] : 0.f;
             }
             *reinterpret_cast<f4 *>(xu + tile + (k * 64 + l) * 4) = v;
+        }
+    }
+}
+
+// ---- rows and iterates as three bfloat16 parts ---------------------------------------------------
+// v = v1 + v2 + v3, each part the bfloat16 nearest to what the ones before leave: 3 x 8 bits hold all 24 of a
+// float32.  A product of two such numbers is taken as its six largest part products, each exact in float32, by the
+// 16-bit matrix instructions: dropped are (2,3), (3,2) and (3,3), at most 2^-25 of the product (a float32 rounding), and
+// six products cost 0.375 of the time of the float32 instructions' one.
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+constexpr int kSplitFloats = kTileFloats * 3 / 2;            // one window x one block, split: 6 KB
+
+// two neighbouring values: their first, second and third parts, packed
+__device__ __forceinline__ void split2(float a, float b, unsigned &p1, unsigned &p2, unsigned &p3)
+{
+    auto pack = [](float x, float y) { return __builtin_bit_cast(unsigned, __builtin_convertvector(f2{x, y}, bf2)); };
+    auto lo = [](unsigned p) { return __uint_as_float(p << 16); };
+    auto hi = [](unsigned p) { return __uint_as_float(p & 0xFFFF0000u); };
+    p1 = pack(a, b);
+    const float ra = a - lo(p1), rb = b - hi(p1);
+    p2 = pack(ra, rb);
+    p3 = pack(ra - lo(p2), rb - hi(p2));
+}
+__device__ __forceinline__ f4 mfma_bf16(u4 a, u4 b, f4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+
+// The round rows of the windows w0 .. w0 + gridDim.y - 1 in parts, as dense_window_shared_kernel wants them.  v_mfma_f32_16x16x32_bf16
+// takes A 16x32 and B 32x16, lane l with A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16]; which depth index is which
+// coordinate or round is free.  One wavefront per (window, block of 16 coordinates), 16 bytes per lane and KB:
+//   xq: KB rb = 0 .. 3: parts 1 (four coordinates 4 (l / 16) ..) and 2 of round 16 rb + l % 16; KB 4, 5: part 3 of rounds
+//       16 rb + l % 16 for rb = 0, 1 and 2, 3 -- a depth of 32 is the block's 16 coordinates for two products at once;
+//   xu: KB 2 p + s: part p of coordinate l % 16, rounds 32 s + 8 (l / 16) ..
+__global__ void __launch_bounds__(64) dense_tile_split_kernel(const float *x, int d, WinPlanD plan, int w0, float *xq, float *xu)
+{
+    const int blk = blockIdx.x, w = w0 + blockIdx.y, nblk = gridDim.x;
+    const int ws = plan.start(w), wl = plan.len(w);
+    const int l = threadIdx.x, lr = l & 15, lk = l >> 4;
+    const int64_t tile = ((int64_t)blockIdx.y * nblk + blk) * kSplitFloats;
+    const float *xw = x + (int64_t)ws * d + blk * 16;
+    {
+        u4 *out = reinterpret_cast<u4 *>(xq + tile) + l;
+        u4 third[2];
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+            const int t = rb * 16 + lr;
+            f4 v = f4{0.f, 0.f, 0.f, 0.f};
+            if (blk * 16 + 4 * lk < d && t < wl) v = *reinterpret_cast<const f4 *>(xw + (int64_t)t * d + 4 * lk);
+            unsigned a1, a2, a3, b1, b2, b3;
+            split2(v[0], v[1], a1, a2, a3);
+            split2(v[2], v[3], b1, b2, b3);
+            out[rb * 64] = u4{a1, b1, a2, b2};
+            third[rb >> 1][2 * (rb & 1)] = a3;
+            third[rb >> 1][2 * (rb & 1) + 1] = b3;
+        }
+        out[4 * 64] = third[0];
+        out[5 * 64] = third[1];
+    }
+    {
+        u4 *out = reinterpret_cast<u4 *>(xu + tile) + l;
+        const int c = blk * 16 + lr;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            u4 p[3];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int t = 32 * s + 8 * lk + 2 * j;
+                const float v0 = (c < d && t < wl) ? xw[(int64_t)t * d + lr] : 0.f;
+                const float v1 = (c < d && t + 1 < wl) ? xw[(int64_t)(t + 1) * d + lr] : 0.f;
+                unsigned q1, q2, q3;
+                split2(v0, v1, q1, q2, q3);
+                p[0][j] = q1; p[1][j] = q2; p[2][j] = q3;
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) out[(2 * k + s) * 64] = p[k];
         }
     }
 }
@@ -754,9 +834,8 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
 // the step's two blocks -- window k's in the lane order of (3), window k + 1's in that of (1) --
 // which serve all four tiles (4 KB of L2 traffic per tile and block where a wavefront that loads
 // its own rows needs 8 KB), and the eight blocks of iterates of the step; their registers are the
-// prefetch buffer (the loads of four steps are on their way).  The working wavefronts read the
-// operands of step s + 1 from LDS while the matrix instructions of step s run, and store the
-// new block; they never wait for a memory instruction.  (On this hardware one counter per
+// prefetch buffer (the loads of three steps are on their way).  The working wavefronts read
+// operands from LDS while matrix instructions run, and store the new block; they never wait for a memory instruction.  (On this hardware one counter per
 // wavefront covers loads and stores alike and runs in issue order, so a wavefront that stores
 // cannot wait for a younger load without also waiting for the acknowledgement of every older
 // store, several microseconds here.)
@@ -768,14 +847,23 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
 // once per window, after the dependent rounds); the barriers are therefore bare s_barrier
 // instructions behind a wait for the LDS operations of the wavefront (__syncthreads() would also
 // wait for every store's acknowledgement).
-// Measured on c4 (one workgroup per compute unit, 128 steps per window): 1.07 us per step with the
-// loads switched off against 0.85 us of matrix instructions, 1.35 us with them, whether the
-// loads go through registers or straight to LDS and whatever their distance; the dependent rounds
-// (not overlapped) and the hand-over between the phases add 35 us per window.
+// Rows and iterates enter the matrix instructions as three bfloat16 parts (split2): the rows are split once per launch
+// (dense_tile_split_kernel), -Bm once per window, an iterate's block when it has been updated; sums and the iterates
+// themselves stay float32.  Per block 24 instructions of 16 clocks in place of 32 of 32, for 6 KB of rows per window and
+// block instead of 4.  Error against float64 on c4: 4.9e-7, with float32 instructions 6.9e-7.
+// Measured on c4 (one workgroup per compute unit, 128 steps per window; us per step): 1.1, with float32 instructions
+// 1.45; 0.75 with the loads switched off (LDS reads, matrix and vector instructions), 0.84 with either the
+// rows or the iterates loaded alone, as long without matrix instructions as with them.  What bounds it is thus rows
+// (from L2) and iterates (through L2) together: the iterates are loaded and stored with the streaming hint, both or
+// neither (one of them: 10 ms per step worse), and lie in blocks (below).  Workgroups of an XCD held to one pace
+// by a counter: 10 ms worse; a different first block per XCD or workgroup: no difference; rows and iterates on loading
+// wavefronts of their own: no better with the hint, 17 ms worse without; four steps ahead instead of three: spills.
 constexpr int kQT = 4, kQS = 2;              // tiles per workgroup, working wavefronts per tile
 constexpr int kQW = kQT * kQS;               // working wavefronts; wavefront kQW loads
 constexpr int kQStages = 3;
-constexpr int kQL = 4, kQSets = 4;           // loading wavefronts; steps of loads each keeps in registers
+constexpr int kQL = 4, kQSets = 3;           // loading wavefronts; steps of loads each keeps in registers
+constexpr int kQUnroll = 6;                  // steps are walked in multiples of this (of kQStages and of kQSets)
+static_assert(kQUnroll % kQStages == 0 && kQUnroll % kQSets == 0, "stages and register sets are compile-time constants");
 struct LdsQ {
     using G = double;
     using S = float;
@@ -785,13 +873,12 @@ struct LdsQ {
     static constexpr int gd_bytes = kB * 4 * kGStride * 8;
     static constexpr int tile_f = kB * kM * 4, tile_s = tile_f;
     static constexpr int yb_bytes = kQT * tile_f, zb_bytes = kQT * tile_f, bm_bytes = kQT * tile_f, fv_bytes = kQT * kM * 4;
-    static constexpr int rows_bytes = kQS * 2 * 4096;              // per step and block: rows for (3), rows for (1)
+    static constexpr int blk_bytes = kSplitFloats * 4;             // a block's rows of one window
+    static constexpr int rows_bytes = kQS * 2 * blk_bytes;         // per step and block: rows for (3), rows for (1)
     static constexpr int stage_bytes = rows_bytes + kQW * 1024;    // ... and a block of iterates per working wavefront
     static constexpr int gd = 0;
     static constexpr int yb = gd + gd_bytes;
-    static constexpr int zb = yb + yb_bytes;
-    static constexpr int bm = zb + zb_bytes;
-    static constexpr int fv = bm + bm_bytes;
+    static constexpr int fv = yb + yb_bytes;
     static constexpr int n2 = fv + fv_bytes;                       // float [kQT][kQS * 4][16]: shares of ||w||^2
     static constexpr int hg = n2 + kQT * kQS * 4 * kM * 4;         // float [64]: <x_{t-1}, x_t> of the window's rounds (optimistic update)
     static constexpr int hg_bytes = kB * 4;
@@ -802,10 +889,41 @@ struct LdsQ {
     static constexpr int part_bytes = kQT * tile_f;
     static constexpr int st = ring + kQS * part_bytes;
     static constexpr int fl = st + kQT * tile_f;
+    // ... and the predictions and -Bm, which are read before the barrier that lets the loaders write stage 1
+    static constexpr int zb = fl + kQT * tile_s;
+    static constexpr int bm = zb + zb_bytes;
     static constexpr int corr = 0;                                 // (unused)
     static constexpr int total = ring + kQStages * stage_bytes;
 };
-static_assert(LdsQ::fl + kQT * LdsQ::tile_s <= LdsQ::total && LdsQ::total <= 160 * 1024, "LDS of a gfx950 compute unit");
+static_assert(LdsQ::bm + LdsQ::bm_bytes <= LdsQ::total && LdsQ::total <= 160 * 1024, "LDS of a gfx950 compute unit");
+static_assert(LdsQ::zb >= LdsQ::ring + LdsQ::stage_bytes, "stage 0 is written while -Bm and the predictions are read");
+
+// The iterates of a tile of 16 learners, in place from rows [16][d] to blocks of 16 coordinates [d / 16][64][4] as a wavefront
+// of the sweep loads and stores them (lane l: coordinates 4 (l / 16) .. of learner l % 16), or back: a block is then 1 KB of
+// memory in one piece instead of sixteen 64-byte pieces d floats apart.  One workgroup holds the tile in registers in between.
+// c4 with rows in parts: 65.6 ms per step from rows, 59.1 from blocks (0.1 ms each way); with float32 rows 68.4 and 65.4.
+constexpr int kBlocksMaxD = 4096;
+template <bool BACK> __global__ void __launch_bounds__(1024) tile_blocks_kernel(float *V, int d)
+{
+    f4 *v = reinterpret_cast<f4 *>(V + (int64_t)blockIdx.x * kM * d);
+    const int n = kM * d / 4, d4 = d / 4;
+    constexpr int N = kM * kBlocksMaxD / 4 / 1024;
+    f4 o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int e = (int)threadIdx.x + i * 1024;
+        if (e < n) o[i] = v[e];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // everything is in registers before the first store
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int e = (int)threadIdx.x + i * 1024;
+        if (e >= n) continue;
+        if (BACK) v[(e & 15) * d4 + (e >> 6) * 4 + ((e >> 4) & 3)] = o[i];
+        else v[(e % d4 >> 2) * 64 + (e % d4 & 3) * 16 + e / d4] = o[i];
+    }
+}
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -814,7 +932,9 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
                                                                                const float *xq, const float *xu, float *misc,
                                                                                WinPlanD plan, int w0, int nw)
 {
-    (void)gxt;
+    // (gxt: no cross Gram matrix here; not null: the iterates lie in blocks, see tile_blocks_kernel)
+    const bool blocked = gxt != nullptr;
+    const int vstep = blocked ? 16 * kM : 16;                    // from a block of a lane's learner to the next
     using Lds = LdsQ;
     constexpr int NT = kQW * kWave;                              // working threads
     extern __shared__ __align__(16) char lds[];
@@ -822,17 +942,13 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
     const int nq = a.R * K;
     const int nblk = (d + 15) / 16;
     const int nstep = (nblk + kQS - 1) / kQS;
-    const int npad = (nstep + kQSets * kQStages - 1) / (kQSets * kQStages) * (kQSets * kQStages);   // steps every wavefront walks
+    const int npad = (nstep + kQUnroll - 1) / kQUnroll * kQUnroll;   // steps every wavefront walks
     const int q_base = (int)blockIdx.x * kQT * kM;
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool loader = wave >= kQW;
     const int tau = wave & (kQT - 1), sg = (wave / kQT) & (kQS - 1);
     const int lr = lane & 15, lk = lane >> 4;
-    const int q_sw = q_base + tau * kM + lr;                     // this lane's learner in the sweep
-    const bool q_ok = q_sw < nq;
-    float *vrow = a.V + (int64_t)(q_ok ? q_sw : 0) * d + 4 * lk;
-    float *sink = misc + kMiscZeros + (tid & (NT - 1)) * 4;
 
     // dependent rounds: wavefront m < kQT, lane = 4 learner + quad lane
     float eta = 0.f;
@@ -864,13 +980,18 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
 #endif
 
     // The loader's side of a sweep: rows for (3) from window wu of the piece, rows for (1) from window wq.
-    struct Regs { f4 r[6]; };
-    Regs rg[kQSets];                                             // loaders: four steps of loads (the prefetch buffer)
+    struct Regs { f4 r[8]; };
+    Regs rg[kQSets];                                             // loaders: kQSets steps of loads (the prefetch buffer)
     // The loaders' side of a sweep: rows for (3) from window wu of the piece, rows for (1) from window wq.
     // `first`: the loads of the first four steps are issued here; otherwise they were issued at the end of
     // the sweep before (nwu >= 0: issue those of the next sweep, rows from windows nwu / nwq), so that
     // they travel while the dependent rounds run.
     auto load_sweep = [&](int wu, int wq, bool first, int nwu, int nwq) __attribute__((always_inline)) {
+        // (what a lane is, from an index the compiler cannot see through: kept across the dependent rounds it would be
+        // spilled, and every reload in the loop would wait for all the loads on their way)
+        int tid_l = (int)threadIdx.x;
+        asm volatile("" : "+v"(tid_l));
+        const int lane = tid_l & 63, lr = lane & 15, lk = lane >> 4;
         // the learners whose blocks this lane loads, tile by tile
         const float *vr[2];
         bool vok[2];
@@ -878,7 +999,7 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         for (int m = 0; m < 2; ++m) {
             const int q = q_base + (2 * ((wave - kQW) >> 1) + m) * kM + lr;
             vok[m] = q < nq;
-            vr[m] = a.V + (int64_t)(vok[m] ? q : 0) * d + 4 * lk;
+            vr[m] = a.V + (blocked ? (int64_t)(vok[m] ? q / kM : 0) * kM * d + 4 * lane : (int64_t)(vok[m] ? q : 0) * d + 4 * lk);
         }
         // loader j: block kQS s + (j & 1) of step s; j < 2 its rows for (3) and the iterates of tiles 0, 1,
         // j >= 2 its rows for (1) and the iterates of tiles 2, 3
@@ -887,25 +1008,25 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
             const int sc = step < nstep ? step : nstep - 1;
             int blk = sc * kQS + L;
             blk = blk < nblk ? blk : nblk - 1;                   // (rows past the last block: loaded again, not used)
-            const float *src = (part == 0 ? xu + ((int64_t)fu * nblk + blk) * kTileFloats
-                                          : xq + ((int64_t)fq * nblk + blk) * kTileFloats) + lane * 4;
+            const float *src = (part == 0 ? xu + ((int64_t)fu * nblk + blk) * kSplitFloats
+                                          : xq + ((int64_t)fq * nblk + blk) * kSplitFloats) + lane * 4;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) o.r[c] = *reinterpret_cast<const f4 *>(src + c * 256);
+            for (int c = 0; c < 6; ++c) o.r[c] = *reinterpret_cast<const f4 *>(src + c * 256);
             const int vblk = step * kQS + L;
             const bool bok = step < nstep && vblk < nblk && vblk * 16 + 4 * lk < d;
 #pragma unroll
-            for (int m = 0; m < 2; ++m) o.r[4 + m] = *reinterpret_cast<const f4 *>((bok && vok[m]) ? vr[m] + vblk * 16 : misc);
+            for (int m = 0; m < 2; ++m) o.r[6 + m] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>((bok && vok[m]) ? vr[m] + (int64_t)vblk * vstep : misc));
         };
         auto fetch = [&](int step, Regs &o) __attribute__((always_inline)) { fetch_of(wu, wq, step, o); };
         auto put = [&](int stage, const Regs &o) __attribute__((always_inline)) {
             char *st = lds + Lds::ring + stage * Lds::stage_bytes + lane * 16;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) *reinterpret_cast<f4 *>(st + L * 8192 + part * 4096 + c * 1024) = o.r[c];
+            for (int c = 0; c < 6; ++c) *reinterpret_cast<f4 *>(st + (2 * L + part) * Lds::blk_bytes + c * 1024) = o.r[c];
 #pragma unroll
-            for (int m = 0; m < 2; ++m) *reinterpret_cast<f4 *>(st + Lds::rows_bytes + (L * kQT + 2 * part + m) * 1024) = o.r[4 + m];
+            for (int m = 0; m < 2; ++m) *reinterpret_cast<f4 *>(st + Lds::rows_bytes + (L * kQT + 2 * part + m) * 1024) = o.r[6 + m];
         };
         // Phase p (up to barrier p): step p's operands from registers to stage p % 3, then the loads of step
-        // p + kQSets into the registers they came from (the registers are the prefetch buffer: four steps of
+        // p + kQSets into the registers they came from (the registers are the prefetch buffer: kQSets steps of
         // loads are on their way).  After barrier p the working wavefronts read stage p while they work step
         // p - 1; the stage was last read two phases earlier.
         if (first) {
@@ -915,8 +1036,8 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         put(0, rg[0]);
         fetch(kQSets, rg[0]);
         lds_barrier();
-        for (int sb = 0; sb < npad; sb += kQSets * kQStages) {
-            static_for<kQSets * kQStages>([&](auto uc) __attribute__((always_inline)) {
+        for (int sb = 0; sb < npad; sb += kQUnroll) {
+            static_for<kQUnroll>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
                 put((u + 1) % kQStages, rg[(u + 1) % kQSets]);
                 fetch(sb + u + 1 + kQSets, rg[(u + 1) % kQSets]);
@@ -981,8 +1102,15 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
     // The working wavefronts' side.  F and -Bm of this lane's learner (bmr[rs]: round 4 rs + lk); do_q: take
     // the shares of W X^T.  stage_next: first write the staged labels and Gram table to LDS; flush_prev >= 0:
     // write the predictions of window flush_prev to Z.
-    auto sweep = [&](auto stager, bool do_q, float F, const float (&bmr)[16], bool stage_next, int flush_prev)
+    auto sweep = [&](auto stager, bool do_q, float F, const u4 (&bmr)[2][3], bool stage_next, int flush_prev)
         __attribute__((always_inline)) {
+        int tid_s = (int)threadIdx.x;                            // (see load_sweep)
+        asm volatile("" : "+v"(tid_s));
+        const int tid = tid_s, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+        const int q_sw = q_base + tau * kM + lr;                 // this lane's learner
+        const bool q_ok = q_sw < nq;
+        float *vrow = a.V + (blocked ? (int64_t)(q_ok ? q_sw / kM : 0) * kM * d + 4 * lane : (int64_t)(q_ok ? q_sw : 0) * d + 4 * lk);
+        float *sink = misc + kMiscZeros + (tid & (NT - 1)) * 4;
         if (flush_prev >= 0) {
             const int w = w0 + flush_prev;
             const int ws = plan.start(w), wl = plan.len(w);
@@ -1003,60 +1131,83 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         for (int rb = 0; rb < 4; ++rb) acc[rb] = f4{0.f, 0.f, 0.f, 0.f};
         float nn = 0.f;
         PROF_T(1);
-        // Two sets of operand registers: while the matrix instructions of step r - 1 run, the
-        // operands of step r come from LDS (the eight wavefronts would otherwise all read right
-        // after the barrier, 72 KB through the LDS port with the matrix cores idle).
-        struct In { f4 xu[4], xq[4], vb; };
-        In in[2];
-        auto read_stage = [&](int stage, In &o) __attribute__((always_inline)) {
+        // A step's operands of (3) and its block of iterates come from LDS while the matrix instructions of the
+        // step before run, those of (1) while its own of (3) do.
+        u4 ux[2][3];
+        f4 vin;
+        auto read_u = [&](int stage) __attribute__((always_inline)) {
             const char *stg = lds + Lds::ring + stage * Lds::stage_bytes;
-            const char *rows = stg + sg * 8192 + lane * 16;
-            o.vb = *reinterpret_cast<const f4 *>(stg + Lds::rows_bytes + (sg * kQT + tau) * 1024 + lane * 16);
+            vin = *reinterpret_cast<const f4 *>(stg + Lds::rows_bytes + (sg * kQT + tau) * 1024 + lane * 16);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) o.xu[c] = *reinterpret_cast<const f4 *>(rows + c * 1024);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) o.xq[c] = *reinterpret_cast<const f4 *>(rows + 4096 + c * 1024);
+            for (int c = 0; c < 6; ++c) ux[c & 1][c >> 1] = *reinterpret_cast<const u4 *>(stg + 2 * sg * Lds::blk_bytes + c * 1024 + lane * 16);
         };
+        // all but the seven youngest stores acknowledged means those of the first steps, which the loaders read
+        // again right after the sweep, where there are enough of them
+        const bool many = nstep > kQSets + 8;
         lds_barrier();                                           // the loader has stage 0 complete
-        read_stage(0, in[0]);
-        for (int sb = 0; sb < npad; sb += 2 * kQStages) {
-            static_for<2 * kQStages>([&](auto uc) __attribute__((always_inline)) {
+        read_u(0);
+        for (int sb = 0; sb < npad; sb += kQUnroll) {
+            static_for<kQUnroll>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
                 const int step = sb + u;
                 const int blk = step * kQS + sg;
-                // all but the seven youngest stores have been acknowledged: among them those of the first four
-                // steps (npad >= 12), which the loaders read again right after this barrier
-                if (step == npad - 1) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
-                lds_barrier();                                   // stage step + 1 complete, own reads of stage step done
-                read_stage((u + 1) % kQStages, in[(u + 1) & 1]);
+                if (step == npad - 1) {
+                    if (many) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                }
+                lds_barrier();                                   // stage step + 1 complete; stage step - 1 is not read any more
+                u4 q12[4], q3[2];
+                {
+                    const char *qs = lds + Lds::ring + (u % kQStages) * Lds::stage_bytes + (2 * sg + 1) * Lds::blk_bytes + lane * 16;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) q12[c] = *reinterpret_cast<const u4 *>(qs + c * 1024);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) q3[c] = *reinterpret_cast<const u4 *>(qs + (4 + c) * 1024);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 const bool active = step < nstep && blk < nblk;  // wavefront-uniform
+                f4 vb = vin, vo = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) vb[r] *= F;
+                // the small products first, apart from the large ones
+                vo = mfma_bf16(ux[0][2], bmr[0][0], vo);
+                vb = mfma_bf16(ux[0][0], bmr[0][0], vb);
+                vo = mfma_bf16(ux[0][0], bmr[0][2], vo);
+                vb = mfma_bf16(ux[1][0], bmr[1][0], vb);
+                vo = mfma_bf16(ux[1][2], bmr[1][0], vo);
+                vo = mfma_bf16(ux[1][0], bmr[1][2], vo);
+                vo = mfma_bf16(ux[0][1], bmr[0][1], vo);
+                vo = mfma_bf16(ux[1][1], bmr[1][1], vo);
+                vo = mfma_bf16(ux[0][1], bmr[0][0], vo);
+                vo = mfma_bf16(ux[0][0], bmr[0][1], vo);
+                vo = mfma_bf16(ux[1][1], bmr[1][0], vo);
+                vo = mfma_bf16(ux[1][0], bmr[1][1], vo);
+                __builtin_amdgcn_sched_barrier(0);
+                read_u((u + 1) % kQStages);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) vb[r] += vo[r];
                 if (active) {
-                    In &c = in[u & 1];
-                    f4 vb = c.vb;
-                    f4 vo = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) vb[r] *= F;
-#pragma unroll
-                    for (int rs = 0; rs < 16; rs += 2) {
-                        vb = __builtin_amdgcn_mfma_f32_16x16x4f32(c.xu[rs >> 2][rs & 3], bmr[rs], vb, 0, 0, 0);
-                        vo = __builtin_amdgcn_mfma_f32_16x16x4f32(c.xu[rs >> 2][(rs & 3) + 1], bmr[rs + 1], vo, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) vb[r] += vo[r];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) nn = fmaf(vb[r], vb[r], nn);
                     {
                         const bool ok = q_ok && blk * 16 + 4 * lk < d;
-                        float *dst = ok ? vrow + blk * 16 : sink;
-                        *reinterpret_cast<f4 *>(dst) = vb;
+                        float *dst = ok ? vrow + (int64_t)blk * vstep : sink;
+                        __builtin_nontemporal_store(vb, reinterpret_cast<f4 *>(dst));   // (streams: the rows stay in L2)
                     }
                     if (do_q) {
+                        unsigned a1, a2, a3, b1, b2, b3;
+                        split2(vb[0], vb[1], a1, a2, a3);
+                        split2(vb[2], vb[3], b1, b2, b3);
+                        const u4 w11 = u4{a1, b1, a1, b1}, w22 = u4{a2, b2, a2, b2}, w31 = u4{a3, b3, a1, b1};
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
+                        for (int rb = 0; rb < 4; ++rb) {
+                            const u4 x13 = u4{q12[rb][0], q12[rb][1], q3[rb >> 1][2 * (rb & 1)], q3[rb >> 1][2 * (rb & 1) + 1]};
+                            acc[rb] = mfma_bf16(x13, w31, acc[rb]);
+                        }
 #pragma unroll
-                            for (int rb = 0; rb < 4; ++rb)
-                                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.xq[rb][r], vb[r], acc[rb], 0, 0, 0);
+                        for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_bf16(q12[rb], w22, acc[rb]);
+#pragma unroll
+                        for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_bf16(q12[rb], w11, acc[rb]);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -1094,9 +1245,9 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         using Stager = std::integral_constant<bool, !CHAIN>;
         {
             // the stored iterates times the rows of the first window: a sweep whose step changes nothing
-            float zero[16];
+            u4 zero[2][3];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+            for (int i = 0; i < 6; ++i) zero[i & 1][i >> 1] = u4{0u, 0u, 0u, 0u};
             if constexpr (!CHAIN) load_next(0);
             sweep(Stager{}, true, 1.f, zero, true, -1);
         }
@@ -1116,10 +1267,17 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();
             PROF_T(4);
-            float bmr[16];
-            const float *bml = reinterpret_cast<const float *>(lds + Lds::bm + tau * Lds::tile_f);
+            u4 bmr[2][3];                                        // -Bm in parts: rounds 32 s + 8 lk .. of this lane's learner
+            const float *bml = reinterpret_cast<const float *>(lds + Lds::bm + tau * Lds::tile_f) + lr;
 #pragma unroll
-            for (int rs = 0; rs < 16; ++rs) bmr[rs] = bml[(rs * 4 + lk) * kM + lr];
+            for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 32 * s2 + 8 * lk + 2 * j;
+                    unsigned p1, p2, p3;
+                    split2(bml[r * kM], bml[(r + 1) * kM], p1, p2, p3);
+                    bmr[s2][0][j] = p1; bmr[s2][1][j] = p2; bmr[s2][2][j] = p3;
+                }
             const float F = reinterpret_cast<const float *>(lds + Lds::fv)[tau * kM + lr];
             sweep(Stager{}, more, F, bmr, more, k);
         }
@@ -1309,13 +1467,31 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        lds_bytes);
     if (e != hipSuccess) return e;
-    for (int w0 = 0; w0 < nwin; w0 += (int)sc.piece_windows) {
-        const int nw = std::min<int>((int)sc.piece_windows, nwin - w0);
-        hipLaunchKernelGGL(dense_tile_kernel, dim3((unsigned)nblk, (unsigned)nw), dim3(64), 0, s, a.x, a.d, plan, w0, xq, xu, misc);
+    // rows in parts are half as long again: two thirds of the windows in the same scratch
+    const bool blocked = mode == 3 && a.d % 16 == 0 && a.d <= kBlocksMaxD && (int64_t)a.R * a.K % kM == 0;
+    auto turn_blocks = [&](bool to_rows) -> hipError_t {
+        if (!blocked) return hipSuccess;
+        if (to_rows) hipLaunchKernelGGL(tile_blocks_kernel<true>, dim3((unsigned)(a.R * a.K / kM)), dim3(1024), 0, s, a.V, a.d);
+        else hipLaunchKernelGGL(tile_blocks_kernel<false>, dim3((unsigned)(a.R * a.K / kM)), dim3(1024), 0, s, a.V, a.d);
+        return hipGetLastError();
+    };
+    e = turn_blocks(false);
+    if (e != hipSuccess) return e;
+    const int pw = mode == 3 ? std::max(1, (int)sc.piece_windows * 2 / 3) : (int)sc.piece_windows;
+    if (mode == 3 && (size_t)pw * nblk * 2 * kSplitFloats > 2 * sc.tile_floats) return hipErrorInvalidValue;
+    for (int w0 = 0; w0 < nwin; w0 += pw) {
+        const int nw = std::min<int>(pw, nwin - w0);
+        hipLaunchKernelGGL(dense_tile_kernel, dim3((unsigned)nblk, (unsigned)nw), dim3(64), 0, s, a.x, a.d, plan, w0, xq,
+                           mode == 3 ? nullptr : xu, misc);
         hipLaunchKernelGGL(dense_gram_kernel, dim3((unsigned)nw), dim3(512), 0, s, xq, nblk, gram, gxt);
+        if (mode == 3) {                                         // (in the place of the float32 copies, which the Gram matrices are done with)
+            xu = xq + (size_t)pw * nblk * kSplitFloats;
+            hipLaunchKernelGGL(dense_tile_split_kernel, dim3((unsigned)nblk, (unsigned)nw), dim3(64), 0, s, a.x, a.d, plan, w0, xq, xu);
+        }
         e = clock_begin(a.clock, s, mode == 3 ? "dense_window_shared_kernel" : "dense_window_kernel");
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(waves * kWave), lds_bytes, s, a, gram, gxt, xq, xu, misc, plan, w0, nw);
+        hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(waves * kWave), lds_bytes, s, a, gram,
+                           mode == 3 && !blocked ? nullptr : gxt, xq, xu, misc, plan, w0, nw);
         e = hipGetLastError();
         if (e == hipSuccess) e = clock_end(a.clock, s);
         if (e == hipSuccess && beside) {
@@ -1324,6 +1500,8 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
         }
         if (e != hipSuccess) return e;
     }
+    e = turn_blocks(true);
+    if (e != hipSuccess) return e;
     return a.optimistic ? launch_keep_last_row(a, s) : hipSuccess;
 }
 
