@@ -22,6 +22,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
+PEAK_SPLIT_TFLOPS = 2516.6 / 6   # float32 products as six products of bfloat16 parts on the matrix cores
 PEAK_FP32_TFLOPS = 157.3     # MI355X fp32: vector (256 CUs x 2.4 GHz x 128 lanes x 2, packed) and matrix cores alike
 NONPACKED_FP32_TFLOPS = 78.65  # what vector code reaches when every instruction works 64 lanes x 1 (this build: packed fp32 off)
 PEAK_HBM_GBS = 8000.0
@@ -71,7 +72,8 @@ def algorithmic_hbm_bytes(wl, kernel, launches, in_registers=False):
     x = 4.0 * wl.T * wl.d * (1 if wl.x_shared else wl.R)
     b = x + 4.0 * wl.R * wl.T + 4.0 * wl.R * (wl.K + 1) * wl.T + 8.0 * wl.R * wl.K * wl.d * max(launches, 1)
     if kernel.startswith("dense_window"):
-        b += 4.0 * x
+        # (the kernel with loading wavefronts: a float32 copy for the Gram matrices, then two of three 16-bit parts)
+        b += 8.0 * x if kernel == "dense_window_shared_kernel" else 4.0 * x
         if not in_registers:
             b += 8.0 * wl.R * wl.K * wl.d * ((wl.T + 63) // 64)
     return b
@@ -102,9 +104,10 @@ def roofline_block(wl, kt, config_key):
         per_unit = 5.0 + 2.0 / wl.K
         executed = 4.0 if kernel.startswith("dense_window") else 4.0 + 2.0 / wl.K
         ach = per_unit * wl.units / launches / (avg_ms * 1e-3) / 1e12
-        rl.update(bound="mfma" if kernel.startswith("dense_window") else "alu", achieved=ach, peak=PEAK_FP32_TFLOPS,
-                  unit="TFLOP/s", frac=ach / PEAK_FP32_TFLOPS, flops_per_unit=per_unit,
-                  executed_flops_per_unit=executed, executed_flops_frac=ach * executed / per_unit / PEAK_FP32_TFLOPS)
+        peak = PEAK_SPLIT_TFLOPS if kernel == "dense_window_shared_kernel" else PEAK_FP32_TFLOPS
+        rl.update(bound="mfma" if kernel.startswith("dense_window") else "alu", achieved=ach, peak=peak,
+                  unit="TFLOP/s", frac=ach / peak, flops_per_unit=per_unit,
+                  executed_flops_per_unit=executed, executed_flops_frac=ach * executed / per_unit / peak)
         if not kernel.startswith("dense_window"):
             rl["non_packed_ceiling"] = {"peak": NONPACKED_FP32_TFLOPS, "unit": "TFLOP/s",
                                         "executed_flops_frac": ach * executed / per_unit / NONPACKED_FP32_TFLOPS,
