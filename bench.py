@@ -72,8 +72,8 @@ def algorithmic_hbm_bytes(wl, kernel, launches, in_registers=False):
     x = 4.0 * wl.T * wl.d * (1 if wl.x_shared else wl.R)
     b = x + 4.0 * wl.R * wl.T + 4.0 * wl.R * (wl.K + 1) * wl.T + 8.0 * wl.R * wl.K * wl.d * max(launches, 1)
     if kernel.startswith("dense_window"):
-        # (the kernel with loading wavefronts: a float32 copy for the Gram matrices, then two of three 16-bit parts)
-        b += 8.0 * x if kernel == "dense_window_shared_kernel" else 4.0 * x
+        # (loading wavefronts, rows in parts: a float32 copy for the Gram matrices, then two of three 16-bit parts)
+        b += 8.0 * x if kernel == "dense_window_parts_kernel" else 4.0 * x
         if not in_registers:
             b += 8.0 * wl.R * wl.K * wl.d * ((wl.T + 63) // 64)
     return b
@@ -104,7 +104,7 @@ def roofline_block(wl, kt, config_key):
         per_unit = 5.0 + 2.0 / wl.K
         executed = 4.0 if kernel.startswith("dense_window") else 4.0 + 2.0 / wl.K
         ach = per_unit * wl.units / launches / (avg_ms * 1e-3) / 1e12
-        peak = PEAK_SPLIT_TFLOPS if kernel == "dense_window_shared_kernel" else PEAK_FP32_TFLOPS
+        peak = PEAK_SPLIT_TFLOPS if kernel == "dense_window_parts_kernel" else PEAK_FP32_TFLOPS
         rl.update(bound="mfma" if kernel.startswith("dense_window") else "alu", achieved=ach, peak=peak,
                   unit="TFLOP/s", frac=ach / peak, flops_per_unit=per_unit,
                   executed_flops_per_unit=executed, executed_flops_frac=ach * executed / per_unit / peak)

@@ -127,7 +127,6 @@ __global__ void __launch_bounds__(64) dense_tile_kernel(const float *x, int d, W
 // 16-bit matrix instructions: dropped are (2,3), (3,2) and (3,3), at most 2^-25 of the product (a float32 rounding), and
 // six products cost 0.375 of the time of the float32 instructions' one.
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
-typedef unsigned u2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -832,9 +831,9 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
 // tile tau, blocks 2 s + sigma), and four wavefronts that only load.  All step through the blocks
 // together, one barrier per step.  The loaders bring to a ring of three LDS stages the rows of
 // the step's two blocks -- window k's in the lane order of (3), window k + 1's in that of (1) --
-// which serve all four tiles (4 KB of L2 traffic per tile and block where a wavefront that loads
-// its own rows needs 8 KB), and the eight blocks of iterates of the step; their registers are the
-// prefetch buffer (the loads of three steps are on their way).  The working wavefronts read
+// which serve all four tiles (2 KB of rows from L2 per tile and block, in parts 3, where a wavefront that loads
+// its own rows needs 8), and the eight blocks of iterates of the step; their registers are the
+// prefetch buffer (the loads of four steps are on their way, in parts of three).  The working wavefronts read
 // operands from LDS while matrix instructions run, and store the new block; they never wait for a memory instruction.  (On this hardware one counter per
 // wavefront covers loads and stores alike and runs in issue order, so a wavefront that stores
 // cannot wait for a younger load without also waiting for the acknowledgement of every older
@@ -847,12 +846,16 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
 // once per window, after the dependent rounds); the barriers are therefore bare s_barrier
 // instructions behind a wait for the LDS operations of the wavefront (__syncthreads() would also
 // wait for every store's acknowledgement).
-// Rows and iterates enter the matrix instructions as three bfloat16 parts (split2): the rows are split once per launch
+// Measured with float32 rows on c4 (one workgroup per compute unit, 128 steps per window): 1.07 us per step with the
+// loads switched off against 0.85 us of matrix instructions, 1.35 to 1.45 us with them, whether the
+// loads go through registers or straight to LDS and whatever their distance; the dependent rounds
+// (not overlapped) and the hand-over between the phases add 35 us per window.
+// Long calls of whole blocks (parts_pay) are the PARTS form: rows and iterates enter the matrix instructions as three
+// bfloat16 parts (split2).  The rows are split once per launch
 // (dense_tile_split_kernel), -Bm once per window, an iterate's block when it has been updated; sums and the iterates
 // themselves stay float32.  Per block 24 instructions of 16 clocks in place of 32 of 32, for 6 KB of rows per window and
 // block instead of 4.  Error against float64 on c4: 4.9e-7, with float32 instructions 6.9e-7.
-// Measured on c4 (one workgroup per compute unit, 128 steps per window; us per step): 1.1, with float32 instructions
-// 1.45; 0.75 with the loads switched off (LDS reads, matrix and vector instructions), 0.84 with either the
+// Measured on c4 as above, us per step: 1.1; 0.75 with the loads switched off (LDS reads, matrix and vector instructions), 0.84 with either the
 // rows or the iterates loaded alone, as long without matrix instructions as with them.  What bounds it is thus rows
 // (from L2) and iterates (through L2) together: the iterates are loaded and stored with the streaming hint, both or
 // neither (one of them: 10 ms per step worse), and lie in blocks (below).  Workgroups of an XCD held to one pace
@@ -861,10 +864,13 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
 constexpr int kQT = 4, kQS = 2;              // tiles per workgroup, working wavefronts per tile
 constexpr int kQW = kQT * kQS;               // working wavefronts; wavefront kQW loads
 constexpr int kQStages = 3;
-constexpr int kQL = 4, kQSets = 3;           // loading wavefronts; steps of loads each keeps in registers
-constexpr int kQUnroll = 6;                  // steps are walked in multiples of this (of kQStages and of kQSets)
-static_assert(kQUnroll % kQStages == 0 && kQUnroll % kQSets == 0, "stages and register sets are compile-time constants");
-struct LdsQ {
+constexpr int kQL = 4;                       // loading wavefronts
+// steps of loads each of them keeps in registers; steps are walked in multiples of the second (of kQStages and of the first)
+template <bool PARTS> constexpr int kQSets = PARTS ? 3 : 4;
+template <bool PARTS> constexpr int kQUnroll = PARTS ? 6 : 12;
+static_assert(kQUnroll<true> % kQStages == 0 && kQUnroll<true> % kQSets<true> == 0 && kQUnroll<false> % kQStages == 0 &&
+              kQUnroll<false> % kQSets<false> == 0 && kQUnroll<false> % 2 == 0, "stages and register sets are compile-time constants");
+template <bool PARTS> struct LdsQ {
     using G = double;
     using S = float;
     static constexpr int g_reads = 0;
@@ -873,12 +879,12 @@ struct LdsQ {
     static constexpr int gd_bytes = kB * 4 * kGStride * 8;
     static constexpr int tile_f = kB * kM * 4, tile_s = tile_f;
     static constexpr int yb_bytes = kQT * tile_f, zb_bytes = kQT * tile_f, bm_bytes = kQT * tile_f, fv_bytes = kQT * kM * 4;
-    static constexpr int blk_bytes = kSplitFloats * 4;             // a block's rows of one window
+    static constexpr int blk_bytes = (PARTS ? kSplitFloats : kTileFloats) * 4;   // a block's rows of one window
     static constexpr int rows_bytes = kQS * 2 * blk_bytes;         // per step and block: rows for (3), rows for (1)
     static constexpr int stage_bytes = rows_bytes + kQW * 1024;    // ... and a block of iterates per working wavefront
     static constexpr int gd = 0;
     static constexpr int yb = gd + gd_bytes;
-    static constexpr int fv = yb + yb_bytes;
+    static constexpr int fv = yb + yb_bytes + (PARTS ? 0 : zb_bytes + bm_bytes);
     static constexpr int n2 = fv + fv_bytes;                       // float [kQT][kQS * 4][16]: shares of ||w||^2
     static constexpr int hg = n2 + kQT * kQS * 4 * kM * 4;         // float [64]: <x_{t-1}, x_t> of the window's rounds (optimistic update)
     static constexpr int hg_bytes = kB * 4;
@@ -889,14 +895,20 @@ struct LdsQ {
     static constexpr int part_bytes = kQT * tile_f;
     static constexpr int st = ring + kQS * part_bytes;
     static constexpr int fl = st + kQT * tile_f;
-    // ... and the predictions and -Bm, which are read before the barrier that lets the loaders write stage 1
-    static constexpr int zb = fl + kQT * tile_s;
+    // ... and, beside the longer rows of the parts, the predictions and -Bm, which are read before the barrier that lets the
+    // loaders write stage 1
+    static constexpr int zb = PARTS ? fl + kQT * tile_s : yb + yb_bytes;
     static constexpr int bm = zb + zb_bytes;
     static constexpr int corr = 0;                                 // (unused)
     static constexpr int total = ring + kQStages * stage_bytes;
 };
-static_assert(LdsQ::bm + LdsQ::bm_bytes <= LdsQ::total && LdsQ::total <= 160 * 1024, "LDS of a gfx950 compute unit");
-static_assert(LdsQ::zb >= LdsQ::ring + LdsQ::stage_bytes, "stage 0 is written while -Bm and the predictions are read");
+template <bool PARTS> constexpr bool lds_q_ok()
+{
+    using L = LdsQ<PARTS>;
+    return L::fl + kQT * L::tile_s <= L::total && L::bm + L::bm_bytes <= L::total && L::total <= 160 * 1024;
+}
+static_assert(lds_q_ok<false>() && lds_q_ok<true>(), "LDS of a gfx950 compute unit");
+static_assert(LdsQ<true>::zb >= LdsQ<true>::ring + LdsQ<true>::stage_bytes, "stage 0 is written while -Bm and the predictions are read");
 
 // The iterates of a tile of 16 learners, in place from rows [16][d] to blocks of 16 coordinates [d / 16][64][4] as a wavefront
 // of the sweep loads and stores them (lane l: coordinates 4 (l / 16) .. of learner l % 16), or back: a block is then 1 KB of
@@ -927,22 +939,30 @@ template <bool BACK> __global__ void __launch_bounds__(1024) tile_blocks_kernel(
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int LOSS, bool OPT = false>
+// -Bm of a lane's learner: as float32, round 4 rs + l / 16, or in parts, rounds 32 s + 8 (l / 16) ..
+struct StepsF { float v[16]; };
+struct StepsP { u4 p[2][3]; };
+
+// PARTS: rows and iterates as bfloat16 parts (such launches are timed under the name dense_window_parts_kernel)
+template <int LOSS, bool OPT, bool PARTS>
 __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kernel(const DenseArgs a, const float *gram, const float *gxt,
                                                                                const float *xq, const float *xu, float *misc,
                                                                                WinPlanD plan, int w0, int nw)
 {
     // (gxt: no cross Gram matrix here; not null: the iterates lie in blocks, see tile_blocks_kernel)
-    const bool blocked = gxt != nullptr;
+    const bool blocked = PARTS && gxt != nullptr;
     const int vstep = blocked ? 16 * kM : 16;                    // from a block of a lane's learner to the next
-    using Lds = LdsQ;
+    using Lds = LdsQ<PARTS>;
+    using Steps = std::conditional_t<PARTS, StepsP, StepsF>;
+    constexpr int SETS = kQSets<PARTS>, UNROLL = kQUnroll<PARTS>;
+    constexpr int NC = Lds::blk_bytes / 1024;                    // 16-byte loads per lane and block of rows
     constexpr int NT = kQW * kWave;                              // working threads
     extern __shared__ __align__(16) char lds[];
     const int d = a.d, K = a.K;
     const int nq = a.R * K;
     const int nblk = (d + 15) / 16;
     const int nstep = (nblk + kQS - 1) / kQS;
-    const int npad = (nstep + kQUnroll - 1) / kQUnroll * kQUnroll;   // steps every wavefront walks
+    const int npad = (nstep + UNROLL - 1) / UNROLL * UNROLL;   // steps every wavefront walks
     const int q_base = (int)blockIdx.x * kQT * kM;
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -979,11 +999,10 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
     unsigned long long prof_[8] = {0, 0, 0, 0, 0, 0, 0, 0}, last_ = wall_clock64();
 #endif
 
-    // The loader's side of a sweep: rows for (3) from window wu of the piece, rows for (1) from window wq.
-    struct Regs { f4 r[8]; };
-    Regs rg[kQSets];                                             // loaders: kQSets steps of loads (the prefetch buffer)
+    struct Regs { f4 r[NC + 2]; };
+    Regs rg[SETS];                                               // loaders: SETS steps of loads (the prefetch buffer)
     // The loaders' side of a sweep: rows for (3) from window wu of the piece, rows for (1) from window wq.
-    // `first`: the loads of the first four steps are issued here; otherwise they were issued at the end of
+    // `first`: the loads of the first SETS steps are issued here; otherwise they were issued at the end of
     // the sweep before (nwu >= 0: issue those of the next sweep, rows from windows nwu / nwq), so that
     // they travel while the dependent rounds run.
     auto load_sweep = [&](int wu, int wq, bool first, int nwu, int nwq) __attribute__((always_inline)) {
@@ -1008,39 +1027,42 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
             const int sc = step < nstep ? step : nstep - 1;
             int blk = sc * kQS + L;
             blk = blk < nblk ? blk : nblk - 1;                   // (rows past the last block: loaded again, not used)
-            const float *src = (part == 0 ? xu + ((int64_t)fu * nblk + blk) * kSplitFloats
-                                          : xq + ((int64_t)fq * nblk + blk) * kSplitFloats) + lane * 4;
+            const float *src = (part == 0 ? xu + ((int64_t)fu * nblk + blk) * (Lds::blk_bytes / 4)
+                                          : xq + ((int64_t)fq * nblk + blk) * (Lds::blk_bytes / 4)) + lane * 4;
 #pragma unroll
-            for (int c = 0; c < 6; ++c) o.r[c] = *reinterpret_cast<const f4 *>(src + c * 256);
+            for (int c = 0; c < NC; ++c) o.r[c] = *reinterpret_cast<const f4 *>(src + c * 256);
             const int vblk = step * kQS + L;
             const bool bok = step < nstep && vblk < nblk && vblk * 16 + 4 * lk < d;
 #pragma unroll
-            for (int m = 0; m < 2; ++m) o.r[6 + m] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>((bok && vok[m]) ? vr[m] + (int64_t)vblk * vstep : misc));
+            for (int m = 0; m < 2; ++m) {
+                const f4 *vp = reinterpret_cast<const f4 *>((bok && vok[m]) ? vr[m] + (int64_t)vblk * vstep : misc);
+                o.r[NC + m] = PARTS ? __builtin_nontemporal_load(vp) : *vp;
+            }
         };
         auto fetch = [&](int step, Regs &o) __attribute__((always_inline)) { fetch_of(wu, wq, step, o); };
         auto put = [&](int stage, const Regs &o) __attribute__((always_inline)) {
             char *st = lds + Lds::ring + stage * Lds::stage_bytes + lane * 16;
 #pragma unroll
-            for (int c = 0; c < 6; ++c) *reinterpret_cast<f4 *>(st + (2 * L + part) * Lds::blk_bytes + c * 1024) = o.r[c];
+            for (int c = 0; c < NC; ++c) *reinterpret_cast<f4 *>(st + (2 * L + part) * Lds::blk_bytes + c * 1024) = o.r[c];
 #pragma unroll
-            for (int m = 0; m < 2; ++m) *reinterpret_cast<f4 *>(st + Lds::rows_bytes + (L * kQT + 2 * part + m) * 1024) = o.r[6 + m];
+            for (int m = 0; m < 2; ++m) *reinterpret_cast<f4 *>(st + Lds::rows_bytes + (L * kQT + 2 * part + m) * 1024) = o.r[NC + m];
         };
         // Phase p (up to barrier p): step p's operands from registers to stage p % 3, then the loads of step
-        // p + kQSets into the registers they came from (the registers are the prefetch buffer: kQSets steps of
+        // p + SETS into the registers they came from (the registers are the prefetch buffer: SETS steps of
         // loads are on their way).  After barrier p the working wavefronts read stage p while they work step
         // p - 1; the stage was last read two phases earlier.
         if (first) {
 #pragma unroll
-            for (int s0 = 0; s0 < kQSets; ++s0) fetch(s0, rg[s0]);
+            for (int s0 = 0; s0 < SETS; ++s0) fetch(s0, rg[s0]);
         }
         put(0, rg[0]);
-        fetch(kQSets, rg[0]);
+        fetch(SETS, rg[0]);
         lds_barrier();
-        for (int sb = 0; sb < npad; sb += kQUnroll) {
-            static_for<kQUnroll>([&](auto uc) __attribute__((always_inline)) {
+        for (int sb = 0; sb < npad; sb += UNROLL) {
+            static_for<UNROLL>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
-                put((u + 1) % kQStages, rg[(u + 1) % kQSets]);
-                fetch(sb + u + 1 + kQSets, rg[(u + 1) % kQSets]);
+                put((u + 1) % kQStages, rg[(u + 1) % SETS]);
+                fetch(sb + u + 1 + SETS, rg[(u + 1) % SETS]);
                 lds_barrier();
             });
         }
@@ -1048,7 +1070,7 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         // working wavefronts have waited for those stores before the last barrier above)
         if (nwu >= 0) {
 #pragma unroll
-            for (int s0 = 0; s0 < kQSets; ++s0) fetch_of(nwu, nwq, s0, rg[s0]);
+            for (int s0 = 0; s0 < SETS; ++s0) fetch_of(nwu, nwq, s0, rg[s0]);
         }
         lds_barrier();
         lds_barrier();
@@ -1099,10 +1121,9 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         if (OPT && tp < kB) reinterpret_cast<float *>(lds + Lds::hg)[tp] = hgpre;
     };
 
-    // The working wavefronts' side.  F and -Bm of this lane's learner (bmr[rs]: round 4 rs + lk); do_q: take
-    // the shares of W X^T.  stage_next: first write the staged labels and Gram table to LDS; flush_prev >= 0:
+    // The working wavefronts' side.  F and -Bm of this lane's learner; do_q: take the shares of W X^T.  stage_next: first write the staged labels and Gram table to LDS; flush_prev >= 0:
     // write the predictions of window flush_prev to Z.
-    auto sweep = [&](auto stager, bool do_q, float F, const u4 (&bmr)[2][3], bool stage_next, int flush_prev)
+    auto sweep = [&](auto stager, bool do_q, float F, const Steps &bmr, bool stage_next, int flush_prev)
         __attribute__((always_inline)) {
         int tid_s = (int)threadIdx.x;                            // (see load_sweep)
         asm volatile("" : "+v"(tid_s));
@@ -1131,87 +1152,150 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         for (int rb = 0; rb < 4; ++rb) acc[rb] = f4{0.f, 0.f, 0.f, 0.f};
         float nn = 0.f;
         PROF_T(1);
-        // A step's operands of (3) and its block of iterates come from LDS while the matrix instructions of the
-        // step before run, those of (1) while its own of (3) do.
-        u4 ux[2][3];
-        f4 vin;
-        auto read_u = [&](int stage) __attribute__((always_inline)) {
-            const char *stg = lds + Lds::ring + stage * Lds::stage_bytes;
-            vin = *reinterpret_cast<const f4 *>(stg + Lds::rows_bytes + (sg * kQT + tau) * 1024 + lane * 16);
-#pragma unroll
-            for (int c = 0; c < 6; ++c) ux[c & 1][c >> 1] = *reinterpret_cast<const u4 *>(stg + 2 * sg * Lds::blk_bytes + c * 1024 + lane * 16);
-        };
-        // all but the seven youngest stores acknowledged means those of the first steps, which the loaders read
+        // all but the seven youngest stores acknowledged means those of the first SETS steps, which the loaders read
         // again right after the sweep, where there are enough of them
-        const bool many = nstep > kQSets + 8;
-        lds_barrier();                                           // the loader has stage 0 complete
-        read_u(0);
-        for (int sb = 0; sb < npad; sb += kQUnroll) {
-            static_for<kQUnroll>([&](auto uc) __attribute__((always_inline)) {
-                constexpr int u = decltype(uc)::value;
-                const int step = sb + u;
-                const int blk = step * kQS + sg;
-                if (step == npad - 1) {
-                    if (many) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
-                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                }
-                lds_barrier();                                   // stage step + 1 complete; stage step - 1 is not read any more
-                u4 q12[4], q3[2];
-                {
-                    const char *qs = lds + Lds::ring + (u % kQStages) * Lds::stage_bytes + (2 * sg + 1) * Lds::blk_bytes + lane * 16;
+        const bool many = nstep > SETS + 8;
+        auto wait_stores = [&](int step) __attribute__((always_inline)) {
+            if (step == npad - 1) {
+                if (many) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+        };
+        if constexpr (PARTS) {
+            // A step's operands of (3) and its block of iterates come from LDS while the matrix instructions of the
+            // step before run, those of (1) while its own of (3) do.
+            u4 ux[2][3];
+            f4 vin;
+            auto read_u = [&](int stage) __attribute__((always_inline)) {
+                const char *stg = lds + Lds::ring + stage * Lds::stage_bytes;
+                vin = *reinterpret_cast<const f4 *>(stg + Lds::rows_bytes + (sg * kQT + tau) * 1024 + lane * 16);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) q12[c] = *reinterpret_cast<const u4 *>(qs + c * 1024);
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) q3[c] = *reinterpret_cast<const u4 *>(qs + (4 + c) * 1024);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                const bool active = step < nstep && blk < nblk;  // wavefront-uniform
-                f4 vb = vin, vo = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) vb[r] *= F;
-                // the small products first, apart from the large ones
-                vo = mfma_bf16(ux[0][2], bmr[0][0], vo);
-                vb = mfma_bf16(ux[0][0], bmr[0][0], vb);
-                vo = mfma_bf16(ux[0][0], bmr[0][2], vo);
-                vb = mfma_bf16(ux[1][0], bmr[1][0], vb);
-                vo = mfma_bf16(ux[1][2], bmr[1][0], vo);
-                vo = mfma_bf16(ux[1][0], bmr[1][2], vo);
-                vo = mfma_bf16(ux[0][1], bmr[0][1], vo);
-                vo = mfma_bf16(ux[1][1], bmr[1][1], vo);
-                vo = mfma_bf16(ux[0][1], bmr[0][0], vo);
-                vo = mfma_bf16(ux[0][0], bmr[0][1], vo);
-                vo = mfma_bf16(ux[1][1], bmr[1][0], vo);
-                vo = mfma_bf16(ux[1][0], bmr[1][1], vo);
-                __builtin_amdgcn_sched_barrier(0);
-                read_u((u + 1) % kQStages);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) vb[r] += vo[r];
-                if (active) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) nn = fmaf(vb[r], vb[r], nn);
+                for (int c = 0; c < NC; ++c) ux[c & 1][c >> 1] = *reinterpret_cast<const u4 *>(stg + 2 * sg * Lds::blk_bytes + c * 1024 + lane * 16);
+            };
+            lds_barrier();                                       // the loader has stage 0 complete
+            read_u(0);
+            for (int sb = 0; sb < npad; sb += UNROLL) {
+                static_for<UNROLL>([&](auto uc) __attribute__((always_inline)) {
+                    constexpr int u = decltype(uc)::value;
+                    const int step = sb + u;
+                    const int blk = step * kQS + sg;
+                    wait_stores(step);
+                    lds_barrier();                                   // stage step + 1 complete; stage step - 1 is not read any more
+                    u4 q12[4], q3[2];
                     {
-                        const bool ok = q_ok && blk * 16 + 4 * lk < d;
-                        float *dst = ok ? vrow + (int64_t)blk * vstep : sink;
-                        __builtin_nontemporal_store(vb, reinterpret_cast<f4 *>(dst));   // (streams: the rows stay in L2)
-                    }
-                    if (do_q) {
-                        unsigned a1, a2, a3, b1, b2, b3;
-                        split2(vb[0], vb[1], a1, a2, a3);
-                        split2(vb[2], vb[3], b1, b2, b3);
-                        const u4 w11 = u4{a1, b1, a1, b1}, w22 = u4{a2, b2, a2, b2}, w31 = u4{a3, b3, a1, b1};
+                        const char *qs = lds + Lds::ring + (u % kQStages) * Lds::stage_bytes + (2 * sg + 1) * Lds::blk_bytes + lane * 16;
 #pragma unroll
-                        for (int rb = 0; rb < 4; ++rb) {
-                            const u4 x13 = u4{q12[rb][0], q12[rb][1], q3[rb >> 1][2 * (rb & 1)], q3[rb >> 1][2 * (rb & 1) + 1]};
-                            acc[rb] = mfma_bf16(x13, w31, acc[rb]);
+                        for (int c = 0; c < 4; ++c) q12[c] = *reinterpret_cast<const u4 *>(qs + c * 1024);
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) q3[c] = *reinterpret_cast<const u4 *>(qs + (4 + c) * 1024);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    const bool active = step < nstep && blk < nblk;  // wavefront-uniform
+                    f4 vb = vin, vo = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) vb[r] *= F;
+                    // the small products first, apart from the large ones
+                    vo = mfma_bf16(ux[0][2], bmr.p[0][0], vo);
+                    vb = mfma_bf16(ux[0][0], bmr.p[0][0], vb);
+                    vo = mfma_bf16(ux[0][0], bmr.p[0][2], vo);
+                    vb = mfma_bf16(ux[1][0], bmr.p[1][0], vb);
+                    vo = mfma_bf16(ux[1][2], bmr.p[1][0], vo);
+                    vo = mfma_bf16(ux[1][0], bmr.p[1][2], vo);
+                    vo = mfma_bf16(ux[0][1], bmr.p[0][1], vo);
+                    vo = mfma_bf16(ux[1][1], bmr.p[1][1], vo);
+                    vo = mfma_bf16(ux[0][1], bmr.p[0][0], vo);
+                    vo = mfma_bf16(ux[0][0], bmr.p[0][1], vo);
+                    vo = mfma_bf16(ux[1][1], bmr.p[1][0], vo);
+                    vo = mfma_bf16(ux[1][0], bmr.p[1][1], vo);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_u((u + 1) % kQStages);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) vb[r] += vo[r];
+                    if (active) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) nn = fmaf(vb[r], vb[r], nn);
+                        {
+                            const bool ok = q_ok && blk * 16 + 4 * lk < d;
+                            float *dst = ok ? vrow + (int64_t)blk * vstep : sink;
+                            __builtin_nontemporal_store(vb, reinterpret_cast<f4 *>(dst));   // (streams: the rows stay in L2)
+                        }
+                        if (do_q) {
+                            unsigned a1, a2, a3, b1, b2, b3;
+                            split2(vb[0], vb[1], a1, a2, a3);
+                            split2(vb[2], vb[3], b1, b2, b3);
+                            const u4 w11 = u4{a1, b1, a1, b1}, w22 = u4{a2, b2, a2, b2}, w31 = u4{a3, b3, a1, b1};
+#pragma unroll
+                            for (int rb = 0; rb < 4; ++rb) {
+                                const u4 x13 = u4{q12[rb][0], q12[rb][1], q3[rb >> 1][2 * (rb & 1)], q3[rb >> 1][2 * (rb & 1) + 1]};
+                                acc[rb] = mfma_bf16(x13, w31, acc[rb]);
+                            }
+#pragma unroll
+                            for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_bf16(q12[rb], w22, acc[rb]);
+#pragma unroll
+                            for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_bf16(q12[rb], w11, acc[rb]);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            }
+        } else {
+            // Two sets of operand registers: while the matrix instructions of step r - 1 run, the
+            // operands of step r come from LDS (the eight wavefronts would otherwise all read right
+            // after the barrier, 72 KB through the LDS port with the matrix cores idle).
+            struct In { f4 xu[4], xq[4], vb; };
+            In in[2];
+            auto read_stage = [&](int stage, In &o) __attribute__((always_inline)) {
+                const char *stg = lds + Lds::ring + stage * Lds::stage_bytes;
+                const char *rows = stg + 2 * sg * Lds::blk_bytes + lane * 16;
+                o.vb = *reinterpret_cast<const f4 *>(stg + Lds::rows_bytes + (sg * kQT + tau) * 1024 + lane * 16);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o.xu[c] = *reinterpret_cast<const f4 *>(rows + c * 1024);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o.xq[c] = *reinterpret_cast<const f4 *>(rows + Lds::blk_bytes + c * 1024);
+            };
+            lds_barrier();                                       // the loader has stage 0 complete
+            read_stage(0, in[0]);
+            for (int sb = 0; sb < npad; sb += 2 * kQStages) {
+                static_for<2 * kQStages>([&](auto uc) __attribute__((always_inline)) {
+                    constexpr int u = decltype(uc)::value;
+                    const int step = sb + u;
+                    const int blk = step * kQS + sg;
+                    wait_stores(step);
+                    lds_barrier();                               // stage step + 1 complete, own reads of stage step done
+                    read_stage((u + 1) % kQStages, in[(u + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const bool active = step < nstep && blk < nblk;  // wavefront-uniform
+                    if (active) {
+                        In &c = in[u & 1];
+                        f4 vb = c.vb;
+                        f4 vo = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) vb[r] *= F;
+#pragma unroll
+                        for (int rs = 0; rs < 16; rs += 2) {
+                            vb = __builtin_amdgcn_mfma_f32_16x16x4f32(c.xu[rs >> 2][rs & 3], bmr.v[rs], vb, 0, 0, 0);
+                            vo = __builtin_amdgcn_mfma_f32_16x16x4f32(c.xu[rs >> 2][(rs & 3) + 1], bmr.v[rs + 1], vo, 0, 0, 0);
                         }
 #pragma unroll
-                        for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_bf16(q12[rb], w22, acc[rb]);
+                        for (int r = 0; r < 4; ++r) vb[r] += vo[r];
 #pragma unroll
-                        for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_bf16(q12[rb], w11, acc[rb]);
+                        for (int r = 0; r < 4; ++r) nn = fmaf(vb[r], vb[r], nn);
+                        {
+                            const bool ok = q_ok && blk * 16 + 4 * lk < d;
+                            float *dst = ok ? vrow + blk * 16 : sink;
+                            *reinterpret_cast<f4 *>(dst) = vb;
+                        }
+                        if (do_q) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                                for (int rb = 0; rb < 4; ++rb)
+                                    acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.xq[rb][r], vb[r], acc[rb], 0, 0, 0);
+                        }
                     }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            });
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            }
         }
         PROF_T(2);
         lds_barrier();                                           // every wavefront is done with the ring
@@ -1245,9 +1329,7 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         using Stager = std::integral_constant<bool, !CHAIN>;
         {
             // the stored iterates times the rows of the first window: a sweep whose step changes nothing
-            u4 zero[2][3];
-#pragma unroll
-            for (int i = 0; i < 6; ++i) zero[i & 1][i >> 1] = u4{0u, 0u, 0u, 0u};
+            const Steps zero{};
             if constexpr (!CHAIN) load_next(0);
             sweep(Stager{}, true, 1.f, zero, true, -1);
         }
@@ -1267,17 +1349,22 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();
             PROF_T(4);
-            u4 bmr[2][3];                                        // -Bm in parts: rounds 32 s + 8 lk .. of this lane's learner
+            Steps bmr;
             const float *bml = reinterpret_cast<const float *>(lds + Lds::bm + tau * Lds::tile_f) + lr;
+            if constexpr (PARTS) {
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
+                for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = 32 * s2 + 8 * lk + 2 * j;
-                    unsigned p1, p2, p3;
-                    split2(bml[r * kM], bml[(r + 1) * kM], p1, p2, p3);
-                    bmr[s2][0][j] = p1; bmr[s2][1][j] = p2; bmr[s2][2][j] = p3;
-                }
+                    for (int j = 0; j < 4; ++j) {
+                        const int r = 32 * s2 + 8 * lk + 2 * j;
+                        unsigned p1, p2, p3;
+                        split2(bml[r * kM], bml[(r + 1) * kM], p1, p2, p3);
+                        bmr.p[s2][0][j] = p1; bmr.p[s2][1][j] = p2; bmr.p[s2][2][j] = p3;
+                    }
+            } else {
+#pragma unroll
+                for (int rs = 0; rs < 16; ++rs) bmr.v[rs] = bml[(rs * 4 + lk) * kM];
+            }
             const float F = reinterpret_cast<const float *>(lds + Lds::fv)[tau * kM + lr];
             sweep(Stager{}, more, F, bmr, more, k);
         }
@@ -1316,18 +1403,19 @@ using WindowKernel = void (*)(const DenseArgs, const float *, const float *, con
 // (8 wavefronts); 2: streamed, one tile, 16 wavefronts; 3: four tiles, loading wavefronts; 4: iterates
 // of two tiles in registers (8 wavefronts, d <= 1024)
 // (opt: the optimistic update, built into the three kernels the launcher picks by itself)
-template <int LOSS> WindowKernel pick_window_kernel(int nblk, int mode, bool opt, int *waves, int *tiles, int *lds_bytes)
+template <int LOSS> WindowKernel pick_window_kernel(int nblk, int mode, bool parts, bool opt, int *waves, int *tiles, int *lds_bytes)
 {
+    if (mode == 3) {
+        *waves = kQW + kQL; *tiles = kQT; *lds_bytes = parts ? LdsQ<true>::total : LdsQ<false>::total;
+        if (parts) return opt ? dense_window_shared_kernel<LOSS, true, true> : dense_window_shared_kernel<LOSS, false, true>;
+        return opt ? dense_window_shared_kernel<LOSS, true, false> : dense_window_shared_kernel<LOSS, false, false>;
+    }
     if (mode == 4) {
         *waves = kNW8; *tiles = 2; *lds_bytes = LdsT<kNW8, 2>::total;
         if (opt) return dense_window_kernel<LOSS, 9, true, kNW8, 2, true>;
         return dense_window_kernel<LOSS, 9, true, kNW8, 2>;
     }
     if (opt) {
-        if (mode == 3) {
-            *waves = kQW + kQL; *tiles = kQT; *lds_bytes = LdsQ::total;
-            return dense_window_shared_kernel<LOSS, true>;
-        }
         *waves = kNW8; *tiles = 2; *lds_bytes = LdsT<kNW8, 2>::total;
         return dense_window_kernel<LOSS, 1, false, kNW8, 2, true>;
     }
@@ -1339,10 +1427,6 @@ template <int LOSS> WindowKernel pick_window_kernel(int nblk, int mode, bool opt
     if (mode == 1) {
         *waves = kNW8; *tiles = 2; *lds_bytes = LdsT<kNW8, 2>::total;
         return dense_window_kernel<LOSS, 1, false, kNW8, 2>;
-    }
-    if (mode == 3) {
-        *waves = kQW + kQL; *tiles = kQT; *lds_bytes = LdsQ::total;
-        return dense_window_shared_kernel<LOSS>;
     }
     *waves = kNW16; *tiles = 1; *lds_bytes = LdsT<kNW16, 1>::total;
     return dense_window_kernel<LOSS, 1, false, kNW16, 1>;
@@ -1398,6 +1482,31 @@ bool dense_window_wanted(const DenseArgs &a)
     return a.d > 64 * kWave || ((int64_t)a.R * a.K >= 2048 && a.d >= 512);
 }
 
+namespace {
+
+// Loading wavefronts: whether a call of nwin windows takes its products as bfloat16 parts or in float32.  Parts need iterates in
+// blocks or at least whole 64-byte pieces for the streaming hint: of rows that do not end with a block of 16, calls of 4096
+// rounds take 10.5 ms in float32 and 14.7 in parts (d = 3000), 14.9 / 25.2 (d = 4100), 8.2 / 11.6 (2052); rows longer than a tile's blocks hold
+// lose too (d = 8192 27.3 / 29.9, d = 6144 20.5 / 21.9; 16384 learners).  A call pays once for turning the iterates and for two thirds of the
+// windows per launch, and gains by the window: 23 us while every compute unit has a workgroup, d = 4096, and two to three times that
+// for the workgroups of a last, partial turn (200 us per window in float32 however few they are, 127 to 165 in parts).  Turned
+// iterates cost 11 such gains per 256 workgroups, launches the rest up to 20.  Measured, ms per call, float32 / parts:
+//   16384 learners (256 workgroups), d = 4096   64 rounds 0.73 / 0.99   512 2.25 / 2.53   1024 3.91 / 3.92   1280 4.78 / 4.66   4096 14.3 / 12.5
+//                                    d = 2048   64 rounds 0.34 / 0.50   512 1.16 / 1.35   1024 2.10 / 2.14   1280 2.58 / 2.58   4096 7.74 / 7.11
+//   17408 learners (272),            d = 4096   64 rounds 1.00 / 1.18   320 2.65 / 2.68    512 3.86 / 3.57   1024 7.27 / 5.97   4096 27.1 / 20.8
+//   24576 learners (384),            d = 4096   64 rounds 1.05 / 1.37   320 2.64 / 2.94    512 3.85 / 3.90   1024 7.12 / 6.50   4096 26.7 / 22.0
+//   28672 learners (448),            d = 4096   64 rounds 1.07 / 1.51   512 3.88 / 4.24    640 4.75 / 4.96   1024 7.11 / 6.89   4096 26.7 / 23.0
+//   65536 learners (1024),           d = 4096   64 rounds 1.84 / 2.89   768 10.8 / 11.1   1024 14.2 / 14.0   1280 17.3 / 16.7   4096 53.9 / 46.7
+bool parts_pay(int64_t nq, int d, int nwin, int ncu)
+{
+    if (d % 16 != 0 || d > kBlocksMaxD) return false;
+    const int64_t wgs = (nq + kQT * kM - 1) / (kQT * kM), rest = wgs % ncu;
+    const int64_t gain = wgs / ncu + (rest == 0 ? 0 : 2 * rest <= ncu ? 3 : 2);
+    return nwin * gain * ncu >= 20 * wgs;
+}
+
+}  // namespace
+
 hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, const PieceHook *hook)
 {
     DenseArgs a = a0;
@@ -1438,24 +1547,6 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
                : ((ropt == 4 || (ropt < 0 && nblk >= 32)) && fits2) ? 4 : 1;
     if (a.optimistic && mode != 3 && mode != 4) mode = 1;    // (the optimistic update: three of the kernels only)
     const bool resident = mode == 0 || mode == 4;
-    if (a.tune->get(OCO_OPT_VERBOSE) == 1)
-        fprintf(stderr, "dense plan: windowed contraction kernel, %d windows in pieces of %lld, %d tiles, iterates %s\n",
-                nwin, (long long)sc.piece_windows, (a.R * a.K + kM - 1) / kM,
-                mode == 4 ? "in registers, two tiles per workgroup" : resident ? "in registers" : mode == 1 ? "streamed from HBM, two tiles per workgroup"
-                : mode == 3 ? "streamed from HBM, four tiles per workgroup, rows through LDS" : "streamed from HBM");
-    WindowKernel kern = nullptr;
-    int waves = 0, tiles = 1, lds_bytes = 0;
-    switch (loss) {
-        case 0: kern = pick_window_kernel<0>(nblk, mode, a.optimistic != 0, &waves, &tiles, &lds_bytes); break;
-        case 1: kern = pick_window_kernel<1>(nblk, mode, a.optimistic != 0, &waves, &tiles, &lds_bytes); break;
-        case 2: kern = pick_window_kernel<2>(nblk, mode, a.optimistic != 0, &waves, &tiles, &lds_bytes); break;
-        default: return hipErrorInvalidValue;
-    }
-    const int ntiles = (a.R * a.K + kM * tiles - 1) / (kM * tiles);   // workgroups
-    // The caller's work on a piece's rounds (the meta kernel) goes beside the window kernel of the following
-    // piece where that leaves a quarter of the compute units or more without a workgroup (c3: 136 of 256;
-    // 46.7 -> 45.8 ms per step: the window kernel is slower beside it, 6.25 against 5.72 ms per launch.
-    // Handed over only behind the following piece's pre-passes: 46.2 ms).
     int ncu = 256;
     {
         int dev = 0;
@@ -1463,12 +1554,32 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
             ncu <= 0)
             ncu = 256;
     }
+    const bool parts = mode == 3 && parts_pay((int64_t)a.R * a.K, a.d, nwin, ncu);
+    if (a.tune->get(OCO_OPT_VERBOSE) == 1)
+        fprintf(stderr, "dense plan: windowed contraction kernel, %d windows in pieces of %lld, %d tiles, iterates %s\n",
+                nwin, (long long)sc.piece_windows, (a.R * a.K + kM - 1) / kM,
+                mode == 4 ? "in registers, two tiles per workgroup" : resident ? "in registers" : mode == 1 ? "streamed from HBM, two tiles per workgroup"
+                : parts ? "streamed from HBM, four tiles per workgroup, rows through LDS in bfloat16 parts"
+                : mode == 3 ? "streamed from HBM, four tiles per workgroup, rows through LDS" : "streamed from HBM");
+    WindowKernel kern = nullptr;
+    int waves = 0, tiles = 1, lds_bytes = 0;
+    switch (loss) {
+        case 0: kern = pick_window_kernel<0>(nblk, mode, parts, a.optimistic != 0, &waves, &tiles, &lds_bytes); break;
+        case 1: kern = pick_window_kernel<1>(nblk, mode, parts, a.optimistic != 0, &waves, &tiles, &lds_bytes); break;
+        case 2: kern = pick_window_kernel<2>(nblk, mode, parts, a.optimistic != 0, &waves, &tiles, &lds_bytes); break;
+        default: return hipErrorInvalidValue;
+    }
+    const int ntiles = (a.R * a.K + kM * tiles - 1) / (kM * tiles);   // workgroups
+    // The caller's work on a piece's rounds (the meta kernel) goes beside the window kernel of the following
+    // piece where that leaves a quarter of the compute units or more without a workgroup (c3: 136 of 256;
+    // 46.7 -> 45.8 ms per step: the window kernel is slower beside it, 6.25 against 5.72 ms per launch.
+    // Handed over only behind the following piece's pre-passes: 46.2 ms).
     const bool beside = hook && hook->fn && 4 * (int64_t)ntiles <= 3 * (int64_t)ncu;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        lds_bytes);
     if (e != hipSuccess) return e;
     // rows in parts are half as long again: two thirds of the windows in the same scratch
-    const bool blocked = mode == 3 && a.d % 16 == 0 && a.d <= kBlocksMaxD && (int64_t)a.R * a.K % kM == 0;
+    const bool blocked = parts && (int64_t)a.R * a.K % kM == 0;
     auto turn_blocks = [&](bool to_rows) -> hipError_t {
         if (!blocked) return hipSuccess;
         if (to_rows) hipLaunchKernelGGL(tile_blocks_kernel<true>, dim3((unsigned)(a.R * a.K / kM)), dim3(1024), 0, s, a.V, a.d);
@@ -1477,18 +1588,18 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
     };
     e = turn_blocks(false);
     if (e != hipSuccess) return e;
-    const int pw = mode == 3 ? std::max(1, (int)sc.piece_windows * 2 / 3) : (int)sc.piece_windows;
-    if (mode == 3 && (size_t)pw * nblk * 2 * kSplitFloats > 2 * sc.tile_floats) return hipErrorInvalidValue;
+    const int pw = parts ? std::max(1, (int)sc.piece_windows * 2 / 3) : (int)sc.piece_windows;
+    if (parts && (size_t)pw * nblk * 2 * kSplitFloats > 2 * sc.tile_floats) return hipErrorInvalidValue;
     for (int w0 = 0; w0 < nwin; w0 += pw) {
         const int nw = std::min<int>(pw, nwin - w0);
         hipLaunchKernelGGL(dense_tile_kernel, dim3((unsigned)nblk, (unsigned)nw), dim3(64), 0, s, a.x, a.d, plan, w0, xq,
-                           mode == 3 ? nullptr : xu, misc);
+                           parts ? nullptr : xu, misc);
         hipLaunchKernelGGL(dense_gram_kernel, dim3((unsigned)nw), dim3(512), 0, s, xq, nblk, gram, gxt);
-        if (mode == 3) {                                         // (in the place of the float32 copies, which the Gram matrices are done with)
+        if (parts) {                                             // (in the place of the float32 copies, which the Gram matrices are done with)
             xu = xq + (size_t)pw * nblk * kSplitFloats;
             hipLaunchKernelGGL(dense_tile_split_kernel, dim3((unsigned)nblk, (unsigned)nw), dim3(64), 0, s, a.x, a.d, plan, w0, xq, xu);
         }
-        e = clock_begin(a.clock, s, mode == 3 ? "dense_window_shared_kernel" : "dense_window_kernel");
+        e = clock_begin(a.clock, s, parts ? "dense_window_parts_kernel" : mode == 3 ? "dense_window_shared_kernel" : "dense_window_kernel");
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(waves * kWave), lds_bytes, s, a, gram,
                            mode == 3 && !blocked ? nullptr : gxt, xq, xu, misc, plan, w0, nw);

@@ -402,3 +402,24 @@ def test_loading_wavefronts_at_the_edges_of_blocks_and_tiles(over, optimistic):
     again = _gpu(wl, data, options=opt)
     for k in ("regret", "L", "W", "p", "wbar"):
         assert np.array_equal(got[k], again[k]), k
+
+
+# which form of the kernel with loading wavefronts a call takes by default: the first and last number of windows on either side of
+# the line, for one workgroup per compute unit and for one more (257); rows that do not end with a block and rows longer than the
+# blocks of a tile stay in float32 however long the call.
+@pytest.mark.parametrize("d,R,n,parts", [
+    (2064, 1024, 19 * 64, False), (2064, 1024, 20 * 64, True),
+    (2064, 1025, 5 * 64, False), (2064, 1025, 6 * 64, True),
+    (2052, 1024, 20 * 64, False),
+    (4112, 1024, 20 * 64, False),
+])
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_loading_wavefronts_take_parts_where_they_were_measured_to_pay(d, R, n, parts, optimistic, capfd):
+    wl = WL.make("c4", T=n, d=d, K=16, R=R, optimistic=optimistic)
+    data = WL.generate(wl)
+    print("case loading wavefronts by default", d, R, n, flush=True)
+    capfd.readouterr()
+    got = _gpu(wl, data, options=dict(verbose=1))
+    plan = capfd.readouterr().err
+    assert "rows through LDS" in plan and ("bfloat16 parts" in plan) == parts, plan
+    _check(wl, data, got, runs=[0, R - 1], label="loading wavefronts d=%d R=%d n=%d" % (d, R, n))
