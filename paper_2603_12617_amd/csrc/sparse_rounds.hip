@@ -492,6 +492,139 @@ __device__ __forceinline__ void stage_window(const WinStage &st, const SparseArg
 }
 
 
+template <typename T> __device__ __forceinline__ T *uniform_global(T *p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+    const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+    return (T *)(__attribute__((address_space(1))) T *)(lo | hi << 32);
+}
+// Scales the columns of a workgroup's learners by their fs (this lane's learner: its scale in the rounds; left alone where it is not
+// below the joining scale) and returns this lane's share of its learner's ||v||^2 in units of 2^-52 D^2: the columns of the call's
+// rounds lo .. t1 - 1, each once by way of its mark, or all rows where lo < 0 or those rounds have more entries.
+template <int LPW>
+__device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t *col_, int RKp_, int d_, double D, int nnz, int blk_,
+                                                            int lo_, int t1, float fs)
+{
+    constexpr int EPI = kWave / LPW;
+    // (arguments arrive in vector registers and as pointers into any memory: they are the same in all lanes, and into global memory)
+    const int RKp = __builtin_amdgcn_readfirstlane(RKp_), d = __builtin_amdgcn_readfirstlane(d_);
+    const int blk = __builtin_amdgcn_readfirstlane(blk_), lo = __builtin_amdgcn_readfirstlane(lo_);
+    float *V = uniform_global(V_);
+    const int32_t *col = uniform_global(col_);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = lane % LPW, e = lane / LPW;
+    const bool mine = fs < kSparseFoldJoinF;
+    const int64_t nslots = kSpWaves * EPI;
+    float *Vq = V + blk * LPW + l;
+    // (whole turns without a branch, so that the loads of four rows are on their way together: a learner that is not folded gets back what was read)
+    auto rows = [&](auto &&folded) {
+        constexpr int NR = 4;
+        int64_t j0 = wave * EPI;
+        for (; j0 + EPI - 1 + (NR - 1) * nslots < d; j0 += NR * nslots) {
+            float *p = Vq + (j0 + e) * RKp;
+            float vv[NR];
+#pragma unroll
+            for (int u = 0; u < NR; ++u) vv[u] = ldv(p + u * nslots * RKp);
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const float w = folded(vv[u]);
+                p[u * nslots * RKp] = mine ? w : vv[u];
+            }
+        }
+        for (int64_t j = j0 + e; j < d; j += nslots) {
+            const float v = ldv(Vq + j * RKp);
+            if (mine) Vq[j * RKp] = folded(v);
+        }
+    };
+    // ||v||^2 of a folded learner (at most about D^2) in units of 2^-52 D^2: whole numbers, whose sum does
+    // not depend on which entry of a column was first
+    const double unit = 0x1p52 / (D * D);
+    long long m2 = 0;
+    auto folded = [&](float vv) {
+        float wv = vv * fs;
+        wv = fabsf(wv) < 0x1p-126f ? 0.f : wv;
+        m2 += (long long)((double)wv * (double)wv * unit);
+        return wv;
+    };
+    const int64_t e0 = (int64_t)lo * nnz, e1 = (int64_t)t1 * nnz;
+    if (lo < 0 || kFoldEntriesPerRow * (e1 - e0) >= d) {
+        rows(folded);
+        return m2;
+    }
+    unsigned *mark = reinterpret_cast<unsigned *>(V) + RKp - kPadWords + blk / 32;
+    const unsigned bit = 1u << (blk % 32);
+    // one pass: NF entries in flight per slot (past the end: the slot's first entry again, not used)
+    int cc[4];
+    auto visit = [&](auto nf, int64_t kb) {
+        constexpr int NF = decltype(nf)::value;
+        const int64_t k0 = kb + wave * EPI + e;
+        if (k0 >= e1) return;
+        unsigned seen[NF];
+        float vv[NF];
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            const int64_t k = k0 + u * nslots;
+            cc[u] = col[k < e1 ? k : k0];
+        }
+        // rows and marks are on their way together: a row read by a slot that then finds itself first is as it was before the fold
+#pragma unroll
+        for (int u = 0; u < NF; ++u) vv[u] = ldv(Vq + (int64_t)cc[u] * RKp);
+#pragma unroll
+        for (int u = 0; u < NF; ++u) seen[u] = bit;
+        if (l == 0) {
+#pragma unroll
+            for (int u = 0; u < NF; ++u)
+                seen[u] = __hip_atomic_fetch_or(mark + (int64_t)cc[u] * RKp, k0 + u * nslots < e1 ? bit : 0u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            const bool first = k0 + u * nslots < e1 && (__shfl(seen[u], e * LPW) & bit) == 0;
+            if (first && mine) Vq[(int64_t)cc[u] * RKp] = folded(vv[u]);
+        }
+    };
+    for (int64_t kb = e0; kb < e1; kb += 4 * nslots) {
+        if (e1 - kb > 2 * nslots) visit(std::integral_constant<int, 4>(), kb);
+        else if (e1 - kb > nslots) visit(std::integral_constant<int, 2>(), kb);
+        else visit(std::integral_constant<int, 1>(), kb);
+    }
+    wg_sync();
+    auto clear = [&](int c) { __hip_atomic_fetch_and(mark + (int64_t)c * RKp, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (e1 - e0 <= 4 * nslots) {                     // one pass: the columns are at hand
+        if (l == 0) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (e0 + wave * EPI + e + u * nslots < e1) clear(cc[u]);
+        }
+    } else {
+        for (int64_t k = e0 + threadIdx.x; k < e1; k += kSpWaves * kWave) clear(col[k]);
+    }
+    return m2;
+}
+
+// The same as a call: inlined, what it needs costs the window loop registers, whether a call ever folds or not.  Spilled, plain / optimistic,
+// before, inlined and as a call: 8 learners per workgroup 0 / 4, 5 / 11 and 0 / 0; 16: 10 / 31, 23 / 41 and 4 / 11; 32: 11 / 23, 23 / 30
+// and 5 / 11; 64: 0 / 0, 0 / 3 and 0 / 0.  8192 learners without folds, optimistic: 17.00, 17.18 and 16.94 ms.  With four learners per workgroup a
+// fold is short enough for the call itself to show (the call 0.3 us of 6); there it is inlined behind values the compiler can
+// take nothing out of the window loop from (128 learners without folds, optimistic: 4.77 ms before, 4.70 now, 4.84 as a call).
+template <int LPW>
+__device__ __attribute__((noinline)) long long fold_columns_call(float *V, const int32_t *col, int RKp, int d, double D, int nnz, int blk, int lo,
+                                                                 int t1, float fs)
+{
+    return fold_columns_here<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs);
+}
+template <int LPW>
+__device__ __forceinline__ long long fold_columns(float *V, const int32_t *col, int RKp, int d, double D, int nnz, int blk, int lo, int t1, float fs)
+{
+    if constexpr (LPW == 4) {
+        asm volatile("" : "+v"(V), "+v"(col), "+v"(RKp), "+v"(d), "+v"(D), "+v"(nnz), "+v"(blk));
+        return fold_columns_here<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs);
+    } else {
+        return fold_columns_call<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs);
+    }
+}
+
 // A workgroup owns LPW learners (LPW = 64, 32, 16, 8 or 4; fewer learners per workgroup spread a
 // small problem over more compute units).  A wavefront is EPI = 64 / LPW slots of LPW lanes:
 // lane = slot * LPW + learner, and one memory instruction touches EPI rows of V.
@@ -1185,69 +1318,7 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
         wg_sync();
         {
             for (int rd = (int)threadIdx.x / LPW; rd <= ft; rd += kSpWaves * EPI) bw[rd][l] = 0.f;   // applied
-            const float fs = fold_sf[l];
-            const bool mine = fs < kSparseFoldJoinF;
-            const int64_t nslots = kSpWaves * EPI;
-            // ||v||^2 of a folded learner (at most about D^2) in units of 2^-52 D^2: whole numbers, whose sum does
-            // not depend on which entry of a column was first
-            double Dv = a.D;
-            int blkv = blk, dv = a.d;
-            asm volatile("" : "+v"(Dv), "+s"(blkv), "+s"(dv));   // nothing of the fold is taken out of the window loop: registers
-            const double unit = 0x1p52 / (Dv * Dv);
-            long long m2 = 0;
-            auto folded = [&](float vv) {
-                float wv = vv * fs;
-                wv = fabsf(wv) < 0x1p-126f ? 0.f : wv;
-                m2 += (long long)((double)wv * (double)wv * unit);
-                return wv;
-            };
-            const int lo = fold_lo;
-            const int64_t e0 = (int64_t)lo * nnz, e1 = (int64_t)(v.ws + ft + 1) * nnz;
-            if (lo >= 0 && kFoldEntriesPerRow * (e1 - e0) < dv) {
-                unsigned *mark = reinterpret_cast<unsigned *>(a.V) + a.RKp - kPadWords + blkv / 32;
-                const unsigned bit = 1u << (blkv % 32);
-                constexpr int NF = 4;                        // entries in flight per slot
-                for (int64_t k0 = e0 + wave * EPI + e; k0 < e1; k0 += NF * nslots) {
-                    int cc[NF];
-                    unsigned seen[NF];
-                    float vv[NF];
-#pragma unroll
-                    for (int u = 0; u < NF; ++u) {
-                        const int64_t k = k0 + u * nslots;
-                        cc[u] = a.col[k < e1 ? k : k0];
-                    }
-#pragma unroll
-                    for (int u = 0; u < NF; ++u) {
-                        seen[u] = bit;
-                        if (l == 0 && k0 + u * nslots < e1)
-                            seen[u] = __hip_atomic_fetch_or(mark + (int64_t)cc[u] * a.RKp, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-#pragma unroll
-                    for (int u = 0; u < NF; ++u) vv[u] = ldv(Vq + (int64_t)cc[u] * a.RKp);
-#pragma unroll
-                    for (int u = 0; u < NF; ++u) {
-                        const bool first = (__shfl(seen[u], e * LPW) & bit) == 0;
-                        if (first && mine) Vq[(int64_t)cc[u] * a.RKp] = folded(vv[u]);
-                    }
-                }
-                wg_sync();
-                for (int64_t k = e0 + threadIdx.x; k < e1; k += kSpWaves * kWave)
-                    __hip_atomic_fetch_and(mark + (int64_t)a.col[k] * a.RKp, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                for (int64_t j0 = wave * EPI + e; j0 < dv; j0 += 4 * nslots) {
-                    float vv[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int64_t j = j0 + u * nslots;
-                        vv[u] = j < dv ? ldv(Vq + j * a.RKp) : 0.f;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int64_t j = j0 + u * nslots;
-                        if (j < dv && mine) Vq[j * a.RKp] = folded(vv[u]);
-                    }
-                }
-            }
+            long long m2 = fold_columns<LPW>(a.V, a.col, a.RKp, a.d, a.D, nnz, blk, fold_lo, v.ws + ft + 1, fold_sf[l]);
 #pragma unroll
             for (int sh = 32; sh >= LPW; sh >>= 1) m2 += __shfl_xor(m2, sh);
             if (lane < LPW) fold_part[wave][l] = m2;
