@@ -56,9 +56,10 @@
 // speed, and a no-op otherwise).  Should a sigma fall below 2^-100 inside a
 // segment (steps larger than the ball: sigma then shrinks by a constant factor
 // every round), the chain stops after that round and the workgroup folds its
-// own columns: all wavefronts apply the window's steps so far, scale the
-// columns, measure ||v||^2 exactly (fixed order) and gather the remaining
-// rounds' <v, x_t> afresh; then the chain goes on.  Windows are
+// own learners: all wavefronts apply the window's steps so far, scale the
+// columns of the learners near the threshold, measure their ||v||^2 (in whole
+// units of D^2, so in any order) and gather the remaining rounds' <v, x_t>
+// afresh; then the chain goes on.  Windows are
 // aligned to multiples of 64 rounds of the horizon and all fold decisions
 // depend on the state and the absolute round index only.
 //
@@ -134,6 +135,9 @@ constexpr int kSegment = OCO_SEGMENT;        // rounds per launch segment (absol
 // The fold inside the kernel: learners below this scale are folded (the one that stopped the chain and whoever will
 // soon follow), the others of the workgroup keep their scale.
 constexpr float kSparseFoldJoinF = 0x1p-72f;
+// A fold sets to zero what it leaves below this many times D: far below a rounding of the iterate, and above whatever a column can
+// hold that was not touched since the learner's third-last fold (D 2^-144, see the fold).
+constexpr double kFoldZero = 0x1p-136;
 // The 32 words that pad a row of V (oco_create): words 0 .. 15 of row j mark column j as visited, a bit per workgroup
 // (all clear outside a fold), words 16 .. 18 of row q hold the rounds learner q was last folded at (below).
 constexpr int kPadWords = 32, kPadFolds = 16, kMarkWorkgroups = 32 * kPadFolds;
@@ -499,8 +503,24 @@ template <typename T> __device__ __forceinline__ T *uniform_global(T *p)
     const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
     return (T *)(__attribute__((address_space(1))) T *)(lo | hi << 32);
 }
+// ||v||^2 of a folded learner as a whole number of units of 2^-60 D^2, so that it does not depend on the order of the sum: a folded
+// iterate lies in the ball of radius D (to a rounding), so the sum has three bits to spare.  Every square is rounded to the nearest
+// unit: an error of at most 2^-61 D^2 per nonzero coordinate, on a value that is compared with D^2.  A sum with what is
+// not a finite number in it is negative, and so is every sum it goes into.
+constexpr double kNormUnit = 0x1p-60;
+constexpr long long kNormInf = -(1ll << 62), kNormNan = 2 * kNormInf;
+__device__ __forceinline__ long long norm_add(long long a, long long b)
+{
+    const long long m = a < b ? a : b;
+    return m < 0 ? (m < kNormInf ? kNormNan : kNormInf) : a + b;
+}
+__device__ __forceinline__ double norm_of_units(long long m, double D)
+{
+    return m >= 0 ? (double)m * (D * D * kNormUnit) : m < kNormInf ? (double)NAN : (double)INFINITY;
+}
+
 // Scales the columns of a workgroup's learners by their fs (this lane's learner: its scale in the rounds; left alone where it is not
-// below the joining scale) and returns this lane's share of its learner's ||v||^2 in units of 2^-52 D^2: the columns of the call's
+// below the joining scale) and returns this lane's share of its learner's ||v||^2 in those units: the columns of the call's
 // rounds lo .. t1 - 1, each once by way of its mark, or all rows where lo < 0 or those rounds have more entries.
 template <int LPW>
 __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t *col_, int RKp_, int d_, double D, int nnz, int blk_,
@@ -537,20 +557,23 @@ __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t 
             if (mine) Vq[j * RKp] = folded(v);
         }
     };
-    // ||v||^2 of a folded learner (at most about D^2) in units of 2^-52 D^2: whole numbers, whose sum does
-    // not depend on which entry of a column was first
-    const double unit = 0x1p52 / (D * D);
+    const double r = 0x1p30 / D;
+    const float zero_below = (float)(D * kFoldZero);
     long long m2 = 0;
+    double plain = 0.0;                        // (the same sum as a float64, which keeps infinities and NaN)
     auto folded = [&](float vv) {
         float wv = vv * fs;
-        wv = fabsf(wv) < 0x1p-126f ? 0.f : wv;
-        m2 += (long long)((double)wv * (double)wv * unit);
+        wv = fabsf(wv) < zero_below ? 0.f : wv;
+        const double q = (double)wv * r, t = q * q;
+        m2 += (long long)__builtin_rint(t);
+        plain += t;
         return wv;
     };
+    auto share = [&]() { return plain < 0x1p62 ? m2 : plain == plain ? kNormInf : kNormNan; };
     const int64_t e0 = (int64_t)lo * nnz, e1 = (int64_t)t1 * nnz;
     if (lo < 0 || kFoldEntriesPerRow * (e1 - e0) >= d) {
         rows(folded);
-        return m2;
+        return share();
     }
     unsigned *mark = reinterpret_cast<unsigned *>(V) + RKp - kPadWords + blk / 32;
     const unsigned bit = 1u << (blk % 32);
@@ -600,7 +623,7 @@ __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t 
     } else {
         for (int64_t k = e0 + threadIdx.x; k < e1; k += kSpWaves * kWave) clear(col[k]);
     }
-    return m2;
+    return share();
 }
 
 // The same as a call: inlined, what it needs costs the window loop registers, whether a call ever folds or not.  Spilled, plain / optimistic,
@@ -1292,8 +1315,8 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
         // steps taken so far, scale the columns of the learners at or near the threshold by their
         // sigma with all wavefronts, measure their ||v||^2, and take the remaining rounds' <v, x_t>
         // afresh.  Which rows of V: a column holds values of at most D sigma after the first fold that
-        // follows its last touch, so of at most D 2^-144 after the third, and what falls below the
-        // smallest normal number is set to zero.  So a learner's columns are those of the rounds since
+        // follows its last touch, so of at most D 2^-144 after the third, and what falls below
+        // D 2^-136 is set to zero.  So a learner's columns are those of the rounds since
         // its third-last fold (a stretch of the stream), each visited once by way of a mark; rounds
         // of earlier calls are not at hand, and a long stretch has more entries than V rows: then all
         // rows.  Either way the same values come out.  (Steps larger than the ball shrink sigma by a
@@ -1320,14 +1343,14 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
             for (int rd = (int)threadIdx.x / LPW; rd <= ft; rd += kSpWaves * EPI) bw[rd][l] = 0.f;   // applied
             long long m2 = fold_columns<LPW>(a.V, a.col, a.RKp, a.d, a.D, nnz, blk, fold_lo, v.ws + ft + 1, fold_sf[l]);
 #pragma unroll
-            for (int sh = 32; sh >= LPW; sh >>= 1) m2 += __shfl_xor(m2, sh);
+            for (int sh = 32; sh >= LPW; sh >>= 1) m2 = norm_add(m2, __shfl_xor(m2, sh));
             if (lane < LPW) fold_part[wave][l] = m2;
         }
         wg_sync();
         if (chain && fold_sf[l] < kSparseFoldJoinF) {
             long long m2 = 0;
-            for (int wv = 0; wv < kSpWaves; ++wv) m2 += fold_part[wv][l];
-            hd = 0.5 * (double)m2 * (a.D * a.D * 0x1p-52);
+            for (int wv = 0; wv < kSpWaves; ++wv) m2 = norm_add(m2, fold_part[wv][l]);
+            hd = 0.5 * norm_of_units(m2, a.D);
             sigma = 1.0; sf = 1.f; isf = 1.f;
         }
         if (threadIdx.x == 0) fold_t = -1;

@@ -433,6 +433,70 @@ def test_folds_that_visit_the_columns_of_recent_rounds(lpw, d, nnz):
         assert np.array_equal(whole[k], part[k]), k
 
 
+def _folding(D, eta, **over):
+    """Rounds, targets and comparator of size D: the same problem in a ball of another radius."""
+    wl = WL.make("c5", D=D, noise=0.1 * D, wstar_norm=0.5 * D, wstar_nnz=32, eta=eta, **over)
+    return wl, WL.generate(wl)
+
+
+@pytest.mark.parametrize("lpw", [4, 16])
+def test_folds_scale_with_the_radius(lpw):
+    """Everything in the ball of radius 2^18 is 2^7 times what it is in the ball of radius 2^11, to the bit: which
+    columns a fold visits, what it sets to zero and the units of ||v||^2 are all relative to the radius.  (Radii at
+    which the smallest number a fold keeps, 2^-136 of the radius, is not subnormal.  What is read back has been
+    multiplied by the scale since then, 2^-100 or more: coordinates that are subnormal by that are compared as such.)"""
+    eta = (0.02, 0.9, 3.0, 40.0)
+    W = []
+    for D in (2.0 ** 11, 2.0 ** 18):
+        wl, data = _folding(D, eta, T=4500, R=3, d=20011, K=4, nnz=4)
+        if W:
+            data = dict(first, u=first["u"] * np.float32(2.0 ** 7), y=first["y"] * np.float32(2.0 ** 7))
+        else:
+            first = data
+        print("case c5 folds radius", D, "lpw", lpw, flush=True)
+        whole = _gpu(wl, data, options=dict(sparse_lpw=lpw))
+        part = _gpu(wl, data, chunk=4096, n_max=4096, options=dict(sparse_lpw=lpw))
+        for k in ("regret", "L", "W", "p", "wbar"):
+            assert np.array_equal(whole[k], part[k]), k
+        ref = _oracle().run_workload(wl, data, norm_every=0)
+        assert np.abs(whole["W"] - ref["W"]).max() <= ABS_TOL * D
+        W.append(whole["W"])
+    assert (np.abs(W[0]) > 0).any(axis=2).all()
+    tiny = np.abs(W[1]) < 2.0 ** -118
+    assert np.array_equal(W[0][~tiny] * np.float32(2.0 ** 7), W[1][~tiny])
+    assert (np.abs(W[0][tiny]) <= 2.0 ** -125).all()
+
+
+@pytest.mark.parametrize("D", [1e-34, 1e-3, 1e6])
+def test_folds_in_small_and_large_balls(D):
+    """Against the oracle, relative to the radius; in the smallest ball many coordinates are subnormal numbers
+    (steps of 2^-149, below 2^-35 of the radius)."""
+    wl, data = _folding(D, (0.02, 0.9, 3.0, 40.0, 200.0), T=1500, R=2, d=9001, K=5, nnz=8)
+    print("case c5 folds radius", D, flush=True)
+    got = _gpu(wl, data)
+    ref = _oracle().run_workload(wl, data, norm_every=0)
+    dW = np.abs(got["W"] - ref["W"]).max() / D
+    print("D=%g W %.2e of D" % (D, dW))
+    assert np.isfinite(got["W"]).all() and dW <= ABS_TOL
+
+
+@pytest.mark.parametrize("over,optimistic", [
+    (dict(R=30, d=20011, K=5, nnz=4), True),      # 38 workgroups: marks in two words of a row
+    (dict(R=30, d=20011, K=5, nnz=4), False),
+    (dict(R=30, d=64, K=5, nnz=4), False),        # more learners than rows of V: no place for the marks
+    (dict(R=30, d=64, K=5, nnz=4), True),
+])
+def test_folds_of_many_workgroups(over, optimistic):
+    wl = WL.make("c5", T=4300, wstar_nnz=32, eta=(0.02, 0.9, 3.0, 40.0, 5000.0), optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    print("case c5 folds of many workgroups", over, optimistic, flush=True)
+    whole = _gpu(wl, data, options=dict(sparse_lpw=4))
+    _check(wl, data, whole, norm_every=0, label="c5 folds %s" % (over,))
+    part = _gpu(wl, data, chunk=4096, n_max=4096, options=dict(sparse_lpw=4))
+    for k in ("regret", "L", "W", "p", "wbar"):
+        assert np.array_equal(whole[k], part[k]), k
+
+
 @pytest.mark.parametrize("lpw", [4, 8, 64])
 def test_sparse_rounds_with_a_column_in_every_round(lpw):
     """A feature present in every round (a bias column) makes every pair of rounds of a window
