@@ -133,7 +133,7 @@ constexpr double kSparseFoldSoft = OCO_FOLD_SOFT;  // fold between segments
 #endif
 constexpr int kSegment = OCO_SEGMENT;        // rounds per launch segment (absolute alignment)
 // The fold inside the kernel: learners below this scale are folded (the one that stopped the chain and whoever will
-// soon follow), the others of the workgroup keep their scale.
+// soon follow), the others of the workgroup keep their scale.  (Where few_columns_per_fold says no: every learner.)
 constexpr float kSparseFoldJoinF = 0x1p-72f;
 // A fold sets to zero what it leaves below this many times D: far below a rounding of the iterate, and above whatever a column can
 // hold that was not touched since the learner's third-last fold (D 2^-144, see the fold).
@@ -144,6 +144,16 @@ constexpr int kPadWords = 32, kPadFolds = 16, kMarkWorkgroups = 32 * kPadFolds;
 // A fold visits the columns of the rounds in question while their entries are fewer than this many times d, else all d.
 // (one visit by entry: a mark, the row, the mark again; by row: the row)
 constexpr int kFoldEntriesPerRow = 2;
+// Where rows are few for a round's entries a fold's rounds cover them anyway; every fold is then one of all rows and of all the
+// workgroup's learners, as learners that fold apart stop the workgroup more often.  3000 optimistic rounds, ms, all rows and learners / columns
+// of recent rounds:
+//   64 learners, 8 entries    d = 1024 2.8 / 3.9   4096 3.06 / 3.32   6144 3.34 / 3.29   8192 4.1 / 3.3   12288 5.9 / 3.1
+//                32           d = 4096 8.2 / 10.7  12288 8.6 / 8.6    16384 10.2 / 8.1   24576 13.1 / 7.7  49152 22.3 / 7.5
+//                64           d = 8192 15.8 / 20.6  16384 15.4 / 18.1  24576 17.5 / 16.1  32768 20.0 / 14.8  98304 43.4 / 13.7
+//   520 learners, 8           d = 1024 2.38 / 2.63  4096 2.53 / 2.64   6144 2.93 / 2.76   12288 4.2 / 2.7
+//                 32          d = 4096 6.2 / 7.0   12288 6.3 / 6.9    16384 7.0 / 7.1    24576 8.7 / 7.2   49152 14.5 / 7.5
+//                 64          d = 8192 12.2 / 13.6  24576 12.0 / 13.3  32768 13.4 / 13.4  49152 16.7 / 13.9  98304 28.2 / 14.1
+__device__ __forceinline__ bool few_columns_per_fold(int d, int nnz) { return d - 2048 >= 448 * nnz; }
 constexpr int kWin = 64;                     // rounds per window (absolute alignment)
 constexpr int kSpWaves = 16;                 // wavefronts per workgroup
 constexpr int kBesideMaxWorkgroups = 128;    // window grids up to this size leave half the chip idle
@@ -524,7 +534,7 @@ __device__ __forceinline__ double norm_of_units(long long m, double D)
 // rounds lo .. t1 - 1, each once by way of its mark, or all rows where lo < 0 or those rounds have more entries.
 template <int LPW>
 __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t *col_, int RKp_, int d_, double D, int nnz, int blk_,
-                                                            int lo_, int t1, float fs)
+                                                            int lo_, int t1, float fs, float join)
 {
     constexpr int EPI = kWave / LPW;
     // (arguments arrive in vector registers and as pointers into any memory: they are the same in all lanes, and into global memory)
@@ -534,7 +544,7 @@ __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t 
     const int32_t *col = uniform_global(col_);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = lane % LPW, e = lane / LPW;
-    const bool mine = fs < kSparseFoldJoinF;
+    const bool mine = fs < join;
     const int64_t nslots = kSpWaves * EPI;
     float *Vq = V + blk * LPW + l;
     // (whole turns without a branch, so that the loads of four rows are on their way together: a learner that is not folded gets back what was read)
@@ -633,18 +643,18 @@ __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t 
 // take nothing out of the window loop from (128 learners without folds, optimistic: 4.77 ms before, 4.70 now, 4.84 as a call).
 template <int LPW>
 __device__ __attribute__((noinline)) long long fold_columns_call(float *V, const int32_t *col, int RKp, int d, double D, int nnz, int blk, int lo,
-                                                                 int t1, float fs)
+                                                                 int t1, float fs, float join)
 {
-    return fold_columns_here<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs);
+    return fold_columns_here<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs, join);
 }
 template <int LPW>
-__device__ __forceinline__ long long fold_columns(float *V, const int32_t *col, int RKp, int d, double D, int nnz, int blk, int lo, int t1, float fs)
+__device__ __forceinline__ long long fold_columns(float *V, const int32_t *col, int RKp, int d, double D, int nnz, int blk, int lo, int t1, float fs, float join)
 {
     if constexpr (LPW == 4) {
         asm volatile("" : "+v"(V), "+v"(col), "+v"(RKp), "+v"(d), "+v"(D), "+v"(nnz), "+v"(blk));
-        return fold_columns_here<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs);
+        return fold_columns_here<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs, join);
     } else {
-        return fold_columns_call<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs);
+        return fold_columns_call<LPW>(V, col, RKp, d, D, nnz, blk, lo, t1, fs, join);
     }
 }
 
@@ -803,7 +813,8 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
     const float *yrow = a.y ? a.y + (int64_t)r * a.y_run_stride : nullptr;
     const unsigned zoff4 = 4u * (unsigned)(r * a.zl.zs_r + i * a.zl.zs_i);    // byte offset inside a round's slice of Z
     const int64_t zstep = 4 * a.zl.zs_t;
-    const bool fold_sel = nq <= a.d && nblk <= kMarkWorkgroups;   // the padding holds the marks and every learner's folds
+    // the padding holds the marks and every learner's folds, and the columns of recent rounds are few
+    const bool fold_sel = nq <= a.d && nblk <= kMarkWorkgroups && few_columns_per_fold(a.d, nnz);
     const WinRec *recs = reinterpret_cast<const WinRec *>(static_cast<const char *>(a.scratch) + kProgBytes);
     // the lanes that run the dependent rounds (padding learners of the last workgroup take no part:
     // their step sizes stay zero and their scale stays one)
@@ -1322,10 +1333,11 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
         // rows.  Either way the same values come out.  (Steps larger than the ball shrink sigma by a
         // constant factor per round, a fold every 10 .. 100 rounds; visiting all rows each time, 3435 rounds
         // of 348 learners, d = 745735, took 456 ms.) -----------------------------------------------------
+        const float join = fold_sel ? kSparseFoldJoinF : 1.f;
         apply(v, bw, ft, std::true_type());
         if (wave == 0) {
             int lo = 0x7fffffff;
-            if (chain && fold_sf[l] < kSparseFoldJoinF && fold_sel) {
+            if (chain && fold_sf[l] < join && fold_sel) {
                 int *h = reinterpret_cast<int *>(a.V) + (int64_t)q * a.RKp + a.RKp - kPadWords + kPadFolds;
                 const int h0 = __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const int h1 = __hip_atomic_load(h + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1341,15 +1353,23 @@ __global__ void __launch_bounds__(kSpWaves *kWave) sparse_window_kernel(const Sp
         wg_sync();
         {
             for (int rd = (int)threadIdx.x / LPW; rd <= ft; rd += kSpWaves * EPI) bw[rd][l] = 0.f;   // applied
-            long long m2 = fold_columns<LPW>(a.V, a.col, a.RKp, a.d, a.D, nnz, blk, fold_lo, v.ws + ft + 1, fold_sf[l]);
+            long long m2 = fold_columns<LPW>(a.V, a.col, a.RKp, a.d, a.D, nnz, blk, fold_lo, v.ws + ft + 1, fold_sf[l], join);
 #pragma unroll
-            for (int sh = 32; sh >= LPW; sh >>= 1) m2 = norm_add(m2, __shfl_xor(m2, sh));
+            for (int sh = 32; sh >= LPW; sh >>= 1) {
+                const long long o = __shfl_xor(m2, sh);
+                m2 = __builtin_expect(__any(m2 < 0), 0) ? norm_add(m2, o) : m2 + o;
+            }
             if (lane < LPW) fold_part[wave][l] = m2;
         }
         wg_sync();
-        if (chain && fold_sf[l] < kSparseFoldJoinF) {
+        if (chain && fold_sf[l] < join) {
             long long m2 = 0;
-            for (int wv = 0; wv < kSpWaves; ++wv) m2 = norm_add(m2, fold_part[wv][l]);
+            bool odd = false;
+            for (int wv = 0; wv < kSpWaves; ++wv) { m2 += fold_part[wv][l]; odd |= fold_part[wv][l] < 0; }
+            if (__builtin_expect(odd, 0)) {
+                m2 = 0;
+                for (int wv = 0; wv < kSpWaves; ++wv) m2 = norm_add(m2, fold_part[wv][l]);
+            }
             hd = 0.5 * norm_of_units(m2, a.D);
             sigma = 1.0; sf = 1.f; isf = 1.f;
         }

@@ -485,6 +485,8 @@ def test_folds_in_small_and_large_balls(D):
     (dict(R=30, d=20011, K=5, nnz=4), False),
     (dict(R=30, d=64, K=5, nnz=4), False),        # more learners than rows of V: no place for the marks
     (dict(R=30, d=64, K=5, nnz=4), True),
+    (dict(R=30, d=3839, K=5, nnz=4), False),      # the last d whose folds are of all rows and learners,
+    (dict(R=30, d=3840, K=5, nnz=4), False),      # and the first whose folds may visit columns
 ])
 def test_folds_of_many_workgroups(over, optimistic):
     wl = WL.make("c5", T=4300, wstar_nnz=32, eta=(0.02, 0.9, 3.0, 40.0, 5000.0), optimistic=optimistic, **over)
@@ -495,6 +497,22 @@ def test_folds_of_many_workgroups(over, optimistic):
     part = _gpu(wl, data, chunk=4096, n_max=4096, options=dict(sparse_lpw=4))
     for k in ("regret", "L", "W", "p", "wbar"):
         assert np.array_equal(whole[k], part[k]), k
+
+
+@pytest.mark.parametrize("d", [3001, 20011])
+def test_folds_beside_a_run_that_is_not_finite(d):
+    """One run's labels hold an infinity and a NaN: its learners are lost, those of the runs that share their
+    workgroups agree with the oracle.  (They fold in other rounds than beside a finite run, so not to the bit.)"""
+    wl = WL.make("c5", T=1500, R=3, d=d, K=5, nnz=4, wstar_nnz=32, eta=(0.02, 0.9, 3.0, 40.0, 5000.0))
+    data = WL.generate(wl)
+    print("case c5 folds beside a run that is not finite", d, flush=True)
+    ref = _oracle().run_workload(wl, data, norm_every=0)
+    y = data["y"].copy()
+    y[1, 700], y[1, 900] = np.inf, np.nan
+    got = _gpu(wl, dict(data, y=y), options=dict(sparse_lpw=16))
+    for k in ("regret", "L", "W", "p", "wbar"):
+        np.testing.assert_allclose(got[k][[0, 2]], ref[k][[0, 2]], rtol=REG_RTOL if k in ("regret", "L") else 0, atol=ABS_TOL, err_msg=k)
+    assert not np.isfinite(got["L"][1]).any() and not np.isfinite(got["W"][1]).all(axis=1).any()
 
 
 @pytest.mark.parametrize("lpw", [4, 8, 64])
