@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(64) dense_tile_kernel(const float *x, int d, W
 // ---- rows and iterates as three bfloat16 parts ---------------------------------------------------
 // v = v1 + v2 + v3, each part the bfloat16 nearest to what the ones before leave: 3 x 8 bits hold all 24 of a
 // float32.  A product of two such numbers is taken as its six largest part products, each exact in float32, by the
-// 16-bit matrix instructions: dropped are (2,3), (3,2) and (3,3), at most 2^-25 of the product (a float32 rounding), and
+// 16-bit matrix instructions: dropped are (2,3), (3,2) and (3,3), at most 2^-24 of the product (|v2| <= 2^-8 |v|, |v3| <= 2^-17 |v|), 2^-27.5 in the mean square;
 // six products cost 0.375 of the time of the float32 instructions' one.
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
@@ -1407,7 +1407,9 @@ template <int LOSS> WindowKernel pick_window_kernel(int nblk, int mode, bool par
 {
     if (mode == 3) {
         *waves = kQW + kQL; *tiles = kQT; *lds_bytes = parts ? LdsQ<true>::total : LdsQ<false>::total;
-        if (parts) return opt ? dense_window_shared_kernel<LOSS, true, true> : dense_window_shared_kernel<LOSS, false, true>;
+        if constexpr (LOSS != 0) {                               // (the linear loss: see parts_pay)
+            if (parts) return opt ? dense_window_shared_kernel<LOSS, true, true> : dense_window_shared_kernel<LOSS, false, true>;
+        }
         return opt ? dense_window_shared_kernel<LOSS, true, false> : dense_window_shared_kernel<LOSS, false, false>;
     }
     if (mode == 4) {
@@ -1497,9 +1499,13 @@ namespace {
 //   24576 learners (384),            d = 4096   64 rounds 1.05 / 1.37   320 2.64 / 2.94    512 3.85 / 3.90   1024 7.12 / 6.50   4096 26.7 / 22.0
 //   28672 learners (448),            d = 4096   64 rounds 1.07 / 1.51   512 3.88 / 4.24    640 4.75 / 4.96   1024 7.11 / 6.89   4096 26.7 / 23.0
 //   65536 learners (1024),           d = 4096   64 rounds 1.84 / 2.89   768 10.8 / 11.1   1024 14.2 / 14.0   1280 17.3 / 16.7   4096 53.9 / 46.7
-bool parts_pay(int64_t nq, int d, int nwin, int ncu)
+// The linear loss stays in float32.  Its losses are the predictions themselves, summed over the rounds, and the 16-bit instructions' sums
+// lean to one side by a few 2^-26 of a prediction: 1536 optimistic rounds of d = 2048 had cumulative losses 2.2e-6 off by 2-norm in
+// parts, 5.3e-7 in float32 (d = 4096 9.3e-7 and 2.2e-7).  With the other losses none is further off (squared 1.9e-8 and 1.9e-8, logistic
+// 2.0e-10 and 2.0e-10), and the iterates are nearer with all three (squared 5.8e-7 and 6.0e-7, logistic 1.3e-7 and 2.0e-7).
+bool parts_pay(int64_t nq, int d, int nwin, int ncu, int loss)
 {
-    if (d % 16 != 0 || d > kBlocksMaxD) return false;
+    if (loss == 0 || d % 16 != 0 || d > kBlocksMaxD) return false;
     const int64_t wgs = (nq + kQT * kM - 1) / (kQT * kM), rest = wgs % ncu;
     const int64_t gain = wgs / ncu + (rest == 0 ? 0 : 2 * rest <= ncu ? 3 : 2);
     return nwin * gain * ncu >= 20 * wgs;
@@ -1554,7 +1560,7 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
             ncu <= 0)
             ncu = 256;
     }
-    const bool parts = mode == 3 && parts_pay((int64_t)a.R * a.K, a.d, nwin, ncu);
+    const bool parts = mode == 3 && parts_pay((int64_t)a.R * a.K, a.d, nwin, ncu, loss);
     if (a.tune->get(OCO_OPT_VERBOSE) == 1)
         fprintf(stderr, "dense plan: windowed contraction kernel, %d windows in pieces of %lld, %d tiles, iterates %s\n",
                 nwin, (long long)sc.piece_windows, (a.R * a.K + kM - 1) / kM,
