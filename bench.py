@@ -86,7 +86,8 @@ def roofline_block(wl, kt, config_key):
     product 2, gradient step 2, projection scale 1, the comparator's inner product 2 per run.
     Executed: the projection is one scalar per learner (lazy scale), so the register kernel
     issues 4 + 2/K and the windowed kernel 4 (two contractions; the comparator's inner products
-    run in a kernel of their own)."""
+    run in a kernel of their own).  With rows in bfloat16 parts the iterates' way through HBM
+    bounds the kernel, and the matrix cores' share stands beside it."""
     launches = max(kt["launches"], 1)
     avg_ms = kt["ms_sum"] / max(kt["timed"], 1)
     kernel = kt["kernel"]
@@ -105,9 +106,13 @@ def roofline_block(wl, kt, config_key):
         executed = 4.0 if kernel.startswith("dense_window") else 4.0 + 2.0 / wl.K
         ach = per_unit * wl.units / launches / (avg_ms * 1e-3) / 1e12
         peak = PEAK_SPLIT_TFLOPS if kernel == "dense_window_parts_kernel" else PEAK_FP32_TFLOPS
-        rl.update(bound="mfma" if kernel.startswith("dense_window") else "alu", achieved=ach, peak=peak,
-                  unit="TFLOP/s", frac=ach / peak, flops_per_unit=per_unit,
-                  executed_flops_per_unit=executed, executed_flops_frac=ach * executed / per_unit / peak)
+        flops = dict(achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak, flops_per_unit=per_unit,
+                     executed_flops_per_unit=executed, executed_flops_frac=ach * executed / per_unit / peak)
+        if kernel == "dense_window_parts_kernel":
+            gbs = hbm_bytes / launches / (avg_ms * 1e-3) / 1e9
+            rl.update(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s", frac=gbs / PEAK_HBM_GBS, matrix_cores=flops)
+        else:
+            rl.update(bound="mfma" if kernel.startswith("dense_window") else "alu", **flops)
         if not kernel.startswith("dense_window"):
             rl["non_packed_ceiling"] = {"peak": NONPACKED_FP32_TFLOPS, "unit": "TFLOP/s",
                                         "executed_flops_frac": ach * executed / per_unit / NONPACKED_FP32_TFLOPS,
@@ -141,13 +146,17 @@ def binding_block(wl, res, config_key, floor=None):
     elif kernel.startswith("dense_window"):
         kt = res["kernel_timing"]
         step_ms = kt["ms_sum"] / max(kt["timed"], 1) * max(kt["launches"], 1)      # all launches of a step
-        floor_ms = 4.0 * wl.units / (PEAK_FP32_TFLOPS * 1e12) * 1e3
-        where = ("matrix cores, fed from L2 (round rows), the iterates in registers"
+        parts, loaders = kernel == "dense_window_parts_kernel", kernel in ("dense_window_parts_kernel", "dense_window_shared_kernel")
+        floor_ms = 4.0 * wl.units / ((PEAK_SPLIT_TFLOPS if parts else PEAK_FP32_TFLOPS) * 1e12) * 1e3
+        hbm_ms = algorithmic_hbm_bytes(wl, kernel, max(kt["launches"], 1), kt.get("iterates") == "registers") / (PEAK_HBM_GBS * 1e6)
+        where = ("HBM (iterates in and out once per window) beside L2 (round rows in bfloat16 parts)" if parts else
+                 "matrix cores, fed from L2 (round rows), the iterates in registers"
                  if kt.get("iterates") == "registers" else "matrix cores, fed from L2 (round rows) and HBM (iterates)")
         b.update(resource=where + "; the dependent rounds of a window "
-                          "(64 rounds on float64 scalars, one wavefront per tile of 16 learners) run beside the sweep",
+                          "(64 rounds on float64 scalars, one wavefront per tile of 16 learners) "
+                          + ("run between the sweeps" if loaders else "run beside the sweep"),
                  tiles=(wl.R * wl.K + 15) // 16, windows=(wl.T + 63) // 64,
-                 matrix_core_floor_ms=floor_ms, utilisation=floor_ms / step_ms,
+                 matrix_core_floor_ms=floor_ms, hbm_floor_ms=hbm_ms, utilisation=(hbm_ms if parts else floor_ms) / step_ms,
                  dependent_rounds_us_per_round=step_ms * 1e3 / wl.T)
     else:
         b.update(resource="vector ALU issue (fused multiply-adds of the inner product and the step)")

@@ -855,9 +855,11 @@ __global__ void __launch_bounds__(NW *kWave) dense_window_kernel(const DenseArgs
 // (dense_tile_split_kernel), -Bm once per window, an iterate's block when it has been updated; sums and the iterates
 // themselves stay float32.  Per block 24 instructions of 16 clocks in place of 32 of 32, for 6 KB of rows per window and
 // block instead of 4.  Error against float64 on c4: 4.9e-7, with float32 instructions 6.9e-7.
-// Measured on c4 as above, us per step: 1.1; 0.75 with the loads switched off (LDS reads, matrix and vector instructions), 0.84 with either the
-// rows or the iterates loaded alone, as long without matrix instructions as with them.  What bounds it is thus rows
-// (from L2) and iterates (through L2) together: the iterates are loaded and stored with the streaming hint, both or
+// Measured on c4 as above, us per step: 1.02; 0.75 with the loads switched off (LDS reads, matrix and vector instructions), 0.84 with either the
+// rows or the iterates loaded alone, as long without matrix instructions as with them.  Of a window 131 us are the sweep, 10.7 the
+// dependent rounds, 3.7 inputs and shares.  What bounds it is the iterates' way through HBM, with the rows (from L2) beside it: by
+// the byte counters the sweep moves 4.5 TB/s, 0.86 of what a device copy does, the matrix cores are busy a third of the time and
+// LDS 0.36.  The iterates are loaded and stored with the streaming hint, both or
 // neither (one of them: 10 ms per step worse), and lie in blocks (below).  Workgroups of an XCD held to one pace
 // by a counter: 10 ms worse; a different first block per XCD or workgroup: no difference; rows and iterates on loading
 // wavefronts of their own: no better with the hint, 17 ms worse without; four steps ahead instead of three: spills.
@@ -1121,8 +1123,8 @@ __global__ void __launch_bounds__((kQW + kQL) * kWave) dense_window_shared_kerne
         if (OPT && tp < kB) reinterpret_cast<float *>(lds + Lds::hg)[tp] = hgpre;
     };
 
-    // The working wavefronts' side.  F and -Bm of this lane's learner; do_q: take the shares of W X^T.  stage_next: first write the staged labels and Gram table to LDS; flush_prev >= 0:
-    // write the predictions of window flush_prev to Z.
+    // The working wavefronts' side.  F and -Bm of this lane's learner; do_q: take the shares of W X^T.  stage_next:
+    // first write the staged labels and Gram table to LDS; flush_prev >= 0: write the predictions of window flush_prev to Z.
     auto sweep = [&](auto stager, bool do_q, float F, const Steps &bmr, bool stage_next, int flush_prev)
         __attribute__((always_inline)) {
         int tid_s = (int)threadIdx.x;                            // (see load_sweep)
@@ -1475,7 +1477,7 @@ bool dense_window_wanted(const DenseArgs &a)
     const int64_t path = a.tune->get(OCO_OPT_DENSE_PATH);
     if (path == 1) return a.d > 64 * kWave;                     // the register kernel cannot hold more
     if (path == 2) return true;
-    // measured on MI355X: c4 (16384 learners, d = 4096) 72 ms against the register kernel's 136 ms; c3 (4352
+    // measured on MI355X: c4 (16384 learners, d = 4096) 58 ms against the register kernel's 138 ms; c3 (4352
     // learners, d = 1000) 50 ms against 62 ms.  Fewer learners stay with the register kernel (a round costs about
     // 0.35 us here whatever d is, as long as the workgroups fit the chip at once), and so do narrower models: from 3072
     // learners on this kernel would be up to twice as fast there (8192 learners, 2048 rounds 1.48 / 0.74 ms at d = 16, 1.65 / 1.02 at
@@ -1542,8 +1544,9 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
     // Unset: streamed, two tiles -- on c4 as fast as the registers (every round row a wavefront loads
     // serves two tiles), on c3 half as many workgroups --, two tiles in registers where they fit and the
     // wavefronts have several blocks each (c3: 41.8 against 46.4 ms), or, with at least four tiles per compute unit's
-    // workgroup on every one of 256 compute units and wide rows, the loading wavefronts (c4: 67.4 against
-    // 70.4 ms; c3, bound by the dependent rounds, which that kernel does not overlap: 101 against 47.5 ms).
+    // workgroup on every one of 256 compute units and wide rows, the loading wavefronts (ms against two tiles, 16384
+    // learners: c4 57.3 / 72.0; 4096 rounds of d = 2048 7.2 / 7.8; 2048 of d = 8192 13.6 / 16.3; 512 of d = 4096 2.43 / 2.40, 64 1.00 / 0.92;
+    // c3, bound by the dependent rounds, which that kernel does not overlap: 101 / 47.5).
     // (5, the kernel with split coordinates, which did not take the call: as unset)
     const int64_t ropt = a.tune->get(OCO_OPT_WINDOW_RESIDENT) == 5 ? -1 : a.tune->get(OCO_OPT_WINDOW_RESIDENT);
     const bool fits = a.d <= 16 * kNW8 * 32;
