@@ -1588,6 +1588,8 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
                                        lds_bytes);
     if (e != hipSuccess) return e;
     // rows in parts are half as long again: two thirds of the windows in the same scratch
+    const int pw = parts ? std::max(1, (int)sc.piece_windows * 2 / 3) : (int)sc.piece_windows;
+    if (parts && (size_t)pw * nblk * 2 * kSplitFloats > 2 * sc.tile_floats) return hipErrorInvalidValue;
     const bool blocked = parts && (int64_t)a.R * a.K % kM == 0;
     auto turn_blocks = [&](bool to_rows) -> hipError_t {
         if (!blocked) return hipSuccess;
@@ -1597,8 +1599,6 @@ hipError_t launch_dense_window(const DenseArgs &a0, int loss, hipStream_t s, con
     };
     e = turn_blocks(false);
     if (e != hipSuccess) return e;
-    const int pw = parts ? std::max(1, (int)sc.piece_windows * 2 / 3) : (int)sc.piece_windows;
-    if (parts && (size_t)pw * nblk * 2 * kSplitFloats > 2 * sc.tile_floats) return hipErrorInvalidValue;
     for (int w0 = 0; w0 < nwin; w0 += pw) {
         const int nw = std::min<int>(pw, nwin - w0);
         hipLaunchKernelGGL(dense_tile_kernel, dim3((unsigned)nblk, (unsigned)nw), dim3(64), 0, s, a.x, a.d, plan, w0, xq,
