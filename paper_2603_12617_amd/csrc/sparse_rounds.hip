@@ -637,10 +637,13 @@ __device__ __forceinline__ long long fold_columns_here(float *V_, const int32_t 
 }
 
 // The same as a call: inlined, what it needs costs the window loop registers, whether a call ever folds or not.  Spilled, plain / optimistic,
-// before, inlined and as a call: 8 learners per workgroup 0 / 4, 5 / 11 and 0 / 0; 16: 10 / 31, 23 / 41 and 4 / 11; 32: 11 / 23, 23 / 30
-// and 5 / 11; 64: 0 / 0, 0 / 3 and 0 / 0.  8192 learners without folds, optimistic: 17.00, 17.18 and 16.94 ms.  With four learners per workgroup a
-// fold is short enough for the call itself to show (the call 0.3 us of 6); there it is inlined behind values the compiler can
-// take nothing out of the window loop from (128 learners without folds, optimistic: 4.77 ms before, 4.70 now, 4.84 as a call).
+// before columns were visited, inlined and as a call: 8 learners per workgroup 0 / 4, 5 / 11 and 0 / 2; 16: 10 / 31, 23 / 41 and 5 / 11;
+// 32: 11 / 23, 23 / 30 and 8 / 11; 64: 0 / 0, 0 / 3 and 0 / 1.  With four learners per workgroup it is inlined behind values the compiler
+// can take nothing out of the window loop from.  Rounds without folds, ms, before columns were visited / now:
+//   16384 of 32 entries, 128 learners, by 4 plain 3.43 / 3.36, optimistic 4.29 / 4.32; by 8 3.59 / 3.57, 4.17 / 4.20; by 16 4.37 / 4.36,
+//   6.20 / 4.59; by 32 6.27 / 6.39, 7.47 / 6.56; by 64 10.6 / 10.5, 11.3 / 11.4
+//   8192 of 32, 1024 learners, by 4 5.11 / 5.02, 5.68 / 5.63; by 8 4.70 / 4.68, 5.33 / 5.28; by 16 4.71 / 4.77, 5.60 / 5.41
+//   50000 of 32, 128 learners, d = 2^20, by 4 9.39 / 9.36, optimistic 11.9 / 12.04 (as a call 12.04, in a form that spills nothing 12.07)
 template <int LPW>
 __device__ __attribute__((noinline)) long long fold_columns_call(float *V, const int32_t *col, int RKp, int d, double D, int nnz, int blk, int lo,
                                                                  int t1, float fs, float join)
