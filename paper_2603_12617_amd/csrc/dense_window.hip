@@ -122,7 +122,8 @@ __global__ void __launch_bounds__(64) dense_tile_kernel(const float *x, int d, W
 }
 
 // ---- rows and iterates as three bfloat16 parts ---------------------------------------------------
-// v = v1 + v2 + v3, each part the bfloat16 nearest to what the ones before leave: 3 x 8 bits hold all 24 of a
+// (The splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision
+// computations", ARITH 2019.)  v = v1 + v2 + v3, each part the bfloat16 nearest to what the ones before leave: 3 x 8 bits hold all 24 of a
 // float32.  A product of two such numbers is taken as its six largest part products, each exact in float32, by the
 // 16-bit matrix instructions: dropped are (2,3), (3,2) and (3,3), at most 2^-24 of the product (|v2| <= 2^-8 |v|, |v3| <= 2^-17 |v|), 2^-27.5 in the mean square;
 // six products cost 0.375 of the time of the float32 instructions' one.

@@ -387,12 +387,12 @@ def test_projections_of_split_coordinates_do_not_add_up_their_errors(d):
     dict(T=130, R=5, d=48, K=16),          # an odd number of blocks, a workgroup with three tiles missing
     dict(T=331, R=9, d=272, K=16),         # more steps than the loads run ahead
     dict(T=200, R=3, d=2064, K=16),        # a long sweep, the last step half empty
-    dict(T=70, R=4, d=4112, K=16),         # beyond the longest row that is turned into blocks
+    dict(T=70, R=4, d=4112, K=16),         # beyond the longest row that is turned into blocks: float32
     dict(T=150, R=3, d=528, K=15),         # learners that do not fill their tiles: rows as they lie
-    dict(T=150, R=2, d=1004, K=16),        # a row that does not end with a block: likewise
+    dict(T=150, R=2, d=1004, K=16),        # a row that does not end with a block: float32
 ])
 def test_loading_wavefronts_at_the_edges_of_blocks_and_tiles(over, optimistic):
-    """Rows in three bfloat16 parts, iterates in blocks or in rows: against the oracle, and the same bits again."""
+    """Rows in three bfloat16 parts, iterates in blocks or in rows, and rows in float32: against the oracle, and the same bits again."""
     wl = WL.make("c4", optimistic=optimistic, **over)
     data = WL.generate(wl)
     print("case loading wavefronts", over, optimistic, flush=True)
