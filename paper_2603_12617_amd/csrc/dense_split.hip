@@ -6,9 +6,9 @@
 // window of 64 rounds takes 940 us, nearly all of it one compute unit's matrix instructions and loads.  Here
 // a window is ONE launch in which workgroup (tile, chunk) owns a range of the tile's coordinates:
 //   (1) it sums the chunks' shares of W X_k^T that the launch before left (fixed order, float64),
-//   (2) runs the 64 dependent rounds of its tile (chain_window) on one wavefront -- every chunk of a tile
-//       repeats them from the same inputs, which costs nothing on compute units that would idle and saves a
-//       second launch per window --, while the other seven wavefronts fetch the operands of (3),
+//   (2) runs the 64 dependent rounds of its tile (chain_rounds) on four wavefronts, four learners each -- every chunk of
+//       a tile repeats them from the same inputs, which costs nothing on compute units that would idle and saves a
+//       second launch per window --, while the other four wavefronts fetch the operands of (3),
 //   (3) applies the window's step to its coordinates, W <- F W - Bm X_k, and takes its share of
 //       W X_{k+1}^T and of ||W||^2 of the new iterates for the launch after.
 // The launch boundary is the only synchronisation between workgroups: what a launch reads of other
@@ -16,15 +16,15 @@
 // products are those of the iterates themselves (no cross-Gram correction as in dense_window_kernel) and
 // ||w||^2 is measured every window.
 // What bounds it (wall clock per window; 256 learners of d = 2048, optimistic, logistic / 16 learners of d = 32768, plain,
-// squared): the dependent rounds 11.1 / 8.2 us, the sum over the chunks' shares and the other inputs in front of them
-// 2.5 (16 chunks) / 5.4 (64), the sweep 2.2 / 6.1, shares out 0.5, start and end of a launch 2.5 - 3.  4000 rounds of the first take
-// 1.48 ms against 3.0 ms on the register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 1.1 ms against
-// 29.4 ms on dense_window_kernel.
+// squared): the dependent rounds 8.4 / 3.9 us (on one wavefront, a quad of lanes per learner, 11.1 / 8.2), the sum over the chunks'
+// shares and the other inputs in front of them 3.6 (16 chunks) / 6.9 (64), the sweep 2.2 / 5 and the loads of half of its blocks
+// behind the rounds 0.4 / 3.2, start and end of a launch 3.  4000 rounds of the first take 1.45 ms (1.48) against 3.0 ms on the
+// register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 1.07 ms (1.13) against 29.4 ms on dense_window_kernel.
 //
 // The round rows are read as they are, without the re-tiled copies of dense_window.hip: with few tiles
 // a copy would cost more than it saves.  The Gram matrices of the windows are taken by
 // split_gram_kernel, depth-split as well, from the same rows.
-#include "dense_window_common.h"
+#include "dense_chain.h"
 #include "../../include/oco.h"
 
 #include <algorithm>
@@ -33,38 +33,27 @@
 namespace oco {
 namespace {
 
-constexpr int kSW = 8;                        // wavefronts per workgroup: one runs the dependent rounds, seven sweep
-constexpr int kSweepers = kSW - 1;
-constexpr int kPre = 4;                       // blocks of 16 coordinates a sweeping wavefront fetches beside the dependent rounds
+constexpr int kSW = 8;                        // wavefronts per workgroup: all sweep, the first four run the dependent rounds before
+constexpr int kPre = 4;                       // blocks of 16 coordinates a wavefront fetches in front of (beside) the dependent rounds
 constexpr int kSplitMaxTiles = 128;           // two chunks each on 256 compute units (beyond: dense_window_kernel, two tiles per workgroup)
 constexpr int kHookRounds = 256;              // rounds whose meta work goes beside the following windows (one tile of the meta kernel; the last are on their own)
 constexpr int kShareFloats = kB * kM + kM;    // a chunk's share of W X^T, then of ||W||^2
 
 struct LdsS {
-    using G = double;
-    using S = double;
-    static constexpr int g_reads = 2;
-    static constexpr bool carry_norm = true;
-    static constexpr bool has_corr = false;
-    static constexpr int gd_bytes = kB * 4 * kGStride * 8;
-    static constexpr int tile_f = kB * kM * 4, tile_s = kB * kM * 8;
-    static constexpr int yb_bytes = tile_f, zb_bytes = tile_f, bm_bytes = tile_f, fv_bytes = kM * 4, hg_bytes = kB * 4;
     static constexpr int gd = 0;
-    static constexpr int yb = gd + gd_bytes;
-    static constexpr int zb = yb + yb_bytes;
-    static constexpr int bm = zb + zb_bytes;
-    static constexpr int fv = bm + bm_bytes;
-    static constexpr int q0 = fv + fv_bytes;
-    static constexpr int fl = q0 + tile_s;
-    static constexpr int st = fl + tile_s;
-    static constexpr int hg = st + tile_f;
-    static constexpr int n2 = hg + hg_bytes;                       // float [kSweepers][4][16]: shares of ||w||^2
-    static constexpr int corr = 0;                                 // (unused)
-    static constexpr int total = n2 + kSweepers * 4 * kM * 4;
+    static constexpr int scal = gd + kGramBytes;
+    static constexpr int yb = scal + kScalBytes;
+    static constexpr int zb = yb + kYBytes;
+    static constexpr int bm = zb + kYBytes;
+    static constexpr int fv = bm + kBmBytes;
+    static constexpr int q0 = fv + kM * 4;
+    static constexpr int rec = q0 + kQBytes;
+    static constexpr int n2 = rec + kQBytes;                       // float [kSW][4][16]: shares of ||w||^2
+    static constexpr int total = n2 + kSW * 4 * kM * 4;
     // once the dependent rounds are done the Gram table's space holds the wavefronts' shares of W X^T
     static constexpr int part = gd;
 };
-static_assert(LdsS::part + kSweepers * LdsS::tile_f <= LdsS::yb, "shares in the Gram table's space");
+static_assert(LdsS::part + kSW * kB * kM * 4 <= LdsS::scal, "shares in the Gram table's space");
 
 struct SplitArgs {
     WinPlanD plan;
@@ -100,15 +89,16 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     const int wu_s = upd ? sp.plan.start(sp.wu) : 0, wu_l = upd ? sp.plan.len(sp.wu) : 0;
     const int wq_s = do_q ? sp.plan.start(sp.wu + 1) : 0, wq_l = do_q ? sp.plan.len(sp.wu + 1) : 0;
 
-    // ---- inputs of the dependent rounds: scalars of the wavefront that runs them, the rest to LDS ----
+    // ---- inputs of the dependent rounds: scalars of the wavefronts that run them, the rest to LDS ----
     // (all loads are on their way before the first is waited for: with the scalars and the sum of ||w||^2 loaded
     // behind the barrier the rounds of 64 chunks started 3 us later)
-    double n2 = 0.0;                                                // wavefront 0, lane = 4 learner + quad lane
+    const int lc = 4 * wave + lk;                                   // wavefronts 0 .. 3, the learner whose rounds this lane runs
+    double n2 = 0.0;
     float eta = 0.f;
     Hint hint{0.f, 0.f, 0.f};
     if (upd) {
-        if (wave == 0) {
-            const int q = q_base + (lane >> 2);
+        if (wave < kNP) {
+            const int q = q_base + lc;
             if (q < nq) {
                 eta = a.eta[q % K];
                 if (OPT) {
@@ -118,10 +108,10 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
                 }
             }
         }
-        constexpr int kGPer = kB * kB / NT;                         // 8 consecutive entries of a row of G
-        f4 gv[kGPer / 4];
+        constexpr int kGPer = kB * kB / NT;                         // rows wave, wave + 8, ... of G, a column per lane
+        float gv[kGPer];
 #pragma unroll
-        for (int i = 0; i < kGPer / 4; ++i) gv[i] = *reinterpret_cast<const f4 *>(sp.gram + tid * kGPer + 4 * i);
+        for (int i = 0; i < kGPer; ++i) gv[i] = sp.gram[tid + i * NT];
         float yv[kB * kM / NT];
 #pragma unroll
         for (int i = 0; i < kB * kM / NT; ++i) {
@@ -133,7 +123,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         double s0 = 0.0, s1 = 0.0;
         auto sum_shares = [&](auto norms) __attribute__((always_inline)) {
             constexpr bool N = decltype(norms)::value;              // ||w||^2 of the stored iterates as well
-            const float *pn = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + kB * kM + (lane >> 2);
+            const float *pn = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + kB * kM + (lc & (kM - 1));
 #pragma unroll 16
             for (int c = 0; c < sp.chunks; ++c) {
                 const float2 v = *reinterpret_cast<const float2 *>(p0 + (int64_t)c * kShareFloats);
@@ -142,38 +132,57 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
                 if (N) n2 += (double)pn[(int64_t)c * kShareFloats];
             }
         };
-        if (wave == 0) sum_shares(std::true_type{});
+        if (wave < kNP) sum_shares(std::true_type{});
         else sum_shares(std::false_type{});
         double *q0d = reinterpret_cast<double *>(lds + Lds::q0);
-        q0d[tid * 2] = s0;
-        q0d[tid * 2 + 1] = s1;
+        *reinterpret_cast<d2 *>(q0d + (tid >> 3) * kQStride + 2 * (tid & 7)) = d2{s0, s1};
         double *gd = reinterpret_cast<double *>(lds + Lds::gd);
-        const int t = (tid * kGPer) >> 6, t2b = (tid * kGPer) & 63;
+        double *scal = reinterpret_cast<double *>(lds + Lds::scal);
 #pragma unroll
-        for (int i = 0; i < kGPer; ++i) {                           // masked to t2 > t, the diagonal in the rows' padding
-            const int t2 = t2b + i;
-            const float v = gv[i >> 2][i & 3];
-            gd[(t * 4 + (i & 3)) * kGStride + (t2 >> 2)] = t2 > t ? (double)v : 0.0;
-            if (t2 == t) *reinterpret_cast<float *>(gd + t * 4 * kGStride + 16) = v;
-        }
+        for (int i = 0; i < kGPer; ++i) put_gram(gd, scal, wave + kSW * i, lane, gv[i]);
         float *yb = reinterpret_cast<float *>(lds + Lds::yb);
 #pragma unroll
         for (int i = 0; i < kB * kM / NT; ++i) {
             const int e = tid + i * NT;
-            yb[(e & 63) * kM + (e >> 6)] = yv[i];
+            yb[(e >> 6) * kYStride + (e & 63)] = yv[i];
         }
-        if (OPT && tid < kB) reinterpret_cast<float *>(lds + Lds::hg)[tid] = tid < wu_l ? a.g01[wu_s + tid] : 0.f;
+        if (OPT && tid < kB) scal[2 * tid + 1] = tid < wu_l ? (double)a.g01[wu_s + tid] : 0.0;
         __syncthreads();
     }
 
-    // ---- the sweep's side: blocks b_lo + wave - 1, + kSweepers, ... --------------------------------
+    // ---- the sweep's side -----------------------------------------------------------------------
+    // Of 32 consecutive blocks the wavefronts without dependent rounds take the first sixteen, four each, which they fetch beside
+    // the rounds; the others take theirs behind them.
+    auto nth_block = [&](int i) __attribute__((always_inline)) {
+        return b_lo + (i / kPre) * (kSW * kPre) + (wave < kNP ? kPre * kNP : 0) + i % kPre * kNP + (wave & (kNP - 1));
+    };
     const int q_sw = q_base + lr;
     const bool q_ok = q_sw < nq;
     float *vrow = a.V + (int64_t)(q_ok ? q_sw : 0) * d + 4 * lk;
+    const bool whole = (!upd || wu_l == kB) && (!do_q || wq_l == kB);
     auto fetch = [&](int blk, SplitBlock &o) __attribute__((always_inline)) {
+        if (blk >= b_hi) return;                                    // uniform over the wavefront, as in step()
         const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
-        const bool in4 = blk < b_hi && blk * 16 + 4 * lk < d, in1 = blk < b_hi && blk * 16 + lr < d;
-        o.v = (in4 && q_ok) ? *reinterpret_cast<const f4 *>(vrow + blk * 16) : zero;
+        if (whole && blk * 16 + 16 <= d) {
+            // nothing to leave out: scalar bases and one offset per lane (with a condition per load a block's addresses and masks
+            // are 170 instructions, so 60; lanes without a learner read learner 0's row, see step())
+            o.v = *reinterpret_cast<const f4 *>(vrow + blk * 16);
+            if (upd) {
+                const float *x = a.x + (int64_t)wu_s * d + blk * 16;
+                const unsigned off = (unsigned)(lk * d + lr);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o.xu[i] = (x + (int64_t)(4 * i) * d)[off];
+            }
+            if (do_q) {
+                const float *x = a.x + (int64_t)wq_s * d + blk * 16;
+                const unsigned off = (unsigned)(lr * d + 4 * lk);
+#pragma unroll
+                for (int rb = 0; rb < 4; ++rb) o.xq[rb] = *reinterpret_cast<const f4 *>(x + (int64_t)(16 * rb) * d + off);
+            }
+            return;
+        }
+        const bool in4 = blk * 16 + 4 * lk < d, in1 = blk * 16 + lr < d;
+        o.v = in4 ? *reinterpret_cast<const f4 *>(vrow + blk * 16) : zero;
         if (upd) {
             const float *x = a.x + (int64_t)wu_s * d + blk * 16 + lr;
 #pragma unroll
@@ -192,20 +201,16 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         }
     };
     SplitBlock pre[kPre];
-    if (wave == 0) {
-        if (upd) {
-            const int q = q_base + (lane >> 2);
-            bool projected;
-            (void)chain_window<LOSS, Lds, OPT>(lds, 0, 0, lane, wu_l, eta, (double)a.D, 1.0, 1.0, n2, projected, &hint);
-            if (OPT && chunk == 0 && q < nq && (lane & 3) == 0) {
-                sp.ha_out[q] = hint.ha;
-                sp.hp_out[q] = hint.hp;
-            }
+    if (upd && wave < kNP) {
+        (void)chain_rounds<LOSS, Lds, OPT>(lds, 0, wave, lane, wu_l, eta, (double)a.D, 1.0, 1.0, n2, &hint);
+        const int q = q_base + lc;
+        if (OPT && chunk == 0 && q < nq && lr == 0) {
+            sp.ha_out[q] = hint.ha;
+            sp.hp_out[q] = hint.hp;
         }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kPre; ++i) fetch(b_lo + wave - 1 + kSweepers * i, pre[i]);
     }
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) fetch(nth_block(i), pre[i]);
     __syncthreads();
 
     if (upd && chunk == 0) {                                        // the window's predictions
@@ -213,16 +218,16 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         for (int e = tid; e < kM * kB; e += NT) {
             const int l = e >> 6, t = e & 63, q = q_base + l;
             if (q < nq && t < wu_l)
-                a.Z[(int64_t)(q / K) * a.zl.zs_r + (int64_t)(q % K) * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = zb[t * kM + l];
+                a.Z[(int64_t)(q / K) * a.zl.zs_r + (int64_t)(q % K) * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = zb[l * kYStride + t];
         }
     }
-    if (wave != 0) {
+    {
         float bmr[16];
         float F = 1.f;
         if (upd) {
             const float *bml = reinterpret_cast<const float *>(lds + Lds::bm);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) bmr[i] = bml[(4 * i + lk) * kM + lr];
+            for (int i = 0; i < 16; ++i) bmr[i] = bml[(4 * i + lk) * kBmStride + lr];
             F = reinterpret_cast<const float *>(lds + Lds::fv)[lr];
         } else if (q_ok) {
             F = a.sigma[q_sw];                                      // the state's lazy scale goes into the iterates
@@ -233,9 +238,9 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         float nn = 0.f;
         auto step = [&](int blk, SplitBlock &o) __attribute__((always_inline)) {
             if (blk >= b_hi) return;                                // uniform over the wavefront
-            f4 vb = o.v;
+            f4 vb;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) vb[r] *= F;
+            for (int r = 0; r < 4; ++r) vb[r] = q_ok ? o.v[r] * F : 0.f;
             if (upd) {
                 f4 vo = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -258,17 +263,17 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
             }
         };
 #pragma unroll
-        for (int i = 0; i < kPre; ++i) step(b_lo + wave - 1 + kSweepers * i, pre[i]);
-        for (int blk = b_lo + wave - 1 + kSweepers * kPre; blk < b_hi; blk += kSweepers) {
+        for (int i = 0; i < kPre; ++i) step(nth_block(i), pre[i]);
+        for (int i = kPre, blk = nth_block(i); blk < b_hi; blk = nth_block(++i)) {
             fetch(blk, pre[0]);
             step(blk, pre[0]);
         }
-        float *part = reinterpret_cast<float *>(lds + Lds::part) + (wave - 1) * kB * kM;
+        float *part = reinterpret_cast<float *>(lds + Lds::part) + wave * kB * kM;
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) part[(rb * 16 + 4 * lk + r) * kM + lr] = acc[rb][r];
-        reinterpret_cast<float *>(lds + Lds::n2)[((wave - 1) * 4 + lk) * kM + lr] = nn;
+        reinterpret_cast<float *>(lds + Lds::n2)[(wave * 4 + lk) * kM + lr] = nn;
     }
     __syncthreads();
     float *po = sp.pout + (int64_t)blockIdx.x * kShareFloats;
@@ -279,7 +284,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
             const int e = tid + u * NT;
             double sum = 0.0;
 #pragma unroll
-            for (int v = 0; v < kSweepers; ++v) sum += (double)part[v * kB * kM + e];
+            for (int v = 0; v < kSW; ++v) sum += (double)part[v * kB * kM + e];
             po[e] = (float)sum;
         }
     }
@@ -287,7 +292,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         const float *n2s = reinterpret_cast<const float *>(lds + Lds::n2) + tid;
         double sum = 0.0;
 #pragma unroll
-        for (int i = 0; i < kSweepers * 4; ++i) sum += (double)n2s[i * kM];
+        for (int i = 0; i < kSW * 4; ++i) sum += (double)n2s[i * kM];
         po[kB * kM + tid] = (float)sum;
     }
 }
@@ -404,7 +409,7 @@ bool make_split_plan(const DenseArgs &a, SplitPlan *p)
     const int nwin = (int)std::min<int64_t>(a.n_max / kB + 2, 1 << 20);
     const size_t room = dense_window_scratch_floats(a.n_max, a.d);
     p->hint_floats = (size_t)(nq + 63) / 64 * 64;
-    p->chunks = std::max(1, std::min({64, 256 / p->tiles, (nblk + kSweepers - 1) / kSweepers}));
+    p->chunks = std::max(1, std::min({64, 256 / p->tiles, (nblk + kSW - 1) / kSW}));
     if (p->chunks >= 8) p->chunks &= ~7;
     for (;; --p->chunks) {
         p->share_floats = (size_t)p->tiles * p->chunks * kShareFloats;
