@@ -44,9 +44,12 @@
  *    inside it: the same calls give the same bits, different splits agree to
  *    float32 rounding.  (By default: shared streams of d > 4096, of at least 2048
  *    learners with d >= 512, and calls of at least 512 rounds with d > 512 and
- *    at most 2048 learners: those with the coordinates split over workgroups,
- *    where splits at multiples of 64 are bit-identical if every call but the last
- *    of the horizon is that long.  With OCO_OPT_DENSE_PATH 1 a stream of d <= 4096
+ *    at most 2048 learners: those with the coordinates split over workgroups;
+ *    also calls of at least 768 rounds of narrow models, up to d = 448, or 1024 where
+ *    d is not a multiple of 4, on streams of their own (with many learners up to
+ *    d = 2048) or on a shared one with at most 2048 learners.  With these two
+ *    splits at multiples of 64 are bit-identical if every call but the last
+ *    of the horizon is that long.  With OCO_OPT_DENSE_PATH 1 a configuration of d <= 4096
  *    stays on the register kernel, and any split gives the same bits.)
  *    Sparse configurations work in segments of 4096 rounds of
  *    the horizon: splits at multiples of 4096 are bit-identical, other splits

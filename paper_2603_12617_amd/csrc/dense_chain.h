@@ -16,6 +16,17 @@ template <int SEL> __device__ __forceinline__ float row_bcast(float v)
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + SEL, 0xF, 0xF, true));
 }
 
+// sum over the lanes of a row of 16, the same in every lane (each step adds the sums of two halves of a coset)
+__device__ __forceinline__ double row_sum(double v)
+{
+    static_for<4>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int ror = 0x120 + (8 >> decltype(ic)::value);     // row_ror 8, 4, 2, 1
+        v += __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ror, 0xF, 0xF, false),
+                              __builtin_amdgcn_mov_dpp(__double2loint(v), ror, 0xF, 0xF, false));
+    });
+    return v;
+}
+
 // What the dependent rounds of a window read of its rows alone, in LDS: G[t][t2] for t2 > t, else 0, and of every round
 // ||x_t||^2 / 2 and <x_{t-1}, x_t> (optimistic update).  Lane s of the 16 lanes that share a learner reads the entries
 // t2 = 16 j + s of a row, two j at a time.
@@ -26,15 +37,16 @@ constexpr int kGramBytes = kB * kB * 8, kScalBytes = kB * 2 * 8;
 constexpr int kYStride = 68, kQStride = 18, kBmStride = 20;
 constexpr int kYBytes = kM * kYStride * 4, kQBytes = kB * kQStride * 8, kBmBytes = kB * kBmStride * 4;
 // entry (t, t2) of the Gram matrix
-__device__ __forceinline__ void put_gram(double *gd, double *scal, int t, int t2, float v)
+__device__ __forceinline__ void put_gram(double *gd, double *scal, int t, int t2, double v)
 {
-    gd[((t * (kNP / 2) + (t2 / kL >> 1)) * kL + t2 % kL) * 2 + (t2 / kL & 1)] = t2 > t ? (double)v : 0.0;
-    if (t2 == t) scal[2 * t] = 0.5 * (double)v;
+    gd[((t * (kNP / 2) + (t2 / kL >> 1)) * kL + t2 % kL) * 2 + (t2 / kL & 1)] = t2 > t ? v : 0.0;
+    if (t2 == t) scal[2 * t] = 0.5 * v;
 }
 
 // The 64 dependent rounds of window k for four learners of a tile of 16: one wavefront, 16 lanes per learner, lane s of them
 // with the pending inner products of the rounds t2 = 16 j + s.  (Four wavefronts run a tile's rounds; `part` says which this is.)
 // In: q0 such that pmul q0 = W_k X_k^T, labels, the tables above; n2 = ||w_k||^2.
+// (tab: where the two tables lie, in bytes past Lds::gd and Lds::scal.)
 // Out: predictions, -Bm, F = fscale times what is left of w_k in w_{k+1}; n2 becomes ||w_{k+1}||^2 by the scalar identity.
 //
 // Within the window an iterate is w_t = v_t / s_t, as in the register kernel: a step is linear in v,
@@ -56,17 +68,17 @@ __device__ __forceinline__ void put_gram(double *gd, double *scal, int t, int t2
 // taken back to below 2 by a power of two (exact), so that the norm stays within float64 for steps up to 2^60 times the ball.
 //
 // Straight-line code: a window shorter than 64 rounds (first / last window of a call) runs its
-// missing rounds with rows, labels and inner products of zero, which change nothing (the linear loss has a b there: it meets rows of
-// zeros only).
+// missing rounds with rows of G, labels and inner products of zero, which change nothing (the linear loss has a b there, which is
+// left out of Bm).
 template <int LOSS, class Lds, bool OPT>
 __device__ __forceinline__ double chain_rounds(char *lds, int m, int part, int lane, int wl, float eta, double D, double pmul,
-                                               double fscale, double &n2, Hint *hint)
+                                               double fscale, double &n2, Hint *hint, int tab = 0)
 {
     constexpr bool RECIP = OPT || LOSS == 2;                     // the chain needs the predictions themselves
     constexpr int L = kL, NP = kNP;
     const int lc = part * (kWave / L) + lane / L, s = lane % L;
-    const d2 *gd = reinterpret_cast<const d2 *>(lds + Lds::gd) + s;
-    const d2 *sc = reinterpret_cast<const d2 *>(lds + Lds::scal);
+    const d2 *gd = reinterpret_cast<const d2 *>(lds + Lds::gd + tab) + s;
+    const d2 *sc = reinterpret_cast<const d2 *>(lds + Lds::scal + tab);
     const double *q0d = reinterpret_cast<const double *>(lds + Lds::q0 + m * kQBytes) + s * kQStride + lc;
     double *rec = reinterpret_cast<double *>(lds + Lds::rec + m * kQBytes) + lc;          // b_t, or S_t where that gives all the rest
     const float *yb = reinterpret_cast<const float *>(lds + Lds::yb + m * kYBytes) + lc * kYStride;
@@ -211,7 +223,7 @@ __device__ __forceinline__ double chain_rounds(char *lds, int m, int part, int l
         double b;
         if (RECIP || t < made) b = rec[t * kQStride];
         else b = make_b(j);
-        bm[t * kBmStride] = -(float)(b * left);
+        bm[t * kBmStride] = t < wl ? -(float)(b * left) : 0.f;
         if (RECIP) zb[t] *= ikappa;
     }
     if (OPT) {

@@ -605,9 +605,10 @@ static hipError_t make_dense_plan(DenseArgs &a, int loss, DensePlan *out)
 hipError_t launch_dense_rounds(const DenseArgs &a0, int loss, hipStream_t s, const PieceHook *hook, bool *meta_done)
 {
     if (a0.n <= 0) return hipSuccess;
-    const bool split = dense_split_wanted(a0);
-    a0.plan->after_split = split;
+    const bool split = dense_split_wanted(a0), run = !split && dense_run_wanted(a0);
+    a0.plan->after_split = split || run;
     if (split) return launch_dense_split(a0, loss, s, hook);
+    if (run) return launch_dense_run(a0, loss, s, hook);
     if (dense_window_wanted(a0)) return launch_dense_window(a0, loss, s, hook);
     if (a0.d > 64 * kWave) return hipErrorInvalidValue;
     DenseArgs a = a0;

@@ -35,7 +35,7 @@ struct DensePlanCache {
     int wpb = 0, rt = 0, rt0 = 0;
     int64_t nwg = 0, batches = 0;
     int per_run = 0;
-    bool after_split = false;    // the call before was worked by dense_split.hip (not part of the plan: survives a change of options)
+    bool after_split = false;    // the call before was worked by dense_split.hip or dense_run.hip (not part of the plan: survives a change of options)
 };
 
 // Called after the round kernel of every piece of a call has been enqueued: rounds
@@ -131,6 +131,9 @@ hipError_t launch_dense_window(const DenseArgs &a, int loss, hipStream_t s, cons
 // the windowed path with a tile's coordinates split over workgroups (dense_split.hip)
 bool dense_split_wanted(const DenseArgs &a);
 hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
+// windows of a stream per tile of learners (dense_run.hip)
+bool dense_run_wanted(const DenseArgs &a);
+hipError_t launch_dense_run(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook);
 hipError_t launch_hint_scalars(const DenseArgs &a, hipStream_t s);
 hipError_t launch_keep_last_row(const DenseArgs &a, hipStream_t s);
 size_t dense_gram_bytes(int64_t n_max, int64_t d);

@@ -1,0 +1,130 @@
+"""Windows of 64 rounds of a stream per tile of learners (the default of calls of at least 768 rounds of streams of their own of
+narrow models or many learners, and of few learners of a narrow shared stream), against the float64 reference through the C ABI.  Tolerances as in the
+other parity tests."""
+import numpy as np
+import pytest
+
+from paper_2603_12617_amd import binding as B
+from paper_2603_12617_amd import workloads as WL
+from test_gpu_parity import _check, _gpu
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("regret", "L", "W", "p", "wbar")
+
+
+def _runs_plan(err):
+    return err.count("windows of a stream's own Gram matrices")
+
+
+# d: less than a block of 16 coordinates, whole blocks and one more coordinate; one wavefront's two blocks full (128) and exceeded;
+# the first d of instances with more blocks (272, 528) and rows of any length up to the last that few learners come here with.  K: a wavefront of the rounds full or not, a tile full, two, three and
+# five tiles.  Streams shared and not; horizons that end within a window.
+CASES = [
+    ("c2", dict(T=780, R=3, d=1, K=2)),
+    ("c2", dict(T=833, R=2, d=15, K=5)),
+    ("c2", dict(T=832, R=2, d=16, K=16)),
+    ("c2", dict(T=790, R=3, d=17, K=17)),
+    ("c2", dict(T=1100, R=2, d=100, K=15)),
+    ("c2", dict(T=769, R=2, d=127, K=4)),
+    ("c2", dict(T=768, R=2, d=143, K=33)),
+    ("c2", dict(T=800, R=2, d=144, K=3)),
+    ("c2", dict(T=771, R=2, d=271, K=3)),
+    ("c2", dict(T=771, R=2, d=272, K=64)),
+    ("c2", dict(T=780, R=2, d=529, K=4)),
+    ("c2", dict(T=771, R=2, d=777, K=5)),
+    ("c2", dict(T=769, R=2, d=448, K=3)),
+    ("c2", dict(T=769, R=1, d=1023, K=2)),
+    ("c1", dict(T=1000, R=1, d=10, K=1)),
+    ("c1", dict(T=800, R=3, d=64, K=1, x_shared=False)),
+    ("c3", dict(T=810, R=5, d=130, K=7, seg_len=90)),              # a shared stream, tiles of several runs' learners
+    ("c3", dict(T=790, R=2, d=448, K=16, seg_len=1)),
+    ("c4", dict(T=800, R=2, d=100, K=6, x_shared=False, eta=(0.01, 0.1, 1.0, 10.0, 100.0, 1000.0))),
+]
+
+
+@pytest.mark.parametrize("name,over", CASES)
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_windows_of_a_stream_match_the_oracle(name, over, optimistic, capfd):
+    wl = WL.make(name, optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    print("case run", name, over, "optimistic", optimistic, flush=True)
+    capfd.readouterr()
+    got = _gpu(wl, data, options=dict(verbose=1))
+    assert _runs_plan(capfd.readouterr().err) == 1
+    _check(wl, data, got, label="run %s %s optimistic=%d" % (name, over, optimistic))
+    again = _gpu(wl, data)
+    for k in KEYS:
+        assert np.array_equal(got[k], again[k]), k
+
+
+# the instance with the most blocks is for many learners: its first d and its last
+@pytest.mark.parametrize("d,optimistic", [(1057, 1), (2048, 0)])
+def test_windows_of_a_stream_of_wide_models_of_many_learners(d, optimistic, capfd):
+    wl = WL.make("c2", T=768, R=64, d=d, K=64, optimistic=optimistic)
+    data = WL.generate(wl)
+    capfd.readouterr()
+    got = _gpu(wl, data, options=dict(verbose=1))
+    assert _runs_plan(capfd.readouterr().err) == 1
+    _check(wl, data, got, runs=[0, 31, 63], label="run many learners d=%d" % d)
+
+
+@pytest.mark.parametrize("loss", ["linear", "squared", "logistic"])
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_cuts_at_windows_give_the_same_bits_and_others_the_same_results(loss, optimistic):
+    """Calls of at least 768 rounds, the horizon's last as short as it comes; cuts inside a window regroup float32 sums."""
+    wl = WL.make("c3", T=1700, R=3, d=83, K=18, x_shared=False, seg_len=0 if loss == "linear" else 400, loss=loss, optimistic=optimistic)
+    data = WL.generate(wl)
+    whole = _gpu(wl, data)
+    _check(wl, data, whole, label="run whole %s" % loss)
+    for c in (768, 832, 1024):
+        got = _gpu(wl, data, chunk=c)
+        for k in KEYS:
+            assert np.array_equal(got[k], whole[k]), (k, c)
+    got = _gpu(wl, data, chunk=801)
+    _check(wl, data, got, label="run chunk 801")
+    for k in KEYS:
+        np.testing.assert_allclose(got[k], whole[k], rtol=0, atol=2e-6 * max(1.0, float(np.abs(whole[k]).max())), err_msg=k)
+
+
+@pytest.mark.parametrize("optimistic", [0, 1, 2])
+def test_a_state_changes_between_windows_and_the_register_kernel(optimistic, capfd):
+    wl = WL.make("c2", T=2000, R=2, d=90, K=6, optimistic=optimistic, eta=(0.01, 0.1, 1.0, 10.0, 100.0, 1000.0))
+    data = WL.generate(wl)
+    sim = B.Simulation(wl, data, options=dict(verbose=1))
+    capfd.readouterr()
+    for t0, n in ((0, 100), (100, 800), (900, 70), (970, 768), (1738, 262)):
+        sim.run(t0, n)
+    assert _runs_plan(capfd.readouterr().err) == 3               # the two long calls and the horizon's last behind one of them
+    got = dict(regret=sim.regret(), L=sim.cum_losses())
+    got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+    sim.close()
+    _check(wl, data, got, label="run and register optimistic=%d" % optimistic)
+
+
+@pytest.mark.parametrize("d", [33, 100])
+def test_rows_at_any_address_give_the_same_bits(d):
+    wl = WL.make("c2", T=790, R=2, d=d, K=5)
+    data = WL.generate(wl)
+    out = []
+    for shift in (0, 1, 3):
+        sim = B.Simulation(wl, data)
+        flat = sim.torch.zeros(sim.x.numel() + 4, dtype=sim.torch.float32, device=sim.dev)
+        flat[shift:shift + sim.x.numel()] = sim.x.reshape(-1)
+        B.oco_run_rounds(sim.h, 0, wl.T, x_ptr=flat.data_ptr() + 4 * shift, x_run_stride=wl.T * d, y=sim.y)
+        out.append(dict(regret=sim.regret(), W=sim.state()[0].cpu().numpy()))
+        sim.close()
+    for got in out[1:]:
+        for k in got:
+            assert np.array_equal(got[k], out[0][k]), k
+
+
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_steps_far_larger_than_the_ball_and_a_tiny_radius(optimistic):
+    """The scale of an iterate grows by up to 2^31 per round and is taken back every eight rounds."""
+    wl = WL.make("c2", T=790, R=2, d=20, K=3, eta=(1e4, 1e6, 3.0), D=1e-3, optimistic=optimistic)
+    data = WL.generate(wl)
+    _check(wl, data, _gpu(wl, data), label="run huge eta optimistic=%d" % optimistic)
+    wl = WL.make("c4", T=800, R=2, d=64, K=4, x_shared=False, eta=(1e-3, 1.0, 1e3, 1e8), optimistic=optimistic)
+    data = WL.generate(wl)
+    _check(wl, data, _gpu(wl, data), label="run logistic huge eta optimistic=%d" % optimistic)
