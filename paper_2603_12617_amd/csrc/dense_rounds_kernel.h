@@ -200,23 +200,26 @@ constexpr int kWholeRounds = 64;
 // LDS words behind the ring: ||x_t||^2, then <x_{t-1}, x_t>
 constexpr int kWholeFloats = 2 * kWholeRounds;
 
+// What wavefront 0 keeps for the meta work: the run's cumulative and last losses (a learner per lane) and its regret, loaded with
+// everything else the kernel starts from.
+struct WholeState { double L = 0.0, last = 0.0, regret = 0.0; };
+
 // The meta kernel's work on run r for the n rounds of a short call: called by all wavefronts (wavefront i holds the
-// predictions of learner i, i = K the comparator, a round per lane; those behind only help) once the ring's space is free.
+// predictions of learner i, i = K the comparator, a round per lane, and the labels; those behind only help) once the ring's space is free.
 template <int LOSS>
-__device__ __forceinline__ void whole_meta(const DenseArgs &a, float *ring, int r, int i, int lane, float zreg)
+__device__ __forceinline__ void whole_meta(const DenseArgs &a, float *ring, int r, int i, int lane, float zreg, float yreg, const WholeState &st)
 {
     const int K = a.K, n = a.n;
     float *zs = ring;                                               // [K + 1][64]
     double *lm = reinterpret_cast<double *>(ring + (K + 1) * 64);   // [n][K]: losses, then cumulative losses before the round
     double *diff = lm + 64 * K;
-    const float *yrow = a.y ? a.y + (int64_t)r * a.y_run_stride : nullptr;
-    const double yt = (yrow && lane < n) ? (double)yrow[lane] : 0.0;
+    const double yt = (double)yreg;
     if (i <= K) zs[i * 64 + lane] = zreg;
     if (i < K && lane < n) lm[lane * K + i] = phi<LOSS>((double)zreg, yt);
     __syncthreads();
     const bool hint = a.last != nullptr;
     if (i == 0 && lane < K) {                                       // running sums in round order
-        double Lacc = a.L[(int64_t)r * K + lane], lprev = hint ? a.last[(int64_t)r * K + lane] : 0.0;
+        double Lacc = st.L, lprev = st.last;
         for (int t = 0; t < n; ++t) {
             const double l = lm[t * K + lane];
             lm[t * K + lane] = hint ? Lacc + lprev : Lacc;
@@ -240,7 +243,7 @@ __device__ __forceinline__ void whole_meta(const DenseArgs &a, float *ring, int 
     }
     __syncthreads();
     if (i == 0 && lane == 0) {
-        double reg = a.regret[r];
+        double reg = st.regret;
         for (int t = 0; t < n; ++t) reg += diff[t];
         a.regret[r] = reg;
     }
@@ -320,13 +323,55 @@ dense_rounds_kernel(const DenseArgs a)
         }
     };
 
-    // padding coordinates (j >= d) of the ring are never written again: zero them once
+    // padding coordinates (j >= d) of the ring are never written again: zero them once (rows past the call may hold anything: what is
+    // made of them is not used)
     const int ntiles = (n + RT - 1) / RT;
-    for (int e = tid; e < min(kRing, ntiles + 1) * TILE / 4; e += nthreads) smem4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-    tile_sync();
     issue_tile(0);
     if (ntiles > 1) issue_tile(1);
+    {
+        const int rows = min(kRing, ntiles + 1) * RT, rpi = nthreads >= DP ? nthreads / DP : 1;
+        for (int row = tid / DP; row < rows && tid / DP < rpi; row += rpi)
+            for (int j = d + tid % DP; j < DP; j += nthreads >= DP ? DP : nthreads) ring[row * DP + j] = 0.f;
+    }
     float *whole_x2 = ring + kRing * TILE;
+    // A short call is mostly latencies of loads, one behind the other: everything it starts from is on its way before the first barrier.
+    // (With that, the last row kept beside the rounds and the ring cleared only where rows do not write it, a call of 8 optimistic rounds of 3
+    // learners, d = 1000, is 11.1 us of this kernel, 13.3 before; 64 of them with the model read back after each 1084 -> 881 us.)
+    // (The vector itself not beyond 2048 coordinates: there it would be spilled.)
+    constexpr bool PRE = WHOLE && !kOneRowSet<NPL>;
+    float first[PRE ? NV : 1][VW];              // V row of a learner, u of the comparator
+    float sigma0 = 0.f, eta0 = 0.f, ha0 = 0.f, hp0 = 0.f, x2last0 = 0.f, y0 = 0.f;
+    double n20 = 0.0;
+    WholeState ws;
+    int seg0 = 0;
+    if (WHOLE && active) {
+        const float *src;
+        if (is_cmp) {
+            while (seg0 + 1 < a.S && a.seg_start[seg0 + 1] <= a.t0) ++seg0;
+            src = a.u + ((int64_t)r * a.S + seg0) * d;
+        } else {
+            const int64_t q = (int64_t)r * K + i;
+            src = a.V + q * d;
+            sigma0 = a.sigma[q];
+            n20 = a.n2[q];
+            eta0 = a.eta[i];
+            if (OPT) { ha0 = a.ha[q]; hp0 = a.hp[q]; x2last0 = a.x2last[a.x_shared ? 0 : r]; }
+            if (a.y && lane < n) y0 = a.y[(int64_t)r * a.y_run_stride + lane];
+            if (i == 0) {
+                if (lane < K) { ws.L = a.L[q + lane]; if (a.last) ws.last = a.last[q + lane]; }
+                if (lane == 0) ws.regret = a.regret[r];
+            }
+        }
+        if constexpr (PRE) {
+#pragma unroll
+            for (int m = 0; m < NV; ++m)
+#pragma unroll
+                for (int e = 0; e < VW; ++e) {
+                    const int j = (m * kWave + lane) * VW + e;
+                    first[m][e] = j < d ? src[j] : 0.f;
+                }
+        }
+    }
     if (WHOLE) {
         for (int t = wave; t < n; t += wpb) {
             const float *src = xg + (int64_t)t * d;
@@ -336,6 +381,13 @@ dense_rounds_kernel(const DenseArgs a)
         }
     }
     tile_sync();
+    // The last row, for the next call's hint (the only workgroup that read the old one, before the barrier; the launcher does not send a
+    // shared stream of several runs here): by the first wavefront without a task, beside the last tile's rounds, if there is one.
+    auto keep_last_row = [&]() {
+        const int64_t rr = a.x_shared ? 0 : r;
+        for (int j = lane; j < d; j += kWave) a.xlast[rr * d + j] = xg[(int64_t)(n - 1) * d + j];
+        if (lane == 0) a.x2last[rr] = whole_x2[n - 1];
+    };
 
     const V *row0 = reinterpret_cast<const V *>(ring);
     const float *yrow = a.y ? a.y + (int64_t)r * a.y_run_stride : nullptr;
@@ -345,9 +397,10 @@ dense_rounds_kernel(const DenseArgs a)
     if (!active) {
         for (int k = 0; k < ntiles; ++k) {
             if (k + 2 < ntiles) issue_tile(k + 2);
+            if (WHOLE && OPT && k + 1 == ntiles && i == a.per_run) keep_last_row();
             tile_sync();
         }
-        if (WHOLE) whole_meta<LOSS>(a, ring, r, i, lane, 0.f);
+        if (WHOLE) whole_meta<LOSS>(a, ring, r, i, lane, 0.f, 0.f, ws);
         return;
     }
 
@@ -378,10 +431,18 @@ dense_rounds_kernel(const DenseArgs a)
             }
             return wave_sum(combine<VW>(acc));
         };
-        int seg = 0;
-        while (seg + 1 < a.S && a.seg_start[seg + 1] <= a.t0) ++seg;
+        int seg = seg0;
+        if (!WHOLE)
+            while (seg + 1 < a.S && a.seg_start[seg + 1] <= a.t0) ++seg;
         int64_t next_seg = seg + 1 < a.S ? a.seg_start[seg + 1] : INT64_MAX;   // absolute round
-        load_u(seg);
+        if constexpr (PRE) {
+#pragma unroll
+            for (int m = 0; m < NV; ++m)
+#pragma unroll
+                for (int e = 0; e < VW; ++e) uv[m][e] = first[m][e];
+        } else {
+            load_u(seg);
+        }
         float z = dot_u(row0), zreg = 0.f;
         float *zrow = a.Z + (int64_t)r * a.zl.zs_r + (int64_t)K * a.zl.zs_i;
         for (int k = 0; k < ntiles; ++k) {
@@ -405,7 +466,7 @@ dense_rounds_kernel(const DenseArgs a)
             }
             tile_sync();
         }
-        if (WHOLE) whole_meta<LOSS>(a, ring, r, i, lane, zreg);
+        if (WHOLE) whole_meta<LOSS>(a, ring, r, i, lane, zreg, 0.f, ws);
         return;
     }
 
@@ -417,16 +478,16 @@ dense_rounds_kernel(const DenseArgs a)
     };
     float wv[NV][VW];           // v = iterate / sigma
     float xa[NV][VW], xb[NV][VW];   // x_t / x_{t+1}, swapping roles every round
-    float sigma = a.sigma[(int64_t)r * K + i];
-    float n2 = (float)a.n2[(int64_t)r * K + i];  // ||v||^2 (kept as float64 in the state)
-    const float eta = a.eta[i];
+    float sigma = WHOLE ? sigma0 : a.sigma[(int64_t)r * K + i];
+    float n2 = (float)(WHOLE ? n20 : a.n2[(int64_t)r * K + i]);  // ||v||^2 (kept as float64 in the state)
+    const float eta = WHOLE ? eta0 : a.eta[i];
     float qv, z, zreg = 0.f, yreg = 0.f, x2reg = 0.f;   // qv = <v, x_t>, z = sigma qv
     // optimistic update: the hint is ha * x_{t-1}; hp = <w^_t, x_{t-1}>; g01 = <x_{t-1}, x_t>
     float ha = 0.f, hp = 0.f, x2prev = 0.f, g01reg = 0.f;
     if (OPT) {
-        ha = a.ha[(int64_t)r * K + i];
-        hp = a.hp[(int64_t)r * K + i];
-        x2prev = a.x2last[a.x_shared ? 0 : r];
+        ha = WHOLE ? ha0 : a.ha[(int64_t)r * K + i];
+        hp = WHOLE ? hp0 : a.hp[(int64_t)r * K + i];
+        x2prev = WHOLE ? x2last0 : a.x2last[a.x_shared ? 0 : r];
     }
     {
         const float *src = a.V + ((int64_t)r * K + i) * d;
@@ -439,7 +500,7 @@ dense_rounds_kernel(const DenseArgs a)
 #pragma unroll
             for (int e = 0; e < VW; ++e) {
                 const int j = (m * kWave + lane) * VW + e;
-                wv[m][e] = j < d ? src[j] : 0.f;
+                wv[m][e] = PRE ? first[PRE ? m : 0][e] : j < d ? src[j] : 0.f;
                 acc[e & (NACC - 1)] = fmaf(wv[m][e], xa[m][e], acc[e & (NACC - 1)]);   // same order as the passes
                 xb[m][e] = 0.f;
             }
@@ -539,12 +600,13 @@ dense_rounds_kernel(const DenseArgs a)
     // predictions of the rounds (t & ~63) .. t to Z: both happen at tile boundaries only (a tile's length divides
     // 64), so the tile loop does them and a round does not test for them.
     auto load_round_scalars = [&](int t) {
-        if (yrow) yreg = (t + lane < n) ? yrow[t + lane] : 0.f;
         if (WHOLE) {
+            yreg = y0;
             x2reg = (lane < n) ? whole_x2[lane] : 0.f;
             if (OPT) g01reg = (lane < n) ? whole_x2[kWholeRounds + lane] : 0.f;
             return;
         }
+        if (yrow) yreg = (t + lane < n) ? yrow[t + lane] : 0.f;
         x2reg = (t + lane < n) ? x2row[t + lane] : 0.f;
         if (OPT) g01reg = (t + lane < n) ? g01row[t + lane] : 0.f;
     };
@@ -657,14 +719,8 @@ dense_rounds_kernel(const DenseArgs a)
         if (OPT && lane == 0) { a.ha[(int64_t)r * K + i] = ha; a.hp[(int64_t)r * K + i] = hp; }
     }
     if (WHOLE) {
-        whole_meta<LOSS>(a, ring, r, i, lane, zreg);
-        // the last row, for the next call's hint (the only workgroup that read the old one; the launcher does not
-        // send a shared stream of several runs here)
-        if (OPT && i == 0) {
-            const int64_t rr = a.x_shared ? 0 : r;
-            for (int j = lane; j < d; j += kWave) a.xlast[rr * d + j] = xg[(int64_t)(n - 1) * d + j];
-            if (lane == 0) a.x2last[rr] = whole_x2[n - 1];
-        }
+        whole_meta<LOSS>(a, ring, r, i, lane, zreg, yreg, ws);
+        if (OPT && i == 0 && wpb == a.per_run) keep_last_row();
     }
 }
 

@@ -112,54 +112,78 @@ __global__ void __launch_bounds__(256) meta_kernel(const MetaArgs a)
     if (j == 0) a.regret[r] = reg;
 }
 
-// p = softmax(-eps L) of one run, into shared memory (first K threads)
-// (last: the meta learner's hint, the last observed losses, or null)
-__device__ void hedge_weights(const double *L, const double *last, int K, double eps, double *p_sh)
-{
-    if (threadIdx.x == 0) {
-        double Lmin = L[0] + (last ? last[0] : 0.0);
-        for (int i = 1; i < K; ++i) Lmin = fmin(Lmin, L[i] + (last ? last[i] : 0.0));
-        double S = 0.0;
-        for (int i = 0; i < K; ++i) { p_sh[i] = exp(-eps * (L[i] + (last ? last[i] : 0.0) - Lmin)); S += p_sh[i]; }
-        for (int i = 0; i < K; ++i) p_sh[i] /= S;
-    }
-    __syncthreads();
-}
-
 // dense layout: V[R][K][d], sigma float [R][K].  Optimistic mode: V holds the intermediate
 // model and the iterate handed out is the one played next, Proj[sigma V - ha x_last] (Eq. (3)).
+// With few coordinates and learners it is latencies of loads: all are on their way before the first is waited for (the vectors of the
+// first kExpAhead learners, beyond that as many at a time), and the weights' exponentials are a thread each.
+constexpr int kExpAhead = 8;
 __global__ void __launch_bounds__(256) export_dense_kernel(const ExportArgs a)
 {
-    __shared__ double p_sh[64];
+    __shared__ double l_sh[64], e_sh[64], p_sh[64];
     __shared__ float s_sh[64], h_sh[64], f_sh[64];
     const int r = blockIdx.y;
-    const int K = a.K;
-    hedge_weights(a.L + (int64_t)r * K, a.last ? a.last + (int64_t)r * K : nullptr, K, a.eps, p_sh);
-    if (threadIdx.x < K) {
-        const int64_t q = (int64_t)r * K + threadIdx.x;
-        const float sg = static_cast<const float *>(a.sigma)[q];
-        float ha = 0.f, f = 1.f;
+    const int K = a.K, i0 = threadIdx.x;
+    const int64_t q = (int64_t)r * K + i0;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool vec = j < a.d && (a.W || a.wbar);
+    const float *v = a.V + (int64_t)r * K * a.d + (vec ? j : 0);
+    float ahead[kExpAhead], xl = 0.f;
+    double L = 0.0, hp = 0.0, n2 = 0.0, x2l = 0.0;
+    float sg = 0.f, ha = 0.f;
+    if (i0 < K) {
+        L = a.L[q] + (a.last ? a.last[q] : 0.0);                  // (last: the meta learner's hint, the last observed losses)
+        sg = static_cast<const float *>(a.sigma)[q];
         if (a.optimistic) {
             ha = a.ha[q];
-            const double x2l = (double)a.x2last[a.x_shared ? 0 : r];
-            const double m = fma((double)ha * (double)ha, x2l,
-                                 fma(-2.0 * (double)ha, (double)a.hp[q], (double)sg * (double)sg * a.n2[q]));
+            hp = (double)a.hp[q];
+            n2 = a.n2[q];
+            x2l = (double)a.x2last[a.x_shared ? 0 : r];
+        }
+    }
+    if (vec) {
+        if (a.optimistic) xl = a.xlast[(a.x_shared ? 0 : (int64_t)r * a.d) + j];
+#pragma unroll
+        for (int i = 0; i < kExpAhead; ++i) ahead[i] = i < K ? v[(int64_t)i * a.d] : 0.f;
+    }
+    if (i0 < K) l_sh[i0] = L;
+    __syncthreads();
+    if (i0 < K) {                                                  // p = softmax(-eps L), the sum in learner order
+        double Lmin = l_sh[0];
+        for (int i = 1; i < K; ++i) Lmin = fmin(Lmin, l_sh[i]);
+        e_sh[i0] = exp(-a.eps * (L - Lmin));
+        float f = 1.f;
+        if (a.optimistic) {
+            const double m = fma((double)ha * (double)ha, x2l, fma(-2.0 * (double)ha, hp, (double)sg * (double)sg * n2));
             const float mf = (float)m;
             if (mf > a.D * a.D) f = a.D * __builtin_amdgcn_rsqf(mf);
         }
-        s_sh[threadIdx.x] = sg; h_sh[threadIdx.x] = ha; f_sh[threadIdx.x] = f;
+        s_sh[i0] = sg; h_sh[i0] = ha; f_sh[i0] = f;
     }
     __syncthreads();
-    if (a.p && blockIdx.x == 0 && threadIdx.x < K) a.p[(int64_t)r * K + threadIdx.x] = (float)p_sh[threadIdx.x];
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= a.d) return;
-    const float xl = a.optimistic ? a.xlast[(a.x_shared ? 0 : (int64_t)r * a.d) + j] : 0.f;
+    if (i0 < K) {
+        double S = 0.0;
+        for (int i = 0; i < K; ++i) S += e_sh[i];
+        const double p = e_sh[i0] / S;
+        p_sh[i0] = p;
+        if (a.p && blockIdx.x == 0) a.p[q] = (float)p;
+    }
+    __syncthreads();
+    if (!vec) return;
     double acc = 0.0;
-    for (int i = 0; i < K; ++i) {
-        float w = s_sh[i] * a.V[((int64_t)r * K + i) * a.d + j];
-        if (a.optimistic) w = f_sh[i] * fmaf(-h_sh[i], xl, w);
-        if (a.W) a.W[((int64_t)r * K + i) * a.d + j] = w;
-        acc += p_sh[i] * (double)w;
+    for (int ib = 0; ib < K; ib += kExpAhead) {
+        if (ib > 0) {
+#pragma unroll
+            for (int i = 0; i < kExpAhead; ++i) ahead[i] = ib + i < K ? v[(int64_t)(ib + i) * a.d] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kExpAhead; ++u) {
+            const int i = ib + u;
+            if (i >= K) break;
+            float w = s_sh[i] * ahead[u];
+            if (a.optimistic) w = f_sh[i] * fmaf(-h_sh[i], xl, w);
+            if (a.W) a.W[((int64_t)r * K + i) * a.d + j] = w;
+            acc += p_sh[i] * (double)w;
+        }
     }
     if (a.wbar) a.wbar[(int64_t)r * a.d + j] = (float)acc;
 }
