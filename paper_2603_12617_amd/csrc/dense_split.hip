@@ -55,11 +55,15 @@ struct LdsS {
 };
 static_assert(LdsS::part + kSW * kB * kM * 4 <= LdsS::scal, "shares in the Gram table's space");
 
+// where the comparators' predictions of a window lie in its Gram matrix, below the diagonal: four blocks of 16 rounds of up to 16 runs
+__device__ __forceinline__ int cmp_at(int run, int t) { return ((t < 16 ? 2 : 3) * 16 + run) * kB + (t < 16 ? t : t - 16); }
+
 struct SplitArgs {
     WinPlanD plan;
     int wu;                  // window whose rounds and step this launch works; -1: none (the call's first launch)
     int chunks;              // workgroups per tile
     const float *gram;       // of window wu
+    int cmp;                 // ... with the comparators' predictions in it
     const float *pin;        // shares of W X_wu^T and ||W||^2, [tile][chunk][kShareFloats]
     float *pout;             // ... of W X_{wu+1}^T
     const float *ha_in, *hp_in;   // [R K]: the hint scalars before window wu
@@ -213,6 +217,12 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     for (int i = 0; i < kPre; ++i) fetch(nth_block(i), pre[i]);
     __syncthreads();
 
+    if (upd && sp.cmp && blockIdx.x == 0) {                         // the comparators' predictions of the window
+        for (int e = tid; e < a.R * kB; e += NT) {
+            const int r = e >> 6, t = e & 63;
+            if (t < wu_l) a.Z[(int64_t)r * a.zl.zs_r + (int64_t)K * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = sp.gram[cmp_at(r, t)];
+        }
+    }
     if (upd && chunk == 0) {                                        // the window's predictions
         const float *zb = reinterpret_cast<const float *>(lds + Lds::zb);
         for (int e = tid; e < kM * kB; e += NT) {
@@ -313,7 +323,10 @@ __global__ void __launch_bounds__(64) split_finish_kernel(const DenseArgs a, int
 
 // G = X_w X_w^T of window w0 + blockIdx.x over the depth blocks of chunk blockIdx.y, out[(window gridDim.y +
 // chunk) 4096].  The dependent rounds of a window read G[t][t2] for t2 >= t only: of the sixteen 16 x 16 blocks
-// the ten on and above the diagonal are taken, dealt to the four wavefronts, the others are left unwritten.
+// the ten on and above the diagonal are taken, dealt to the four wavefronts, the others are left unwritten -- but for four that, with at
+// most sixteen runs and one comparator segment, hold the comparators' predictions U X_w^T of the chunk (CMP; cmp_at), a block per wavefront
+// from the rows it has anyway.  (In a kernel of their own they read the stream once more: 2000 rounds of d = 32768 and 4 runs 142 us beside the
+// 99 of this kernel, before the first window, which waits for both; so 120.)
 // Every wavefront reads the 64 rows (from L1 for three of the four), three depth blocks ahead of its matrix instructions.
 // The sums of a depth block (16 products) are added up in float64: as one float32 chain over a chunk's depth (270 products
 // at d = 516) their error was that of ||x||^2 in every projection, and the iterates of large steps had up to three times the
@@ -321,25 +334,29 @@ __global__ void __launch_bounds__(64) split_finish_kernel(const DenseArgs a, int
 constexpr int kGramBlocks[4] = {3, 3, 2, 2};                        // of a wavefront, and where they lie
 constexpr int kGramRow[4][3] = {{0, 0, 0}, {1, 1, 1}, {2, 0, 0}, {3, 2, 0}};
 constexpr int kGramCol[4][3] = {{0, 1, 2}, {1, 2, 3}, {2, 3, 0}, {3, 3, 0}};
-__global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, WinPlanD plan, int w0, float *out)
+template <bool CMP>
+__global__ void __launch_bounds__(256) split_gram_kernel(const float *x, const float *u, int runs, int d, WinPlanD plan, int w0, float *out)
 {
     const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int w = w0 + (int)blockIdx.x, nblk = (d + 15) / 16;
     const int ws = plan.start(w), wl = plan.len(w);
     const int b_lo = (int)((int64_t)blockIdx.y * nblk / gridDim.y), b_hi = (int)((int64_t)(blockIdx.y + 1) * nblk / gridDim.y);
-    const float *xr = x + (int64_t)ws * d + 4 * lk;
-    auto fetch = [&](int blk, f4 (&o)[4]) __attribute__((always_inline)) {
+    const float *xr = x + (int64_t)ws * d + 4 * lk, *ur = u + (int64_t)(lr < runs ? lr : 0) * d + 4 * lk;
+    struct Rows { f4 v[4], u; };
+    auto fetch = [&](int blk, Rows &o) __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int t = 16 * b + lr;
             const bool ok = t < wl && blk < b_hi && blk * 16 + 4 * lk < d;
-            o[b] = ok ? *reinterpret_cast<const f4 *>(xr + (int64_t)t * d + blk * 16) : f4{0.f, 0.f, 0.f, 0.f};
+            o.v[b] = ok ? *reinterpret_cast<const f4 *>(xr + (int64_t)t * d + blk * 16) : f4{0.f, 0.f, 0.f, 0.f};
         }
+        if (CMP) o.u = (lr < runs && blk < b_hi && blk * 16 + 4 * lk < d) ? *reinterpret_cast<const f4 *>(ur + blk * 16) : f4{0.f, 0.f, 0.f, 0.f};
     };
     auto blocks = [&](auto wc) __attribute__((always_inline)) {
-        constexpr int W = decltype(wc)::value, N = kGramBlocks[W];
-        f4 acc[N], o[4][4];
+        constexpr int W = decltype(wc)::value, NG = kGramBlocks[W], N = NG + (CMP ? 1 : 0);
+        f4 acc[N];
+        Rows o[4];
         double tot[N][4];
 #pragma unroll
         for (int b = 0; b < N; ++b)
@@ -355,10 +372,11 @@ __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, 
                 for (int b = 0; b < N; ++b) acc[b] = f4{0.f, 0.f, 0.f, 0.f};
                 static_for<4>([&](auto rc) __attribute__((always_inline)) {
                     constexpr int r = decltype(rc)::value;
-                    static_for<N>([&](auto bc) __attribute__((always_inline)) {
+                    static_for<NG>([&](auto bc) __attribute__((always_inline)) {
                         constexpr int b = decltype(bc)::value, ra = kGramRow[W][b], cb = kGramCol[W][b];
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[i][ra][r], o[i][cb][r], acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[i].v[ra][r], o[i].v[cb][r], acc[b], 0, 0, 0);
                     });
+                    if (CMP) acc[N - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(o[i].u[r], o[i].v[W][r], acc[N - 1], 0, 0, 0);
                 });
 #pragma unroll
                 for (int b = 0; b < N; ++b)
@@ -367,11 +385,15 @@ __global__ void __launch_bounds__(256) split_gram_kernel(const float *x, int d, 
             });
         }
         float *g = out + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * kB * kB;
-        static_for<N>([&](auto bc) __attribute__((always_inline)) {
+        static_for<NG>([&](auto bc) __attribute__((always_inline)) {
             constexpr int b = decltype(bc)::value, ra = kGramRow[W][b], cb = kGramCol[W][b];
 #pragma unroll
             for (int r = 0; r < 4; ++r) g[(ra * 16 + 4 * lk + r) * kB + cb * 16 + lr] = (float)tot[b][r];
         });
+        if (CMP) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) g[cmp_at(4 * lk + r, 16 * W + lr)] = (float)tot[N - 1][r];
+        }
     };
     if (wave == 0) blocks(std::integral_constant<int, 0>{});
     else if (wave == 1) blocks(std::integral_constant<int, 1>{});
@@ -472,8 +494,9 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
     g.d = a.d; g.K = a.K; g.R = a.R; g.t0 = a.t0; g.n = a.n; g.vec_ok = a.vec_ok;
     g.chunks = p.cmp_chunks; g.part = a.gram + p.cmp_off; g.fine = true;
     hipStream_t cs = s;
+    const bool cmp = a.R <= 16 && a.S == 1;                         // the comparators' predictions come with the Gram matrices
     hipError_t e = beside ? hook->beside(hook->ctx, &cs) : hipSuccess;   // only the meta kernel reads its output
-    if (e == hipSuccess) e = launch_comparator_gemm(g, cs);
+    if (e == hipSuccess && !cmp) e = launch_comparator_gemm(g, cs);
     if (e == hipSuccess && a.optimistic) e = launch_hint_scalars(a, s);
     if (e != hipSuccess) return e;
     void (*kern)(const DenseArgs, const SplitArgs) = nullptr;
@@ -497,12 +520,13 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
         if (w >= 0 && in_group == 0) {
             const int nw = std::min(p.group, nwin - w);
             float *to = p.gram_chunks > 1 ? gpart : gram;
-            hipLaunchKernelGGL(split_gram_kernel, dim3((unsigned)nw, (unsigned)p.gram_chunks), dim3(256), 0, s, a.x, a.d, plan, w, to);
+            if (cmp) hipLaunchKernelGGL(split_gram_kernel<true>, dim3((unsigned)nw, (unsigned)p.gram_chunks), dim3(256), 0, s, a.x, a.u, a.R, a.d, plan, w, to);
+            else hipLaunchKernelGGL(split_gram_kernel<false>, dim3((unsigned)nw, (unsigned)p.gram_chunks), dim3(256), 0, s, a.x, a.x, 0, a.d, plan, w, to);
             if (p.gram_chunks > 1)
                 hipLaunchKernelGGL(split_gram_sum_kernel, dim3((unsigned)nw * 16), dim3(256), 0, s, gpart, p.gram_chunks, gram);
         }
         SplitArgs sp{};
-        sp.plan = plan; sp.wu = w; sp.chunks = p.chunks;
+        sp.plan = plan; sp.wu = w; sp.chunks = p.chunks; sp.cmp = cmp;
         sp.gram = gram + (size_t)in_group * kB * kB;
         sp.pin = share[w & 1]; sp.pout = share[(w + 1) & 1];
         float *hin = hint0 + (size_t)(w & 1) * 2 * p.hint_floats, *hout = hint0 + (size_t)((w + 1) & 1) * 2 * p.hint_floats;
