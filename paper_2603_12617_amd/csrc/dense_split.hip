@@ -17,9 +17,12 @@
 // ||w||^2 is measured every window.
 // What bounds it (wall clock per window; 256 learners of d = 2048, optimistic, logistic / 16 learners of d = 32768, plain,
 // squared): the dependent rounds 8.4 / 3.9 us (on one wavefront, a quad of lanes per learner, 11.1 / 8.2), the sum over the chunks'
-// shares and the other inputs in front of them 3.6 (16 chunks) / 6.9 (64), the sweep 2.2 / 5 and the loads of half of its blocks
-// behind the rounds 0.4 / 3.2, start and end of a launch 3.  4000 rounds of the first take 1.45 ms (1.48) against 3.0 ms on the
-// register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 1.07 ms (1.13) against 29.4 ms on dense_window_kernel.
+// shares and the other inputs in front of them 3 (16 chunks) / 6.3 (64: 26 bytes a clock, as many as a compute unit gets from
+// L2; touching the lines beforehand gives nothing), the sweep 2.2 / 4.3 and the loads of half of its blocks
+// behind the rounds 0.4 / 3, start and end of a launch 3.  4000 rounds of the first take 1.43 ms (1.48) against 3.0 ms on the
+// register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 0.93 ms (1.13) against 29.4 ms on dense_window_kernel.
+// (A chunk's range of blocks comes with the arguments and its place from the grid: two 64-bit divisions stood 0.7 us before
+// the first load.)
 //
 // The round rows are read as they are, without the re-tiled copies of dense_window.hip: with few tiles
 // a copy would cost more than it saves.  The Gram matrices of the windows are taken by
@@ -62,6 +65,7 @@ struct SplitArgs {
     WinPlanD plan;
     int wu;                  // window whose rounds and step this launch works; -1: none (the call's first launch)
     int chunks;              // workgroups per tile
+    int per, more;           // depth blocks of a chunk, and how many chunks have one more
     const float *gram;       // of window wu
     int cmp;                 // ... with the comparators' predictions in it
     const float *pin;        // shares of W X_wu^T and ||W||^2, [tile][chunk][kShareFloats]
@@ -81,9 +85,8 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     constexpr int NT = kSW * kWave;
     extern __shared__ __align__(16) char lds[];
     const int d = a.d, K = a.K, nq = a.R * K;
-    const int nblk = (d + 15) / 16;
-    const int chunk = (int)blockIdx.x % sp.chunks, tile = (int)blockIdx.x / sp.chunks;
-    const int b_lo = (int)((int64_t)chunk * nblk / sp.chunks), b_hi = (int)((int64_t)(chunk + 1) * nblk / sp.chunks);
+    const int chunk = (int)blockIdx.x, tile = (int)blockIdx.y;
+    const int b_lo = chunk * sp.per + min(chunk, sp.more), b_hi = b_lo + sp.per + (chunk < sp.more ? 1 : 0);
     const int q_base = tile * kM;
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -125,19 +128,46 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         // the chunks' shares, summed in chunk order
         const float *p0 = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + tid * 2;
         double s0 = 0.0, s1 = 0.0;
-        auto sum_shares = [&](auto norms) __attribute__((always_inline)) {
+        // (in batches whose loads are all on their way before the first is added)
+        auto sum_shares = [&](int c0, auto batch, auto norms) __attribute__((always_inline)) {
+            constexpr int U = decltype(batch)::value;
             constexpr bool N = decltype(norms)::value;              // ||w||^2 of the stored iterates as well
-            const float *pn = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + kB * kM + (lc & (kM - 1));
-#pragma unroll 16
-            for (int c = 0; c < sp.chunks; ++c) {
-                const float2 v = *reinterpret_cast<const float2 *>(p0 + (int64_t)c * kShareFloats);
-                s0 += (double)v.x;
-                s1 += (double)v.y;
-                if (N) n2 += (double)pn[(int64_t)c * kShareFloats];
+            const float *p = p0 + (int64_t)c0 * kShareFloats;
+            const float *pn = sp.pin + ((int64_t)tile * sp.chunks + c0) * kShareFloats + kB * kM + (lc & (kM - 1));
+            float2 v[U];
+            float m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                v[u] = *reinterpret_cast<const float2 *>(p + u * kShareFloats);
+                if (N) m[u] = pn[u * kShareFloats];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                s0 += (double)v[u].x;
+                s1 += (double)v[u].y;
+                if (N) n2 += (double)m[u];
             }
         };
-        if (wave < kNP) sum_shares(std::true_type{});
-        else sum_shares(std::false_type{});
+        auto batches = [&](auto norms) __attribute__((always_inline)) {
+            int c = 0;
+            for (; c + 16 <= sp.chunks; c += 16) sum_shares(c, std::integral_constant<int, 16>{}, norms);
+            if (c + 8 <= sp.chunks) {
+                sum_shares(c, std::integral_constant<int, 8>{}, norms);
+                c += 8;
+            }
+            switch (sp.chunks - c) {
+                case 7: sum_shares(c, std::integral_constant<int, 7>{}, norms); break;
+                case 6: sum_shares(c, std::integral_constant<int, 6>{}, norms); break;
+                case 5: sum_shares(c, std::integral_constant<int, 5>{}, norms); break;
+                case 4: sum_shares(c, std::integral_constant<int, 4>{}, norms); break;
+                case 3: sum_shares(c, std::integral_constant<int, 3>{}, norms); break;
+                case 2: sum_shares(c, std::integral_constant<int, 2>{}, norms); break;
+                case 1: sum_shares(c, std::integral_constant<int, 1>{}, norms); break;
+                default: break;
+            }
+        };
+        if (wave < kNP) batches(std::true_type{});
+        else batches(std::false_type{});
         double *q0d = reinterpret_cast<double *>(lds + Lds::q0);
         *reinterpret_cast<d2 *>(q0d + (tid >> 3) * kQStride + 2 * (tid & 7)) = d2{s0, s1};
         double *gd = reinterpret_cast<double *>(lds + Lds::gd);
@@ -217,7 +247,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     for (int i = 0; i < kPre; ++i) fetch(nth_block(i), pre[i]);
     __syncthreads();
 
-    if (upd && sp.cmp && blockIdx.x == 0) {                         // the comparators' predictions of the window
+    if (upd && sp.cmp && chunk == 0 && tile == 0) {             // the comparators' predictions of the window
         for (int e = tid; e < a.R * kB; e += NT) {
             const int r = e >> 6, t = e & 63;
             if (t < wu_l) a.Z[(int64_t)r * a.zl.zs_r + (int64_t)K * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = sp.gram[cmp_at(r, t)];
@@ -286,7 +316,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         reinterpret_cast<float *>(lds + Lds::n2)[(wave * 4 + lk) * kM + lr] = nn;
     }
     __syncthreads();
-    float *po = sp.pout + (int64_t)blockIdx.x * kShareFloats;
+    float *po = sp.pout + ((int64_t)tile * sp.chunks + chunk) * kShareFloats;
     if (do_q) {
         const float *part = reinterpret_cast<const float *>(lds + Lds::part);
 #pragma unroll
@@ -431,8 +461,10 @@ bool make_split_plan(const DenseArgs &a, SplitPlan *p)
     const int nwin = (int)std::min<int64_t>(a.n_max / kB + 2, 1 << 20);
     const size_t room = dense_window_scratch_floats(a.n_max, a.d);
     p->hint_floats = (size_t)(nq + 63) / 64 * 64;
-    p->chunks = std::max(1, std::min({64, 256 / p->tiles, (nblk + kSW - 1) / kSW}));
-    if (p->chunks >= 8) p->chunks &= ~7;
+    // as many chunks as the chip has compute units for; more than 64 (the sum over their shares takes 1.1 us per sixteen) only
+    // while a wavefront has four blocks or more: 1000 rounds of d = 65536, 16 learners, 64 / 128 chunks 750 / 670 us.  (Rounded
+    // down to a multiple of 8, 19 tiles of d = 40000 have 8 chunks, not 13: 1500 / 1114 us for 800 rounds.)
+    p->chunks = std::max(1, std::min({std::max(64, nblk / (kSW * kPre)), 256 / p->tiles, (nblk + kSW - 1) / kSW}));
     for (;; --p->chunks) {
         p->share_floats = (size_t)p->tiles * p->chunks * kShareFloats;
         const size_t fixed = 2 * p->share_floats + 4 * p->hint_floats;
@@ -526,7 +558,9 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
                 hipLaunchKernelGGL(split_gram_sum_kernel, dim3((unsigned)nw * 16), dim3(256), 0, s, gpart, p.gram_chunks, gram);
         }
         SplitArgs sp{};
-        sp.plan = plan; sp.wu = w; sp.chunks = p.chunks; sp.cmp = cmp;
+        sp.plan = plan; sp.wu = w; sp.chunks = p.chunks;
+        const int nblk = (a.d + 15) / 16;
+        sp.per = nblk / p.chunks; sp.more = nblk % p.chunks; sp.cmp = cmp;
         sp.gram = gram + (size_t)in_group * kB * kB;
         sp.pin = share[w & 1]; sp.pout = share[(w + 1) & 1];
         float *hin = hint0 + (size_t)(w & 1) * 2 * p.hint_floats, *hout = hint0 + (size_t)((w + 1) & 1) * 2 * p.hint_floats;
@@ -534,7 +568,7 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
         sp.ha_out = hout; sp.hp_out = hout + p.hint_floats;
         e = clock_begin(a.clock, s, "dense_split_kernel");
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles * p.chunks)), dim3(kSW * kWave), LdsS::total, s, a, sp);
+        hipLaunchKernelGGL(kern, dim3((unsigned)p.chunks, (unsigned)p.tiles), dim3(kSW * kWave), LdsS::total, s, a, sp);
         e = hipGetLastError();
         if (e == hipSuccess) e = clock_end(a.clock, s);
         if (e == hipSuccess && beside && w >= 0) {
