@@ -60,6 +60,12 @@ def window_iterates_in_registers(wl, options):
     return (wl.d + 15) // 16 >= 32 and wl.d <= 1024
 
 
+def windows_of_a_stream(wl, kernel):
+    """Whether the windows are those of a workgroup's own stream (iterates in registers, no re-tiled copies of the rounds),
+    which carry the other windowed kernel's name: streams per run, or a shared one of few learners."""
+    return kernel == "dense_window_kernel" and (not wl.x_shared or wl.R * wl.K <= 2048)
+
+
 def algorithmic_hbm_bytes(wl, kernel, launches, in_registers=False):
     """Compulsory HBM bytes of the round kernels of one step.  Dense: the round stream once, the
     labels, the predictions out, the state in and out per launch; the windowed kernel also
@@ -71,7 +77,7 @@ def algorithmic_hbm_bytes(wl, kernel, launches, in_registers=False):
         return float(wl.R * wl.K * wl.T * wl.nnz * 8 + wl.T * wl.nnz * 8 + wl.R * wl.T * 4 + wl.R * wl.T * wl.nnz * 4)
     x = 4.0 * wl.T * wl.d * (1 if wl.x_shared else wl.R)
     b = x + 4.0 * wl.R * wl.T + 4.0 * wl.R * (wl.K + 1) * wl.T + 8.0 * wl.R * wl.K * wl.d * max(launches, 1)
-    if kernel.startswith("dense_window"):
+    if kernel.startswith("dense_window") and not windows_of_a_stream(wl, kernel):
         # (loading wavefronts, rows in parts: a float32 copy for the Gram matrices, then two of three 16-bit parts)
         b += 8.0 * x if kernel == "dense_window_parts_kernel" else 4.0 * x
         if not in_registers:
@@ -137,7 +143,9 @@ def binding_block(wl, res, config_key, floor=None):
     kernel = res["kernel_timing"]["kernel"]
     b = {"us_per_round": us_round}
     if floor is not None:
-        b.update(resource="dependent chain of a round (latency): one wavefront reduction and the scalars behind it",
+        b.update(resource="dependent rounds of a window (64 rounds on float64 scalars, four learners per wavefront)"
+                 if windows_of_a_stream(wl, kernel) else
+                 "dependent chain of a round (latency): one wavefront reduction and the scalars behind it",
                  floor_us_per_round=floor["us_per_round"], floor=floor["what"],
                  over_floor=us_round / floor["us_per_round"])
     elif wl.nnz:
@@ -194,7 +202,8 @@ def run_workload(name, steps, warmup, WL, B, torch, keep=None, optimistic=False,
     kt = dict(kernel=ktim[0]["kernel"], launches=ktim[0]["launches"], timed=sum(k["timed"] for k in ktim),
               ms_sum=sum(k["ms_sum"] for k in ktim))
     if kt["kernel"].startswith("dense_window"):
-        kt["iterates"] = "registers" if window_iterates_in_registers(wl, options) else "hbm"
+        own = windows_of_a_stream(wl, kt["kernel"])
+        kt["iterates"] = "registers" if own or window_iterates_in_registers(wl, options) else "hbm"
     out = dict(wl=wl, ms_per_step=ms, value=wl.units / (dt / steps),
                round_kernel_ms=float(sum(k[0] for k in kern_ms) / steps),
                meta_kernel_ms=float(sum(k[1] for k in kern_ms) / steps),
