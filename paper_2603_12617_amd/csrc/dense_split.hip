@@ -21,7 +21,7 @@
 // L2; touching the lines beforehand gives nothing), the sweep 2.2 / 4.3 and the loads of half of its blocks
 // behind the rounds 0.4 / 3, start and end of a launch 3.  4000 rounds of the first take 1.43 ms (1.48) against 3.0 ms on the
 // register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 0.93 ms (1.13) against 29.4 ms on dense_window_kernel.
-// (A chunk's range of blocks comes with the arguments and its place from the grid: two 64-bit divisions stood 0.7 us before
+// (A chunk's range of blocks comes with the arguments and its place from the grid, a learner's run from a multiplication: two 64-bit divisions stood 0.7 us before
 // the first load.)
 //
 // The round rows are read as they are, without the re-tiled copies of dense_window.hip: with few tiles
@@ -66,6 +66,8 @@ struct SplitArgs {
     int wu;                  // window whose rounds and step this launch works; -1: none (the call's first launch)
     int chunks;              // workgroups per tile
     int per, more;           // depth blocks of a chunk, and how many chunks have one more
+    unsigned per_run;        // 2^31 / K, rounded up: a learner's run without a division (exact while q K < 2^31)
+    __device__ __forceinline__ int run_of(int q) const { return (int)(((uint64_t)(unsigned)q * per_run) >> 31); }
     const float *gram;       // of window wu
     int cmp;                 // ... with the comparators' predictions in it
     const float *pin;        // shares of W X_wu^T and ||W||^2, [tile][chunk][kShareFloats]
@@ -107,7 +109,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         if (wave < kNP) {
             const int q = q_base + lc;
             if (q < nq) {
-                eta = a.eta[q % K];
+                eta = a.eta[q - sp.run_of(q) * K];
                 if (OPT) {
                     hint.ha = sp.ha_in[q];
                     hint.hp = sp.hp_in[q];
@@ -122,8 +124,8 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         float yv[kB * kM / NT];
 #pragma unroll
         for (int i = 0; i < kB * kM / NT; ++i) {
-            const int e = tid + i * NT, l = e >> 6, t = e & 63, q = q_base + l;
-            yv[i] = (a.y && q < nq && t < wu_l) ? a.y[(int64_t)(q / K) * a.y_run_stride + wu_s + t] : 0.f;
+            const int q = q_base + wave + kSW * i;                  // a learner per wavefront, a round per lane
+            yv[i] = (a.y && q < nq && lane < wu_l) ? a.y[(int64_t)sp.run_of(q) * a.y_run_stride + wu_s + lane] : 0.f;
         }
         // the chunks' shares, summed in chunk order
         const float *p0 = sp.pin + (int64_t)tile * sp.chunks * kShareFloats + tid * 2;
@@ -177,8 +179,7 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
         float *yb = reinterpret_cast<float *>(lds + Lds::yb);
 #pragma unroll
         for (int i = 0; i < kB * kM / NT; ++i) {
-            const int e = tid + i * NT;
-            yb[(e >> 6) * kYStride + (e & 63)] = yv[i];
+            yb[(wave + kSW * i) * kYStride + lane] = yv[i];
         }
         if (OPT && tid < kB) scal[2 * tid + 1] = tid < wu_l ? (double)a.g01[wu_s + tid] : 0.0;
         __syncthreads();
@@ -248,17 +249,16 @@ __global__ void __launch_bounds__(kSW *kWave) dense_split_kernel(const DenseArgs
     __syncthreads();
 
     if (upd && sp.cmp && chunk == 0 && tile == 0) {             // the comparators' predictions of the window
-        for (int e = tid; e < a.R * kB; e += NT) {
-            const int r = e >> 6, t = e & 63;
-            if (t < wu_l) a.Z[(int64_t)r * a.zl.zs_r + (int64_t)K * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = sp.gram[cmp_at(r, t)];
-        }
+        for (int r = wave; r < a.R; r += kSW)
+            if (lane < wu_l) a.Z[(int64_t)r * a.zl.zs_r + (int64_t)K * a.zl.zs_i + (int64_t)(wu_s + lane) * a.zl.zs_t] = sp.gram[cmp_at(r, lane)];
     }
     if (upd && chunk == 0) {                                        // the window's predictions
         const float *zb = reinterpret_cast<const float *>(lds + Lds::zb);
-        for (int e = tid; e < kM * kB; e += NT) {
-            const int l = e >> 6, t = e & 63, q = q_base + l;
-            if (q < nq && t < wu_l)
-                a.Z[(int64_t)(q / K) * a.zl.zs_r + (int64_t)(q % K) * a.zl.zs_i + (int64_t)(wu_s + t) * a.zl.zs_t] = zb[l * kYStride + t];
+#pragma unroll
+        for (int l = wave; l < kM; l += kSW) {
+            const int q = q_base + l, r = sp.run_of(q);
+            if (q < nq && lane < wu_l)
+                a.Z[(int64_t)r * a.zl.zs_r + (int64_t)(q - r * K) * a.zl.zs_i + (int64_t)(wu_s + lane) * a.zl.zs_t] = zb[l * kYStride + lane];
         }
     }
     {
@@ -561,6 +561,7 @@ hipError_t launch_dense_split(const DenseArgs &a, int loss, hipStream_t s, const
         sp.plan = plan; sp.wu = w; sp.chunks = p.chunks;
         const int nblk = (a.d + 15) / 16;
         sp.per = nblk / p.chunks; sp.more = nblk % p.chunks; sp.cmp = cmp;
+        sp.per_run = (unsigned)((0x80000000u + (unsigned)a.K - 1) / (unsigned)a.K);
         sp.gram = gram + (size_t)in_group * kB * kB;
         sp.pin = share[w & 1]; sp.pout = share[(w + 1) & 1];
         float *hin = hint0 + (size_t)(w & 1) * 2 * p.hint_floats, *hout = hint0 + (size_t)((w + 1) & 1) * 2 * p.hint_floats;
