@@ -19,7 +19,7 @@
 // squared): the dependent rounds 8.4 / 3.9 us (on one wavefront, a quad of lanes per learner, 11.1 / 8.2), the sum over the chunks'
 // shares and the other inputs in front of them 3 (16 chunks) / 6.3 (64: 26 bytes a clock, as many as a compute unit gets from
 // L2; touching the lines beforehand gives nothing), the sweep 2.2 / 4.3 and the loads of half of its blocks
-// behind the rounds 0.4 / 3, start and end of a launch 3.  4000 rounds of the first take 1.43 ms (1.48) against 3.0 ms on the
+// behind the rounds 0.4 / 3, start and end of a launch 3.  4000 rounds of the first take 1.30 ms (1.48) against 3.0 ms on the
 // register kernel; 2000 rounds of the second (64 chunks of 512 coordinates) 0.93 ms (1.13) against 29.4 ms on dense_window_kernel.
 // (A chunk's range of blocks comes with the arguments and its place from the grid, a learner's run from a multiplication: two 64-bit divisions stood 0.7 us before
 // the first load.)
@@ -465,6 +465,15 @@ bool make_split_plan(const DenseArgs &a, SplitPlan *p)
     // while a wavefront has four blocks or more: 1000 rounds of d = 65536, 16 learners, 64 / 128 chunks 750 / 670 us.  (Rounded
     // down to a multiple of 8, 19 tiles of d = 40000 have 8 chunks, not 13: 1500 / 1114 us for 800 rounds.)
     p->chunks = std::max(1, std::min({std::max(64, nblk / (kSW * kPre)), 256 / p->tiles, (nblk + kSW - 1) / kSW}));
+    // The meta work of every 256 rounds runs beside a window, a workgroup per run: two of this kernel's wavefronts fill the registers of
+    // a SIMD, so a chunk whose compute unit has one waits for it (25 us; that window took 28 us instead of 16).  Fewer chunks leave those
+    // compute units free, where that costs a wavefront at most one block more, and none beyond those it fetches beforehand: 256
+    // learners of d = 2048 in 32 runs 16 -> 14 chunks, 4000 rounds 1430 -> 1297 us; 720 of d = 600 in 60 5 -> 4, 1256 -> 1104; but a fifth
+    // block (240 of d = 8192 in 60) 841 -> 880.
+    const int apart = (int)std::max<int64_t>(0, 256 - a.R) / p->tiles;
+    auto depth = [&](int chunks) { return (nblk + chunks * kSW - 1) / (chunks * kSW); };
+    if (apart >= 1 && apart < p->chunks && (depth(apart) == depth(p->chunks) || depth(apart) <= std::min(kPre, depth(p->chunks) + 1)))
+        p->chunks = apart;
     for (;; --p->chunks) {
         p->share_floats = (size_t)p->tiles * p->chunks * kShareFloats;
         const size_t fixed = 2 * p->share_floats + 4 * p->hint_floats;
