@@ -49,7 +49,9 @@
  *    d is not a multiple of 4, on streams of their own (with many learners up to
  *    d = 2048) or on a shared one with at most 2048 learners.  With these two
  *    splits at multiples of 64 are bit-identical if every call but the last
- *    of the horizon is that long.  With OCO_OPT_DENSE_PATH 1 a configuration of d <= 4096
+ *    of the horizon is that long.  Neither takes configurations whose D^2 is not a normal
+ *    float32 -- a D that stands for no bound -- or whose steps, the largest eta times G, are
+ *    beyond 2^59 D or so.  With OCO_OPT_DENSE_PATH 1 a configuration of d <= 4096
  *    stays on the register kernel, and any split gives the same bits.)
  *    Sparse configurations work in segments of 4096 rounds of
  *    the horizon: splits at multiples of 4096 are bit-identical, other splits

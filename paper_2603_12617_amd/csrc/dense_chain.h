@@ -65,7 +65,8 @@ __device__ __forceinline__ void put_gram(double *gd, double *scal, int t, int t2
 // 238 / 271 / 299 optimistic, linear / squared / logistic.  The quad of lanes per learner that chain_window gives a wavefront of
 // sixteen learners takes 264 / 280 / 306 and 306 / 329 / 358: its lanes have sixteen pending products where these have four.
 // s grows by the factor a step leaves the ball by, every round: every eighth round a learner whose s has grown beyond 2^20 is
-// taken back to below 2 by a power of two (exact), so that the norm stays within float64 for steps up to 2^60 times the ball.
+// taken back to below 2 by a power of two (exact), so that the norm stays within float64 for steps up to 2^60 times the ball
+// (chain_holds says for which configurations; others do not come here).
 //
 // Straight-line code: a window shorter than 64 rounds (first / last window of a call) runs its
 // missing rounds with rows of G, labels and inner products of zero, which change nothing (the linear loss has a b there, which is

@@ -552,6 +552,7 @@ bool dense_run_wanted(const DenseArgs &a)
     if (a.tune->get(OCO_OPT_DENSE_PATH) >= 0 || a.tune->get(OCO_OPT_WINDOW_RESIDENT) >= 0 || a.tune->get(OCO_OPT_DENSE_WPB) >= 0 ||
         a.tune->get(OCO_OPT_DENSE_HALF) >= 0 || a.tune->get(OCO_OPT_COMPARATOR_GEMM) == 0)
         return false;                                               // (a choice that only the register kernel has)
+    if (!a.scaled) return false;
     constexpr int kSimds = 1024;
     const int64_t waves = (int64_t)a.R * (a.K + 1);                 // of the register kernel
     int most = a.d % 4 == 0 ? 448 : 1024;

@@ -501,7 +501,7 @@ bool make_split_plan(const DenseArgs &a, SplitPlan *p)
 
 bool dense_split_wanted(const DenseArgs &a)
 {
-    if (!a.x_shared || !a.vec_ok || !a.gram || a.tune->get(OCO_OPT_DENSE_PATH) == 1) return false;
+    if (!a.x_shared || !a.vec_ok || !a.gram || !a.scaled || a.tune->get(OCO_OPT_DENSE_PATH) == 1) return false;
     const int64_t ropt = a.tune->get(OCO_OPT_WINDOW_RESIDENT);
     if (ropt != -1 && ropt != 5) return false;
     SplitPlan p;

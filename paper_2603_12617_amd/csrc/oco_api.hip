@@ -473,6 +473,9 @@ int oco_run_rounds(oco_state *st, const oco_rounds *rd, int64_t t0, int64_t n)
         a.tune = &st->tune; a.plan = &st->dense_plan; a.clock = st->timing ? &st->clock : nullptr;
         a.gram = l.off_gram ? st->at<float>(l.off_gram) : nullptr;
         a.n_max = l.n_max; a.T = c.T;
+        double eta_max = 0.0;
+        for (int64_t i = 0; i < c.K; ++i) eta_max = std::fmax(eta_max, st->eta[i]);
+        a.scaled = chain_holds(c.D, eta_max * c.G);
         a.L = m.L; a.last = m.last; a.regret = m.regret; a.eps = m.eps;
         e = launch_dense_rounds(a, c.loss, st->stream, overlap ? &hook : nullptr, &meta_done);
     }

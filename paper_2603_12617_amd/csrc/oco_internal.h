@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+
 namespace oco {
 
 constexpr int kWave = 64;          // gfx950 wavefront width
@@ -120,7 +122,22 @@ struct DenseArgs {
     float *gram;             // shared streams: dense_gram_bytes(n_max, d) of scratch for the windowed path
     int64_t n_max;           // the state's largest call (lays that scratch out)
     int64_t T;               // the horizon
+    bool scaled;             // chain_holds of the configuration
 };
+
+// Whether the dependent rounds in scaled coordinates (chain_rounds, dense_chain.h) hold a configuration of radius D whose steps
+// are at most `step` long (the largest eta times the bound G of Assumption 2; the kernels that have them are not wanted otherwise).
+//  - Squared norms are kept in float32 between windows, so D^2 has to be a normal float32.  (The other kernels never project where
+//    it is infinite, as with a radius that stands for no bound at all; here the scale of the iterates, D / sqrt 2, would be infinite too.)
+//  - The scale grows by 1 + r, r = step / D, in every round that leaves the ball and is taken back below 2 every eighth round if it is
+//    beyond 2^20, so a squared norm reaches 2^40 D^2 (1 + r)^16, which has to stay within float64's 2^1024: 8 log2 r + log2 D < 491.
+//    15 of these are left for gradients beyond G (3.6 times).  The step grid of Corollary 3 is within it at K = 64 for D <= 1000 (T >= 768).
+inline bool chain_holds(double D, double step)
+{
+    if (!(D >= 0x1p-63 && D < 0x1p64)) return false;
+    const double r = step / D;
+    return r <= 1.0 || 8.0 * std::log2(r) + std::log2(D) < 476.0;
+}
 // *meta_done: the call's meta work is enqueued as well (a.L, a.last, a.regret)
 hipError_t launch_dense_rounds(const DenseArgs &a, int loss, hipStream_t s, const PieceHook *hook, bool *meta_done);
 bool dense_short_supported(const DenseArgs &a);

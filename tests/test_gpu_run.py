@@ -128,3 +128,21 @@ def test_steps_far_larger_than_the_ball_and_a_tiny_radius(optimistic):
     wl = WL.make("c4", T=800, R=2, d=64, K=4, x_shared=False, eta=(1e-3, 1.0, 1e3, 1e8), optimistic=optimistic)
     data = WL.generate(wl)
     _check(wl, data, _gpu(wl, data), label="run logistic huge eta optimistic=%d" % optimistic)
+
+
+# radii that stand for no bound (beyond float32, then beyond what its square can be), and steps so long that eight of them leave the
+# range of float64 in the scaled coordinates of the windows: both stay with kernels that hold them.  A stream of its own, a shared one of a
+# model too wide for the register kernel, and one that would be split over workgroups.
+@pytest.mark.parametrize("name,over", [
+    ("c2", dict(T=800, R=2, d=40, K=3)),
+    ("c4", dict(T=800, R=2, d=40, K=3, x_shared=False)),
+    ("c3", dict(T=600, R=2, d=1000, K=3, seg_len=100)),
+    ("c4", dict(T=130, R=2, d=4104, K=3)),
+])
+@pytest.mark.parametrize("D,eta", [(1e300, (0.01, 0.1, 0.3)), (1e39, (0.01, 0.1, 0.3)), (1e25, (0.01, 0.1, 0.3)), (1e-12, (1e-12, 1.0, 1e12))])
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_radii_and_steps_that_scaled_coordinates_do_not_hold(name, over, D, eta, optimistic):
+    wl = WL.make(name, D=D, eta=eta, optimistic=optimistic, **over)
+    data = WL.generate(wl)
+    print("case radius", name, over, D, "optimistic", optimistic, flush=True)
+    _check(wl, data, _gpu(wl, data), label="radius %s %g optimistic=%d" % (name, D, optimistic))
