@@ -45,9 +45,12 @@
  *    float32 rounding.  (By default: shared streams of d > 4096, of at least 2048
  *    learners with d >= 512, and calls of at least 512 rounds with d > 512 and
  *    at most 2048 learners: those with the coordinates split over workgroups;
- *    also calls of at least 768 rounds of narrow models, up to d = 448, or 1024 where
- *    d is not a multiple of 4, on streams of their own (with many learners up to
- *    d = 2048) or on a shared one with at most 2048 learners.  With these two
+ *    also calls of at least 768 rounds of narrow models on streams of their own or on a
+ *    shared one with at most 2048 learners: up to d = 448, or 1024 where d is not a multiple
+ *    of 4.  On streams of their own that is 640, not 1024, from R (K + 1) = 1024 on; from 4096 on it
+ *    is 2048 for every d, but 800 where d is a multiple of 4 and K < 16; and where 16 learners of a run
+ *    to a workgroup are more than 160 workgroups, runs of few learners stay on the register
+ *    kernel.  With these two
  *    splits at multiples of 64 are bit-identical if every call but the last
  *    of the horizon is that long.  Neither takes configurations whose D^2 is not a normal
  *    float32 -- a D that stands for no bound -- or whose steps, the largest eta times G, are

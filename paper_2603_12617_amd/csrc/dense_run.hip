@@ -547,6 +547,19 @@ template <int LOSS, bool OPT> RunKernel pick_run_kernel(int nfull)
 // rounds the two take the same (d = 100 0.223 / 0.222 and 0.203 / 0.205), 1000 of one learner 0.250 / 0.198: hence the least n.  The horizon's
 // last call, which is as short as the cuts leave it, stays with the kernel of the calls before it, as in dense_split.hip.
 // (The rules look at the configuration and the call's length only, not at addresses.)
+//
+// A workgroup takes a compute unit's LDS, so more than 256 of them are turns of the chip, each as long whether its tiles hold one
+// learner or sixteen, while what the register kernel takes goes by its wavefronts.  Streams of their own, 1200 rounds, the same loss, ms, learners x runs:
+//               1 x 1024      4 x 1024      8 x 512       17 x 256      16 x 258      16 x 1024     32 x 512
+//   d = 64      0.53 / 0.70   0.63 / 0.72   0.50 / 0.44   0.51 / 0.46   0.58 / 0.50   1.72 / 0.96   1.73 / 0.98
+//   d = 448     1.33 / 1.85   1.26 / 1.85   0.84 / 1.01   0.78 / 0.89   1.07 / 0.89   2.74 / 2.05   2.72 / 1.90
+//   d = 1000    1.87 / 3.57   2.07 / 3.66   1.31 / 1.98   1.12 / 1.70   1.35 / 1.56   4.98 / 3.87   3.87 / 3.50
+// So beyond a turn tiles have to be three quarters full (half of narrow models, whose sweeps are short beside their rounds; all of wide
+// aligned ones), and the register kernel needs a number of wavefronts per SIMD and turn: 1.5, 2, 2.75 and 3 as models get wider (d = 1000,
+// 300 runs of sixteen, 2.5 of them 1.46 / 1.66; 640 runs, 3.5 of them 3.27 / 2.77).  Within a turn workgroups slow each other only by their draw on the caches: from 161 of
+// them and d = 321 tiles have to be half full (800 rounds of d = 448, 192 runs of one learner 0.34 / 0.39, of sixteen 0.50 / 0.43).  A run of
+// up to fifteen learners and its comparator is one workgroup of the register kernel, which a compute unit works as fast as a wavefront or two
+// per SIMD: such runs of wide aligned models stay there (256 of fifteen, d = 2048 1.70 / 1.91; of sixteen 2.54 / 1.92).
 bool dense_run_wanted(const DenseArgs &a)
 {
     if (a.tune->get(OCO_OPT_DENSE_PATH) >= 0 || a.tune->get(OCO_OPT_WINDOW_RESIDENT) >= 0 || a.tune->get(OCO_OPT_DENSE_WPB) >= 0 ||
@@ -555,13 +568,22 @@ bool dense_run_wanted(const DenseArgs &a)
     if (!a.scaled) return false;
     constexpr int kSimds = 1024;
     const int64_t waves = (int64_t)a.R * (a.K + 1);                 // of the register kernel
-    int most = a.d % 4 == 0 ? 448 : 1024;
+    const bool aligned = a.d % 4 == 0;
+    int most = aligned ? 448 : 1024;
     if (a.x_shared) {
         if ((int64_t)a.R * a.K > 2048) return false;
-    } else if (waves >= 4 * kSimds) {
-        most = 16 * kRunMaxBlocks;
-    } else if (waves >= kSimds && a.d % 4 != 0) {
-        most = 640;
+    } else {
+        constexpr int kUnits = 256;
+        const int64_t tiles = (a.K + kM - 1) / kM, wgs = a.R * tiles, turns = (wgs + kUnits - 1) / kUnits;
+        const bool narrow = a.d <= 160, wide = aligned && a.d > 448, full = aligned && a.d > 800;
+        if (turns > 1) {
+            const int64_t quarters = narrow ? 6 : full ? 12 : wide ? 11 : 8;    // of a wavefront per SIMD
+            if (a.K < (narrow ? 8 : full ? 16 : 12) * tiles || waves * 4 < quarters * kSimds * turns) return false;
+        } else if (wgs > 160 && a.d > 320 && a.K < 8 * tiles) {
+            return false;
+        }
+        if (waves >= 4 * kSimds) most = aligned && a.K < 16 ? 800 : 16 * kRunMaxBlocks;
+        else if (waves >= kSimds && !aligned) most = 640;
     }
     const bool rest = a.plan->after_split && a.t0 + a.n == a.T;
     return a.d <= most && (a.n >= 768 || rest);

@@ -146,3 +146,47 @@ def test_radii_and_steps_that_scaled_coordinates_do_not_hold(name, over, D, eta,
     data = WL.generate(wl)
     print("case radius", name, over, D, "optimistic", optimistic, flush=True)
     _check(wl, data, _gpu(wl, data), label="radius %s %g optimistic=%d" % (name, D, optimistic))
+
+
+def _call_of(R, K, d, shared=False, T=768, n=0):
+    """A call of n rounds of zeros: what is looked at is its route."""
+    import torch
+    wl = WL.make("c2", T=T, R=R, K=K, d=d, x_shared=shared)
+    data = dict(x=None, y=np.zeros((R, T), np.float32), u=np.zeros((R, 1, d), np.float32), seg_start=np.zeros(1, np.int64))
+    sim = B.Simulation(wl, data, options=dict(verbose=1))
+    sim.x = torch.zeros((T, d) if shared else (R, T, d), device=sim.dev)
+    sim.run(0, n or T)
+    assert sim.regret().shape == (R,)
+    sim.close()
+
+
+# The lines of the rule, on both sides: learners of a tile and register wavefronts per turn beyond 256 workgroups; workgroups and learners of
+# a tile within a turn; what rows of any length and many learners change; the least rounds and the most learners of a shared stream.
+@pytest.mark.parametrize("windows,R,K,d,over", [
+    (False, 1024, 1, 100, {}), (False, 257, 1, 10, {}), (False, 400, 7, 10, {}), (False, 341, 8, 10, {}), (True, 342, 8, 10, {}),
+    (True, 342, 8, 160, {}), (False, 342, 8, 161, {}), (False, 512, 11, 161, {}), (False, 315, 12, 161, {}), (True, 316, 12, 161, {}),
+    (False, 512, 17, 161, {}), (True, 258, 16, 448, {}), (False, 331, 16, 452, {}), (True, 332, 16, 452, {}),
+    (False, 361, 16, 804, {}), (True, 362, 16, 804, {}), (False, 512, 31, 804, dict(T=768)), (True, 258, 16, 449, {}),
+    (True, 160, 1, 448, {}), (False, 161, 1, 448, {}), (True, 161, 1, 320, {}), (False, 161, 7, 324, {}), (True, 161, 8, 324, {}),
+    (True, 160, 1, 777, {}), (False, 161, 1, 777, {}), (True, 128, 7, 639, {}), (True, 113, 8, 641, {}), (False, 114, 8, 641, {}),
+    (True, 2, 3, 448, {}), (False, 2, 3, 452, {}), (True, 2, 3, 1023, {}), (False, 2, 3, 1025, {}),
+    (True, 256, 15, 800, {}), (False, 256, 15, 804, {}), (True, 241, 16, 804, {}), (False, 240, 16, 804, {}), (True, 256, 15, 805, {}),
+    (True, 241, 16, 2048, {}), (False, 241, 16, 2049, {}),
+    (False, 2, 3, 100, dict(T=1000, n=767)), (True, 2, 3, 100, dict(T=1000, n=768)),
+    (True, 32, 64, 10, dict(shared=True)), (False, 33, 64, 10, dict(shared=True)),
+])
+def test_which_calls_are_worked_in_windows_of_a_stream(windows, R, K, d, over, capfd):
+    print("case route", R, K, d, over, flush=True)
+    capfd.readouterr()
+    _call_of(R, K, d, **over)
+    assert _runs_plan(capfd.readouterr().err) == windows
+
+
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_more_tiles_than_compute_units(optimistic, capfd):
+    wl = WL.make("c2", T=770, R=342, K=9, d=11, optimistic=optimistic)
+    data = WL.generate(wl)
+    capfd.readouterr()
+    got = _gpu(wl, data, options=dict(verbose=1))
+    assert _runs_plan(capfd.readouterr().err) == 1
+    _check(wl, data, got, runs=[0, 255, 256, 341], label="run 342 workgroups optimistic=%d" % optimistic)
