@@ -186,10 +186,12 @@ typedef enum {
                                     1: beside them on the library's second stream where the launcher allows */
     OCO_OPT_DENSE_PATH = 1,      /* (~) 1: one wavefront per learner, iterate in registers;
                                     2: windows of 64 rounds as contractions on the matrix cores (shared stream) */
-    OCO_OPT_DENSE_WPB = 2,       /* wavefronts per workgroup of the register kernel */
+    OCO_OPT_DENSE_WPB = 2,       /* wavefronts per workgroup of the register kernel (where a call goes there) */
     OCO_OPT_COMPARATOR_GEMM = 3, /* (~) comparator predictions of a shared stream: 0 in the round kernel, 1 as a contraction */
-    OCO_OPT_DENSE_HALF = 4,      /* (~) 1: two learners per wavefront (shared stream, d <= 1024); 0: never */
-    OCO_OPT_DENSE_PIECES = 5,    /* launches a dense call is cut into */
+    OCO_OPT_DENSE_HALF = 4,      /* (~) 1: two learners per wavefront (shared stream, d <= 1024); 0: never.  (Either, and
+                                    OCO_OPT_COMPARATOR_GEMM 0, leaves calls of narrow models to the register kernel) */
+    OCO_OPT_DENSE_PIECES = 5,    /* launches a dense call is cut into, of at least 512 rounds each (calls of the register kernel and
+                                    of narrow models in windows; the other kernels launch as their work needs) */
     OCO_OPT_SPARSE_LPW = 6,      /* (~) learners per workgroup of the sparse kernel: 4, 8, 16, 32, 64 */
     OCO_OPT_SPARSE_PIPE = 7,     /* (~) 0: sparse windows one after the other, no pipeline */
     OCO_OPT_VERBOSE = 8,         /* 1: launch plans on stderr */

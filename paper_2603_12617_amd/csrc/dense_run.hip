@@ -562,9 +562,9 @@ template <int LOSS, bool OPT> RunKernel pick_run_kernel(int nfull)
 // per SIMD: such runs of wide aligned models stay there (256 of fifteen, d = 2048 1.70 / 1.91; of sixteen 2.54 / 1.92).
 bool dense_run_wanted(const DenseArgs &a)
 {
-    if (a.tune->get(OCO_OPT_DENSE_PATH) >= 0 || a.tune->get(OCO_OPT_WINDOW_RESIDENT) >= 0 || a.tune->get(OCO_OPT_DENSE_WPB) >= 0 ||
-        a.tune->get(OCO_OPT_DENSE_HALF) >= 0 || a.tune->get(OCO_OPT_COMPARATOR_GEMM) == 0)
-        return false;                                               // (a choice that only the register kernel has)
+    if (a.tune->get(OCO_OPT_DENSE_PATH) >= 0 || a.tune->get(OCO_OPT_WINDOW_RESIDENT) >= 0 || a.tune->get(OCO_OPT_DENSE_HALF) >= 0 ||
+        a.tune->get(OCO_OPT_COMPARATOR_GEMM) == 0)
+        return false;                                               // (a choice that only the register kernel has, of those that may regroup sums)
     if (!a.scaled) return false;
     constexpr int kSimds = 1024;
     const int64_t waves = (int64_t)a.R * (a.K + 1);                 // of the register kernel
@@ -632,10 +632,14 @@ hipError_t launch_dense_run(const DenseArgs &a, int loss, hipStream_t s, const P
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
-    // pieces of 4, 3, 2 and 1 tenths of the windows: what follows the last is the meta work of a tenth
+    // pieces of 4, 3, 2 and 1 tenths of the windows: what follows the last is the meta work of a tenth (as many equal ones as the option
+    // asks for, none shorter than the register kernel's)
+    const int64_t asked = std::min<int64_t>(a.tune->get(OCO_OPT_DENSE_PIECES), std::max(a.n / 512, 1));
+    const int pieces = asked >= 1 ? (int)asked : beside ? 4 : 1;
+    auto piece_end = [&](int i) { return asked >= 1 ? (int)((int64_t)nwin * (i + 1) / pieces) : nwin * (i == 0 ? 4 : i == 1 ? 7 : 9) / 10; };
     int done = 0, w0 = 0;
-    for (int i = 0; i < 4 && w0 < nwin; ++i) {
-        const int w1 = !beside || i == 3 ? nwin : std::min(nwin, std::max(w0 + 1, nwin * (i == 0 ? 4 : i == 1 ? 7 : 9) / 10));
+    for (int i = 0; i < pieces && w0 < nwin; ++i) {
+        const int w1 = i == pieces - 1 ? nwin : std::min(nwin, std::max(w0 + 1, piece_end(i)));
         e = clock_begin(a.clock, s, "dense_window_kernel");
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)(a.x_shared ? 1 : a.R)), dim3(kRT), lds_bytes, s, a, plan, w0, w1 - w0, per_tile);

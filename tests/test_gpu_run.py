@@ -190,3 +190,34 @@ def test_more_tiles_than_compute_units(optimistic, capfd):
     got = _gpu(wl, data, options=dict(verbose=1))
     assert _runs_plan(capfd.readouterr().err) == 1
     _check(wl, data, got, runs=[0, 255, 256, 341], label="run 342 workgroups optimistic=%d" % optimistic)
+
+
+# Choices that regroup no sums: neither the route nor a bit depends on them, and the launches asked for are those that are made (at least 512
+# rounds each; without a choice four where the meta work goes beside them, one beyond 192 workgroups).
+@pytest.mark.parametrize("over,default", [
+    (dict(T=2600, R=3, d=100, K=15), 4),
+    (dict(T=2600, R=2, d=320, K=3, optimistic=1), 4),
+    (dict(T=2600, R=5, d=37, K=9, x_shared=True, seg_len=700), 4),
+    (dict(T=2600, R=200, d=7, K=4), 1),
+])
+def test_the_launches_of_a_call_change_no_bit(over, default, capfd):
+    wl = WL.make("c2", **over)
+    data = WL.generate(wl)
+    base = None
+    for opt, launches in ((dict(), default), (dict(dense_pieces=1), 1), (dict(dense_pieces=3), 3), (dict(dense_pieces=5), 5),
+                          (dict(dense_pieces=900), 5), (dict(dense_pieces=3, meta_beside=0), 3), (dict(meta_beside=0), 1), (dict(dense_wpb=4), default)):
+        print("case launches", over, opt, flush=True)
+        capfd.readouterr()
+        sim = B.Simulation(wl, data, options=dict(opt, verbose=1))
+        B.oco_set_timing(sim.h, True)
+        sim.run_all(0)
+        got = dict(regret=sim.regret(), L=sim.cum_losses())
+        got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+        assert _runs_plan(capfd.readouterr().err) == 1
+        assert B.oco_last_kernel_timing(sim.h)["launches"] == launches
+        sim.close()
+        if base is None:
+            base = got
+            _check(wl, data, got, runs=[0, wl.R - 1], label="launches %s" % over)
+        for k in KEYS:
+            assert np.array_equal(got[k], base[k]), (k, opt)
