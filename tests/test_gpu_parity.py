@@ -599,6 +599,41 @@ def test_results_do_not_depend_on_how_a_call_is_enqueued(name, over):
     sim.close()
 
 
+# the register kernel's own cutting of a call (launch by launch: rows, labels, row scalars, predictions, the last row kept for the next piece):
+# asked for, and where it is the default route; shared streams and the runs' own, both updates
+@pytest.mark.parametrize("name,over,path", [
+    ("c3", dict(T=2600, R=2, d=256, K=5, seg_len=700), 1),
+    ("c2", dict(T=2100, R=3, d=100, K=15), 1),
+    ("c2", dict(T=2570, R=2, d=77, K=4, optimistic=True), 1),
+    ("c3", dict(T=2200, R=2, d=320, K=3, seg_len=500, optimistic=True), 1),
+    ("c3", dict(T=1600, R=2, d=1000, K=5, seg_len=700), 1),
+    ("c2", dict(T=2100, R=2, d=1000, K=5), None),
+    ("c2", dict(T=2100, R=2, d=1000, K=5, optimistic=True), None),
+    ("c4", dict(T=2100, R=1, d=2052, K=3, x_shared=False, optimistic=True), None),
+])
+def test_pieces_of_a_call_of_the_register_kernel_change_no_bit(name, over, path):
+    wl = WL.make(name, **over)
+    data = WL.generate(wl)
+    base = None
+    for opt, launches in ((dict(dense_pieces=1), 1), (dict(dense_pieces=2), 2), (dict(dense_pieces=3), 3), (dict(), 4),
+                          (dict(dense_pieces=900), wl.T // 512), (dict(dense_pieces=3, meta_beside=0), 3), (dict(meta_beside=0), 1),
+                          (dict(dense_wpb=4), 4)):
+        print("case pieces", name, over, opt, flush=True)
+        sim = B.Simulation(wl, data, options=opt if path is None else dict(opt, dense_path=path))
+        B.oco_set_timing(sim.h, True)
+        sim.run_all(0)
+        got = dict(regret=sim.regret(), L=sim.cum_losses())
+        got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+        kt = B.oco_last_kernel_timing(sim.h)
+        sim.close()
+        assert kt["kernel"] == "dense_round_kernel" and kt["launches"] == min(launches, wl.T // 512), (opt, kt)
+        if base is None:
+            base = got
+            _check(wl, data, got, label="%s pieces" % name)
+        for k in ("regret", "L", "W", "p", "wbar"):
+            assert np.array_equal(base[k], got[k]), (k, opt)
+
+
 # the norms of the round rows take 1, 4 or 16 steps of 64 coordinates at a time: a step, a group and a row that are full,
 # one coordinate short and one over
 @pytest.mark.parametrize("d", [63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 1279, 1280, 1281])
