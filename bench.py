@@ -60,24 +60,29 @@ def window_iterates_in_registers(wl, options):
     return (wl.d + 15) // 16 >= 32 and wl.d <= 1024
 
 
-def windows_of_a_stream(wl, kernel):
-    """Whether the windows are those of a workgroup's own stream (iterates in registers, no re-tiled copies of the rounds),
-    which carry the other windowed kernel's name: streams per run, or a shared one of few learners."""
-    return kernel == "dense_window_kernel" and (not wl.x_shared or wl.R * wl.K <= 2048)
+def windows_of_a_stream(wl, kernel, options=None):
+    """Whether the windows are those of a workgroup's own stream (iterates in registers, no re-tiled copies of the rounds), which
+    are timed under the family's name.  Of streams per run there are no others; of a shared stream those of few learners of a narrow
+    model, the launcher's rule (include/oco.h) restated, unless an option chooses the kernel."""
+    if kernel != "dense_window_kernel":
+        return False
+    if any((options or {}).get(k, -1) >= 0 for k in ("dense_path", "window_resident", "dense_half")) or (options or {}).get("comparator_gemm", -1) == 0:
+        return False
+    return not wl.x_shared or (wl.R * wl.K <= 2048 and wl.T >= 768 and wl.d <= (1024 if wl.d % 4 else 448))
 
 
-def algorithmic_hbm_bytes(wl, kernel, launches, in_registers=False):
+def algorithmic_hbm_bytes(wl, kernel, launches, in_registers=False, own=False):
     """Compulsory HBM bytes of the round kernels of one step.  Dense: the round stream once, the
     labels, the predictions out, the state in and out per launch; the windowed kernel also
     reads the two re-tiled copies of the stream that its pre-pass wrote and, unless it keeps
-    them in registers, moves every iterate in and out once per window of 64 rounds.  Sparse: per
-    touched learner coordinate 4 B read + 4 B written, the round stream (8 B per entry), labels
-    and the comparator's gathers."""
+    them in registers, moves every iterate in and out once per window of 64 rounds (not the one
+    whose windows are of a workgroup's `own` stream).  Sparse: per touched learner coordinate
+    4 B read + 4 B written, the round stream (8 B per entry), labels and the comparator's gathers."""
     if wl.nnz:
         return float(wl.R * wl.K * wl.T * wl.nnz * 8 + wl.T * wl.nnz * 8 + wl.R * wl.T * 4 + wl.R * wl.T * wl.nnz * 4)
     x = 4.0 * wl.T * wl.d * (1 if wl.x_shared else wl.R)
     b = x + 4.0 * wl.R * wl.T + 4.0 * wl.R * (wl.K + 1) * wl.T + 8.0 * wl.R * wl.K * wl.d * max(launches, 1)
-    if kernel.startswith("dense_window") and not windows_of_a_stream(wl, kernel):
+    if kernel.startswith("dense_window") and not own:
         # (loading wavefronts, rows in parts: a float32 copy for the Gram matrices, then two of three 16-bit parts)
         b += 8.0 * x if kernel == "dense_window_parts_kernel" else 4.0 * x
         if not in_registers:
@@ -97,11 +102,11 @@ def roofline_block(wl, kt, config_key):
     launches = max(kt["launches"], 1)
     avg_ms = kt["ms_sum"] / max(kt["timed"], 1)
     kernel = kt["kernel"]
-    hbm_bytes = algorithmic_hbm_bytes(wl, kernel, launches, kt.get("iterates") == "registers")
+    hbm_bytes = algorithmic_hbm_bytes(wl, kernel, launches, kt.get("iterates") == "registers", kt.get("own_stream", False))
     entry = profile_json("hbm_traffic.json").get(config_key)
     entry = entry if isinstance(entry, dict) and entry.get("kernel") == kernel else None
     traffic = entry["bytes_per_launch"] if entry else None
-    rl = {"kernel": kernel, "launches_per_step": launches, "avg_launch_ms": avg_ms}
+    rl = {"kernel": "dense_run_kernel" if kt.get("own_stream") else kernel, "launches_per_step": launches, "avg_launch_ms": avg_ms}
     if kernel.startswith("dense_window"):
         rl["iterates"] = kt.get("iterates", "hbm")
     if wl.nnz:
@@ -144,7 +149,7 @@ def binding_block(wl, res, config_key, floor=None):
     b = {"us_per_round": us_round}
     if floor is not None:
         b.update(resource="dependent rounds of a window (64 rounds on float64 scalars, four learners per wavefront)"
-                 if windows_of_a_stream(wl, kernel) else
+                 if res["kernel_timing"].get("own_stream") else
                  "dependent chain of a round (latency): one wavefront reduction and the scalars behind it",
                  floor_us_per_round=floor["us_per_round"], floor=floor["what"],
                  over_floor=us_round / floor["us_per_round"])
@@ -156,7 +161,8 @@ def binding_block(wl, res, config_key, floor=None):
         step_ms = kt["ms_sum"] / max(kt["timed"], 1) * max(kt["launches"], 1)      # all launches of a step
         parts, loaders = kernel == "dense_window_parts_kernel", kernel in ("dense_window_parts_kernel", "dense_window_shared_kernel")
         floor_ms = 4.0 * wl.units / ((PEAK_SPLIT_TFLOPS if parts else PEAK_FP32_TFLOPS) * 1e12) * 1e3
-        hbm_ms = algorithmic_hbm_bytes(wl, kernel, max(kt["launches"], 1), kt.get("iterates") == "registers") / (PEAK_HBM_GBS * 1e6)
+        hbm_ms = algorithmic_hbm_bytes(wl, kernel, max(kt["launches"], 1), kt.get("iterates") == "registers",
+                                       kt.get("own_stream", False)) / (PEAK_HBM_GBS * 1e6)
         where = ("HBM (iterates in and out once per window) beside L2 (round rows in bfloat16 parts)" if parts else
                  "matrix cores, fed from L2 (round rows), the iterates in registers"
                  if kt.get("iterates") == "registers" else "matrix cores, fed from L2 (round rows) and HBM (iterates)")
@@ -202,8 +208,8 @@ def run_workload(name, steps, warmup, WL, B, torch, keep=None, optimistic=False,
     kt = dict(kernel=ktim[0]["kernel"], launches=ktim[0]["launches"], timed=sum(k["timed"] for k in ktim),
               ms_sum=sum(k["ms_sum"] for k in ktim))
     if kt["kernel"].startswith("dense_window"):
-        own = windows_of_a_stream(wl, kt["kernel"])
-        kt["iterates"] = "registers" if own or window_iterates_in_registers(wl, options) else "hbm"
+        kt["own_stream"] = windows_of_a_stream(wl, kt["kernel"], options)
+        kt["iterates"] = "registers" if kt["own_stream"] or window_iterates_in_registers(wl, options) else "hbm"
     out = dict(wl=wl, ms_per_step=ms, value=wl.units / (dt / steps),
                round_kernel_ms=float(sum(k[0] for k in kern_ms) / steps),
                meta_kernel_ms=float(sum(k[1] for k in kern_ms) / steps),
@@ -218,7 +224,8 @@ def run_workload(name, steps, warmup, WL, B, torch, keep=None, optimistic=False,
 
 def empty_round_floor(name, WL, B, torch):
     """us per round of the same kernel on one learner of d = 4: a round is then only its
-    dependent chain (inner product reduction, slope, step scalars) and the hand-over to the next."""
+    dependent chain (inner product, slope, step scalars) and the hand-over to the next.  (The
+    one learner of d = 10 is that itself: its ratio is 1 to within what two runs differ by.)"""
     r = run_workload(name, 2, 1, WL, B, torch, over=dict(d=4, K=1, R=1))
     return {"us_per_round": r["round_kernel_ms"] * 1e3 / r["wl"].T,
             "what": "same kernel, one learner of d=4, same T and loss (measured in this run)"}

@@ -268,8 +268,13 @@ int oco_last_timing(oco_state *st, float *ms_host);
  * works the rounds (Sec. 3.1 / 3.3 update of the base learners), without the passes that prepare
  * its inputs or the meta kernel.  *ms_sum_host = summed duration of the launches that were timed
  * (event pairs on the state's stream), *timed_host = how many those were (at most 64 per call),
- * *launches_host = launches of that kernel in the call, *kernel (may be null) = its name, a
- * static string.  Same preconditions and errors as oco_last_timing. */
+ * *launches_host = launches of that kernel in the call, *kernel (may be null) = the name of its
+ * family, a static string: "dense_round_kernel" (a wavefront per learner, short calls too),
+ * "dense_window_kernel" (windows of 64 rounds within a workgroup: of a stream that all learners
+ * share, or of the stream of a workgroup's own learners; the plan printed with OCO_OPT_VERBOSE says which),
+ * "dense_window_shared_kernel" and "dense_window_parts_kernel" (the same with loading wavefronts,
+ * rows in float32 and in bfloat16 parts), "dense_split_kernel" (coordinates split over workgroups),
+ * "sparse_window_kernel".  Same preconditions and errors as oco_last_timing. */
 int oco_last_kernel_timing(oco_state *st, float *ms_sum_host, int *timed_host, int *launches_host, const char **kernel);
 
 /* Rounds consumed so far, or a negative oco_status. */

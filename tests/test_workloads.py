@@ -99,3 +99,22 @@ def test_run_slice():
     dat = WL.generate(wl)
     sub_wl, sub = WL.run_slice(wl, dat, [3, 1])
     assert sub_wl.R == 2 and np.array_equal(sub["x"][0], dat["x"][3]) and np.array_equal(sub["y"][1], dat["y"][1])
+
+
+@pytest.mark.parametrize("name,over,kernel,options,own", [
+    ("c1", {}, "dense_window_kernel", None, True),
+    ("c2", {}, "dense_window_kernel", None, True),
+    ("c2", dict(x_shared=True, d=100, R=2, K=15), "dense_window_kernel", None, True),
+    ("c2", dict(x_shared=True, d=100, R=2, K=15), "dense_window_kernel", dict(dense_path=2), False),
+    ("c2", dict(x_shared=True, d=100, R=2, K=15), "dense_window_kernel", dict(window_resident=1), False),
+    ("c2", dict(x_shared=True, d=5001, R=2, K=15), "dense_window_kernel", None, False),
+    ("c3", {}, "dense_window_kernel", None, False),
+    ("c4", {}, "dense_window_parts_kernel", None, False),
+    ("c2", {}, "dense_round_kernel", dict(dense_path=1), False),
+])
+def test_the_benchmark_knows_whose_windows_it_timed(name, over, kernel, options, own):
+    import bench
+    wl = WL.make(name, **over)
+    assert bench.windows_of_a_stream(wl, kernel, options) == own
+    extra = bench.algorithmic_hbm_bytes(wl, kernel, 1, True, own) - bench.algorithmic_hbm_bytes(wl, "dense_round_kernel", 1)
+    assert (extra > 0) == (kernel.startswith("dense_window") and not own)      # re-tiled copies of the rounds
