@@ -221,3 +221,72 @@ def test_the_launches_of_a_call_change_no_bit(over, default, capfd):
             _check(wl, data, got, runs=[0, wl.R - 1], label="launches %s" % over)
         for k in KEYS:
             assert np.array_equal(got[k], base[k]), (k, opt)
+
+
+# the same instance under the other losses: its first d, a partial block, the last d without and with one
+@pytest.mark.parametrize("name,d,optimistic", [("c4", 1040, 1), ("c4", 2047, 0), ("c1", 1500, 0), ("c1", 1041, 1), ("c2", 2048, 1)])
+def test_wide_models_of_many_learners_under_every_loss(name, d, optimistic, capfd):
+    wl = WL.make(name, T=770, R=64, d=d, K=64, x_shared=False, optimistic=optimistic)
+    data = WL.generate(wl)
+    print("case wide", name, d, optimistic, flush=True)
+    capfd.readouterr()
+    got = _gpu(wl, data, options=dict(verbose=1))
+    assert _runs_plan(capfd.readouterr().err) == 1
+    _check(wl, data, got, runs=[0, 63], label="run many learners %s d=%d" % (name, d))
+
+
+# One run's labels hold an infinity and a NaN: its learners are lost, those of the runs that share their tile (learners 0 .. 14, windows of a
+# stream and split ones) are what they are beside a finite run, to the bit: a learner is a column of every contraction.
+@pytest.mark.parametrize("name", ["c2", "c4"])
+@pytest.mark.parametrize("d,plan", [(50, "dense_window_kernel"), (600, "dense_split_kernel")])
+@pytest.mark.parametrize("optimistic", [0, 1])
+def test_learners_beside_one_that_is_not_finite(name, d, plan, optimistic):
+    wl = WL.make(name, T=830, R=3, d=d, K=5, x_shared=True, optimistic=optimistic, eta=(0.01, 0.3, 10.0, 1e3, 1e7))
+    data = WL.generate(wl)
+    out = []
+    for bad in (False, True):
+        y = data["y"].copy()
+        if bad:
+            y[1, 300], y[1, 500] = np.inf, np.nan
+        sim = B.Simulation(wl, dict(data, y=y))
+        B.oco_set_timing(sim.h, True)
+        sim.run_all(0)
+        got = dict(regret=sim.regret(), L=sim.cum_losses())
+        got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+        assert B.oco_last_kernel_timing(sim.h)["kernel"] == plan
+        sim.close()
+        out.append(got)
+    _check(wl, data, out[0], label="beside %s d=%d" % (name, d))
+    for k in KEYS:
+        assert np.array_equal(out[0][k][[0, 2]], out[1][k][[0, 2]]), k
+    assert not np.isfinite(out[1]["L"][1]).any()
+
+
+# Seeded long horizons over sizes, losses, sharing and updates, whichever kernel they go to: one call, the same cut at multiples of 64 in calls of at
+# least 768 rounds (no bit may change), and cut anywhere (the same tolerances).
+@pytest.mark.parametrize("case", range(24))
+def test_random_long_horizons(case):
+    rng = np.random.default_rng(3000 + case)
+    d = int(rng.choice([1, 5, 16, 63, 100, 129, 255, 256, 272, 400, 449, 511, 640, 777, 1000, 1023]))
+    name = ["c1", "c2", "c3", "c4"][int(rng.integers(0, 4))]
+    over = dict(d=d, K=int(rng.integers(1, 21)), R=int(rng.integers(1, 7)), T=int(rng.integers(1600, 2500)), x_shared=bool(rng.integers(0, 2)),
+                optimistic=int(rng.integers(0, 3)), seg_len=0 if name == "c1" else int(rng.choice([0, 64, 333])), seed=case)
+    wl = WL.make(name, **over)
+    data = WL.generate(wl)
+    print("case long", case, name, over, flush=True)
+    whole = _gpu(wl, data)
+    _check(wl, data, whole, label="long %d" % case)
+    for cuts in ((64 * int(rng.integers(12, 24)),), tuple(int(c) for c in rng.integers(100, wl.T // 2, 3))):
+        sim = B.Simulation(wl, data)
+        t = 0
+        while t < wl.T:
+            n = min(cuts[0] if len(cuts) == 1 else cuts[t % 3], wl.T - t)
+            sim.run(t, n)
+            t += n
+        got = dict(regret=sim.regret(), L=sim.cum_losses())
+        got["W"], got["p"], got["wbar"] = (x.cpu().numpy() for x in sim.state())
+        sim.close()
+        _check(wl, data, got, label="long %d cuts %s" % (case, cuts))
+        if len(cuts) == 1:
+            for k in KEYS:
+                assert np.array_equal(got[k], whole[k]), (case, k, cuts)
