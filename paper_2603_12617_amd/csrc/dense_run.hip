@@ -617,8 +617,12 @@ hipError_t launch_dense_run(const DenseArgs &a, int loss, hipStream_t s, const P
         e = launch_hint_scalars(a, s);
         if (e != hipSuccess) return e;
     }
-    // the caller's work on a piece's rounds (the meta kernel) goes beside the following piece where compute units are left
-    const bool beside = hook && hook->fn && hook->beside && wgs <= 192;
+    // The caller's work on a piece's rounds (the meta kernel) goes beside the following piece where compute units are left, and where a call is
+    // long enough for that to be worth the events and launches it takes (ms beside / behind, learners of one stream: 800 rounds, 1 of d = 10
+    // 0.189 / 0.162, 8 of d = 448 0.325 / 0.297, the register kernel 0.309; 1100 rounds 0.211 / 0.196 and 0.399 / 0.384; 1600 rounds 0.253 / 0.255
+    // and 0.508 / 0.510), or the comparators' contraction over a shared stream is: 960 of d = 777, 800 rounds 0.459 / 0.493.
+    const bool worth = a.n >= 1152 || (a.x_shared && a.d > 448);
+    const bool beside = hook && hook->fn && hook->beside && wgs <= 192 && worth;
     hipStream_t cs = s;
     if (beside) e = hook->beside(hook->ctx, &cs);                   // only the meta kernel reads the comparators' predictions
     if (e != hipSuccess) return e;

@@ -290,3 +290,27 @@ def test_random_long_horizons(case):
         if len(cuts) == 1:
             for k in KEYS:
                 assert np.array_equal(got[k], whole[k]), (case, k, cuts)
+
+
+# beside the windows the meta work goes from 1152 rounds on, or with the comparators of a shared stream of rows longer than 448
+@pytest.mark.parametrize("over,launches", [
+    (dict(T=1151, R=3, d=100, K=5), 1), (dict(T=1152, R=3, d=100, K=5), 4), (dict(T=1151, R=3, d=445, K=5, x_shared=True), 1),
+    (dict(T=1151, R=3, d=449, K=5, x_shared=True), 4), (dict(T=1151, R=3, d=449, K=5), 1), (dict(T=1151, R=3, d=449, K=5, optimistic=1), 1),
+])
+def test_short_windows_calls_go_in_one_launch(over, launches):
+    wl = WL.make("c2", **over)
+    data = WL.generate(wl)
+    out = []
+    for opt, n in ((dict(), launches), (dict(meta_beside=0), 1)):
+        sim = B.Simulation(wl, data, options=opt)
+        B.oco_set_timing(sim.h, True)
+        sim.run_all(0)
+        got = dict(regret=sim.regret(), L=sim.cum_losses())
+        got["W"], got["p"], got["wbar"] = (t.cpu().numpy() for t in sim.state())
+        kt = B.oco_last_kernel_timing(sim.h)
+        assert kt["kernel"] == "dense_window_kernel" and kt["launches"] == n
+        sim.close()
+        out.append(got)
+    _check(wl, data, out[0], label="short windows %s" % over)
+    for k in KEYS:
+        assert np.array_equal(out[0][k], out[1][k]), k
