@@ -49,7 +49,7 @@
  *    shared one with at most 2048 learners: up to d = 448, or 1024 where d is not a multiple
  *    of 4.  On streams of their own that is 640, not 1024, from R (K + 1) = 1024 on; from 4096 on it
  *    is 2048 for every d, but 800 where d is a multiple of 4 and K < 16; and where 16 learners of a run
- *    to a workgroup are more than 160 workgroups, runs of few learners stay on the register
+ *    to a workgroup are more than 160 workgroups (128 where d > 800), runs of few learners stay on the register
  *    kernel.  With these two
  *    splits at multiples of 64 are bit-identical if every call but the last
  *    of the horizon is that long.  Neither takes configurations whose D^2 is not a normal

@@ -557,7 +557,8 @@ template <int LOSS, bool OPT> RunKernel pick_run_kernel(int nfull)
 // So beyond a turn tiles have to be three quarters full (half of narrow models, whose sweeps are short beside their rounds; all of wide
 // aligned ones), and the register kernel needs a number of wavefronts per SIMD and turn: 1.5, 2, 2.75 and 3 as models get wider (d = 1000,
 // 300 runs of sixteen, 2.5 of them 1.46 / 1.66; 640 runs, 3.5 of them 3.27 / 2.77).  Within a turn workgroups slow each other only by their draw on the caches: from 161 of
-// them and d = 321 tiles have to be half full (800 rounds of d = 448, 192 runs of one learner 0.34 / 0.39, of sixteen 0.50 / 0.43).  A run of
+// them and d = 321 tiles have to be half full, beyond d = 800 from 129 (800 rounds of d = 448, 192 runs of one learner 0.34 / 0.39, of sixteen
+// 0.50 / 0.43; optimistic, d = 1001, 160 runs of one 0.65 / 0.74).  A run of
 // up to fifteen learners and its comparator is one workgroup of the register kernel, which a compute unit works as fast as a wavefront or two
 // per SIMD: such runs of wide aligned models stay there (256 of fifteen, d = 2048 1.70 / 1.91; of sixteen 2.54 / 1.92).
 bool dense_run_wanted(const DenseArgs &a)
@@ -579,7 +580,7 @@ bool dense_run_wanted(const DenseArgs &a)
         if (turns > 1) {
             const int64_t quarters = narrow ? 6 : full ? 12 : wide ? 11 : 8;    // of a wavefront per SIMD
             if (a.K < (narrow ? 8 : full ? 16 : 12) * tiles || waves * 4 < quarters * kSimds * turns) return false;
-        } else if (wgs > 160 && a.d > 320 && a.K < 8 * tiles) {
+        } else if (wgs > (a.d > 800 ? 128 : 160) && a.d > 320 && a.K < 8 * tiles) {
             return false;
         }
         if (waves >= 4 * kSimds) most = aligned && a.K < 16 ? 800 : 16 * kRunMaxBlocks;

@@ -168,7 +168,7 @@ def _call_of(R, K, d, shared=False, T=768, n=0):
     (False, 512, 17, 161, {}), (True, 258, 16, 448, {}), (False, 331, 16, 452, {}), (True, 332, 16, 452, {}),
     (False, 361, 16, 804, {}), (True, 362, 16, 804, {}), (False, 512, 31, 804, dict(T=768)), (True, 258, 16, 449, {}),
     (True, 160, 1, 448, {}), (False, 161, 1, 448, {}), (True, 161, 1, 320, {}), (False, 161, 7, 324, {}), (True, 161, 8, 324, {}),
-    (True, 160, 1, 777, {}), (False, 161, 1, 777, {}), (True, 128, 7, 639, {}), (True, 113, 8, 641, {}), (False, 114, 8, 641, {}),
+    (True, 160, 1, 777, {}), (False, 161, 1, 777, {}), (True, 128, 1, 1001, {}), (False, 129, 1, 1001, {}), (True, 128, 7, 639, {}), (True, 113, 8, 641, {}), (False, 114, 8, 641, {}),
     (True, 2, 3, 448, {}), (False, 2, 3, 452, {}), (True, 2, 3, 1023, {}), (False, 2, 3, 1025, {}),
     (True, 256, 15, 800, {}), (False, 256, 15, 804, {}), (True, 241, 16, 804, {}), (False, 240, 16, 804, {}), (True, 256, 15, 805, {}),
     (True, 241, 16, 2048, {}), (False, 241, 16, 2049, {}),
