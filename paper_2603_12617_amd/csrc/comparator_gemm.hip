@@ -165,10 +165,9 @@ hipError_t launch_comparator_gemm(const ComparatorGemmArgs &a, hipStream_t s)
     const bool split = a.part && a.chunks > 1 && a.R <= 65535;
     const dim3 grid((unsigned)((a.n + kTileRounds - 1) / kTileRounds), (unsigned)((a.R + kTileRuns - 1) / kTileRuns),
                     split ? (unsigned)a.chunks : 1u);
-    if (a.fine && a.vec_ok)
+    if (a.fine && !a.vec_ok) return hipErrorInvalidValue;
+    if (a.fine)
         hipLaunchKernelGGL((comparator_gemm_kernel<true, true>), grid, dim3(256), 0, s, a);
-    else if (a.fine)
-        hipLaunchKernelGGL((comparator_gemm_kernel<false, true>), grid, dim3(256), 0, s, a);
     else if (a.vec_ok)
         hipLaunchKernelGGL((comparator_gemm_kernel<true, false>), grid, dim3(256), 0, s, a);
     else

@@ -630,7 +630,7 @@ hipError_t launch_dense_run(const DenseArgs &a, int loss, hipStream_t s, const P
     if (a.x_shared) {
         ComparatorGemmArgs g{};
         g.x = a.x; g.u = a.u; g.seg_start = a.seg_start; g.S = a.S; g.Z = a.Z; g.zl = a.zl;
-        g.d = a.d; g.K = a.K; g.R = a.R; g.t0 = a.t0; g.n = a.n; g.vec_ok = a.vec_ok; g.fine = true;
+        g.d = a.d; g.K = a.K; g.R = a.R; g.t0 = a.t0; g.n = a.n; g.vec_ok = a.vec_ok;
         e = launch_comparator_gemm(g, cs);
     } else {
         hipLaunchKernelGGL(run_comparator_kernel, dim3((unsigned)((a.n + 63) / 64), (unsigned)a.R), dim3(256), 0, cs, a);

@@ -169,7 +169,7 @@ struct ComparatorGemmArgs {
     int vec_ok;              // rows of x and u are 16-byte aligned and d % 4 == 0
     int chunks = 1;          // ranges of coordinates summed apart, with
     float *part = nullptr;   // chunks R n floats of scratch (null: one range)
-    bool fine = false;       // short float32 sums, added in float64
+    bool fine = false;       // short float32 sums, added in float64 (vec_ok only)
 };
 hipError_t launch_comparator_gemm(const ComparatorGemmArgs &a, hipStream_t s);
 bool dense_supported(int64_t d, int x_shared);

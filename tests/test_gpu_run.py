@@ -314,24 +314,3 @@ def test_short_windows_calls_go_in_one_launch(over, launches):
     _check(wl, data, out[0], label="short windows %s" % over)
     for k in KEYS:
         assert np.array_equal(out[0][k], out[1][k]), k
-
-
-# The comparators' predictions over a shared stream: rows and comparators of one value each, whose sums round the same way every time (one float32 chain
-# over the depth is off by 3e-6 at d = 448 and 7e-6 at d = 1023), and steps so small that the regret is the comparators' loss alone.  Sums of
-# eight products, eight of them to a chunk, the rest in float64: at most 8 + 8 + 1 roundings.
-@pytest.mark.parametrize("d,c,segments", [(448, 0.82766414, 1), (448, 0.92521304, 5), (1023, 0.87643850, 1), (1023, 0.89019549, 5)])
-def test_comparators_of_a_shared_stream_are_not_summed_in_one_chain(d, c, segments):
-    T, R = 800, 3
-    wl = WL.make("c1", T=T, R=R, d=d, K=2, x_shared=True, eta=(1e-30, 2e-30))
-    x, u = np.float32(c) / np.float32(32), np.float32(0.01)
-    data = dict(x=np.full((T, d), x, np.float32), u=np.full((R, segments, d), u, np.float32),
-                seg_start=np.arange(segments, dtype=np.int64) * (T // segments))
-    sim = B.Simulation(wl, data)
-    B.oco_set_timing(sim.h, True)
-    sim.run_all(0)
-    reg = sim.regret()
-    assert B.oco_last_kernel_timing(sim.h)["kernel"] == "dense_window_kernel"
-    sim.close()
-    err = np.abs(reg / -(T * d * float(x) * float(u)) - 1.0)
-    print("comparators d=%d error %.2e" % (d, err.max()), flush=True)
-    assert err.max() <= 17 * 2.0 ** -24
