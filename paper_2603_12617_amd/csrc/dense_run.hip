@@ -554,9 +554,10 @@ template <int LOSS, bool OPT> RunKernel pick_run_kernel(int nfull)
 //   d = 64      0.53 / 0.70   0.63 / 0.72   0.50 / 0.44   0.51 / 0.46   0.58 / 0.50   1.72 / 0.96   1.73 / 0.98
 //   d = 448     1.33 / 1.85   1.26 / 1.85   0.84 / 1.01   0.78 / 0.89   1.07 / 0.89   2.74 / 2.05   2.72 / 1.90
 //   d = 1000    1.87 / 3.57   2.07 / 3.66   1.31 / 1.98   1.12 / 1.70   1.35 / 1.56   4.98 / 3.87   3.87 / 3.50
-// So beyond a turn tiles have to be three quarters full (half of narrow models, whose sweeps are short beside their rounds; all of wide
-// aligned ones), and the register kernel needs a number of wavefronts per SIMD and turn: 1.5, 2, 2.75 and 3 as models get wider (d = 1000,
-// 300 runs of sixteen, 2.5 of them 1.46 / 1.66; 640 runs, 3.5 of them 3.27 / 2.77).  Within a turn workgroups slow each other only by their draw on the caches: from 161 of
+// So beyond a turn tiles have to be three quarters full, half where the sweeps are short beside the rounds (512 runs of 8: d = 192 0.64 / 0.60, but
+// 448 as above; longer rows that the register kernel copies word by word), all of wide aligned models; and of
+// aligned models the register kernel needs 2, 2.75 or 3 wavefronts per SIMD and turn as they get wider (d = 1000, 300 runs of sixteen,
+// 2.5 of them 1.46 / 1.66; 640 runs, 3.5 of them 3.27 / 2.77).  Within a turn workgroups slow each other only by their draw on the caches: from 161 of
 // them and d = 321 tiles have to be half full, beyond d = 800 from 129 (800 rounds of d = 448, 192 runs of one learner 0.34 / 0.39, of sixteen
 // 0.50 / 0.43; optimistic, d = 1001, 160 runs of one 0.65 / 0.74).  A run of
 // up to fifteen learners and its comparator is one workgroup of the register kernel, which a compute unit works as fast as a wavefront or two
@@ -576,9 +577,9 @@ bool dense_run_wanted(const DenseArgs &a)
     } else {
         constexpr int kUnits = 256;
         const int64_t tiles = (a.K + kM - 1) / kM, wgs = a.R * tiles, turns = (wgs + kUnits - 1) / kUnits;
-        const bool narrow = a.d <= 160, wide = aligned && a.d > 448, full = aligned && a.d > 800;
+        const bool narrow = a.d <= (aligned ? 192 : 320), full = aligned && a.d > 800;
         if (turns > 1) {
-            const int64_t quarters = narrow ? 6 : full ? 12 : wide ? 11 : 8;    // of a wavefront per SIMD
+            const int64_t quarters = narrow || !aligned ? 0 : full ? 12 : a.d > 448 ? 11 : 8;    // of a wavefront per SIMD
             if (a.K < (narrow ? 8 : full ? 16 : 12) * tiles || waves * 4 < quarters * kSimds * turns) return false;
         } else if (wgs > (a.d > 800 ? 128 : 160) && a.d > 320 && a.K < 8 * tiles) {
             return false;

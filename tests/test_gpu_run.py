@@ -160,12 +160,13 @@ def _call_of(R, K, d, shared=False, T=768, n=0):
     sim.close()
 
 
-# The lines of the rule, on both sides: learners of a tile and register wavefronts per turn beyond 256 workgroups; workgroups and learners of
+# The lines of the rule, on both sides: learners of a tile and (aligned rows) register wavefronts per turn beyond 256 workgroups; workgroups and learners of
 # a tile within a turn; what rows of any length and many learners change; the least rounds and the most learners of a shared stream.
 @pytest.mark.parametrize("windows,R,K,d,over", [
-    (False, 1024, 1, 100, {}), (False, 257, 1, 10, {}), (False, 400, 7, 10, {}), (False, 341, 8, 10, {}), (True, 342, 8, 10, {}),
-    (True, 342, 8, 160, {}), (False, 342, 8, 161, {}), (False, 512, 11, 161, {}), (False, 315, 12, 161, {}), (True, 316, 12, 161, {}),
-    (False, 512, 17, 161, {}), (True, 258, 16, 448, {}), (False, 331, 16, 452, {}), (True, 332, 16, 452, {}),
+    (False, 1024, 1, 100, {}), (False, 257, 1, 10, {}), (False, 400, 7, 10, {}), (True, 257, 8, 10, {}), (True, 512, 17, 100, {}),
+    (True, 257, 8, 192, {}), (False, 342, 8, 196, {}), (True, 257, 8, 319, {}), (False, 342, 8, 321, {}), (False, 342, 11, 321, {}),
+    (True, 257, 12, 321, {}), (False, 512, 11, 196, {}), (False, 315, 12, 196, {}), (True, 316, 12, 196, {}),
+    (False, 512, 17, 196, {}), (True, 258, 16, 448, {}), (False, 331, 16, 452, {}), (True, 332, 16, 452, {}),
     (False, 361, 16, 804, {}), (True, 362, 16, 804, {}), (False, 512, 31, 804, dict(T=768)), (True, 258, 16, 449, {}),
     (True, 160, 1, 448, {}), (False, 161, 1, 448, {}), (True, 161, 1, 320, {}), (False, 161, 7, 324, {}), (True, 161, 8, 324, {}),
     (True, 160, 1, 777, {}), (False, 161, 1, 777, {}), (True, 128, 1, 1001, {}), (False, 129, 1, 1001, {}), (True, 128, 7, 639, {}), (True, 113, 8, 641, {}), (False, 114, 8, 641, {}),
