@@ -17,7 +17,7 @@
 // What bounds a window, wall clock: 64 runs of 15 learners, d = 100, plain, squared, 9.0 us (64 rounds on the register kernel 12.8): rounds
 // 4.8 - 6 (3.9 with nothing beside them on their SIMD: the matrix instructions and float64 sums of the Gram matrix, 3.6 us, get in their
 // way), (3) and the wait for it 2.1; 48 of 5, d = 777, optimistic, logistic, 26 us (41): rounds 15 (8 alone) beside a Gram matrix of 14, (3)
-// 9.4; one learner of d = 10 5.5 us (10): rounds 3.4.  Per pass 2.30 -> 1.63 ms, 1.98 -> 1.43 ms, 0.250 -> 0.198 ms.
+// 9.4; one learner of d = 10 5.5 us (10): rounds 3.4.  Per pass 2.30 -> 1.63 ms, 1.98 -> 1.43 ms, 0.250 -> 0.179 ms.
 #include "dense_chain.h"
 #include "../../include/oco.h"
 
@@ -29,7 +29,8 @@ namespace {
 
 constexpr int kRW = 8;                        // wavefronts per workgroup
 constexpr int kRT = kRW * kWave;
-// the ten 16 x 16 blocks of a Gram matrix on and above the diagonal, and dealt to wavefronts 4 .. 7
+// the ten 16 x 16 blocks of a Gram matrix on and above the diagonal, and dealt to wavefronts 4 .. 7 such that a wavefront needs two or three of the four groups of
+// 16 rows (kGramNeeds)
 constexpr int kGramParts = 10;
 constexpr int kPartRow[kGramParts] = {0, 0, 0, 0, 1, 1, 1, 2, 2, 3}, kPartCol[kGramParts] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
 constexpr int kGramBlocks[4] = {3, 3, 2, 2};
@@ -544,7 +545,8 @@ template <int LOSS, bool OPT> RunKernel pick_run_kernel(int nfull)
 // of 8, d = 777 1.73 / 1.23), and at the last d the kernel holds where the register kernel has four wavefronts and more on every SIMD.
 // A shared stream, 1 / 256 / 2048 learners: d = 10 0.60 / 0.39, 0.64 / 0.45, 0.81 / 0.55; d = 400 0.85 / 0.76, 0.88 / 0.80, 1.05 / 0.85; d = 512 0.85 /
 // 0.84, 0.88 / 0.89, 1.11 / 0.94; d = 501, 256 learners 1.13 / 0.88.  More learners than dense_split.hip takes stay where they are.  Of 600
-// rounds the two take the same (d = 100 0.223 / 0.222 and 0.203 / 0.205), 1000 of one learner 0.250 / 0.198: hence the least n.  The horizon's
+// rounds the two took the same when these calls too went in four pieces (d = 100 0.223 / 0.222 and 0.203 / 0.205), 1000 of one learner 0.250 /
+// 0.198, now 0.179: hence the least n.  The horizon's
 // last call, which is as short as the cuts leave it, stays with the kernel of the calls before it, as in dense_split.hip.
 // (The rules look at the configuration and the call's length only, not at addresses.)
 //

@@ -361,7 +361,7 @@ __global__ void __launch_bounds__(64) split_finish_kernel(const DenseArgs a, int
 // The sums of a depth block (16 products) are added up in float64: as one float32 chain over a chunk's depth (270 products
 // at d = 516) their error was that of ||x||^2 in every projection, and the iterates of large steps had up to three times the
 // register kernel's.
-constexpr int kGramBlocks[4] = {3, 3, 2, 2};                        // of a wavefront, and where they lie
+constexpr int kGramBlocks[4] = {3, 3, 2, 2};                        // of a wavefront, and where they lie (each reads all four groups of rows, so any deal does)
 constexpr int kGramRow[4][3] = {{0, 0, 0}, {1, 1, 1}, {2, 0, 0}, {3, 2, 0}};
 constexpr int kGramCol[4][3] = {{0, 1, 2}, {1, 2, 3}, {2, 3, 0}, {3, 3, 0}};
 template <bool CMP>
